@@ -68,8 +68,8 @@ typedef struct sym_tuning {
                               Hq/Hkv = 8, else 0                                          */
   int32_t min_units;       /* smallest piece, in pages, that a long range is cut into;
                               >= 1, default 4                                             */
-  int32_t prefill_min;     /* a pred of at least this many new tokens is computed by tiles
-                              (bf16); >= 2, default 16                                    */
+  int32_t prefill_min;     /* a pred of at least this many new tokens is computed by tiles;
+                              >= 2, default 16 (fp32: 4)                                  */
   int32_t share_min_lips;  /* files of a batch that must share a page-list prefix before
                               the prefix is read once for all of them; 0 = never group,
                               default 4                                                   */
@@ -101,10 +101,10 @@ typedef struct sym_config {
   int32_t n_kv_heads;      /* Hkv, divides Hq; query head h reads kv head h / (Hq/Hkv)   */
   int32_t head_dim;        /* D; D * sizeof(element) must be 256 (bf16: 128, f32: 64)    */
   int32_t page_tokens;     /* P = 16                                                     */
-  int32_t dtype;           /* SYM_F32 or SYM_BF16: storage type of Q, K, V.  The matrix-core
-                              paths (tiles for preds of many tokens and for shared prefixes,
-                              rows of several draft tokens) exist for SYM_BF16 only: with
-                              SYM_F32 every new token is a row of its own that reads the file */
+  int32_t dtype;           /* SYM_F32 or SYM_BF16: storage type of Q, K, V.  Tiles for shared
+                              prefixes and rows of several draft tokens exist for SYM_BF16 only;
+                              a pred of several tokens is computed by tiles with either (SYM_F32:
+                              fp32 matrix cores, fp32 weights and sums)                     */
   int32_t device;          /* HIP device ordinal, or -1 for a host-only context          */
   int64_t n_pages;         /* pages in the pool; page ids are int32, n_pages < 2^27      */
   void*   pool;            /* device, n_pages * sym_page_bytes() bytes, 256-aligned      */
@@ -330,8 +330,10 @@ int sym_plan_copies_first(sym_ctx* ctx);
  * [32] n_segs, [33] offset of the segments, [34] n_bins, [35] wavefronts of a bin,
  * [36] offset of the in-bin merge lists (all five 0 when ranges are cut globally, as the
  * matrix-core decode kernel wants: wave_work is then one record per wavefront slot);
- * [37] n_groups, [38] offset of the order table (0 unless the launch holds tiles and bins)},
- * then the sections:
+ * [37] n_groups, [38] offset of the order table (0 unless the launch holds tiles and bins);
+ * [39] n_rtiles, [40] offset of the row tiles (fp32 storage), [41] n_tmerge, [42] offset of the
+ * merge list of tiles cut into key chunks}, then the sections (the rows of row tiles count in
+ * n_rows and follow the decode rows):
  *   rows      [n_rows][4]   page-table offset, tokens the row's first new token sees, its q/out
  *                           row, and in one word: first page of the row's own range (low 28 bits;
  *                           pages before it belong to a shared prefix) | (new tokens in the
@@ -370,6 +372,11 @@ int sym_plan_copies_first(sym_ctx* ctx);
  *                           partial slot), kind (0 prefill chunk, 1 shared prefix), first page,
  *                           end page, 0, 0, 0; ordered share by share
  *   members   [n_members]   q rows of the members of shared-prefix tiles
+ *   rtiles    [n_rtiles][8]  (fp32) page-table offset, tokens the tile's first row sees, its q/out
+ *                           row, tokens, kv head, first page, end page, first partial slot (-1: the
+ *                           tile holds all keys of its rows and writes the final output)
+ *   tmerge    [n_tmerge][4]  first partial (chunk c, token t: first + c * tokens + t), chunks,
+ *                           tokens, q row * Hq + first query head of the first token
  * Returns the number of words (or a negative status); writes at most cap words.             */
 int64_t sym_build_desc(sym_ctx* ctx, int32_t n_lips, const int32_t* n_tokens,
                        const int32_t* page_table_flat, const int64_t* pt_offsets,

@@ -37,7 +37,10 @@ sym_tuning default_tuning(const sym_config* cfg) {
   sym_tuning t;
   t.decode_mfma = (bf16 && G == 8) ? 1 : 0;   // 8 query heads per kv head are bound by vector issue on the VALU path
   t.min_units = 4;
-  t.prefill_min = 16;
+  // fp32 has no rows of several tokens, so short drafts go to tiles too.  32 files of 500 tokens, 8 new ones each: 55 us per call
+  // as rows, 23 us as tiles; with 2 or 3 new tokens 21 against 17 us, but the rows' sums are slightly finer there (error
+  // against 64 bits 1.7e-7 against 2.0e-7; from 8 tokens on the tiles are as good or better), so those stay rows.
+  t.prefill_min = bf16 ? 16 : 4;
   t.share_min_lips = 4;
   t.share_min_pages = 8;
   t.tile_rows = 256;
@@ -68,6 +71,7 @@ struct sym_ctx {
   sym_config cfg;
   int32_t G = 1;
   int32_t n_layers = 1;
+  int32_t cus = 256;                  // compute units of the device (a host-only context plans for 256)
   int64_t layer_bytes = 0;            // bytes of one layer of the pool: n_pages * page_bytes
   OpenPred pred;
   int64_t page_bytes = 0;
@@ -176,7 +180,8 @@ struct Scratch {
 };
 Scratch workspace_of(const sym_ctx* c) { return Scratch{(uint8_t*)c->cfg.workspace, c->cfg.workspace_bytes, partial_slots(c)}; }
 // fuse_append: the batch's single-token LIPs are appended by the attention kernel itself (bins only)
-DescParams desc_params(const sym_ctx* c, int64_t partials, bool fuse_append = false) {
+// max_words: words there is room for (a bound that every batch without chunked tiles stays under)
+DescParams desc_params(const sym_ctx* c, int64_t partials, int64_t max_words, bool fuse_append = false) {
   DescParams p{c->cfg.n_q_heads, c->cfg.n_kv_heads, c->cfg.page_tokens, c->max_waves, c->min_units, c->range_cost, c->prefill_min,
                c->tile_tokens, c->share_min_lips, c->share_min_pages, (int32_t)std::min<int64_t>(partials, 0x7fffffff), c->row_tokens};
   // the vector-unit decode kernel (up to 4 query heads per kv head, unless the matrix cores are asked for) works on bins
@@ -186,6 +191,9 @@ DescParams desc_params(const sym_ctx* c, int64_t partials, bool fuse_append = fa
   p.mix_lead = c->mix_lead;
   p.mix_spread = c->mix_spread;
   p.share_tiles = c->share_tiles;
+  p.row_tile_rows = c->cfg.dtype == SYM_F32 ? 32 : 0;
+  p.cus = c->cus;
+  p.max_words = max_words;
   return p;
 }
 
@@ -268,7 +276,7 @@ struct Timed {
 int launch_attention(sym_ctx* c, const Scratch& ws, int64_t blob_words, const void* q, float* out, hipStream_t st, bool timed = true,
                      const void* k_new = nullptr, const void* v_new = nullptr, int32_t layer = 0) {
   const BatchDesc& d = c->desc;
-  if (d.n_waves == 0 && d.n_tiles == 0) return SYM_OK;
+  if (d.n_waves == 0 && d.n_tiles == 0 && d.n_rtiles == 0) return SYM_OK;
   const int32_t* hdr = c->desc_hdr;
   // scratch: [descriptor words][partial max/sum][partial accumulators]
   const int32_t* dw = (const int32_t*)ws.base;
@@ -320,14 +328,16 @@ int launch_attention(sym_ctx* c, const Scratch& ws, int64_t blob_words, const vo
   pa.small_shared_only = d.small_shared_only;
   pa.group_map = hdr[H_N_GROUPS] > 0 ? dw + hdr[H_OFF_GROUPS] : nullptr;
   pa.n_groups = hdr[H_N_GROUPS];
+  pa.rtiles = dw + hdr[H_OFF_RTILES];
+  pa.n_rtiles = d.n_rtiles;
   {
     Timed t(c, SYM_K_ATTN, st, true, timed);
     // rows that hold several new tokens exist for the matrix-core decode kernel only
     hipError_t e = launch_attn(a, pa, c->cfg.dtype, (c->decode_mode || d.max_row_tokens > 1) ? 1 : 0, st, t.start(), t.stop());
     if (e != hipSuccess) return fail_hip(c, e, "attention launch");
   }
-  if (d.n_merge > 0) {
-    MergeArgs m{part_acc, part_ml, dw + hdr[H_OFF_MERGE], out, d.n_merge};
+  if (d.n_merge > 0 || d.n_tmerge > 0) {
+    MergeArgs m{part_acc, part_ml, dw + hdr[H_OFF_MERGE], out, d.n_merge, dw + hdr[H_OFF_TMERGE], d.n_tmerge, d.tmerge_tokens, c->cfg.n_q_heads};
     Timed t(c, SYM_K_MERGE, st, false, timed);
     hipError_t e = launch_merge(m, c->G, c->cfg.head_dim, st);
     if (e != hipSuccess) return fail_hip(c, e, "merge launch");
@@ -447,7 +457,7 @@ int64_t desc_from_flat(sym_ctx* c, int32_t n_lips, const int32_t* n_tokens, cons
     for (int64_t i = 0; i < np; ++i)
       if (c->tables[b][i] < 0 || c->tables[b][i] >= c->cfg.n_pages) return fail(c, SYM_EINVAL, "page id out of range");
   }
-  const DescParams prm = desc_params(c, partial_slots(c));
+  const DescParams prm = desc_params(c, partial_slots(c), c->cfg.device < 0 ? 0x7fffffff : (c->cfg.workspace_bytes - partial_bytes(c)) / 4 - 64);
   c->desc.alloc = alloc;
   const int rc = build_desc(prm, n_lips, n_tokens, lengths, c->tables.data(), &c->desc);
   c->desc.alloc = nullptr;
@@ -503,7 +513,8 @@ int pred_plan_locked(sym_ctx* c, int32_t n_lips, const sym_kv* kv, const int32_t
     c->tables[b] = f->pages.data();
     c->len_after[b] = f->len;
   }
-  const DescParams prm = desc_params(c, partials, true);
+  // behind the descriptor lie the copy list (3 words per LIP at most) and the slot map
+  const DescParams prm = desc_params(c, partials, bound - 3 * n_lips - T - 64, true);
   // The descriptor is built straight into the pinned staging buffer; copy list and slot map follow it.
   const int64_t tail_words = (int64_t)c->plan.cow.size() + (int64_t)c->plan.slots.size() + 4;
   int si = -1;
@@ -638,6 +649,7 @@ int sym_init(const sym_config* cfg, sym_ctx** out) {
       delete c;
       return SYM_EHIP;
     }
+    c->cus = std::max(cus, 1);
     // two wavefronts per SIMD; with 8 query heads per kv head a range of the VALU kernel takes two wavefronts
     if (cfg->decode_waves <= 0) c->max_waves = std::max(cus, 1) * ((c->G == 8 && !tun.decode_mfma) ? 4 : 8);
   }

@@ -8,24 +8,69 @@
 
 namespace symkv {
 
+namespace {
+// How many steps over its keys one tile of a batch should take at most, when few tiles would leave compute units idle or a
+// long one would be the batch's tail.  lens: (steps of a tile, number of such tiles).  A batch of `rounds` workgroups per
+// slot, all of b steps, ends after rounds * (b + start) steps; b is the smallest size with which the pieces fit into that many
+// slots.  Cutting costs a partial result per row and chunk and a merge launch (`merge` steps).  0 = leave the tiles whole.
+int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_t slots, int64_t start, int64_t merge, int64_t max_chunks, int64_t unit) {
+  int64_t n = 0, longest = 0, total = 0;
+  for (auto& t : lens) {
+    n += t.second;
+    longest = std::max<int64_t>(longest, t.first);
+    total += (int64_t)t.first * t.second;
+  }
+  if (n == 0 || n > 3 * slots) return 0;
+  const int64_t rounds0 = (n + slots - 1) / slots;
+  int64_t best = rounds0 == 1 ? longest + start : std::max(longest + start, std::min(rounds0 * (longest + start), total / slots + rounds0 * start + longest / 2));
+  best -= best / 8;                              // a cut has to promise an eighth
+  int64_t b_best = 0;
+  for (int64_t rounds = rounds0; rounds <= rounds0 + 2; ++rounds) {
+    int64_t lo = (longest + max_chunks - 1) / max_chunks, hi = longest;       // smallest b in [lo, hi] whose pieces fit
+    lo = std::max((lo + unit - 1) / unit, (int64_t)1);
+    hi = std::max((hi + unit - 1) / unit, lo);
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      int64_t pieces = 0;
+      for (auto& t : lens) pieces += (t.first + mid * unit - 1) / (mid * unit) * t.second;
+      if (pieces <= rounds * slots) hi = mid;
+      else lo = mid + 1;
+    }
+    if (lo * unit >= longest) continue;          // whole tiles
+    const int64_t est = rounds * (lo * unit + start) + merge;
+    if (est < best) {
+      best = est;
+      b_best = lo * unit;
+    }
+  }
+  return b_best;
+}
+}  // namespace
+
 int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, const int64_t* len_after,
                const int32_t* const* tables, BatchDesc* out) {
   const int32_t P = prm.page_tokens, H = prm.n_kv_heads, G = prm.n_q_heads / H;
-  auto is_prefill = [&](int32_t b) { return prm.tile_tokens > 0 && n_tokens[b] >= prm.prefill_min; };
+  auto is_rtile = [&](int32_t b) { return prm.row_tile_rows > 0 && n_tokens[b] >= prm.prefill_min; };
+  auto is_prefill = [&](int32_t b) { return (prm.tile_tokens > 0 && n_tokens[b] >= prm.prefill_min) || is_rtile(b); };   // no decode rows
   // Tiles of a batch with prefill chunks have prm.tile_tokens new tokens (256 query rows by default:
   // eight wavefronts share one staging of K/V); a batch whose only tiles are shared prefixes (few
   // members per group) keeps 128-row tiles, two workgroups per CU.
   bool any_prefill = false;
-  for (int32_t b = 0; b < n_lips && !any_prefill; ++b) any_prefill = n_tokens[b] >= 1 && is_prefill(b);
+  for (int32_t b = 0; b < n_lips && !any_prefill; ++b) any_prefill = n_tokens[b] >= 1 && is_prefill(b) && !is_rtile(b);
   const int32_t TQ = any_prefill ? prm.tile_tokens : std::min(prm.tile_tokens, 128 / G);
   // A decode row holds up to RT consecutive new tokens of one LIP (a short draft to verify):
   // they share one pass over the file's pages.
   const int32_t RT = std::max(1, std::min(prm.row_tokens, (int32_t)ROW_TOKENS_MAX));
   int32_t max_nt = 1;
-  int64_t n_rows = 0, entries = 0, n_tiles = 0, n_tok_total = 0;
+  int64_t n_rows = 0, entries = 0, n_tiles = 0, n_tok_total = 0, n_rrows = 0;
+  auto& rorder = out->rtile_order;
+  rorder.clear();
   for (int32_t b = 0; b < n_lips; ++b) {
     if (n_tokens[b] < 1 || len_after[b] < n_tokens[b] || len_after[b] > (int64_t)0x7fffffff) return SYM_EINVAL;
-    if (is_prefill(b)) n_tiles += (int64_t)((n_tokens[b] + TQ - 1) / TQ) * H;
+    if (is_rtile(b)) {
+      n_rrows += n_tokens[b];
+      rorder.push_back(b);
+    } else if (is_prefill(b)) n_tiles += (int64_t)((n_tokens[b] + TQ - 1) / TQ) * H;
     else {
       n_rows += (n_tokens[b] + RT - 1) / RT;
       max_nt = std::max(max_nt, std::min(RT, n_tokens[b]));
@@ -162,6 +207,42 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     }
   }
   n_tiles += n_shared_tiles;
+
+  // ---- row tiles: RQ new tokens of a LIP x one kv head; the workgroup's eight wavefronts take every eighth page each, so a
+  // step over the keys is eight pages.  Two workgroups of 512 threads fit on a compute unit.
+  const int32_t RQ = std::max(1, prm.row_tile_rows / G);
+  // partial slots left for tiles that are cut into key chunks
+  int64_t chunk_budget = (int64_t)prm.max_partials - 2 * (int64_t)RT * prm.max_waves - 2 * n_shared_partials;
+  int64_t n_rtiles = 0, n_rtile_split = 0, n_chunk_partials = 0, rsteps = 0;
+  constexpr int32_t kRowTileWaves = 8;
+  auto rpages = [&](int32_t b, int32_t t0) { return (int32_t)((len_after[b] - n_tokens[b] + std::min(t0 + RQ, n_tokens[b]) + P - 1) / P); };   // pages the tile reads
+  auto rchunks = [&](int32_t pages) { return rsteps > 0 ? (pages + (int32_t)rsteps * kRowTileWaves - 1) / ((int32_t)rsteps * kRowTileWaves) : 1; };
+  auto count_rtiles = [&]() {
+    n_rtiles = n_rtile_split = n_chunk_partials = 0;
+    for (int32_t b : rorder)
+      for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += RQ) {
+        const int32_t nc = rchunks(rpages(b, t0));
+        n_rtiles += (int64_t)nc * H;
+        if (nc > 1) {
+          n_rtile_split += H;
+          n_chunk_partials += (int64_t)nc * H * std::min(RQ, n_tokens[b] - t0);
+        }
+      }
+  };
+  if (!rorder.empty()) {
+    std::stable_sort(rorder.begin(), rorder.end(), [&](int32_t x, int32_t y) { return len_after[x] > len_after[y]; });
+    auto& lens = out->tile_lens;
+    lens.clear();
+    for (int32_t b : rorder)
+      for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += RQ) lens.emplace_back((rpages(b, t0) + kRowTileWaves - 1) / kRowTileWaves, H);
+    rsteps = chunk_steps(lens, 2 * (int64_t)prm.cus, 4, 4, 64, 1);
+    count_rtiles();
+    if (n_chunk_partials > chunk_budget) {
+      rsteps = 0;
+      count_rtiles();
+    }
+    chunk_budget -= n_chunk_partials;
+  }
 
   // ---- units of the decode kernel
   int64_t total_units = 0;
@@ -365,7 +446,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   }
 
   const int64_t off_rows = DESC_HEADER_WORDS;
-  const int64_t off_waves = off_rows + n_rows * ROW_WORDS;
+  const int64_t off_waves = off_rows + (n_rows + n_rrows) * ROW_WORDS;      // the rows of row tiles follow the decode rows
   const int64_t off_merge = off_waves + nw * WAVE_WORDS;
   // a merge entry per token of a cut (row, head) (at most one cut per wave boundary) and per (member row, head)
   // (a cut (row, head) has a wave boundary inside it, and there are no more of them than (row, head)s);
@@ -380,7 +461,13 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   // the order table of a launch with tiles and bins: a word per group of 8 workgroups (no more tile groups than tiles)
   const int64_t off_groups = off_lmerge + (bins ? n_bins * LMERGE_WORDS : 0);
   const int64_t groups_cap = (bins && n_tiles > 0) ? n_tiles + (n_bins + 7) / 8 : 0;
-  const int64_t total = off_groups + groups_cap;
+  const int64_t off_rtiles = off_groups + groups_cap;
+  if (off_rtiles + n_rtiles * RTILE_WORDS + n_rtile_split * TMERGE_WORDS > prm.max_words && rsteps > 0) {
+    rsteps = 0;                                   // no room for the chunks: whole tiles
+    count_rtiles();
+  }
+  const int64_t off_tmerge = off_rtiles + n_rtiles * RTILE_WORDS;
+  const int64_t total = off_tmerge + n_rtile_split * TMERGE_WORDS;
   if (total > 0x7fffffff) return SYM_EINVAL;
   int32_t* const w = out->alloc ? out->alloc(total) : nullptr;   // the caller's buffer (pinned staging memory on the GPU path)
   if (!w) return SYM_ENOSPC;
@@ -394,14 +481,17 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   int32_t* ptoff = w + off_ptoff;
   int32_t* tiles = w + off_tiles;
   int64_t e = 0, tok = 0, ti = 0;
+  std::vector<int32_t>& tok_of = out->qrow_of;             // token index of each LIP's first row
+  tok_of.resize(n_lips);
   for (int32_t b = 0; b < n_lips; ++b) {
+    tok_of[b] = (int32_t)tok;
     const int64_t skip = full_table[b] ? 0 : share_start[b];      // leading pages left out (see above)
     const int64_t e_lip = e - skip;
     ptoff[b] = (int32_t)e_lip;
     int64_t np = (len_after[b] + P - 1) / P;
     if (np > skip) std::memcpy(pt + e, tables[b] + skip, (size_t)(np - skip) * sizeof(int32_t));
     e += np - skip;
-    if (is_prefill(b)) {
+    if (is_prefill(b) && !is_rtile(b)) {
       // order (kv head, token tile): the tiles that read the same K/V are neighbours
       for (int32_t g = 0; g < H; ++g)
         for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += TQ, ++ti) {
@@ -625,6 +715,49 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
         }
     }
   }
+  // ---- row tiles, longest first; the kv heads of a token tile are neighbours, so that with 8 of them (workgroup b runs on
+  // XCD b % 8) the tiles that read one (file, kv head) share an L2
+  int32_t n_tmerge = 0, tmerge_tokens = 0;
+  if (!rorder.empty()) {
+    int32_t* rt = w + off_rtiles;
+    int32_t* tm = w + off_tmerge;
+    int64_t chunk_base = shared_base + n_shared_partials;
+    int32_t* rr = rows + n_rows * ROW_WORDS;
+    for (int32_t b : rorder) {
+      const int32_t len0 = (int32_t)(len_after[b] - n_tokens[b]), tok0 = tok_of[b];
+      for (int32_t t = 0; t < n_tokens[b]; ++t, rr += ROW_WORDS) {
+        rr[0] = ptoff[b];
+        rr[1] = len0 + t + 1;
+        rr[2] = tok0 + t;
+        rr[3] = 0;
+      }
+      for (int32_t t0 = (n_tokens[b] - 1) / RQ * RQ; t0 >= 0; t0 -= RQ) {
+        const int32_t count = std::min(RQ, n_tokens[b] - t0), pages = rpages(b, t0), nc = rchunks(pages);
+        const int32_t per = (pages + nc - 1) / nc;
+        for (int32_t c = 0; c < nc; ++c)
+          for (int32_t g = 0; g < H; ++g, rt += RTILE_WORDS) {
+            rt[RT_TBL] = ptoff[b];
+            rt[RT_VIS] = len0 + t0 + 1;
+            rt[RT_QROW] = tok0 + t0;
+            rt[RT_COUNT] = count;
+            rt[RT_HEAD] = g;
+            rt[RT_PAGE0] = std::min(c * per, pages);
+            rt[RT_PAGE1] = std::min((c + 1) * per, pages);
+            rt[RT_DEST] = nc > 1 ? (int32_t)(chunk_base + ((int64_t)g * nc + c) * count) : -1;
+          }
+        if (nc > 1) {
+          for (int32_t g = 0; g < H; ++g, tm += TMERGE_WORDS, ++n_tmerge) {
+            tm[TM_FIRST] = (int32_t)(chunk_base + (int64_t)g * nc * count);
+            tm[TM_CHUNKS] = nc;
+            tm[TM_COUNT] = count;
+            tm[TM_QROW] = (tok0 + t0) * prm.n_q_heads + g * G;
+          }
+          tmerge_tokens = std::max(tmerge_tokens, count);
+          chunk_base += (int64_t)nc * H * count;
+        }
+      }
+    }
+  }
   // ---- the tile list in 8 shares of equal cost, one per XCD
   int32_t tile_blocks = 0;
   {
@@ -722,10 +855,17 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       }
     }
   }
-  const int32_t n_partials = shared_base + (int32_t)n_shared_partials;
+  const int32_t n_partials = shared_base + (int32_t)(n_shared_partials + n_chunk_partials);
   if (n_partials > prm.max_partials) return SYM_ENOSPC;
 
-  w[H_N_ROWS] = (int32_t)n_rows;
+  w[H_N_ROWS] = (int32_t)(n_rows + n_rrows);
+  w[H_N_RTILES] = (int32_t)n_rtiles;
+  w[H_OFF_RTILES] = (int32_t)off_rtiles;
+  w[H_N_TMERGE] = n_tmerge;
+  w[H_OFF_TMERGE] = (int32_t)off_tmerge;
+  out->n_rtiles = (int32_t)n_rtiles;
+  out->n_tmerge = n_tmerge;
+  out->tmerge_tokens = tmerge_tokens;
   w[H_N_WAVES] = (int32_t)nw;
   w[H_N_PARTIALS] = n_partials;
   w[H_N_LIPS] = n_lips;

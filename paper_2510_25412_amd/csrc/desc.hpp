@@ -8,6 +8,8 @@
 //  * shared-prefix tiles: decode LIPs whose files start with the same pages (forks of one prefix,
 //    paper Fig. 1 / section 4.2) are grouped; the common full pages are read ONCE per group by
 //    the tile kernel (rows = members x query heads of the group), leaving partial results;
+//  * row tiles (fp32 storage): a LIP that brings several new tokens is cut into tiles of row_tile_rows
+//    query rows x one kv head for the fp32 matrix-core kernel; its tokens stay rows in the row list;
 //  * decode rows: every other new token is a "row" with a visible length (file tokens
 //    0 .. len_before + i); a member of a sharing group is a row that starts after the common pages.
 //    A LIP that brings a few new tokens (a short draft to verify, paper section 4.1) packs up to
@@ -54,7 +56,9 @@ enum {
   H_N_SEGS = 32, H_OFF_SEGS, H_N_BINS, H_BIN_WAVES, H_OFF_LMERGE,
   // order of the workgroups of a launch that holds tiles and decode bins: one word per group of eight workgroups
   // (one per XCD): g >= 0 = tile group g, g < 0 = decode group ~g
-  H_N_GROUPS = 37, H_OFF_GROUPS
+  H_N_GROUPS = 37, H_OFF_GROUPS,
+  // row tiles (fp32 storage): LIPs with several new tokens; and the tiles whose key range is cut into chunks
+  H_N_RTILES = 39, H_OFF_RTILES, H_N_TMERGE, H_OFF_TMERGE
 };
 // segment words: page-table offset, kv head, first page, end page | tokens the row sees, q/out row * Hq + first
 // query head of the kv head, destination (-1 = the final output rows; otherwise a partial slot in device memory), slot of the row's last
@@ -63,6 +67,12 @@ enum { S_TBL = 0, S_HEAD, S_PB, S_PE, S_VIS, S_QROW, S_DEST, S_APPEND };
 // tile words
 enum { T_TBL = 0, T_LEN, T_QROW, T_COUNT, T_HEAD, T_AUX, T_KIND, T_PAGE0, T_PAGE1 };
 enum { TILE_PREFILL = 0, TILE_SHARED = 1 };
+// row tile words: page-table offset, tokens the tile's first row sees, its q / out row, tokens in the tile, kv head, first
+// page, end page, partial slot of the chunk's first token (-1 = the final output rows)
+enum { RT_TBL = 0, RT_VIS, RT_QROW, RT_COUNT, RT_HEAD, RT_PAGE0, RT_PAGE1, RT_DEST, RTILE_WORDS };
+// a tile whose keys are cut into chunks: first partial slot (chunk c, token t: first + c * count + t), chunks, tokens,
+// q / out row * Hq + first query head of its first token
+enum { TM_FIRST = 0, TM_CHUNKS, TM_COUNT, TM_QROW, TMERGE_WORDS };
 // word 3 of a row (and word 11 of a wave record): first page of the row's own range in the low
 // bits, (new tokens in the row) - 1 above them
 enum { ROW_NT_SHIFT = 28, ROW_PAGE_MASK = (1 << ROW_NT_SHIFT) - 1, ROW_TOKENS_MAX = 4 };
@@ -79,6 +89,8 @@ struct BatchDesc {
   int32_t small_shared_only = 0;   // 1: every tile is a shared-prefix tile with at most 64 live rows
   int32_t max_row_tokens = 1;   // > 1: some row holds several new tokens (needs the matrix-core decode kernel)
   int64_t total_units = 0;
+  int32_t n_rtiles = 0;         // row tiles (fp32 storage)
+  int32_t n_tmerge = 0, tmerge_tokens = 0;         // tiles cut into key chunks, and the most tokens such a tile holds
   int32_t n_bins = 0, bin_waves = 0, n_segs = 0;   // bins in use (0 = the global cut)
   int32_t n_fused = 0;          // new tokens whose append the attention kernel carries out itself
   std::vector<uint8_t> fused;   // per LIP: 1 = its (single) new token is one of them
@@ -88,6 +100,8 @@ struct BatchDesc {
   std::vector<uint8_t> full_table;   // per LIP: its whole page table goes into the descriptor (see build_desc)
   std::vector<std::pair<int64_t, int32_t>> tile_groups;
   std::vector<int32_t> share_start, share_base, share_k, share_ml, share_nc, member_rows, shared_tiles, qrow_of, groups, grp_members;
+  std::vector<int32_t> rtile_order;                          // LIPs whose tokens go to row tiles, longest file first
+  std::vector<std::pair<int32_t, int32_t>> tile_lens;        // (steps over the keys, how many such tiles)
   std::vector<int32_t> rows_tmp, row_lip, seg_tmp, item_order, item_bin, bin_first, wave_pos;
   std::vector<int64_t> bin_load;
   std::vector<std::pair<int64_t, int32_t>> bin_heap;
@@ -112,6 +126,9 @@ struct DescParams {
   // order of a launch with tiles and decode bins, in percent of the tile groups: `mix_lead` tile groups first, then
   // all decode groups spread evenly among the next `mix_spread`, then the other tile groups
   int32_t mix_lead = 0, mix_spread = 50;
+  int32_t row_tile_rows = 0;  // fp32 storage: query rows of a row tile (0 = none); LIPs with >= prefill_min new tokens use them
+  int32_t cus = 256;          // compute units: what the tiles of a small batch should fill
+  int64_t max_words = 0x7fffffff;   // words the descriptor may take; tiles are not cut into key chunks beyond it
   int32_t share_tiles = 512;  // shared prefixes are cut by key chunk (up to 8 chunks) until the batch has about this many tiles
 };
 

@@ -1532,6 +1532,270 @@ __global__ __launch_bounds__(128, 2) void decode_pair_kernel(DecodeArgs da) {
 }
 
 // ---------------------------------------------------------------------------------------
+// Row tiles: several new tokens of a LIP in fp32 storage (prompts, chunks of prompts, drafts) on the fp32 matrix cores.
+// A workgroup = 32 query rows (32 / G tokens x G heads of one kv head) as two column tiles of 16; its eight wavefronts take
+// every eighth page of the file each, on their own, and their results are combined through LDS at the end, so that even a
+// prompt of a few hundred tokens gives every compute unit a short chain.  Per page and wavefront, everything transposed as in
+// the bf16 kernels (a lane's column is its query row):
+//   S^T[16 tokens][16 rows] = K · Q^T     16 x v_mfma_f32_16x16x4_f32: step s, lane group g supplies dim 16 g + s, so a lane
+//                                          reads 64 consecutive bytes of one token's K row, and Q sits in 16 registers
+//   O^T[64 dims][16 rows]  += V^T · P^T   4 steps x 4 dim blocks: step v, lane group g supplies token 4 g + v, which is the
+//                                          token whose score the lane holds in register v; block d holds dims 4 i + d, so a
+//                                          lane reads 16 consecutive bytes of V per token
+// Both operands come straight from global memory in whole 1 KiB wavefront loads: no LDS in the loop, no barrier, no transpose.
+// V of a page is requested before its scores are computed and K of the next page after them, so one set of registers each
+// is enough and four wavefronts fit on a SIMD (<= 128 registers).  Bound: fp32 matrix cores (a page costs a wavefront 64 MFMAs
+// of 32 cycles for 8 KiB of K/V).  All sums and weights are fp32.  Measured, whole calls: four prompts of 64..512 tokens on new
+// files, 8 heads: 543 -> 27 us (as rows of the vector-unit kernel: 67 us of kernel that re-read the file per token, and 0.6 ms of
+// planning for 13 500 ranges); 8 prompts of 400..500 tokens on 500, 16 query heads: 1232 -> 133 us (80 of 157 TFLOP/s).
+// ---------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(4))) float f32x4v_t;
+constexpr int kRowTileWaves = 8;
+constexpr int kRowTileRows = 32;
+constexpr int kRowTileStride = 68;            // floats per row of the exchange buffer: 64 dims + 4 (16-byte stores of 16 rows hit all banks)
+
+template <int G>
+__global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(PrefillArgs a) {
+  __shared__ __align__(16) float xch[kRowTileWaves / 2][kRowTileRows][kRowTileStride];
+  __shared__ float stat[kRowTileWaves][kRowTileRows][2];          // (max, sum) per wavefront and row
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int col = lane & 15, grp = lane >> 4;
+  const int32_t* t = a.rtiles + (int64_t)blockIdx.x * 8;
+  auto sload = [&](const int32_t* ptr) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*ptr); };
+  const int32_t* tbl = a.pt + sload(t + 0);
+  const int vis0 = sload(t + 1), qrow = sload(t + 2), count = sload(t + 3), head = sload(t + 4);
+  const int page0 = sload(t + 5), page1 = sload(t + 6), dest = sload(t + 7);
+  const int kv_end = vis0 + count - 1;                             // tokens the tile's last row sees
+  const bool two = count * G > 16;                                 // the second column tile holds rows
+
+  float q[2][16];
+  int vis[2];
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct) {
+    const int rho = ct * 16 + col;
+    const int tl = min(rho / G, count - 1);                        // rows past the last token repeat it (never written)
+    vis[ct] = vis0 + tl;
+    const f32x4v_t* qp = (const f32x4v_t*)((const uint8_t*)a.q + ((int64_t)(qrow + tl) * a.Hq + head * G + rho % G) * kRowBytes + grp * 64);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x4v_t x = qp[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[ct][4 * i + e] = x[e];
+    }
+  }
+  f32x4v_t O[2][4];
+  float m[2], l[2];
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct) {
+    m[ct] = -1e30f;
+    l[ct] = 0.f;
+#pragma unroll
+    for (int db = 0; db < 4; ++db) O[ct][db] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+  }
+
+  const uint8_t* slab = a.pool + (int64_t)head * kSlab;
+  const int k_off = (grp >> 1) * (kP * kHalfBytes) + col * kHalfBytes + (grp & 1) * 64;        // token col, dims 16 grp .. +15
+  const int v_off = kBlk + (col >> 3) * (kP * kHalfBytes) + (4 * grp) * kHalfBytes + (col & 7) * 16;   // tokens 4 grp + v, dims 4 col .. +3
+  f32x4v_t kk[4], vv[4];
+  int p = page0 + wv;
+  int pid = p < page1 ? sload(tbl + p) : 0;                        // a wavefront without pages: page 0, loaded and never used
+  {
+    const f32x4v_t* kp = (const f32x4v_t*)(slab + (int64_t)pid * a.page_bytes + k_off);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kk[i] = kp[i];
+  }
+  for (; p < page1; p += kRowTileWaves) {
+    const uint8_t* base = slab + (int64_t)pid * a.page_bytes;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) vv[v] = *(const f32x4v_t*)(base + v_off + v * kHalfBytes);
+    pid = p + kRowTileWaves < page1 ? sload(tbl + p + kRowTileWaves) : 0;
+    // eight sums of 8 products each, added up as a tree: one chain of 64 would round three times as coarsely as the
+    // vector units' eight lanes per score
+    f32x4v_t S[2];
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+      auto part = [&](int u) __attribute__((always_inline)) {
+        f32x4v_t x = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1)], q[ct][2 * u], f32x4v_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1) + 1], q[ct][2 * u + 1], x, 0, 0, 0);
+      };
+      if (ct == 0 || two) {
+        S[ct] = (part(0) + part(1)) + (part(2) + part(3));
+        __builtin_amdgcn_sched_barrier(0);       // (all eight at once would not fit the registers)
+        S[ct] = S[ct] + ((part(4) + part(5)) + (part(6) + part(7)));
+      } else {
+        S[ct] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    {
+      const f32x4v_t* kp = (const f32x4v_t*)(slab + (int64_t)pid * a.page_bytes + k_off);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kk[i] = kp[i];
+    }
+    const int tok = p * kP + 4 * grp;                              // the lane's first token of the page
+    if ((p + 1) * kP > vis0) {                                     // the causal edge of some row, or the end of the file
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) S[ct][v] = tok + v < vis[ct] ? S[ct][v] : -__builtin_inff();
+      // slots past the file's end may hold anything; their weight is 0, but 0 * NaN is NaN
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (tok + v >= kv_end) vv[v] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+      if (ct == 1 && !two) break;
+      const float mx = fmaxf(fmaxf(S[ct][0], S[ct][1]), fmaxf(S[ct][2], S[ct][3])) * a.scale_log2e;
+      if (__builtin_amdgcn_ballot_w64(mx > m[ct] + kTau) != 0) {   // rare after the first page
+        const float mn = pair32_max(pair16_max(fmaxf(m[ct], mx))); // the four lane groups of a row agree
+        const float al = __builtin_amdgcn_exp2f(m[ct] - mn);
+        l[ct] *= al;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) O[ct][db][v] *= al;
+        m[ct] = mn;
+      }
+      float pw[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        pw[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[ct][v], a.scale_log2e, -m[ct]));
+        l[ct] += pw[v];
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int db = 0; db < 4; ++db) O[ct][db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[v][db], pw[v], O[ct][db], 0, 0, 0);
+    }
+  }
+
+  // combine the eight wavefronts: common maximum per row, everyone's accumulators rescaled to it, added up in two stages
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct) {
+    l[ct] = pair32_sum(pair16_sum(l[ct]));
+    if (grp == 0) {
+      stat[wv][ct * 16 + col][0] = m[ct];
+      stat[wv][ct * 16 + col][1] = l[ct];
+    }
+  }
+  __syncthreads();
+  auto row_max = [&](int row) {
+    float M = stat[0][row][0];
+#pragma unroll
+    for (int w = 1; w < kRowTileWaves; ++w) M = fmaxf(M, stat[w][row][0]);
+    return M;
+  };
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct) {
+    const float f = __builtin_amdgcn_exp2f(m[ct] - row_max(ct * 16 + col));
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) O[ct][db][v] *= f;
+  }
+  // lane's values of column tile ct, register v: dims 16 grp + 4 v .. +3 (one per dim block)
+  auto cell = [&](int w, int ct, int v) { return (f32x4v_t*)&xch[w][ct * 16 + col][16 * grp + 4 * v]; };
+  if (wv >= kRowTileWaves / 2) {
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) *cell(wv - kRowTileWaves / 2, ct, v) = f32x4v_t{O[ct][0][v], O[ct][1][v], O[ct][2][v], O[ct][3][v]};
+  }
+  __syncthreads();
+  if (wv < kRowTileWaves / 2) {
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        f32x4v_t* c = cell(wv, ct, v);
+        *c = *c + f32x4v_t{O[ct][0][v], O[ct][1][v], O[ct][2][v], O[ct][3][v]};
+      }
+  }
+  __syncthreads();
+  const int row = threadIdx.x >> 4, d0 = (threadIdx.x & 15) * 4;   // 32 rows x 64 dims, four dims per thread
+  const int tl = row / G, h = row % G;
+  if (tl >= count) return;
+  f32x4v_t o = *(const f32x4v_t*)&xch[0][row][d0];
+#pragma unroll
+  for (int w = 1; w < kRowTileWaves / 2; ++w) o = o + *(const f32x4v_t*)&xch[w][row][d0];
+  const float M = row_max(row);
+  float L = 0.f;
+#pragma unroll
+  for (int w = 0; w < kRowTileWaves; ++w) L = __builtin_fmaf(stat[w][row][1], __builtin_amdgcn_exp2f(stat[w][row][0] - M), L);
+  if (dest < 0) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = o[e] / L;
+    *(f32x4v_t*)(a.out + ((int64_t)(qrow + tl) * a.Hq + head * G + h) * 64 + d0) = o;
+  } else {
+    const int64_t slot = (int64_t)(dest + tl) * G + h;
+    *(f32x4v_t*)(a.part_acc + slot * 64 + d0) = o;
+    if (d0 == 0) {
+      a.part_ml[slot * 2 + 0] = M;
+      a.part_ml[slot * 2 + 1] = L;
+    }
+  }
+}
+
+// Partials of tiles whose keys were cut into chunks, one wavefront per (token, kv head): the chunks of a token lie `count`
+// slots apart.  Four chunks' loads are in flight together, as in merge_kernel.
+template <int G, int D>
+__global__ __launch_bounds__(kWavesPerBlock * 64) void tile_merge_kernel(MergeArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int32_t* it = a.tile_items + (int64_t)blockIdx.x * 4;
+  const int first = __builtin_amdgcn_readfirstlane(it[0]), chunks = __builtin_amdgcn_readfirstlane(it[1]);
+  const int count = __builtin_amdgcn_readfirstlane(it[2]), qh = __builtin_amdgcn_readfirstlane(it[3]);
+  const int tl = __builtin_amdgcn_readfirstlane((int)(blockIdx.y * kWavesPerBlock + (threadIdx.x >> 6)));
+  if (tl >= count) return;
+  constexpr int VL = G * D / 64;
+  float M[G], ls[G], o[VL];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    M[h] = -__builtin_inff();
+    ls[h] = 0.f;
+  }
+#pragma unroll
+  for (int e = 0; e < VL; ++e) o[e] = 0.f;
+  for (int c0 = 0; c0 < chunks; c0 += 4) {
+    float mv[4][G], lv[4][G], t[4][VL];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t ii = first + (int64_t)min(c0 + u, chunks - 1) * count + tl;
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        mv[u][h] = a.part_ml[(ii * G + h) * 2];
+        lv[u][h] = a.part_ml[(ii * G + h) * 2 + 1];
+      }
+#pragma unroll
+      for (int e = 0; e < VL; ++e) t[u][e] = a.part_acc[ii * G * D + e * 64 + lane];
+    }
+    float w[4][G], sc[G];
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const float mn = fmaxf(fmaxf(fmaxf(mv[0][h], mv[1][h]), fmaxf(mv[2][h], mv[3][h])), M[h]);
+      sc[h] = __builtin_amdgcn_exp2f(M[h] - mn);      // 0 for the first group (M = -inf)
+      M[h] = mn;
+      ls[h] *= sc[h];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        w[u][h] = c0 + u < chunks ? __builtin_amdgcn_exp2f(mv[u][h] - mn) : 0.f;
+        ls[h] = __builtin_fmaf(lv[u][h], w[u][h], ls[h]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < VL; ++e) {
+      o[e] *= sc[(e * 64) / D];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) o[e] = __builtin_fmaf(t[u][e], w[u][(e * 64) / D], o[e]);
+    }
+  }
+  float* out = a.out + ((int64_t)qh + (int64_t)tl * a.Hq) * D + lane;
+#pragma unroll
+  for (int e = 0; e < VL; ++e) out[e * 64] = o[e] / ls[(e * 64) / D];
+}
+
+// ---------------------------------------------------------------------------------------
 // Merge of partial results, one wavefront per (row, kv head) that was cut:
 //   out = sum_i acc_i 2^(m_i - M) / sum_i l_i 2^(m_i - M),  M = max_i m_i.
 // The G*D accumulator values of a piece form one flat list; lane owns entries e*64 + lane.  All
@@ -1890,12 +2154,40 @@ hipError_t static_scratch_address(int device, uint8_t** ptr) {
 }
 
 hipError_t launch_attn(const DecodeArgs& da, const PrefillArgs& pa, int dtype, int decode_mode, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  if (pa.n_rtiles > 0) {
+    if (dtype != 0) return hipErrorInvalidValue;
+    const bool last = da.n_waves <= 0;
+    const dim3 grid((unsigned)pa.n_rtiles), block(64 * kRowTileWaves);
+    const hipEvent_t e1 = last ? ev1 : nullptr;
+#define SYM_ROW_TILE_CASE(GG) \
+  case GG: \
+    if (ev0 || e1) hipExtLaunchKernelGGL(row_tile_kernel<GG>, grid, block, 0, st, ev0, e1, 0, pa); \
+    else hipLaunchKernelGGL(row_tile_kernel<GG>, grid, block, 0, st, pa); \
+    break;
+    switch (da.Hq / da.Hkv) {
+      SYM_ROW_TILE_CASE(1) SYM_ROW_TILE_CASE(2) SYM_ROW_TILE_CASE(4) SYM_ROW_TILE_CASE(8)
+      default: return hipErrorInvalidValue;
+    }
+#undef SYM_ROW_TILE_CASE
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || last) return e;
+    ev0 = nullptr;
+  }
   if (da.n_waves <= 0 && pa.n_tiles <= 0) return hipSuccess;
   if (dtype == 0) return pa.n_tiles > 0 ? hipErrorInvalidValue : launch_attn_g<ElemF32>(da, pa, 0, st, ev0, ev1);
   return launch_attn_g<ElemBF16>(da, pa, decode_mode, st, ev0, ev1);
 }
 
 hipError_t launch_merge(const MergeArgs& a, int G, int D, hipStream_t st) {
+  if (a.n_tile_items > 0) {
+    const dim3 tgrid((unsigned)a.n_tile_items, (unsigned)((a.tile_tokens + kWavesPerBlock - 1) / kWavesPerBlock));
+#define SYM_TILE_MERGE_CASE(GG, DD) \
+  if (G == GG && D == DD) hipLaunchKernelGGL((tile_merge_kernel<GG, DD>), tgrid, dim3(kWavesPerBlock * 64), 0, st, a);
+    SYM_TILE_MERGE_CASE(1, 64) SYM_TILE_MERGE_CASE(2, 64) SYM_TILE_MERGE_CASE(4, 64) SYM_TILE_MERGE_CASE(8, 64)
+#undef SYM_TILE_MERGE_CASE
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   if (a.n_items <= 0) return hipSuccess;
   const dim3 grid((a.n_items + kWavesPerBlock - 1) / kWavesPerBlock), block(kWavesPerBlock * 64);
 #define SYM_MERGE_CASE(GG, DD) \

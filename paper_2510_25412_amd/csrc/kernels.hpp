@@ -52,6 +52,10 @@ struct PrefillArgs {
   int32_t small_shared_only;     // every tile is a shared-prefix tile of at most 64 query rows (members x heads per kv head)
   const int32_t* group_map;      // a launch with tiles and decode bins: per group of 8 workgroups, tile group g or ~(decode group)
   int32_t n_groups;
+  // row tiles (fp32 storage, a launch of their own): a few consecutive new tokens of a LIP x one kv head
+  const int32_t* rtiles;         // [n_rtiles][8]: page-table offset, tokens the first row sees, its q/out row, tokens, kv head,
+                                 //   first page, end page, first partial slot (-1: the final output rows)
+  int32_t n_rtiles;
 };
 
 struct MergeArgs {
@@ -61,6 +65,10 @@ struct MergeArgs {
                             //   pieces of a shared prefix: first, stride, count; 0, 0
   float* out;
   int32_t n_items;
+  // tiles whose keys were cut into chunks (a launch of their own)
+  const int32_t* tile_items;   // [n_tile_items][4]: first partial (chunk c, token t: first + c * tokens + t), chunks, tokens,
+                               //   q row * Hq + first head of its first token
+  int32_t n_tile_items, tile_tokens, Hq;   // ... and the most tokens one of them holds
 };
 
 struct PrologueArgs {

@@ -314,6 +314,25 @@ def test_prefill_chunk_equals_sequential():
     sess2.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 4), (8, 2), (8, 1), (1, 1)])
+def test_fp32_row_tiles(Hq, Hkv):
+    """Several new tokens per LIP in fp32 storage (row tiles: 32 / G tokens x one kv head, every eighth page per
+    wavefront): counts around a column tile and a tile, empty files, ragged last pages, files of fewer pages than
+    wavefronts, single-token LIPs beside them, and contexts long enough to be cut into key chunks.  fp32 sums of at
+    most 64 products of N(0, 1) values and weights of exponentials of them: 1e-5, as for the fp32 decode rows."""
+    shape = synth.Shape(Hq, Hkv, 64, 16, synth.F32)
+    G = Hq // Hkv
+    new = [2, 3, 16 // G + 1, 32 // G, 32 // G + 1, 33, 70, 1, 5]
+    old = [0, 15, 16, 100, 1, 0, 129, 40, 127]
+    for files, batch in (([("new", n) for n in old], list(enumerate(new))),
+                         ([("new", 5000), ("new", 33)], [(0, 7), (1, 2)]), ([("new", 3000)], [(0, 40)])):
+        wl = synth.custom("fp32_tiles", shape, files, batch, 600, seed=77 + Hq + Hkv)
+        got, sess, ref, osess = run_both(wl)
+        check_outputs(got, ref, tol=1e-5)
+        check_state(wl, sess, osess)
+        sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(32, 8), (64, 8), (8, 8)])
 def test_shared_prefix_groups(Hq, Hkv):
     """Forks of a prefix decode through the shared-prefix tiles (prefix pages read once per
