@@ -369,8 +369,9 @@ int sym_plan_copies_first(sym_ctx* ctx);
  *   tiles     [n_tiles][12] page-table offset, file length before the call, first q/out row
  *                           (shared: offset into the member list), new tokens (shared: members)
  *                           in the tile, kv head, token offset in the chunk (shared: first
- *                           partial slot), kind (0 prefill chunk, 1 shared prefix), first page,
- *                           end page, 0, 0, 0; ordered share by share
+ *                           partial slot), kind (0 prefill chunk, 1 shared prefix, 2 prefill chunk over
+ *                           part of its keys), first page, end page, first partial slot of
+ *                           kind 2, 0, 0; ordered share by share
  *   members   [n_members]   q rows of the members of shared-prefix tiles
  *   rtiles    [n_rtiles][8]  (fp32) page-table offset, tokens the tile's first row sees, its q/out
  *                           row, tokens, kv head, first page, end page, first partial slot (-1: the

@@ -13,6 +13,9 @@ namespace {
 // long one would be the batch's tail.  lens: (steps of a tile, number of such tiles).  A batch of `rounds` workgroups per
 // slot, all of b steps, ends after rounds * (b + start) steps; b is the smallest size with which the pieces fit into that many
 // slots.  Cutting costs a partial result per row and chunk and a merge launch (`merge` steps).  0 = leave the tiles whole.
+// bf16, 32 query / 8 kv heads, whole calls cut / whole: 512 tokens on 8000: 102 / 276 us; 64 on 60 000: 100 / 1820; 32 on
+// 2000: 25 / 61; three prompts of 100..700 on 200..4000: 76 / 117; 1024 on nothing: 43 / 53; 512 on nothing stays whole
+// (36.1 / 35.5).
 int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_t slots, int64_t start, int64_t merge, int64_t max_chunks, int64_t unit) {
   int64_t n = 0, longest = 0, total = 0;
   for (auto& t : lens) {
@@ -45,6 +48,8 @@ int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_
   }
   return b_best;
 }
+// bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch
+constexpr int64_t kTileStart = 6, kTileMerge = 11;
 }  // namespace
 
 int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, const int64_t* len_after,
@@ -242,6 +247,42 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       count_rtiles();
     }
     chunk_budget -= n_chunk_partials;
+  }
+
+  // ---- prefill tiles of a small batch: their keys are cut into chunks until the batch fills the compute units.  A step
+  // is a block of 32 keys; a tile of 256 rows has a compute unit to itself, two of 128 rows share one.
+  int64_t bsteps = 0, n_btile_split = 0, n_btile_extra = 0, n_btile_partials = 0;
+  auto bblocks = [&](int32_t b, int32_t t0) { return (int32_t)((len_after[b] - n_tokens[b] + std::min(t0 + TQ, n_tokens[b]) + 31) / 32); };
+  auto bchunks = [&](int32_t blocks) { return bsteps > 0 ? (blocks + (int32_t)bsteps - 1) / (int32_t)bsteps : 1; };
+  auto count_btiles = [&]() {
+    n_btile_split = n_btile_extra = n_btile_partials = 0;
+    if (bsteps == 0) return;
+    for (int32_t b = 0; b < n_lips; ++b) {
+      if (!is_prefill(b) || is_rtile(b)) continue;
+      for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += TQ) {
+        const int32_t nc = bchunks(bblocks(b, t0));
+        if (nc == 1) continue;
+        n_btile_split += H;
+        n_btile_extra += (int64_t)(nc - 1) * H;
+        n_btile_partials += (int64_t)nc * H * std::min(TQ, n_tokens[b] - t0);
+      }
+    }
+  };
+  if (any_prefill) {
+    const int64_t slots = (int64_t)prm.cus * (TQ * G == 256 ? 1 : 2);
+    if (n_tiles - n_shared_tiles <= 3 * slots) {
+      auto& lens = out->tile_lens;
+      lens.clear();
+      for (int32_t b = 0; b < n_lips; ++b)
+        if (is_prefill(b) && !is_rtile(b))
+          for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += TQ) lens.emplace_back(bblocks(b, t0), H);
+      bsteps = chunk_steps(lens, slots, kTileStart, kTileMerge, 64, 3);      // the block loop is unrolled by three
+      count_btiles();
+      if (n_btile_partials > chunk_budget) {
+        bsteps = 0;
+        count_btiles();
+      }
+    }
   }
 
   // ---- units of the decode kernel
@@ -455,6 +496,20 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   const int64_t off_pt = off_merge + merge_cap * MERGE_WORDS;
   const int64_t off_ptoff = off_pt + entries;
   const int64_t off_tiles = off_ptoff + n_lips + 1;
+  {
+    // words without and with the tiles' chunks (a tile record and a place in the order table each, a merge entry per tile)
+    const int64_t base = off_tiles + n_tiles * TILE_WORDS + n_members + (bins ? (n_segs + 2) * SEG_WORDS + n_bins * LMERGE_WORDS : 0) +
+                         ((bins && n_tiles > 0) ? n_tiles + (n_bins + 7) / 8 : 0);
+    if (rsteps > 0 && base + n_rtiles * RTILE_WORDS + n_rtile_split * TMERGE_WORDS > prm.max_words) {
+      rsteps = 0;                                 // no room for the chunks: whole tiles
+      count_rtiles();
+    }
+    if (bsteps > 0 && base + n_btile_extra * (TILE_WORDS + 1) + n_btile_split * TMERGE_WORDS > prm.max_words) {
+      bsteps = 0;
+      count_btiles();
+    }
+    n_tiles += n_btile_extra;
+  }
   const int64_t off_members = off_tiles + n_tiles * TILE_WORDS;
   const int64_t off_segs = off_members + n_members;
   const int64_t off_lmerge = off_segs + (bins ? (n_segs + 2) * SEG_WORDS : 0);       // two spare records: the kernel looks ahead
@@ -462,12 +517,8 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   const int64_t off_groups = off_lmerge + (bins ? n_bins * LMERGE_WORDS : 0);
   const int64_t groups_cap = (bins && n_tiles > 0) ? n_tiles + (n_bins + 7) / 8 : 0;
   const int64_t off_rtiles = off_groups + groups_cap;
-  if (off_rtiles + n_rtiles * RTILE_WORDS + n_rtile_split * TMERGE_WORDS > prm.max_words && rsteps > 0) {
-    rsteps = 0;                                   // no room for the chunks: whole tiles
-    count_rtiles();
-  }
   const int64_t off_tmerge = off_rtiles + n_rtiles * RTILE_WORDS;
-  const int64_t total = off_tmerge + n_rtile_split * TMERGE_WORDS;
+  const int64_t total = off_tmerge + (n_rtile_split + n_btile_split) * TMERGE_WORDS;
   if (total > 0x7fffffff) return SYM_EINVAL;
   int32_t* const w = out->alloc ? out->alloc(total) : nullptr;   // the caller's buffer (pinned staging memory on the GPU path)
   if (!w) return SYM_ENOSPC;
@@ -481,6 +532,9 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   int32_t* ptoff = w + off_ptoff;
   int32_t* tiles = w + off_tiles;
   int64_t e = 0, tok = 0, ti = 0;
+  int32_t n_tmerge = 0, tmerge_tokens = 0;                // tiles cut into key chunks
+  int32_t* tm_next = w + off_tmerge;
+  int64_t n_btile_done = 0;                               // partials handed to chunks of prefill tiles so far
   std::vector<int32_t>& tok_of = out->qrow_of;             // token index of each LIP's first row
   tok_of.resize(n_lips);
   for (int32_t b = 0; b < n_lips; ++b) {
@@ -494,16 +548,35 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     if (is_prefill(b) && !is_rtile(b)) {
       // order (kv head, token tile): the tiles that read the same K/V are neighbours
       for (int32_t g = 0; g < H; ++g)
-        for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += TQ, ++ti) {
-          int32_t* t = tiles + ti * TILE_WORDS;
-          std::memset(t, 0, TILE_WORDS * sizeof(int32_t));
-          t[T_TBL] = (int32_t)e_lip;                                // page-table offset
-          t[T_LEN] = (int32_t)(len_after[b] - n_tokens[b]);         // file length before the call
-          t[T_QROW] = (int32_t)(tok + t0);                          // q / out row of the tile's first token
-          t[T_COUNT] = std::min<int32_t>(TQ, n_tokens[b] - t0);     // tokens in the tile
-          t[T_HEAD] = g;
-          t[T_AUX] = t0;                                            // token offset inside the chunk
-          t[T_KIND] = TILE_PREFILL;
+        for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += TQ) {
+          const int32_t blocks = bblocks(b, t0), nc = bchunks(blocks), per = ((blocks + nc - 1) / nc + 2) / 3 * 3;
+          const int32_t count = std::min<int32_t>(TQ, n_tokens[b] - t0);
+          for (int32_t c = 0; c < nc; ++c, ++ti) {
+            int32_t* t = tiles + ti * TILE_WORDS;
+            std::memset(t, 0, TILE_WORDS * sizeof(int32_t));
+            t[T_TBL] = (int32_t)e_lip;                                // page-table offset
+            t[T_LEN] = (int32_t)(len_after[b] - n_tokens[b]);         // file length before the call
+            t[T_QROW] = (int32_t)(tok + t0);                          // q / out row of the tile's first token
+            t[T_COUNT] = count;                                       // tokens in the tile
+            t[T_HEAD] = g;
+            t[T_AUX] = t0;                                            // token offset inside the chunk
+            t[T_KIND] = nc > 1 ? TILE_CHUNK : TILE_PREFILL;
+            if (nc > 1) {
+              t[T_PAGE0] = 2 * std::min(c * per, blocks);
+              t[T_PAGE1] = 2 * std::min((c + 1) * per, blocks);
+              t[T_DEST] = (int32_t)(n_btile_done + (int64_t)c * count);      // + the first of these partials, added below
+            }
+          }
+          if (nc > 1) {
+            tm_next[TM_FIRST] = (int32_t)n_btile_done;
+            tm_next[TM_CHUNKS] = nc;
+            tm_next[TM_COUNT] = count;
+            tm_next[TM_QROW] = (int32_t)(tok + t0) * prm.n_q_heads + g * G;
+            tm_next += TMERGE_WORDS;
+            ++n_tmerge;
+            tmerge_tokens = std::max(tmerge_tokens, count);
+            n_btile_done += (int64_t)nc * count;
+          }
         }
     }
     tok += n_tokens[b];
@@ -717,11 +790,16 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   }
   // ---- row tiles, longest first; the kv heads of a token tile are neighbours, so that with 8 of them (workgroup b runs on
   // XCD b % 8) the tiles that read one (file, kv head) share an L2
-  int32_t n_tmerge = 0, tmerge_tokens = 0;
+  if (n_btile_partials > 0) {                            // the partials of the prefill tiles' chunks follow those of the shared prefixes
+    const int32_t first = shared_base + (int32_t)n_shared_partials;
+    for (int64_t i = 0; i < n_tiles; ++i)
+      if (tiles[i * TILE_WORDS + T_KIND] == TILE_CHUNK) tiles[i * TILE_WORDS + T_DEST] += first;
+    for (int32_t i = 0; i < n_tmerge; ++i) w[off_tmerge + (int64_t)i * TMERGE_WORDS + TM_FIRST] += first;
+  }
   if (!rorder.empty()) {
     int32_t* rt = w + off_rtiles;
-    int32_t* tm = w + off_tmerge;
-    int64_t chunk_base = shared_base + n_shared_partials;
+    int32_t* tm = tm_next;
+    int64_t chunk_base = shared_base + n_shared_partials + n_btile_partials;
     int32_t* rr = rows + n_rows * ROW_WORDS;
     for (int32_t b : rorder) {
       const int32_t len0 = (int32_t)(len_after[b] - n_tokens[b]), tok0 = tok_of[b];
@@ -765,9 +843,11 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     for (int x = 0; x <= 8; ++x) xo[x] = 0;
     if (n_tiles > 0) {
       auto cost = [&](const int32_t* t) -> int64_t {
-        return t[T_KIND] == TILE_SHARED ? (t[T_PAGE1] - t[T_PAGE0] + 1) / 2 + 1
+        return t[T_KIND] != TILE_PREFILL ? (t[T_PAGE1] - t[T_PAGE0] + 1) / 2 + 1
                                         : ((int64_t)t[T_LEN] + t[T_AUX] + t[T_COUNT] + 31) / 32 + 1;
       };
+      // A batch whose tiles were cut into chunks fills the chip in a known number of rounds of about equal pieces: shares of
+      // equal COUNT, neighbours (same keys) together.  Otherwise shares of equal cost:
       // groups = runs of tiles with the same page table and kv head, split so that none exceeds 1/16 of the work
       int64_t total = 0;
       for (int64_t i = 0; i < n_tiles; ++i) total += cost(tiles + i * TILE_WORDS);
@@ -777,7 +857,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       int64_t acc = 0;
       for (int64_t i = 0; i < n_tiles; ++i) {
         const int32_t* t = tiles + i * TILE_WORDS;
-        const bool same = i > 0 && t[T_TBL] == t[-TILE_WORDS + T_TBL] && t[T_HEAD] == t[-TILE_WORDS + T_HEAD] && t[T_KIND] == t[-TILE_WORDS + T_KIND];
+        const bool same = bsteps == 0 && i > 0 && t[T_TBL] == t[-TILE_WORDS + T_TBL] && t[T_HEAD] == t[-TILE_WORDS + T_HEAD] && t[T_KIND] == t[-TILE_WORDS + T_KIND];
         if (!same || acc >= cap) {
           groups.emplace_back(0, (int32_t)i);
           acc = 0;
@@ -789,14 +869,16 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       auto& order = out->tile_order;                      // group indices, heaviest first
       order.resize(ng);
       for (size_t i = 0; i < ng; ++i) order[i] = (int32_t)i;
-      std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return groups[x].first > groups[y].first; });
+      if (bsteps == 0) std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return groups[x].first > groups[y].first; });
       int64_t load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       std::vector<int32_t> share_of(ng);
       int32_t count[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       for (int32_t gi : order) {
         int best = 0;
-        for (int x = 1; x < 8; ++x)
-          if (load[x] < load[best]) best = x;
+        if (bsteps > 0) best = (int)((int64_t)gi * 8 / (int64_t)ng);
+        else
+          for (int x = 1; x < 8; ++x)
+            if (load[x] < load[best]) best = x;
         share_of[gi] = best;
         load[best] += groups[gi].first;
         const int32_t gend = (size_t)gi + 1 < ng ? groups[gi + 1].second : (int32_t)n_tiles;
@@ -855,7 +937,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       }
     }
   }
-  const int32_t n_partials = shared_base + (int32_t)(n_shared_partials + n_chunk_partials);
+  const int32_t n_partials = shared_base + (int32_t)(n_shared_partials + n_btile_partials + n_chunk_partials);
   if (n_partials > prm.max_partials) return SYM_ENOSPC;
 
   w[H_N_ROWS] = (int32_t)(n_rows + n_rrows);

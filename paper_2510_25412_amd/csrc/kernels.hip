@@ -835,7 +835,8 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   if (tile >= a.xcd_off[block % 8 + 1]) return;
   const int32_t* tw = a.tiles + (int64_t)(a.tile_first + tile) * 12;
   const int tbl_off = tw[0], g = tw[4], count = tw[3];
-  const bool shared = tw[6] != 0;
+  const bool shared = tw[6] == 1;
+  const bool partial = tw[6] != 0;               // shared prefixes and key chunks leave partials
   const int32_t* tbl = a.pt + tbl_off;
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -844,9 +845,11 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   // tokens 0 .. L + t0 + tl.  shared prefix: `count` decode rows (q rows in the member list) that
   // all see the same full pages [page0, page1) of the group's first file.
   const int L = tw[1], t0 = tw[5];
-  const int kv_end = shared ? tw[8] * kP : L + t0 + count;       // tokens the tile's last row sees
-  const int mask_from = shared ? kv_end : L + t0 + 1;            // first token some row may not see
-  const int kb0 = shared ? tw[7] / 2 : 0;                        // first 32-token block (page0 is even)
+  // key chunk of a prefill tile: the same rows over the blocks of pages [page0, page1) only (some rows may see none of them)
+  const int lim = partial ? tw[8] * kP : 0x7fffffff;
+  const int kv_end = shared ? lim : min(L + t0 + count, lim);    // tokens the tile's last row sees
+  const int mask_from = shared ? lim : min(L + t0 + 1, lim);     // first token some row may not see
+  const int kb0 = partial ? tw[7] / 2 : 0;                       // first 32-token block (page0 is even)
   const int nblk = (kv_end + kKvBlock - 1) / kKvBlock;
   const int last_page = max((kv_end + kP - 1) / kP - 1, 0);
   // A shared-prefix tile of four wavefronts with at most 64 live rows would keep two of them busy, each alone
@@ -872,7 +875,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
     h[ct] = rho % G;
     const int tlc = min(tl[ct], count - 1);        // rows past the tile's last token/member repeat it (never written)
     qrow[ct] = shared ? a.members[tw[2] + tlc] : tw[2] + tlc;
-    vis[ct] = shared ? kv_end : L + t0 + tlc + 1;  // tokens this row sees
+    vis[ct] = shared ? kv_end : min(L + t0 + tlc + 1, lim);   // tokens this row sees
     const uint8_t* qp = (const uint8_t*)a.q + ((int64_t)qrow[ct] * a.Hq + g * G + h[ct]) * kRowBytes + hf * 16;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) q[ct][ks] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + ks * 32));
@@ -1185,7 +1188,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   for (int ct = 0; ct < CT; ++ct) {
     const float lt = l[ct] + __shfl_xor(l[ct], 32);
     if (tl[ct] < count) {
-      if (!shared) {
+      if (!partial) {
         const float inv = 1.0f / lt;
         float* o = a.out + ((int64_t)qrow[ct] * a.Hq + g * G + h[ct]) * 128 + 4 * hf;
 #pragma unroll
@@ -1194,8 +1197,8 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
           for (int vb = 0; vb < 4; ++vb)
             *(float4*)(o + db * 32 + vb * 8) = make_float4(O[ct][db][4 * vb] * inv, O[ct][db][4 * vb + 1] * inv, O[ct][db][4 * vb + 2] * inv, O[ct][db][4 * vb + 3] * inv);
       } else {
-        // partial result of member tl for the merge kernel: unnormalised accumulator, max, sum
-        const int64_t part = (int64_t)t0 + tl[ct];           // t0 = first partial slot of this tile
+        // partial result of member (or token) tl for the merge kernel: unnormalised accumulator, max, sum
+        const int64_t part = (int64_t)(shared ? t0 : tw[9]) + tl[ct];           // shared: t0 = first partial slot of this tile
         float* o = a.part_acc + (part * G + h[ct]) * 128 + 4 * hf;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -2184,6 +2187,7 @@ hipError_t launch_merge(const MergeArgs& a, int G, int D, hipStream_t st) {
 #define SYM_TILE_MERGE_CASE(GG, DD) \
   if (G == GG && D == DD) hipLaunchKernelGGL((tile_merge_kernel<GG, DD>), tgrid, dim3(kWavesPerBlock * 64), 0, st, a);
     SYM_TILE_MERGE_CASE(1, 64) SYM_TILE_MERGE_CASE(2, 64) SYM_TILE_MERGE_CASE(4, 64) SYM_TILE_MERGE_CASE(8, 64)
+    SYM_TILE_MERGE_CASE(1, 128) SYM_TILE_MERGE_CASE(2, 128) SYM_TILE_MERGE_CASE(4, 128) SYM_TILE_MERGE_CASE(8, 128)
 #undef SYM_TILE_MERGE_CASE
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

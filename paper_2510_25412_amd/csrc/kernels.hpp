@@ -37,8 +37,8 @@ struct PrefillArgs {
   float* out;               // [tokens][Hq][128]
   const int32_t* tiles;     // [n_tiles][12]: page-table offset, length before, first q/out row (or offset
                             //   into members), tokens (or members) in the tile, kv head, token offset in the
-                            //   chunk (or first partial slot), kind (0 prefill, 1 shared prefix), first page,
-                            //   end page, 0, 0, 0
+                            //   chunk (or first partial slot), kind (0 prefill, 1 shared prefix, 2 prefill
+                            //   over part of its keys), first page, end page, first partial slot of kind 2, 0, 0
   const int32_t* pt;        // flattened page tables
   const int32_t* members;   // q rows of the members of shared-prefix tiles
   float* part_acc;          // partial results (shared-prefix tiles)

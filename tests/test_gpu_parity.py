@@ -314,6 +314,23 @@ def test_prefill_chunk_equals_sequential():
     sess2.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(32, 8), (64, 8), (8, 8), (4, 1), (2, 1)])
+def test_prefill_tiles_cut_into_key_chunks(Hq, Hkv):
+    """Batches of few tiles on long files, whose tiles are cut into chunks of their keys: one token past a tile, ragged
+    ends, chunks that start inside the tile's own tokens (rows that see none of a chunk's keys), several files of
+    different lengths, and decode rows in the same launch."""
+    shape = synth.Shape(Hq, Hkv, 128, 16, synth.BF16)
+    TQ, cut = 256 * Hkv // Hq, 0
+    for files, batch in (([3001], [TQ + 1]), ([0], [1500]), ([4000, 17, 1203], [16, 700, 33]), ([2500, 600, 90], [100, 1, 1])):
+        wl = synth.custom("key_chunks", shape, [("new", n) for n in files], list(enumerate(batch)), 1200, seed=31 + Hq)
+        got, sess, ref, osess = run_both(wl)
+        check_outputs(got, ref)
+        check_state(wl, sess, osess)
+        cut += sess.ctx.get_stats()["last_batch_tiles"] > sum(-(-n // TQ) for n in batch if n > 1) * Hkv
+        sess.close()
+    assert cut >= 3
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 4), (8, 2), (8, 1), (1, 1)])
 def test_fp32_row_tiles(Hq, Hkv):
     """Several new tokens per LIP in fp32 storage (row tiles: 32 / G tokens x one kv head, every eighth page per

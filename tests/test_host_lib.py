@@ -676,6 +676,43 @@ def test_descriptor_tiles_for_prefill_chunks(tile_rows):
     assert int(w32[0]) == sum(n_tok) and int(w32[4]) == 0
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv", [("bf16", 32, 8), ("bf16", 64, 8), ("bf16", 2, 2), ("f32", 8, 8), ("f32", 8, 1)])
+def test_descriptor_key_chunks_cover_every_block_once(dtype, Hq, Hkv):
+    """Tiles of a small batch are cut into chunks of their keys: every tile's chunks tile its keys, their partials do not
+    overlap and are what the merge entry says, every share of the tile list holds about as many, and the descriptor
+    stays inside the bound that the workspace is sized for."""
+    D, G = (128 if dtype == "bf16" else 64), Hq // Hkv
+    c = host_ctx(1 << 14, Hq=Hq, Hkv=Hkv, D=D, dtype=dtype)
+    cut = 0
+    for lengths, n_tok in (([6000], [100]), ([5000, 40, 3000], [65, 16, 300]), ([900] * 3, [200, 1, 350]), ([8192], [8192]), ([30000], [17])):
+        np_l = [-(-L // 16) for L in lengths]
+        off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+        w = c.build_desc(n_tok, np.arange(sum(np_l), dtype=np.int32) % (1 << 14), off, lengths)
+        cfg = binding.make_config(Hq, Hkv, D, 16, dtype, 1 << 14)
+        assert len(w) * 4 <= binding.workspace_bytes(cfg, len(n_tok), sum(n_tok), sum(np_l)) - 4 * int(w[2]) * G * 2
+        tm = w[w[42]:w[42] + 4 * w[41]].reshape(-1, 4)
+        if dtype == "bf16":
+            t = w[w[10]:w[10] + 12 * w[4]].reshape(-1, 12)
+            recs = [(int(x[2]) * Hq + int(x[4]) * G, int(x[3]), int(x[7]), int(x[8]), int(x[9]), (int(x[1]) + int(x[5]) + int(x[3]) + 31) // 32 * 2) for x in t if x[6] == 2]
+            xo = w[20:29]
+            assert not recs or max(np.diff(xo)) <= -(-int(w[4]) // 8)
+        else:
+            t = w[w[40]:w[40] + 8 * w[39]].reshape(-1, 8)
+            recs = [(int(x[2]) * Hq + int(x[4]) * G, int(x[3]), int(x[5]), int(x[6]), int(x[7]), (int(x[1]) + int(x[3]) - 1 + 15) // 16) for x in t if x[7] >= 0]
+        assert len({r[0] for r in recs}) == len(tm)
+        used = []
+        for first, chunks, count, q in tm.tolist():
+            mine = sorted((r for r in recs if r[0] == q), key=lambda r: r[4])
+            assert len(mine) == chunks and all(r[1] == count for r in mine)
+            assert [r[4] for r in mine] == [first + i * count for i in range(chunks)]
+            assert mine[0][2] == 0 and mine[-1][3] == mine[-1][5] and all(a[3] == b[2] for a, b in zip(mine, mine[1:]))
+            assert all(r[2] % 2 == 0 for r in mine) or dtype == "f32"
+            used += range(first, first + chunks * count)
+        assert len(set(used)) == len(used) and (not used or max(used) < int(w[2]))
+        cut += len(tm) > 0
+    assert cut >= 3
+
+
 def test_truncate_errors_change_nothing():
     c = host_ctx(8)
     a, b = c.kv_open(), c.kv_open()
