@@ -32,6 +32,14 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float as_f32(uint32_t u) { return __builtin_bit_cast(float, u); }
 __device__ __forceinline__ uint32_t as_u32(float f) { return __builtin_bit_cast(uint32_t, f); }
 
+// One word of the batch descriptor at a wavefront-uniform address, through the scalar cache.  The constant address space says
+// what the compiler cannot see: nothing writes the descriptor while a kernel runs.  Without it these loads are vector loads as
+// soon as the kernel stores anything, and since vector loads return in order, waiting for a page id then meant waiting for every
+// K/V load in flight (s_waitcnt vmcnt(0) once per page; whole calls without / with: long contexts, 8 heads per kv head 754 / 716
+// us; one file of 2000 tokens x 32 layers 494 / 473; drafts of 4 on 64 files 136.4 / 134.4; the mixed batch 1845 / 1824).
+typedef const __attribute__((address_space(4))) int32_t* const_word_t;
+__device__ __forceinline__ int sload(const int32_t* ptr) { return __builtin_amdgcn_readfirstlane(*(const_word_t)(uintptr_t)ptr); }
+
 // Sum over the 8 lanes of a lane octet (lanes 8k .. 8k+7): three DPP adds.
 __device__ __forceinline__ float octet_sum(float x) {
   x += as_f32(__builtin_amdgcn_update_dpp(0, as_u32(x), 0xB1, 0xf, 0xf, false));    // quad_perm [1,0,3,2]
@@ -147,15 +155,15 @@ __device__ __forceinline__ void merge_bin_pieces(const DecodeArgs& a, const int 
   constexpr int D = 16 * E::kDimsPerChunk, VL = G * D / 64, SLOT = BinLds<E, G>::kSlot, ACC = BinLds<E, G>::kAcc;
   const int lane = threadIdx.x & 63;
   const int32_t* lm = a.lmerge + (int64_t)bin * 32;
-  const int cnt = __builtin_amdgcn_readfirstlane(lm[0]);
+  const int cnt = sload(lm + 0);
   for (int k = wib; k < cnt; k += W) {
-    const int seg = __builtin_amdgcn_readfirstlane(lm[4 + 4 * k + 0]);
-    const int s0 = __builtin_amdgcn_readfirstlane(lm[4 + 4 * k + 1]);
-    const int w0 = __builtin_amdgcn_readfirstlane(lm[4 + 4 * k + 2]);
-    const int n = __builtin_amdgcn_readfirstlane(lm[4 + 4 * k + 3]);
+    const int seg = sload(lm + 4 + 4 * k + 0);
+    const int s0 = sload(lm + 4 + 4 * k + 1);
+    const int w0 = sload(lm + 4 + 4 * k + 2);
+    const int n = sload(lm + 4 + 4 * k + 3);
     const int32_t* sr = a.segs + (int64_t)seg * 8;
-    const int qh = __builtin_amdgcn_readfirstlane(sr[5]);        // q row * Hq + first query head
-    const int dest = __builtin_amdgcn_readfirstlane(sr[6]);
+    const int qh = sload(sr + 5);        // q row * Hq + first query head
+    const int dest = sload(sr + 6);
     float M[G], ls[G], o[VL];
 #pragma unroll
     for (int h = 0; h < G; ++h) {
@@ -211,7 +219,6 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
   const int lane = threadIdx.x & 63;
   const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));      // wavefront within the bin
   const int r = lane >> 3, j = lane & 7;
-  auto sload = [&](const int32_t* ptr) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*ptr); };
   const int32_t* ww = a.waves + ((int64_t)bin * W + wib) * 8;
   int remaining = sload(ww + 2);
 
@@ -539,19 +546,19 @@ __device__ __forceinline__ void decode_ranges(const DecodeArgs& a, const int blo
   const int r = lane >> 3, j = lane & 7;
 
   const int32_t* ww = a.waves + wv * 8;
-  int row = __builtin_amdgcn_readfirstlane(ww[0]);
-  int g = __builtin_amdgcn_readfirstlane(ww[1]);
-  int p = __builtin_amdgcn_readfirstlane(ww[2]);
-  int remaining = __builtin_amdgcn_readfirstlane(ww[3]);
-  int part = __builtin_amdgcn_readfirstlane(ww[4]);
+  int row = sload(ww + 0);
+  int g = sload(ww + 1);
+  int p = sload(ww + 2);
+  int remaining = sload(ww + 3);
+  int part = sload(ww + 4);
   // ids of the first range's first three pages (no table lookup before the first loads)
-  int pid0 = __builtin_amdgcn_readfirstlane(ww[5]);
-  int pid1 = __builtin_amdgcn_readfirstlane(ww[6]);
-  int pid2 = __builtin_amdgcn_readfirstlane(ww[7]);
-  int tbl_off = __builtin_amdgcn_readfirstlane(a.rows[row * 4 + 0]);
-  int vis = __builtin_amdgcn_readfirstlane(a.rows[row * 4 + 1]);
-  int qrow = __builtin_amdgcn_readfirstlane(a.rows[row * 4 + 2]);
-  int pstart = __builtin_amdgcn_readfirstlane(a.rows[row * 4 + 3]);   // first page of the row's own range (pages before it
+  int pid0 = sload(ww + 5);
+  int pid1 = sload(ww + 6);
+  int pid2 = sload(ww + 7);
+  int tbl_off = sload(a.rows + row * 4 + 0);
+  int vis = sload(a.rows + row * 4 + 1);
+  int qrow = sload(a.rows + row * 4 + 2);
+  int pstart = sload(a.rows + row * 4 + 3);   // first page of the row's own range (pages before it
                                                                        // are a shared prefix handled by the tile kernel)
   bool first_range = true;
 
@@ -644,9 +651,9 @@ __device__ __forceinline__ void decode_ranges(const DecodeArgs& a, const int blo
     // memory that every wave touches, so it stays in L2) and its data is never used.
     const int last = cnt - 1;
     if (!first_range) {
-      pid0 = tbl[0];
-      pid1 = tbl[min(1, last)];
-      pid2 = tbl[min(2, last)];
+      pid0 = sload(tbl);
+      pid1 = sload(tbl + min(1, last));
+      pid2 = sload(tbl + min(2, last));
     }
     first_range = false;
     static_assert(kPair, "one wavefront per range is decode_stream's job");
@@ -670,7 +677,7 @@ __device__ __forceinline__ void decode_ranges(const DecodeArgs& a, const int blo
           for (int x = 0; x < 4; ++x) *(uint4*)(buf + x * 1024) = sa[x];
           __syncthreads();                   // both halves of page k are in LDS; the other buffer is free again
           load_half(sa, id2);
-          id2 = k + 4 <= last ? tbl[k + 4] : 0;
+          id2 = k + 4 <= last ? sload(tbl + k + 4) : 0;
           PageRegs R;
           const uint8_t* rb = plds[0] + lane * 16;
 #pragma unroll
@@ -685,7 +692,7 @@ __device__ __forceinline__ void decode_ranges(const DecodeArgs& a, const int blo
 #pragma unroll
           for (int x = 0; x < 4; ++x) *(uint4*)(buf + x * 1024) = sb[x];
           __syncthreads();
-          id1 = k + 3 <= last ? tbl[k + 3] : 0;
+          id1 = k + 3 <= last ? sload(tbl + k + 3) : 0;
           load_half(sb, id1);
           if (k + 1 < cnt) {
             PageRegs R;
@@ -780,10 +787,10 @@ __device__ __forceinline__ void decode_ranges(const DecodeArgs& a, const int blo
         g = 0;
         ++row;
         if (remaining > 0) {
-          tbl_off = __builtin_amdgcn_readfirstlane(a.rows[row * 4 + 0]);
-          vis = __builtin_amdgcn_readfirstlane(a.rows[row * 4 + 1]);
-          qrow = __builtin_amdgcn_readfirstlane(a.rows[row * 4 + 2]);
-          pstart = __builtin_amdgcn_readfirstlane(a.rows[row * 4 + 3]);
+          tbl_off = sload(a.rows + row * 4 + 0);
+          vis = sload(a.rows + row * 4 + 1);
+          qrow = sload(a.rows + row * 4 + 2);
+          pstart = sload(a.rows + row * 4 + 3);
         }
       }
       p = pstart;
@@ -831,12 +838,12 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   constexpr int CT = 1;
   // workgroups go round-robin over the 8 XCDs; the tile list comes in 8 shares of equal cost in which
   // tiles that read the same K/V are neighbours (one L2 per XCD), longest first
-  const int tile = a.xcd_off[block % 8] + block / 8;
-  if (tile >= a.xcd_off[block % 8 + 1]) return;
+  const int tile = sload(a.xcd_off + block % 8) + block / 8;
+  if (tile >= sload(a.xcd_off + block % 8 + 1)) return;
   const int32_t* tw = a.tiles + (int64_t)(a.tile_first + tile) * 12;
-  const int tbl_off = tw[0], g = tw[4], count = tw[3];
-  const bool shared = tw[6] == 1;
-  const bool partial = tw[6] != 0;               // shared prefixes and key chunks leave partials
+  const int tbl_off = sload(tw + 0), g = sload(tw + 4), count = sload(tw + 3);
+  const bool shared = sload(tw + 6) == 1;
+  const bool partial = sload(tw + 6) != 0;               // shared prefixes and key chunks leave partials
   const int32_t* tbl = a.pt + tbl_off;
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -844,12 +851,12 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   // prefill chunk: `count` new tokens from chunk offset t0 on a file of L tokens; row tl sees
   // tokens 0 .. L + t0 + tl.  shared prefix: `count` decode rows (q rows in the member list) that
   // all see the same full pages [page0, page1) of the group's first file.
-  const int L = tw[1], t0 = tw[5];
+  const int L = sload(tw + 1), t0 = sload(tw + 5);
   // key chunk of a prefill tile: the same rows over the blocks of pages [page0, page1) only (some rows may see none of them)
-  const int lim = partial ? tw[8] * kP : 0x7fffffff;
+  const int lim = partial ? sload(tw + 8) * kP : 0x7fffffff;
   const int kv_end = shared ? lim : min(L + t0 + count, lim);    // tokens the tile's last row sees
   const int mask_from = shared ? lim : min(L + t0 + 1, lim);     // first token some row may not see
-  const int kb0 = partial ? tw[7] / 2 : 0;                       // first 32-token block (page0 is even)
+  const int kb0 = partial ? sload(tw + 7) / 2 : 0;                       // first 32-token block (page0 is even)
   const int nblk = (kv_end + kKvBlock - 1) / kKvBlock;
   const int last_page = max((kv_end + kP - 1) / kP - 1, 0);
   // A shared-prefix tile of four wavefronts with at most 64 live rows would keep two of them busy, each alone
@@ -874,7 +881,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
     tl[ct] = rho / G;                              // token (prefill) or member (shared prefix) of the row
     h[ct] = rho % G;
     const int tlc = min(tl[ct], count - 1);        // rows past the tile's last token/member repeat it (never written)
-    qrow[ct] = shared ? a.members[tw[2] + tlc] : tw[2] + tlc;
+    qrow[ct] = shared ? a.members[sload(tw + 2) + tlc] : sload(tw + 2) + tlc;
     vis[ct] = shared ? kv_end : min(L + t0 + tlc + 1, lim);   // tokens this row sees
     const uint8_t* qp = (const uint8_t*)a.q + ((int64_t)qrow[ct] * a.Hq + g * G + h[ct]) * kRowBytes + hf * 16;
 #pragma unroll
@@ -900,7 +907,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   const int dbyte = vc * VD * 2;                            // byte offset of the thread's dims in the 256-byte row
   const int v_off = kBlk + (dbyte >> 7) * (kP * kHalfBytes) + (4 * q4 + 2 * up) * kHalfBytes + (dbyte & 127);
   auto page_base = [&](int pi) {
-    const int pid = __builtin_amdgcn_readfirstlane(tbl[min(pi, last_page)]);
+    const int pid = sload(tbl + min(pi, last_page));
     return slab + (int64_t)pid * a.page_bytes;
   };
   auto issue_loads = [&](int kb, uint4& k0, uint4& k1, uint4& v0, uint4& v1) {
@@ -1198,7 +1205,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
             *(float4*)(o + db * 32 + vb * 8) = make_float4(O[ct][db][4 * vb] * inv, O[ct][db][4 * vb + 1] * inv, O[ct][db][4 * vb + 2] * inv, O[ct][db][4 * vb + 3] * inv);
       } else {
         // partial result of member (or token) tl for the merge kernel: unnormalised accumulator, max, sum
-        const int64_t part = (int64_t)(shared ? t0 : tw[9]) + tl[ct];           // shared: t0 = first partial slot of this tile
+        const int64_t part = (int64_t)(shared ? t0 : sload(tw + 9)) + tl[ct];           // shared: t0 = first partial slot of this tile
         float* o = a.part_acc + (part * G + h[ct]) * 128 + 4 * hf;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -1243,7 +1250,6 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
   const int col = lane & 15, grp = lane >> 4;        // query column, lane group (tokens 4*grp .. 4*grp+3 of a page)
   const int head = col % GT;                          // columns past nt * GT repeat earlier ones; their results are ignored
   const int vq4 = lane >> 4, vc = lane & 15;          // V staging role: tokens 4*vq4 .. +3 of a page, dim chunk vc
-  auto sload = [&](const int32_t* ptr) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*ptr); };
 
   // As in the VALU kernel, the wavefront's units form ONE stream: a load cursor runs ahead of the compute
   // cursor through the same sequence of (row, kv head) ranges, in steps of a pair of pages (a pair never
@@ -1502,7 +1508,7 @@ __global__ __launch_bounds__(64 * TW, 8 / TW) void attn_kernel(DecodeArgs da, Pr
   // 1.85 ms against 1.91 ms with all tiles first; spread over the whole grid: 2.02 ms.  A CU that runs decode
   // ranges alone has only its eight wavefronts' loads in flight, so the gain is small.)
   const uint32_t j = blockIdx.x >> 3, x = blockIdx.x & 7;
-  const int32_t g = pa.group_map ? __builtin_amdgcn_readfirstlane(pa.group_map[j]) : (int32_t)j;   // no table: tiles only
+  const int32_t g = pa.group_map ? sload(pa.group_map + j) : (int32_t)j;   // no table: tiles only
   const bool is_decode = g < 0;
   // LDS: the K/V buffers of a tile workgroup, or the piece slots of a decode bin (a workgroup is one or the other)
   constexpr int kTileLds = E::kDimsPerChunk == 8 ? (SPLIT ? 4 : 3) * (kKLds + kVLds) : 0;      // tiles exist for bf16 storage only
@@ -1565,7 +1571,6 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int col = lane & 15, grp = lane >> 4;
   const int32_t* t = a.rtiles + (int64_t)blockIdx.x * 8;
-  auto sload = [&](const int32_t* ptr) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*ptr); };
   const int32_t* tbl = a.pt + sload(t + 0);
   const int vis0 = sload(t + 1), qrow = sload(t + 2), count = sload(t + 3), head = sload(t + 4);
   const int page0 = sload(t + 5), page1 = sload(t + 6), dest = sload(t + 7);
@@ -1747,8 +1752,8 @@ template <int G, int D>
 __global__ __launch_bounds__(kWavesPerBlock * 64) void tile_merge_kernel(MergeArgs a) {
   const int lane = threadIdx.x & 63;
   const int32_t* it = a.tile_items + (int64_t)blockIdx.x * 4;
-  const int first = __builtin_amdgcn_readfirstlane(it[0]), chunks = __builtin_amdgcn_readfirstlane(it[1]);
-  const int count = __builtin_amdgcn_readfirstlane(it[2]), qh = __builtin_amdgcn_readfirstlane(it[3]);
+  const int first = sload(it + 0), chunks = sload(it + 1);
+  const int count = sload(it + 2), qh = sload(it + 3);
   const int tl = __builtin_amdgcn_readfirstlane((int)(blockIdx.y * kWavesPerBlock + (threadIdx.x >> 6)));
   if (tl >= count) return;
   constexpr int VL = G * D / 64;
@@ -1812,14 +1817,14 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void merge_kernel(MergeArgs a)
   const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));
   if (item >= a.n_items) return;
   const int32_t* it = a.items + item * 8;
-  const int first = __builtin_amdgcn_readfirstlane(it[0]);
-  const int own = __builtin_amdgcn_readfirstlane(it[1]);
-  const int64_t out_row = (int64_t)__builtin_amdgcn_readfirstlane(it[2]) * D;   // (q row * Hq + first head) * D
+  const int first = sload(it + 0);
+  const int own = sload(it + 1);
+  const int64_t out_row = (int64_t)sload(it + 2) * D;   // (q row * Hq + first head) * D
   // pieces own .. own + xcount - 1 are the partials of the row's shared prefix: xfirst + i * xstride
-  const int xfirst = __builtin_amdgcn_readfirstlane(it[3]);
-  const int xstride = __builtin_amdgcn_readfirstlane(it[4]);
-  const int pieces = own + __builtin_amdgcn_readfirstlane(it[5]);
-  const int ostride = __builtin_amdgcn_readfirstlane(it[6]);      // distance between own pieces (tokens in the row)
+  const int xfirst = sload(it + 3);
+  const int xstride = sload(it + 4);
+  const int pieces = own + sload(it + 5);
+  const int ostride = sload(it + 6);      // distance between own pieces (tokens in the row)
   auto slot = [&](int i) -> int64_t {
     i = min(i, pieces - 1);
     return i < own ? first + (int64_t)i * ostride : xfirst + (int64_t)(i - own) * xstride;
