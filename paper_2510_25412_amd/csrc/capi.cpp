@@ -337,7 +337,7 @@ int launch_attention(sym_ctx* c, const Scratch& ws, int64_t blob_words, const vo
     if (e != hipSuccess) return fail_hip(c, e, "attention launch");
   }
   if (d.n_merge > 0 || d.n_tmerge > 0) {
-    MergeArgs m{part_acc, part_ml, dw + hdr[H_OFF_MERGE], out, d.n_merge, dw + hdr[H_OFF_TMERGE], d.n_tmerge, d.tmerge_tokens, c->cfg.n_q_heads};
+    MergeArgs m{part_acc, part_ml, dw + hdr[H_OFF_MERGE], out, d.n_merge, d.merge_pieces, dw + hdr[H_OFF_TMERGE], d.n_tmerge, d.tmerge_tokens, c->cfg.n_q_heads};
     Timed t(c, SYM_K_MERGE, st, false, timed);
     hipError_t e = launch_merge(m, c->G, c->cfg.head_dim, st);
     if (e != hipSuccess) return fail_hip(c, e, "merge launch");

@@ -948,6 +948,8 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   out->n_rtiles = (int32_t)n_rtiles;
   out->n_tmerge = n_tmerge;
   out->tmerge_tokens = tmerge_tokens;
+  out->merge_pieces = 0;
+  for (int32_t i = 0; i < n_merge; ++i) out->merge_pieces = std::max(out->merge_pieces, merge[(int64_t)i * MERGE_WORDS + 1] + merge[(int64_t)i * MERGE_WORDS + 5]);
   w[H_N_WAVES] = (int32_t)nw;
   w[H_N_PARTIALS] = n_partials;
   w[H_N_LIPS] = n_lips;

@@ -89,6 +89,7 @@ struct BatchDesc {
   int32_t small_shared_only = 0;   // 1: every tile is a shared-prefix tile with at most 64 live rows
   int32_t max_row_tokens = 1;   // > 1: some row holds several new tokens (needs the matrix-core decode kernel)
   int64_t total_units = 0;
+  int32_t merge_pieces = 0;     // the most partials of one merge entry
   int32_t n_rtiles = 0;         // row tiles (fp32 storage)
   int32_t n_tmerge = 0, tmerge_tokens = 0;         // tiles cut into key chunks, and the most tokens such a tile holds
   int32_t n_bins = 0, bin_waves = 0, n_segs = 0;   // bins in use (0 = the global cut)

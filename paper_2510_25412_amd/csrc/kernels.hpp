@@ -64,7 +64,7 @@ struct MergeArgs {
   const int32_t* items;     // [n_items][8]: first partial, pieces, q row * Hq + first head, then the extra
                             //   pieces of a shared prefix: first, stride, count; 0, 0
   float* out;
-  int32_t n_items;
+  int32_t n_items, max_pieces;   // entries; the most pieces of one
   // tiles whose keys were cut into chunks (a launch of their own)
   const int32_t* tile_items;   // [n_tile_items][4]: first partial (chunk c, token t: first + c * tokens + t), chunks, tokens,
                                //   q row * Hq + first head of its first token
