@@ -742,13 +742,13 @@ int sym_kv_truncate(sym_ctx* c, int32_t n, const sym_kv* kv, const int64_t* new_
   if (!c || n < 0 || (n > 0 && (!kv || !new_len))) return SYM_EINVAL;
   std::lock_guard<std::mutex> lk(c->mu);
   if (int busy = refuse_if_open(c, "kv_truncate")) return busy;
+  c->fs->begin_marks();
   for (int32_t i = 0; i < n; ++i) {          // validate everything first: all or nothing
     const KvFile* f = c->fs->file_of(kv[i]);
     if (!f) return fail(c, SYM_EBADF, "kv_truncate: bad handle");
     if (f->waiting) return fail(c, SYM_EBUSY, "kv_truncate: file is offloaded");
     if (new_len[i] < 0 || new_len[i] > f->len) return fail(c, SYM_EINVAL, "kv_truncate: length beyond the file");
-    for (int32_t j = 0; j < i; ++j)
-      if (c->fs->file_of(kv[j]) == f) return fail(c, SYM_EBUSY, "kv_truncate: file listed twice");
+    if (!c->fs->mark(kv[i])) return fail(c, SYM_EBUSY, "kv_truncate: file listed twice");
   }
   for (int32_t i = 0; i < n; ++i) (void)c->fs->truncate(kv[i], new_len[i]);
   return SYM_OK;

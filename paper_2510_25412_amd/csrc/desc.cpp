@@ -372,18 +372,21 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     const int64_t total_cost = total_units + alpha * n_rows * H;
     auto& order = out->item_order;
     auto& heap = out->bin_heap;
+    // no more segments than ranges and cuts at bin boundaries; the vectors only ever grow
+    const size_t seg_cap = (size_t)(n_rows * H + n_bins + 1);
+    if (seg_tmp.size() < seg_cap * SEG_WORDS) seg_tmp.resize(seg_cap * SEG_WORDS);
+    if (item_bin.size() < seg_cap) item_bin.resize(seg_cap);
     auto emit = [&](int64_t row, int32_t g, int32_t pb, int32_t pe, int32_t np, int32_t dest, int32_t bin) {
       const int32_t rec[SEG_WORDS] = {rows_tmp[row * ROW_WORDS + 0], g, pb, pe, rows_tmp[row * ROW_WORDS + 1], rows_tmp[row * ROW_WORDS + 2] * prm.n_q_heads + g * G, dest,
                                       (pe == np && !out->row_lip.empty() && out->fused[out->row_lip[row]]) ? (rows_tmp[row * ROW_WORDS + 1] - 1) % P : -1};
-      seg_tmp.insert(seg_tmp.end(), rec, rec + SEG_WORDS);
-      item_bin.push_back(bin);
+      std::memcpy(seg_tmp.data() + n_segs * SEG_WORDS, rec, sizeof rec);
+      item_bin[n_segs++] = bin;
     };
     // Plan A, when there are several ranges per bin (short files, the members of forked prefixes): whole ranges, handed to
     // the bins longest first; nothing is split, so no range leaves partials in device memory because of the bins.
     bool planned = false;
     if (n_rows * H >= 3 * n_bins) {
-      seg_tmp.clear();
-      item_bin.clear();
+      n_segs = 0;
       n_split_partials = n_split_merge = 0;
       for (int64_t row = 0; row < n_rows; ++row) {
         const int32_t np = trow_pages(row), p0 = trow_first(row);
@@ -395,7 +398,6 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
           }
         }
       }
-      n_segs = (int64_t)seg_tmp.size() / SEG_WORDS;
       // longest first by counting sort on the page count (rows come in, the H ranges of a row are equal)
       int32_t longest = 0;
       for (int64_t row = 0; row < n_rows; ++row) longest = std::max(longest, trow_pages(row) - trow_first(row));
@@ -405,18 +407,50 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       auto& sorted = out->tile_tmp;                            // rows, longest first (scratch that the tile list reuses later)
       sorted.resize((size_t)n_rows);
       for (int64_t row = 0; row < n_rows; ++row) sorted[order[longest - (trow_pages(row) - trow_first(row))]++] = (int32_t)row;
-      heap.clear();
-      for (int64_t b = 0; b < n_bins; ++b) heap.emplace_back(0, (int32_t)b);
-      auto worse = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) { return x > y; };   // min-heap on (load, bin)
       int64_t worst = 0;
-      for (int32_t row : sorted) {
-        const int64_t c = trow_pages(row) - trow_first(row) + alpha;
-        for (int32_t g = 0; g < H; ++g) {
-          std::pop_heap(heap.begin(), heap.end(), worse);
-          heap.back().first += c;
-          item_bin[(size_t)row * H + g] = heap.back().second;
-          worst = std::max(worst, heap.back().first);
-          std::push_heap(heap.begin(), heap.end(), worse);
+      // The bin of least load, the lowest of equals, takes the next range.  Loads are small whole numbers: one bit per bin and
+      // load says which bins carry it, and the least load only rises.  (2048 ranges over 256 bins: 12 us; a heap of pairs, which
+      // serves loads too large for the table: 130 us.)
+      const int64_t max_load = total_cost / n_bins + longest + alpha + 1, wpl = (n_bins + 63) / 64;
+      if (max_load * wpl <= (1 << 16)) {
+        auto& bits = out->bin_bits;
+        auto& cnt = out->bin_count;
+        bits.assign((size_t)((max_load + 1) * wpl), 0);
+        cnt.assign((size_t)max_load + 1, 0);
+        for (int64_t b = 0; b < n_bins; ++b) bits[b >> 6] |= 1ull << (b & 63);
+        cnt[0] = (int32_t)n_bins;
+        int64_t lo = 0, word = 0;
+        for (int32_t row : sorted) {
+          const int64_t c = std::max<int64_t>(1, trow_pages(row) - trow_first(row) + alpha);
+          for (int32_t g = 0; g < H; ++g) {
+            if (cnt[lo] == 0) {
+              while (cnt[lo] == 0) ++lo;
+              word = 0;
+            }
+            uint64_t* from = bits.data() + lo * wpl;
+            while (!from[word]) ++word;
+            const uint64_t bit = from[word] & (~from[word] + 1);
+            from[word] ^= bit;
+            --cnt[lo];
+            bits[(lo + c) * wpl + word] |= bit;
+            ++cnt[lo + c];
+            item_bin[(size_t)row * H + g] = (int32_t)(word * 64 + __builtin_ctzll(bit));
+            worst = std::max(worst, lo + c);
+          }
+        }
+      } else {
+        heap.clear();
+        for (int64_t b = 0; b < n_bins; ++b) heap.emplace_back(0, (int32_t)b);
+        auto worse = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) { return x > y; };   // min-heap on (load, bin)
+        for (int32_t row : sorted) {
+          const int64_t c = trow_pages(row) - trow_first(row) + alpha;
+          for (int32_t g = 0; g < H; ++g) {
+            std::pop_heap(heap.begin(), heap.end(), worse);
+            heap.back().first += c;
+            item_bin[(size_t)row * H + g] = heap.back().second;
+            worst = std::max(worst, heap.back().first);
+            std::push_heap(heap.begin(), heap.end(), worse);
+          }
         }
       }
       planned = worst * n_bins * 100 <= total_cost * (100 + prm.bin_tolerance);
@@ -428,21 +462,20 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     // device memory (at most n_bins - 1 ranges); what the wavefront boundaries inside a bin divide is combined through LDS.
     out->wave_pos.clear();
     if (!planned && n_bins > 1) {
-      seg_tmp.clear();
-      item_bin.clear();
+      n_segs = 0;
       n_split_partials = n_split_merge = 0;
       auto& wpos = out->wave_pos;                        // (segment, page) where every wavefront starts
       wpos.reserve((size_t)nw * 2);
-      int64_t k = 0, vstart = 0;
+      int64_t k = 0, vstart = 0, cut = 0;                // cut: where wavefront k starts, total_cost * k / nw
       int32_t bin = 0;
       for (int64_t row = 0; row < n_rows; ++row) {
         const int32_t np = trow_pages(row), p0 = trow_first(row);
         for (int32_t g = 0; g < H; ++g) {
           const int64_t vend = vstart + alpha + (np - p0);
-          const size_t first_seg = seg_tmp.size() / SEG_WORDS;
+          const size_t first_seg = (size_t)n_segs;
           int32_t pb = p0;
-          for (; k < nw && total_cost * k / nw < vend; ++k) {
-            const int32_t at = p0 + (int32_t)std::max<int64_t>(0, total_cost * k / nw - vstart - alpha);
+          for (; k < nw && cut < vend; ++k, cut = total_cost * k / nw) {
+            const int32_t at = p0 + (int32_t)std::max<int64_t>(0, cut - vstart - alpha);
             if (k % W == 0) {                            // a bin begins here
               if (at > pb) {
                 emit(row, g, pb, at, np, 0, bin);
@@ -450,11 +483,11 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
               }
               bin = (int32_t)(k / W);
             }
-            wpos.push_back((int32_t)(seg_tmp.size() / SEG_WORDS));      // the segment that is emitted next holds page `at`
+            wpos.push_back((int32_t)n_segs);      // the segment that is emitted next holds page `at`
             wpos.push_back(at);
           }
           emit(row, g, pb, np, np, 0, bin);
-          const size_t n_here = seg_tmp.size() / SEG_WORDS - first_seg;
+          const size_t n_here = (size_t)n_segs - first_seg;
           const bool partial = n_here > 1 || p0 > 0;
           for (size_t i = 0; i < n_here; ++i) seg_tmp[(first_seg + i) * SEG_WORDS + S_DEST] = partial ? (int32_t)(n_split_partials + i) : -1;
           if (partial) {
@@ -464,13 +497,11 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
           vstart = vend;
         }
       }
-      n_segs = (int64_t)seg_tmp.size() / SEG_WORDS;
       planned = true;
     }
     // One bin (a small batch): every range is a segment of it, cut between its wavefronts only.
     if (!planned) {
-      seg_tmp.clear();
-      item_bin.clear();
+      n_segs = 0;
       n_split_partials = n_split_merge = 0;
       for (int64_t row = 0; row < n_rows; ++row) {
         const int32_t np = trow_pages(row), p0 = trow_first(row);
@@ -482,7 +513,6 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
           }
         }
       }
-      n_segs = (int64_t)seg_tmp.size() / SEG_WORDS;
     }
   }
 
@@ -642,7 +672,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       int32_t* lm = lmerge + b * LMERGE_WORDS;
       lm[1] = (int32_t)s0;                              // the bin's segments (the kernel walks them for the appends that ride along)
       lm[2] = (int32_t)s1;
-      int64_t k = 0, vstart = 0;
+      int64_t k = 0, vstart = 0, cut = 0;               // cut: where wavefront k starts, vt * k / Wb
       if (!out->wave_pos.empty()) {                     // the wavefronts' starts come from the cut of the whole batch
         for (; k < W; ++k) {
           bw[k * WAVE_WORDS + 0] = out->wave_pos[(size_t)(b * W + k) * 2];
@@ -652,12 +682,10 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       for (int64_t i = s0; i < s1 && k < Wb; ++i) {
         const int32_t pb = segs[i * SEG_WORDS + S_PB], pe = segs[i * SEG_WORDS + S_PE];
         const int64_t vend = vstart + alpha + (pe - pb);
-        while (k < Wb && vt * k / Wb < vend) {
-          const int64_t o = vt * k / Wb - vstart;
+        for (; k < Wb && cut < vend; ++k, cut = vt * k / Wb) {
           int32_t* ww = bw + k * WAVE_WORDS;
           ww[0] = (int32_t)i;
-          ww[1] = pb + (int32_t)std::max<int64_t>(0, o - alpha);
-          ++k;
+          ww[1] = pb + (int32_t)std::max<int64_t>(0, cut - vstart - alpha);
         }
         vstart = vend;
       }
@@ -949,7 +977,8 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   out->n_tmerge = n_tmerge;
   out->tmerge_tokens = tmerge_tokens;
   out->merge_pieces = 0;
-  for (int32_t i = 0; i < n_merge; ++i) out->merge_pieces = std::max(out->merge_pieces, merge[(int64_t)i * MERGE_WORDS + 1] + merge[(int64_t)i * MERGE_WORDS + 5]);
+  if (n_merge <= 512)                             // (more entries never use it)
+    for (int32_t i = 0; i < n_merge; ++i) out->merge_pieces = std::max(out->merge_pieces, merge[(int64_t)i * MERGE_WORDS + 1] + merge[(int64_t)i * MERGE_WORDS + 5]);
   w[H_N_WAVES] = (int32_t)nw;
   w[H_N_PARTIALS] = n_partials;
   w[H_N_LIPS] = n_lips;

@@ -180,9 +180,24 @@ int Kvfs::truncate(int32_t h, int64_t new_len) {
   return SYM_OK;
 }
 
+void Kvfs::begin_marks() {
+  seen_in_.resize(files_.size(), 0);
+  if (++batch_no_ == 0) {                    // wrapped: old marks could match again
+    std::fill(seen_in_.begin(), seen_in_.end(), 0u);
+    batch_no_ = 1;
+  }
+}
+
+bool Kvfs::mark(int32_t h) {
+  uint32_t& last = seen_in_[handle_file_[h]];
+  if (last == batch_no_) return false;
+  last = batch_no_;
+  return true;
+}
+
 int64_t Kvfs::pages_needed(int32_t n, const int32_t* handles, const int32_t* n_tokens, std::string* err) {
   pending_.clear();
-  seen_files_.clear();
+  begin_marks();
   int64_t need = 0;
   for (int32_t b = 0; b < n; ++b) {
     const KvFile* f = file_of(handles[b]);
@@ -198,12 +213,10 @@ int64_t Kvfs::pages_needed(int32_t n, const int32_t* handles, const int32_t* n_t
       if (err) *err = "file is offloaded";
       return SYM_EBUSY;
     }
-    int32_t id = handle_file_[handles[b]];
-    if (std::find(seen_files_.begin(), seen_files_.end(), id) != seen_files_.end()) {
+    if (!mark(handles[b])) {
       if (err) *err = "same file twice in one batch";
       return SYM_EBUSY;
     }
-    seen_files_.push_back(id);
     int64_t L = f->len;
     if (L % P_ != 0) {
       int32_t last = f->pages.back();
@@ -251,11 +264,19 @@ int Kvfs::append(int32_t n, const int32_t* handles, const int32_t* n_tokens, App
           break;
         }
     }
-    for (int32_t i = 0; i < n_tokens[b]; ++i) {
-      if (f.len % P_ == 0) f.pages.push_back(alloc_page());
-      if (plan) plan->slots.push_back(f.pages.back() * P_ + (int32_t)(f.len % P_));
-      ++f.len;
+    int32_t* slot = nullptr;
+    if (plan) {
+      const size_t at = plan->slots.size();
+      plan->slots.resize(at + (size_t)n_tokens[b]);
+      slot = plan->slots.data() + at;
     }
+    for (int32_t i = 0, s = (int32_t)(f.len % P_); i < n_tokens[b]; s = 0) {       // page by page
+      if (s == 0) f.pages.push_back(alloc_page());
+      const int32_t n_here = std::min(n_tokens[b] - i, P_ - s);
+      if (slot) std::iota(slot + i, slot + i + n_here, f.pages.back() * P_ + s);
+      i += n_here;
+    }
+    f.len += n_tokens[b];
     tokens_appended += n_tokens[b];
   }
   return SYM_OK;

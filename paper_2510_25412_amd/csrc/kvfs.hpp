@@ -102,6 +102,9 @@ class Kvfs {
   int64_t len(int32_t h) const;
   int truncate(int32_t h, int64_t new_len);   // drop tokens from new_len on; frees pages no longer needed
   const KvFile* file_of(int32_t h) const;
+  // Whether a list of handles names a file twice: begin_marks(), then mark() of each (valid) handle says if its file is new.
+  void begin_marks();
+  bool mark(int32_t h);
 
   // Pages a batch would allocate, LIPs in batch order; negative status on a bad argument.
   int64_t pages_needed(int32_t n, const int32_t* handles, const int32_t* n_tokens, std::string* err);
@@ -171,7 +174,9 @@ class Kvfs {
   std::priority_queue<int32_t, std::vector<int32_t>, std::greater<int32_t>> free_slots_;
   int32_t n_slots_ = 0;
   std::unordered_map<int32_t, int32_t> pending_;   // scratch of pages_needed
-  std::vector<int32_t> seen_files_;                 // scratch of append
+  std::vector<int32_t> seen_files_;                 // scratch of check_swap_args
+  std::vector<uint32_t> seen_in_;                   // file id -> the last list of handles that named it (mark)
+  uint32_t batch_no_ = 0;
 };
 
 }  // namespace symkv
