@@ -363,7 +363,7 @@ int launch_prologue(sym_ctx* c, int si, int64_t copy_words, const int32_t* cow, 
   a.n_tokens = n_tokens;
   a.Hkv = c->cfg.n_kv_heads;
   a.n_cow = n_cow;
-  a.append_blocks = a.copy_blocks = 0;
+  a.append_blocks = a.append_tokens = a.copy_blocks = 0;
   Timed t(c, SYM_K_PROLOGUE, st, false, timed);
   hipError_t e = symkv::launch_prologue(a, st);
   if (e != hipSuccess) return fail_hip(c, e, "prologue launch");

@@ -82,7 +82,7 @@ struct PrologueArgs {
   int32_t* dev_words;           // device workspace
   int64_t copy_words;
   int32_t n_tokens, Hkv, n_cow;
-  int32_t append_blocks, copy_blocks;   // filled by launch_prologue
+  int32_t append_blocks, append_tokens, copy_blocks;   // filled by launch_prologue
 };
 
 struct GatherArgs {
