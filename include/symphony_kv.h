@@ -82,7 +82,8 @@ typedef struct sym_tuning {
   int32_t bin_tolerance;   /* whole ranges are packed into workgroups only if the fullest
                               then holds at most this many percent more than the mean;
                               otherwise ranges are cut at equal cost; >= 0, default 3     */
-  int32_t bin_waves;       /* wavefronts of a decode workgroup: 8 (default) or 4          */
+  int32_t bin_waves;       /* wavefronts of a decode workgroup: 8 (default; 4 for a batch so small
+                              that this gives every compute unit at most one) or 4        */
   int32_t fuse_append;     /* 1 (default): the K/V row of a single new token is written by
                               the wavefront that reads the row's last page; 0: by a launch
                               of its own before attention                                 */

@@ -187,6 +187,7 @@ DescParams desc_params(const sym_ctx* c, int64_t partials, int64_t max_words, bo
   // the vector-unit decode kernel (up to 4 query heads per kv head, unless the matrix cores are asked for) works on bins
   p.bin_waves = (c->G < 8 && !c->decode_mode) ? c->bin_waves : 0;
   p.fuse_append = (fuse_append && p.bin_waves && c->fuse_append) ? 1 : 0;
+  p.spread_small = c->cfg.decode_waves <= 0 ? 1 : 0;
   p.bin_tolerance = c->bin_tolerance;
   p.mix_lead = c->mix_lead;
   p.mix_spread = c->mix_spread;
@@ -302,6 +303,7 @@ int launch_attention(sym_ctx* c, const Scratch& ws, int64_t blob_words, const vo
   a.lmerge = dw + hdr[H_OFF_LMERGE];
   a.n_bins = d.n_bins;
   a.bin_waves = d.bin_waves;
+  a.cached = d.small_decode;
   // the attention kernel requests a chunk of these rows with every segment's query rows, used or not: when it appends
   // nothing, the query rows (no smaller) stand in
   a.k_new = d.n_fused > 0 ? k_new : q;

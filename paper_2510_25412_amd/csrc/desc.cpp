@@ -298,7 +298,13 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   // cut for the matrix-core decode kernel, which rows of several tokens need
   const bool bins = prm.bin_waves > 0 && max_nt == 1 && total_units > 0;
   // a bin is a workgroup: eight wavefronts, or four when the launch has tiles of 128 query rows (four-wavefront workgroups)
-  const int32_t W = !bins ? 0 : n_tiles > 0 ? (TQ * G != 256 ? 4 : 8) : (prm.bin_waves == 4 ? 4 : 8);
+  // A batch that gives no compute unit more than a workgroup of four: workgroups of four instead of eight, so that twice as many
+  // compute units share it, and plain loads.  One compute unit draws about 40 GB/s with nontemporal loads, 60 with plain ones, and
+  // that is what bounds such a launch (a page per wavefront: 1.65 us with eight wavefronts, 0.93 with four, 0.68 with plain loads).
+  // Per layer, 32 query heads, before / after: a file of 2000 tokens 15.7 / 12.3 us, four of 200 15.6 / 12.2, sixteen of 400
+  // 16.9 / 14.5, 64 of 100 18.0 / 15.9; past the line, sixteen of 1000 tokens (8064 units): 21.0 / 22.9.
+  const bool small_decode = bins && prm.spread_small && n_tiles == 0 && total_units <= (int64_t)prm.cus * 4 * prm.min_units_per_wave;
+  const int32_t W = !bins ? 0 : n_tiles > 0 ? (TQ * G != 256 ? 4 : 8) : (prm.bin_waves == 4 || small_decode ? 4 : 8);
   const int64_t max_bins = std::max<int64_t>(1, prm.max_waves / std::max(W, 1));
   int64_t nw = (total_units + prm.min_units_per_wave - 1) / prm.min_units_per_wave;
   nw = std::max<int64_t>(1, std::min<int64_t>(nw, prm.max_waves));
@@ -1003,6 +1009,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   w[H_OFF_LMERGE] = (int32_t)off_lmerge;
   out->n_bins = (int32_t)n_bins;
   out->bin_waves = W;
+  out->small_decode = small_decode ? 1 : 0;
   out->n_segs = (int32_t)(bins ? n_segs : 0);
   out->n_fused = n_fused;
   out->n_rows = (int32_t)n_rows;

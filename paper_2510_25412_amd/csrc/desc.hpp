@@ -93,6 +93,7 @@ struct BatchDesc {
   int32_t n_rtiles = 0;         // row tiles (fp32 storage)
   int32_t n_tmerge = 0, tmerge_tokens = 0;         // tiles cut into key chunks, and the most tokens such a tile holds
   int32_t n_bins = 0, bin_waves = 0, n_segs = 0;   // bins in use (0 = the global cut)
+  int32_t small_decode = 0;     // 1: the decode bins alone, of four wavefronts, spread over the chip (see build_desc)
   int32_t n_fused = 0;          // new tokens whose append the attention kernel carries out itself
   std::vector<uint8_t> fused;   // per LIP: 1 = its (single) new token is one of them
   // scratch of the builder, kept between calls
@@ -123,6 +124,7 @@ struct DescParams {
   int32_t bin_waves = 0;      // != 0: bins (the vector-unit decode kernel) unless a row holds several tokens; as many bins as
                               //   max_waves fills with workgroups of 8 wavefronts (4 beside tiles of 128 query rows; a batch
                               //   without tiles: 4 if this is 4, else 8)
+  int32_t spread_small = 0;   // 1: a small decode batch is spread over more, smaller workgroups (not when the caller set the wavefront slots)
   int32_t bin_tolerance = 3;  // percent by which the fullest bin may exceed the mean before ranges are split finer
   int32_t fuse_append = 0;    // 1: single-token LIPs are appended by the attention kernel (bins only)
   // order of a launch with tiles and decode bins, in percent of the tile groups: `mix_lead` tile groups first, then

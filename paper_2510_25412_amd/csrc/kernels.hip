@@ -105,6 +105,14 @@ struct ElemF32 {
   }
 };
 
+// 16 bytes of K or V.  STREAM: nontemporal, which streams a batch larger than the caches fastest; a compute unit that reads
+// with few others gets its lines sooner without it.
+template <bool STREAM>
+__device__ __forceinline__ uint4 ld16(const uint8_t* p) {
+  if constexpr (STREAM) return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)p));
+  else return *(const uint4*)p;
+}
+
 struct PageRegs {
   uint4 k[4];   // index = row_half * 2 + token_half
   uint4 v[4];
@@ -209,7 +217,7 @@ __device__ __forceinline__ void merge_bin_pieces(const DecodeArgs& a, const int 
   }
 }
 
-template <typename E, int G>
+template <typename E, int G, bool STREAM>
 __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, const int W, float* lds) {
   constexpr int C = E::kDimsPerChunk;    // dims per 16-byte chunk
   constexpr int DPL = 2 * C;             // dims per lane
@@ -279,9 +287,9 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
     // every load is unconditional and off one base address: no control-flow join between a load and its use, so the
     // waits can be for exactly the older page while the newer one is in flight
 #pragma unroll
-    for (int x = 0; x < 4; ++x) R.k[x] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + x * 1024)));
+    for (int x = 0; x < 4; ++x) R.k[x] = ld16<STREAM>(base + x * 1024);
 #pragma unroll
-    for (int x = 0; x < 4; ++x) R.v[x] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + kBlk + x * 1024)));
+    for (int x = 0; x < 4; ++x) R.v[x] = ld16<STREAM>(base + kBlk + x * 1024);
   };
 
   // q chunks of this lane for the G heads of the current segment
@@ -1522,15 +1530,15 @@ __global__ __launch_bounds__(64 * TW, 8 / TW) void attn_kernel(DecodeArgs da, Pr
     }
   }
   if constexpr (G < 8) {
-    if (is_decode) decode_bins<E, G>(da, (int)(~g * 8 + x), TW, (float*)lds);
+    if (is_decode) decode_bins<E, G, true>(da, (int)(~g * 8 + x), TW, (float*)lds);
   }
 }
 
 // A batch without tiles (plain decode): the decode bins alone, W wavefronts per bin.
-template <typename E, int G, int W>
+template <typename E, int G, int W, bool STREAM>
 __global__ __launch_bounds__(64 * W, 8 / W) void decode_only_kernel(DecodeArgs da) {
   __shared__ __align__(16) float lds[2 * W * BinLds<E, G>::kSlot];
-  decode_bins<E, G>(da, (int)blockIdx.x, W, lds);
+  decode_bins<E, G, STREAM>(da, (int)blockIdx.x, W, lds);
 }
 
 // Decode ranges for 8 query heads per kv head: one workgroup of two wavefronts per range.
@@ -2141,8 +2149,9 @@ hipError_t launch_attn_g(const DecodeArgs& da, const PrefillArgs& pa, int decode
     const dim3 dgrid(da.n_bins), dblock(64 * da.bin_waves);
 #define SYM_DECODE_CASE(GG) \
   case GG: \
-    if (da.bin_waves == 8) launch(decode_only_kernel<E, GG, 8>, dgrid, dblock, ev0, ev1, da); \
-    else launch(decode_only_kernel<E, GG, 4>, dgrid, dblock, ev0, ev1, da); \
+    if (da.bin_waves == 8) launch(decode_only_kernel<E, GG, 8, true>, dgrid, dblock, ev0, ev1, da); \
+    else if (da.cached) launch(decode_only_kernel<E, GG, 4, false>, dgrid, dblock, ev0, ev1, da); \
+    else launch(decode_only_kernel<E, GG, 4, true>, dgrid, dblock, ev0, ev1, da); \
     break;
     switch (G) {
       SYM_DECODE_CASE(1) SYM_DECODE_CASE(2) SYM_DECODE_CASE(4)

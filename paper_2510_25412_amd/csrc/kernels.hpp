@@ -26,6 +26,7 @@ struct DecodeArgs {
   const int32_t* lmerge;    // [n_bins][32]: count, then (segment, LDS slot of its first piece, that piece's wavefront,
                             //   pieces) per segment the bin's cut divided, from word 4 on
   int32_t n_bins, bin_waves;
+  int32_t cached;           // bins of four wavefronts without tiles: plain loads of K/V (a small batch), not nontemporal ones
   const void* k_new;        // [rows][Hkv][D]: rows of the new tokens, for segments that append (else unused)
   const void* v_new;
 };
