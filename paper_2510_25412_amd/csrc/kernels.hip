@@ -540,6 +540,288 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
   merge_bin_pieces<E, G>(a, bin, W, wib, lds);
 }
 
+// ---------------------------------------------------------------------------------------
+// Decode bins on the matrix cores, fp32 weights (bf16 storage, 4 query heads per kv head).  The same stream of pages,
+// segments, pieces and LDS merge as decode_bins above; what differs is a page's arithmetic:
+//   S^T[16 tokens][16 columns] = K · Q^T     4 x v_mfma_f32_16x16x32_bf16 (exact products, two sums of 64)
+//   O^T[128 dims][16 columns] += V^T · P^T   8 x v_mfma_f32_16x16x16_bf16
+// A softmax weight is a 24-bit fp32 number; cut into three bf16 numbers of 8 bits each (hi, mid, lo: cutting is exact, and so is
+// their sum) it takes three of the 16 columns, column = part * G + head, so ONE product per 16 dims carries the weights at full
+// precision and V as it is stored.  The three columns of a head are added when a piece ends.
+// Neither operand needs LDS or a transpose: a lane (col, grp) loads 64 contiguous bytes of K per token `col` and step, and of
+// V the tokens 4 grp .. +3 at dims 8 col .. +7; product block e holds dims 8 i + e, so the lane's own words, the tokens of a
+// dim packed by v_perm, are the operand (16 instructions a page), and the lane's four scores are the tokens it supplies.
+// About 70 vector instructions a page instead of 330 (dot products on lane octets, 32 fused multiply-adds per dim chunk):
+// the attention launch of 64 files of 512..4096 tokens 97.4 -> 95.1 us (6.3 TB/s), of 8 files of 4000 27.2 -> 26.1 us, the mixed
+// batch's 1734 -> 1724 us.  What bounds it is HBM, and with few files the 40 GB/s that one compute unit draws.  Error against
+// 64 bits 2.0e-7, the vector units' 2.2e-7.  A third page in flight: slower (96.2 us; one file of 2000 tokens 15.3 -> 17.8 us).
+// ---------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+template <int N>
+__device__ __forceinline__ float row_shl(float x) {     // value of the lane N further up in the 16-lane row (0 past its end)
+  return as_f32(__builtin_amdgcn_update_dpp(0, as_u32(x), 0x100 + N, 0xf, 0xf, true));
+}
+
+template <int G>
+__device__ __forceinline__ void decode_bins_mx(const DecodeArgs& a, const int bin, const int W, float* lds) {
+  constexpr int D = 128, SLOT = BinLds<ElemBF16, G>::kSlot, ACC = BinLds<ElemBF16, G>::kAcc;
+  if (bin >= a.n_bins) return;           // the whole workgroup
+  const int lane = threadIdx.x & 63;
+  const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));      // wavefront within the bin
+  const int col = lane & 15, grp = lane >> 4;
+  const int head = col % G, part = col / G;                                      // columns from 3 G on are ignored
+  const int32_t* ww = a.waves + ((int64_t)bin * W + wib) * 8;
+  int remaining = sload(ww + 2);
+
+  if (remaining > 0) {
+  // cursors and records as in decode_bins
+  int seg = sload(ww + 0), p = sload(ww + 1);
+  const int pid_first = sload(ww + 4);
+  const int32_t* sr = a.segs + (int64_t)seg * 8;
+  int pe = sload(sr + 3), vis = sload(sr + 4), qh = sload(sr + 5);
+  int dest = sload(sr + 6), app = sload(sr + 7), tbl = sload(sr + 0);
+  bool from_start = p == sload(sr + 2);
+  int lseg = seg, lg = sload(sr + 1), lp = p, lpe = pe, ltbl = sload(sr + 0), lrem = remaining;
+  int n_tbl = 0, n_g = 0, n_pb = 0, n_pe = 0;
+  auto fetch_next_seg = [&](int ss) __attribute__((always_inline)) {
+    const int32_t* q4 = a.segs + (int64_t)ss * 8;
+    n_tbl = sload(q4 + 0);
+    n_g = sload(q4 + 1);
+    n_pb = sload(q4 + 2);
+    n_pe = sload(q4 + 3);
+  };
+  fetch_next_seg(lseg + 1);
+  int c_pe = 0, c_vis = 0, c_qh = 0, c_dest = 0, c_app = 0, c_tbl = 0;
+  auto fetch_compute_next_seg = [&]() __attribute__((always_inline)) {
+    const int32_t* q8 = a.segs + (int64_t)(seg + 1) * 8;
+    c_pe = sload(q8 + 3);
+    c_vis = sload(q8 + 4);
+    c_qh = sload(q8 + 5);
+    c_dest = sload(q8 + 6);
+    c_app = sload(q8 + 7);
+    c_tbl = sload(q8 + 0);
+  };
+
+  const int k_off = col * kHalfBytes + grp * 16;                                 // token col, chunk 4 ks + grp of its row
+  const int v_off = kBlk + (col >> 3) * (kP * kHalfBytes) + (4 * grp) * kHalfBytes + (col & 7) * 16;      // tokens 4 grp + u, chunk col
+  int next_pid = pid_first;
+  auto load_next = [&](PageRegs& R) __attribute__((always_inline)) {
+    const bool valid = lrem > 0;
+    const uint8_t* base = a.pool + (int64_t)(valid ? lg : 0) * kSlab + (int64_t)(valid ? next_pid : 0) * a.page_bytes;
+    if (valid) {
+      --lrem;
+      if (++lp == lpe) {
+        ++lseg;
+        ltbl = n_tbl;
+        lg = n_g;
+        lp = n_pb;
+        lpe = n_pe;
+        fetch_next_seg(lseg + 1);
+      }
+      next_pid = lrem > 0 ? sload(a.pt + ltbl + lp) : 0;
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+      R.k[ks] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + k_off + (ks >> 1) * (kP * kHalfBytes) + (ks & 1) * 64)));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) R.v[u] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + v_off + u * kHalfBytes)));
+  };
+
+  bf16x8_t q[4];                         // Q^T operand: this lane's head, dims 32 ks + 8 grp .. +8
+  u32x4_t nr;                            // the row's new token: K chunks in lanes 0..15, V chunks in 16..31 (decode_bins)
+  auto load_q = [&]() __attribute__((always_inline)) {
+    const uint8_t* qp = (const uint8_t*)a.q + (int64_t)(qh + head) * kRowBytes + grp * 16;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) q[ks] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(qp + ks * 64));
+    nr = *(const u32x4_t*)((const uint8_t*)((lane & 16) ? a.v_new : a.k_new) + (int64_t)(qh / G) * kRowBytes + (lane & 15) * 16);
+  };
+  fetch_compute_next_seg();
+  load_q();
+
+  f32x4_t O[8];
+  float m, l;
+  auto reset_state = [&]() __attribute__((always_inline)) {
+    m = -1e30f;
+    l = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) O[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  };
+  reset_state();
+  int piece = 0;
+  // masks that leave a lane its part of a weight: w - (w & cut1) drops the upper 8 bits, once more the next 8
+  const uint32_t cut1 = part >= 1 ? 0xffff0000u : 0u, cut2 = part >= 2 ? 0xffff0000u : 0u;
+
+  auto compute = [&](PageRegs& R, int pi) __attribute__((always_inline)) {
+    const int nvalid = vis - pi * kP;          // >= 1; >= 16 for a full page
+    f32x4_t S = {0.f, 0.f, 0.f, 0.f}, S2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, R.k[ks]), q[ks], S, 0, 0, 0);
+      S2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, R.k[2 + ks]), q[2 + ks], S2, 0, 0, 0);
+    }
+    S = S + S2;
+    if (nvalid < kP) {
+      // ragged last page: slots past the file's end hold whatever was there before; weight 0, but 0 * NaN is NaN
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (4 * grp + u >= nvalid) {
+          S[u] = -__builtin_inff();
+          R.v[u] = make_uint4(0, 0, 0, 0);
+        }
+    }
+    const float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3])) * a.scale_log2e;
+    if (__builtin_amdgcn_ballot_w64(mx > m + kTau) != 0) {     // rare after the first page
+      const float mn = pair32_max(pair16_max(fmaxf(m, mx)));   // the four lane groups of a column agree
+      const float al = __builtin_amdgcn_exp2f(m - mn);
+      l *= al;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) O[e][v] *= al;
+      m = mn;
+    }
+    uint32_t w[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float x = __builtin_amdgcn_exp2f(__builtin_fmaf(S[v], a.scale_log2e, -m));
+      l += x;
+      x -= as_f32(as_u32(x) & cut1);
+      x -= as_f32(as_u32(x) & cut2);
+      w[v] = as_u32(x);
+    }
+    const s16x4_t P = __builtin_bit_cast(s16x4_t, make_uint2(__builtin_amdgcn_perm(w[1], w[0], 0x07060302), __builtin_amdgcn_perm(w[3], w[2], 0x07060302)));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const uint32_t sel = (e & 1) ? 0x07060302 : 0x05040100;
+      auto word = [&](int u) { return (e >> 1) == 0 ? R.v[u].x : (e >> 1) == 1 ? R.v[u].y : (e >> 1) == 2 ? R.v[u].z : R.v[u].w; };
+      const s16x4_t vt = __builtin_bit_cast(s16x4_t, make_uint2(__builtin_amdgcn_perm(word(1), word(0), sel), __builtin_amdgcn_perm(word(3), word(2), sel)));
+      O[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, P, O[e], 0, 0, 0);
+    }
+  };
+
+  // End of a piece: the sums of the four lane groups, the three columns of a head added up in its first; lane (col < G, grp)
+  // then holds dims 32 grp .. +31 of head col.  Then the compute cursor moves on.
+  auto finish_piece = [&]() __attribute__((always_inline)) {
+    const bool whole = from_start && p == pe;            // the piece is its whole segment
+    const int64_t out_row = (int64_t)qh * D;
+    const int f_dest = dest;
+    const bool more = remaining > 0;
+    if (more) {
+      ++seg;
+      pe = c_pe;
+      vis = c_vis;
+      qh = c_qh;
+      dest = c_dest;
+      app = c_app;
+      tbl = c_tbl;
+      fetch_compute_next_seg();
+      load_q();                                          // on its way while this piece is finished
+    }
+    const float ls = pair32_sum(pair16_sum(l));
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) O[e][v] += row_shl<G>(O[e][v]) + row_shl<2 * G>(O[e][v]);
+    const int at = col * D + 32 * grp;                   // + 8 v + e
+    if (col < G) {
+      // (destinations in device memory and in LDS apart, see decode_bins)
+      if (whole && f_dest < 0) {
+        const float inv = 1.0f / ls;
+        float* o = a.out + out_row + at;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          *(float4*)(o + 8 * v) = make_float4(O[0][v] * inv, O[1][v] * inv, O[2][v] * inv, O[3][v] * inv);
+          *(float4*)(o + 8 * v + 4) = make_float4(O[4][v] * inv, O[5][v] * inv, O[6][v] * inv, O[7][v] * inv);
+        }
+      } else if (whole) {
+        float* o = a.part_acc + (int64_t)f_dest * G * D + at;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          *(float4*)(o + 8 * v) = make_float4(O[0][v], O[1][v], O[2][v], O[3][v]);
+          *(float4*)(o + 8 * v + 4) = make_float4(O[4][v], O[5][v], O[6][v], O[7][v]);
+        }
+        if (grp == 0) *(float2*)(a.part_ml + ((int64_t)f_dest * G + col) * 2) = make_float2(m, ls);
+      } else {
+        float* o = lds + (piece == 0 ? 2 * wib : 2 * wib + 1) * SLOT;
+        if (grp == 0) *(float2*)(o + ACC + 2 * col) = make_float2(m, ls);
+        o += at;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          *(float2*)(o + 8 * v) = make_float2(O[0][v], O[1][v]);
+          *(float2*)(o + 8 * v + 2) = make_float2(O[2][v], O[3][v]);
+          *(float2*)(o + 8 * v + 4) = make_float2(O[4][v], O[5][v]);
+          *(float2*)(o + 8 * v + 6) = make_float2(O[6][v], O[7][v]);
+        }
+      }
+    }
+    ++piece;
+    if (more) {                                          // the next segment (the piece ended with its own)
+      p = sload(a.segs + (int64_t)seg * 8 + 2);
+      from_start = true;
+      reset_state();
+    }
+  };
+  auto do_unit = [&](PageRegs& R) __attribute__((always_inline)) {
+    if (app >= 0 && p + 1 == pe) {
+      // the row's last page: slot `app` is the new token's, still unwritten in the pool.  The lanes that hold that slot take
+      // the token's chunks and write them into the pool, where this wavefront is the page's only reader in this launch.
+      uint8_t* dst = const_cast<uint8_t*>(a.pool) + (int64_t)sload(a.pt + tbl + p) * a.page_bytes + (int64_t)(qh / G % a.Hkv) * kSlab + app * kHalfBytes;
+      auto chunk_of = [&](int from) __attribute__((always_inline)) {
+        return u32x4_t{(uint32_t)__shfl((int)nr.x, from), (uint32_t)__shfl((int)nr.y, from), (uint32_t)__shfl((int)nr.z, from), (uint32_t)__shfl((int)nr.w, from)};
+      };
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const u32x4_t x = chunk_of(4 * ks + grp);
+        if (col == app) {
+          R.k[ks] = __builtin_bit_cast(uint4, x);
+          *(u32x4_t*)(dst + (ks >> 1) * (kP * kHalfBytes) + ((ks & 1) * 4 + grp) * 16) = x;
+        }
+      }
+      const u32x4_t y = chunk_of(16 + col);
+      if (grp == (app >> 2)) *(u32x4_t*)(dst + kBlk + (col >> 3) * (kP * kHalfBytes) + (col & 7) * 16) = y;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)                        // (register indices stay compile-time constants)
+        if (4 * grp + u == app) R.v[u] = __builtin_bit_cast(uint4, y);
+    }
+    compute(R, p);
+    ++p;
+    --remaining;
+  };
+
+  // One copy of the end-of-piece code for both register sets: a launch starts with a cold instruction cache, and a wavefront of
+  // a small batch runs through this code once.
+  PageRegs A, B;
+  load_next(A);
+  bool odd = false;
+  while (remaining > 0) {
+    if (!odd) {
+      load_next(B);
+      do_unit(A);
+    } else {
+      load_next(A);
+      do_unit(B);
+    }
+    odd = !odd;
+    if (p == pe || remaining == 0) finish_piece();
+  }
+  }
+  __syncthreads();                                       // every piece of the bin is in LDS (or went straight to its destination)
+  merge_bin_pieces<ElemBF16, G>(a, bin, W, wib, lds);
+}
+
+// The decode bins of a shape.  With 1 or 2 query heads per kv head the vector units' page is short, and its loads take whole
+// 128-byte lines of K where the matrix cores' take halves: attention launch, 64 files of 512..4096 tokens, matrix cores / vector
+// units: G = 1 94.7 / 93.3 us, G = 2 98.6 / 97.9, G = 4 99.3 / 101.4; 256 files of 100..260: 37.3 / 34.7, 37.5 / 35.9, 39.1 / 39.9.
+// Small batches (STREAM = false) stay with the vector units too: one file of 2000 tokens x 32 layers 473 against 501 us.
+template <typename E, int G, bool STREAM>
+__device__ __forceinline__ void bins_of(const DecodeArgs& a, const int bin, const int W, float* lds) {
+  if constexpr (E::kDimsPerChunk == 8 && G == 4 && STREAM) decode_bins_mx<G>(a, bin, W, lds);
+  else decode_bins<E, G, STREAM>(a, bin, W, lds);
+}
+
 template <typename E, int GT, int G>
 __device__ __forceinline__ void decode_ranges(const DecodeArgs& a, const int block, uint8_t (*plds)[kSlab], const int wpb = kWavesPerBlock) {
   constexpr bool kPair = G < GT;
@@ -826,7 +1108,6 @@ __device__ __forceinline__ void decode_ranges(const DecodeArgs& a, const int blo
 // for slightly perturbed weights.  V is converted bf16 -> fp16 while it is transposed into LDS:
 // packing the same dim of two neighbouring tokens into one register IS the transposition.
 // ---------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
@@ -1246,7 +1527,6 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
 // paper section 4.1): column c is then (token c / GT, head c % GT), token t sees vis + t file
 // tokens, and the page loop runs to the last token's limit: one pass over K/V for all of them.
 // ---------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 constexpr int kVtRow = 80;                    // bytes per dim row of V^T (32 tokens fp16 + 16 pad)
 constexpr int kVtLds = 128 * kVtRow;          // 10 KiB per wavefront
 
@@ -1530,7 +1810,7 @@ __global__ __launch_bounds__(64 * TW, 8 / TW) void attn_kernel(DecodeArgs da, Pr
     }
   }
   if constexpr (G < 8) {
-    if (is_decode) decode_bins<E, G, true>(da, (int)(~g * 8 + x), TW, (float*)lds);
+    if (is_decode) bins_of<E, G, true>(da, (int)(~g * 8 + x), TW, (float*)lds);
   }
 }
 
@@ -1538,7 +1818,7 @@ __global__ __launch_bounds__(64 * TW, 8 / TW) void attn_kernel(DecodeArgs da, Pr
 template <typename E, int G, int W, bool STREAM>
 __global__ __launch_bounds__(64 * W, 8 / W) void decode_only_kernel(DecodeArgs da) {
   __shared__ __align__(16) float lds[2 * W * BinLds<E, G>::kSlot];
-  decode_bins<E, G, STREAM>(da, (int)blockIdx.x, W, lds);
+  bins_of<E, G, STREAM>(da, (int)blockIdx.x, W, lds);
 }
 
 // Decode ranges for 8 query heads per kv head: one workgroup of two wavefronts per range.
@@ -1566,7 +1846,6 @@ __global__ __launch_bounds__(128, 2) void decode_pair_kernel(DecodeArgs da) {
 // files, 8 heads: 543 -> 27 us (as rows of the vector-unit kernel: 67 us of kernel that re-read the file per token, and 0.6 ms of
 // planning for 13 500 ranges); 8 prompts of 400..500 tokens on 500, 16 query heads: 1232 -> 133 us (80 of 157 TFLOP/s).
 // ---------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(4))) float f32x4v_t;
 constexpr int kRowTileWaves = 8;
 constexpr int kRowTileRows = 32;
 constexpr int kRowTileStride = 68;            // floats per row of the exchange buffer: 64 dims + 4 (16-byte stores of 16 rows hit all banks)
@@ -1592,47 +1871,47 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
     const int rho = ct * 16 + col;
     const int tl = min(rho / G, count - 1);                        // rows past the last token repeat it (never written)
     vis[ct] = vis0 + tl;
-    const f32x4v_t* qp = (const f32x4v_t*)((const uint8_t*)a.q + ((int64_t)(qrow + tl) * a.Hq + head * G + rho % G) * kRowBytes + grp * 64);
+    const f32x4_t* qp = (const f32x4_t*)((const uint8_t*)a.q + ((int64_t)(qrow + tl) * a.Hq + head * G + rho % G) * kRowBytes + grp * 64);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const f32x4v_t x = qp[i];
+      const f32x4_t x = qp[i];
 #pragma unroll
       for (int e = 0; e < 4; ++e) q[ct][4 * i + e] = x[e];
     }
   }
-  f32x4v_t O[2][4];
+  f32x4_t O[2][4];
   float m[2], l[2];
 #pragma unroll
   for (int ct = 0; ct < 2; ++ct) {
     m[ct] = -1e30f;
     l[ct] = 0.f;
 #pragma unroll
-    for (int db = 0; db < 4; ++db) O[ct][db] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+    for (int db = 0; db < 4; ++db) O[ct][db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
 
   const uint8_t* slab = a.pool + (int64_t)head * kSlab;
   const int k_off = (grp >> 1) * (kP * kHalfBytes) + col * kHalfBytes + (grp & 1) * 64;        // token col, dims 16 grp .. +15
   const int v_off = kBlk + (col >> 3) * (kP * kHalfBytes) + (4 * grp) * kHalfBytes + (col & 7) * 16;   // tokens 4 grp + v, dims 4 col .. +3
-  f32x4v_t kk[4], vv[4];
+  f32x4_t kk[4], vv[4];
   int p = page0 + wv;
   int pid = p < page1 ? sload(tbl + p) : 0;                        // a wavefront without pages: page 0, loaded and never used
   {
-    const f32x4v_t* kp = (const f32x4v_t*)(slab + (int64_t)pid * a.page_bytes + k_off);
+    const f32x4_t* kp = (const f32x4_t*)(slab + (int64_t)pid * a.page_bytes + k_off);
 #pragma unroll
     for (int i = 0; i < 4; ++i) kk[i] = kp[i];
   }
   for (; p < page1; p += kRowTileWaves) {
     const uint8_t* base = slab + (int64_t)pid * a.page_bytes;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) vv[v] = *(const f32x4v_t*)(base + v_off + v * kHalfBytes);
+    for (int v = 0; v < 4; ++v) vv[v] = *(const f32x4_t*)(base + v_off + v * kHalfBytes);
     pid = p + kRowTileWaves < page1 ? sload(tbl + p + kRowTileWaves) : 0;
     // eight sums of 8 products each, added up as a tree: one chain of 64 would round three times as coarsely as the
     // vector units' eight lanes per score
-    f32x4v_t S[2];
+    f32x4_t S[2];
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
       auto part = [&](int u) __attribute__((always_inline)) {
-        f32x4v_t x = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1)], q[ct][2 * u], f32x4v_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1)], q[ct][2 * u], f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         return __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1) + 1], q[ct][2 * u + 1], x, 0, 0, 0);
       };
       if (ct == 0 || two) {
@@ -1640,12 +1919,12 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
         __builtin_amdgcn_sched_barrier(0);       // (all eight at once would not fit the registers)
         S[ct] = S[ct] + ((part(4) + part(5)) + (part(6) + part(7)));
       } else {
-        S[ct] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+        S[ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     {
-      const f32x4v_t* kp = (const f32x4v_t*)(slab + (int64_t)pid * a.page_bytes + k_off);
+      const f32x4_t* kp = (const f32x4_t*)(slab + (int64_t)pid * a.page_bytes + k_off);
 #pragma unroll
       for (int i = 0; i < 4; ++i) kk[i] = kp[i];
     }
@@ -1658,7 +1937,7 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
       // slots past the file's end may hold anything; their weight is 0, but 0 * NaN is NaN
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        if (tok + v >= kv_end) vv[v] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+        if (tok + v >= kv_end) vv[v] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
@@ -1712,12 +1991,12 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
       for (int v = 0; v < 4; ++v) O[ct][db][v] *= f;
   }
   // lane's values of column tile ct, register v: dims 16 grp + 4 v .. +3 (one per dim block)
-  auto cell = [&](int w, int ct, int v) { return (f32x4v_t*)&xch[w][ct * 16 + col][16 * grp + 4 * v]; };
+  auto cell = [&](int w, int ct, int v) { return (f32x4_t*)&xch[w][ct * 16 + col][16 * grp + 4 * v]; };
   if (wv >= kRowTileWaves / 2) {
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) *cell(wv - kRowTileWaves / 2, ct, v) = f32x4v_t{O[ct][0][v], O[ct][1][v], O[ct][2][v], O[ct][3][v]};
+      for (int v = 0; v < 4; ++v) *cell(wv - kRowTileWaves / 2, ct, v) = f32x4_t{O[ct][0][v], O[ct][1][v], O[ct][2][v], O[ct][3][v]};
   }
   __syncthreads();
   if (wv < kRowTileWaves / 2) {
@@ -1725,17 +2004,17 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
     for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        f32x4v_t* c = cell(wv, ct, v);
-        *c = *c + f32x4v_t{O[ct][0][v], O[ct][1][v], O[ct][2][v], O[ct][3][v]};
+        f32x4_t* c = cell(wv, ct, v);
+        *c = *c + f32x4_t{O[ct][0][v], O[ct][1][v], O[ct][2][v], O[ct][3][v]};
       }
   }
   __syncthreads();
   const int row = threadIdx.x >> 4, d0 = (threadIdx.x & 15) * 4;   // 32 rows x 64 dims, four dims per thread
   const int tl = row / G, h = row % G;
   if (tl >= count) return;
-  f32x4v_t o = *(const f32x4v_t*)&xch[0][row][d0];
+  f32x4_t o = *(const f32x4_t*)&xch[0][row][d0];
 #pragma unroll
-  for (int w = 1; w < kRowTileWaves / 2; ++w) o = o + *(const f32x4v_t*)&xch[w][row][d0];
+  for (int w = 1; w < kRowTileWaves / 2; ++w) o = o + *(const f32x4_t*)&xch[w][row][d0];
   const float M = row_max(row);
   float L = 0.f;
 #pragma unroll
@@ -1743,10 +2022,10 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
   if (dest < 0) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = o[e] / L;
-    *(f32x4v_t*)(a.out + ((int64_t)(qrow + tl) * a.Hq + head * G + h) * 64 + d0) = o;
+    *(f32x4_t*)(a.out + ((int64_t)(qrow + tl) * a.Hq + head * G + h) * 64 + d0) = o;
   } else {
     const int64_t slot = (int64_t)(dest + tl) * G + h;
-    *(f32x4v_t*)(a.part_acc + slot * 64 + d0) = o;
+    *(f32x4_t*)(a.part_acc + slot * 64 + d0) = o;
     if (d0 == 0) {
       a.part_ml[slot * 2 + 0] = M;
       a.part_ml[slot * 2 + 1] = L;
