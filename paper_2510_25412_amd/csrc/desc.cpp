@@ -48,6 +48,10 @@ int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_
   }
   return b_best;
 }
+// Longest range (pages) that a small decode batch leaves to one workgroup of four wavefronts.  Per layer, 32 query heads, with a
+// merge launch / without: 32 files of 100 tokens 13.6 / 9.1 us, sixteen of 200 12.8 / 9.7, eight of 300 12.5 / 10.6, one of 400
+// 12.1 / 12.2, one of 500 (32 pages) 12.0 / 13.0.
+constexpr int64_t kWholePages = 24;
 // bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch (a start of 6: three
 // prompts of 100..700 tokens on 200..4000 in two rounds of pieces, 78 us, instead of one, 74; 17 other shapes the same)
 constexpr int64_t kTileStart = 10, kTileMerge = 11;
@@ -287,12 +291,14 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   }
 
   // ---- units of the decode kernel
-  int64_t total_units = 0;
+  int64_t total_units = 0, longest_range = 0;
   for (int32_t b = 0; b < n_lips; ++b) {
     if (is_prefill(b)) continue;
     for (int32_t i = 0; i < n_tokens[b]; i += RT) {
       const int64_t vis_last = len_after[b] - n_tokens[b] + std::min(i + RT, n_tokens[b]);   // what the row's last token sees
-      total_units += ((vis_last + P - 1) / P - share_start[b]) * H;
+      const int64_t pages = (vis_last + P - 1) / P - share_start[b];
+      total_units += pages * H;
+      longest_range = std::max(longest_range, pages);
     }
   }
   // bins (whole ranges per workgroup, pieces combined through LDS) for the vector-unit kernel; the global
@@ -305,6 +311,9 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   // Per layer, 32 query heads, before / after: a file of 2000 tokens 15.7 / 12.3 us, four of 200 15.6 / 12.2, sixteen of 400
   // 16.9 / 14.5, 64 of 100 18.0 / 15.9; past the line, sixteen of 1000 tokens (8064 units): 21.0 / 22.9.
   const bool small_decode = bins && prm.spread_small && n_tiles == 0 && total_units <= (int64_t)prm.cus * 4 * prm.min_units_per_wave;
+  // ... and if there are no more ranges than compute units and all are short, a workgroup per range: nothing is divided between
+  // workgroups, so the merge launch is saved, which is worth about four pages of a wavefront's time.
+  const bool whole_small = small_decode && n_rows * H <= prm.cus && longest_range <= kWholePages;
   const int32_t W = !bins ? 0 : n_tiles > 0 ? (TQ * G != 256 ? 4 : 8) : (prm.bin_waves == 4 || small_decode ? 4 : 8);
   const int64_t max_bins = std::max<int64_t>(1, prm.max_waves / std::max(W, 1));
   int64_t nw = (total_units + prm.min_units_per_wave - 1) / prm.min_units_per_wave;
@@ -314,6 +323,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   if (bins) {
     n_bins = (total_units + (int64_t)prm.min_units_per_wave * W - 1) / ((int64_t)prm.min_units_per_wave * W);
     n_bins = std::max<int64_t>(1, std::min<int64_t>(n_bins, max_bins));
+    if (whole_small) n_bins = n_rows * H;
     nw = n_bins * W;
   }
   const int64_t n_members = (int64_t)member_rows.size();
@@ -392,7 +402,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     // Plan A, when there are several ranges per bin (short files, the members of forked prefixes): whole ranges, handed to
     // the bins longest first; nothing is split, so no range leaves partials in device memory because of the bins.
     bool planned = false;
-    if (n_rows * H >= 3 * n_bins) {
+    if (whole_small || n_rows * H >= 3 * n_bins) {
       n_segs = 0;
       n_split_partials = n_split_merge = 0;
       for (int64_t row = 0; row < n_rows; ++row) {
@@ -460,7 +470,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
           }
         }
       }
-      planned = worst * n_bins * 100 <= total_cost * (100 + prm.bin_tolerance);
+      planned = whole_small || worst * n_bins * 100 <= total_cost * (100 + prm.bin_tolerance);
     }
     // Plan B: the units in (row, head, page) order are cut into n_bins * W contiguous ranges of equal cost, one per wavefront,
     // exactly like the global cut (on a virtual axis where every range occupies range_cost + pages, wavefront k starts at

@@ -331,6 +331,26 @@ def test_prefill_tiles_cut_into_key_chunks(Hq, Hkv):
     assert cut >= 3
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,dtype", [(32, 8, 128, synth.BF16), (8, 8, 128, synth.BF16), (4, 1, 128, synth.BF16), (16, 8, 64, synth.F32)])
+def test_small_decode_batches(Hq, Hkv, D, dtype):
+    """Decode batches around the lines of the planner's rules for small ones: ranges of fewer pages than wavefronts, of 24
+    pages (a workgroup each, no merge) and of 25 (cut, merged), more ranges than compute units, and a batch just past
+    "small"; the last
+    appended row is read back."""
+    shape = synth.Shape(Hq, Hkv, D, 16, dtype)
+    for lens in ([0], [1, 15, 16, 40], [383], [384], [383] * 31, [100] * 33, [2000], [1000, 5], [240] * 40):
+        wl = synth.custom("small_decode", shape, [("new", n) for n in lens], [(i, 1) for i in range(len(lens))], 1500, seed=5 + len(lens))
+        got, sess, ref, osess = run_both(wl)
+        check_outputs(got, ref, tol=1e-5)          # weights and sums in fp32, as for the other single-token rows
+        check_state(wl, sess, osess)
+        last = widen(wl.batch()["v_new"])[-1]
+        v = torch.empty((1, Hkv, D), dtype=torch.float32 if dtype == synth.F32 else torch.bfloat16, device="cuda")
+        sess.ctx.kv_read(sess.h[len(lens) - 1], lens[-1], 1, torch.empty_like(v), v, sess.stream)
+        torch.cuda.synchronize()
+        assert np.array_equal(v.float().cpu().numpy()[0], last)
+        sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 4), (8, 2), (8, 1), (1, 1)])
 def test_fp32_row_tiles(Hq, Hkv):
     """Several new tokens per LIP in fp32 storage (row tiles: 32 / G tokens x one kv head, every eighth page per
