@@ -370,6 +370,55 @@ def test_fp32_row_tiles(Hq, Hkv):
         sess.close()
 
 
+def _run_with_values(wl, edit_old, edit_new, **kw):
+    """Runs a workload whose V rows are edited: edit_old(V, first token of V in its file) for the files' rows,
+    edit_new(V rows of the batch, list of (first row, tokens, length before)) for the batch's.  The scores don't change, so the outputs
+    are the oracle's of the unedited workload wherever a row meets no edited value: returns (outputs, those, session, ranges)."""
+    ref, osess = run_oracle(wl, dtype=np.float64)
+    ops, batch = wl.setup_ops, wl.batch
+    at = np.concatenate([[0], np.cumsum(wl.batch_n)])
+    ranges = [(int(at[i]), n, wl.lengths[f]) for i, (f, n) in enumerate(zip(wl.batch_files, wl.batch_n))]
+
+    def edited_ops():
+        for op in ops():
+            if op[0] == "append":
+                edit_old(op[3])
+            yield op
+
+    def edited_batch():
+        b = batch()
+        edit_new(b["v_new"], ranges)
+        return b
+
+    wl.setup_ops, wl.batch = edited_ops, edited_batch
+    print(f"[case] {wl.name} lips={len(wl.batch_files)} tokens={sum(wl.batch_n)}", flush=True)
+    got, sess = _hip().run_workload(wl, poison=True, **kw)
+    return got, ref, sess, ranges
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,dtype", [(16, 8, 128, synth.BF16), (8, 8, 128, synth.BF16), (16, 8, 64, synth.F32)])
+def test_infinite_values_of_visible_tokens(Hq, Hkv, D, dtype):
+    """Every stored token has one infinite V element, token t in dim t % 48 (negative in odd dims): an output in such a dim is that
+    infinity whatever the key's weight (the maximum's is exactly 1), in batches of every route: large decode batches, one file
+    cut into many pieces (merged in groups with places to spare), prompts whose keys are cut into chunks; the other
+    dims are untouched."""
+    inf = (0x7F80, 0xFF80) if dtype == synth.BF16 else (np.inf, -np.inf)
+
+    def edit(V):
+        t = np.arange(len(V))
+        V[t, :, t % 48] = np.where(t % 2, inf[1], inf[0]).astype(V.dtype)[:, None]
+
+    shape = synth.Shape(Hq, Hkv, D, 16, dtype)
+    for files, batch in (([1100] * 9 + [50, 2500], [1] * 11), ([2000], [1]), ([20000], [1]), ([100, 300], [1, 1]), ([3000], [16]), ([2500, 700], [70, 1])):
+        wl = synth.custom("inf_values", shape, [("new", n) for n in files], list(enumerate(batch)), 1500, seed=3 + len(files))
+        got, ref, sess, ranges = _run_with_values(wl, edit, lambda v, r: None)
+        for dim in range(48):
+            ref[:, :, dim] = -np.inf if dim % 2 else np.inf
+        assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref)), (files, batch)
+        check_outputs(got[:, :, 48:], ref[:, :, 48:])
+        sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(32, 8), (64, 8), (8, 8)])
 def test_shared_prefix_groups(Hq, Hkv):
     """Forks of a prefix decode through the shared-prefix tiles (prefix pages read once per
