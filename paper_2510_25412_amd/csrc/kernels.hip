@@ -721,10 +721,16 @@ __device__ __forceinline__ void decode_bins_mx(const DecodeArgs& a, const int bi
       load_q();                                          // on its way while this piece is finished
     }
     const float ls = pair32_sum(pair16_sum(l));
+    // An infinite V element: a lower part that is 0 (the maximum's weight is exactly 1) makes its column NaN, while the upper
+    // part, never 0 where the weight is not, makes its own what the whole weight makes it.  So lower parts that are NaN are
+    // dropped: where V is NaN, or infinities of both signs meet, the upper part's column says so by itself.
 #pragma unroll
     for (int e = 0; e < 8; ++e)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) O[e][v] += row_shl<G>(O[e][v]) + row_shl<2 * G>(O[e][v]);
+      for (int v = 0; v < 4; ++v) {
+        const float low = row_shl<G>(O[e][v]) + row_shl<2 * G>(O[e][v]);
+        O[e][v] += low == low ? low : 0.f;
+      }
     const int at = col * D + 32 * grp;                   // + 8 v + e
     if (col < G) {
       // (destinations in device memory and in LDS apart, see decode_bins)

@@ -396,7 +396,7 @@ def _run_with_values(wl, edit_old, edit_new, **kw):
     return got, ref, sess, ranges
 
 
-@pytest.mark.parametrize("Hq,Hkv,D,dtype", [(16, 8, 128, synth.BF16), (8, 8, 128, synth.BF16), (16, 8, 64, synth.F32)])
+@pytest.mark.parametrize("Hq,Hkv,D,dtype", [(32, 8, 128, synth.BF16), (16, 8, 128, synth.BF16), (8, 8, 128, synth.BF16), (16, 8, 64, synth.F32)])
 def test_infinite_values_of_visible_tokens(Hq, Hkv, D, dtype):
     """Every stored token has one infinite V element, token t in dim t % 48 (negative in odd dims): an output in such a dim is that
     infinity whatever the key's weight (the maximum's is exactly 1), in batches of every route: large decode batches, one file
