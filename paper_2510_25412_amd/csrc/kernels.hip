@@ -1855,7 +1855,8 @@ __global__ __launch_bounds__(128, 2) void decode_pair_kernel(DecodeArgs da) {
 // Both operands come straight from global memory in whole 1 KiB wavefront loads: no LDS in the loop, no barrier, no transpose.
 // V of a page is requested before its scores are computed and K of the next page after them, so one set of registers each
 // is enough and four wavefronts fit on a SIMD (<= 128 registers).  Bound: fp32 matrix cores (a page costs a wavefront 64 MFMAs
-// of 32 cycles for 8 KiB of K/V).  All sums and weights are fp32.  Measured, whole calls: four prompts of 64..512 tokens on new
+// of 32 cycles for 8 KiB of K/V).  All sums and weights are fp32.  A row must not meet what it does not see, also where that is
+// not finite (0 * Inf is NaN): such V elements of the tile's own tokens are left out of the products and added at the end.  Measured, whole calls: four prompts of 64..512 tokens on new
 // files, 8 heads: 543 -> 27 us (as rows of the vector-unit kernel: 67 us of kernel that re-read the file per token, and 0.6 ms of
 // planning for 13 500 ranges); 8 prompts of 400..500 tokens on 500, 16 query heads: 1232 -> 133 us (80 of 157 TFLOP/s).
 // ---------------------------------------------------------------------------------------
@@ -1867,6 +1868,7 @@ template <int G>
 __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(PrefillArgs a) {
   __shared__ __align__(16) float xch[kRowTileWaves / 2][kRowTileRows][kRowTileStride];
   __shared__ float stat[kRowTileWaves][kRowTileRows][2];          // (max, sum) per wavefront and row
+  __shared__ int left_out[kRowTileWaves];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int col = lane & 15, grp = lane >> 4;
@@ -1903,20 +1905,29 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
   }
 
   const uint8_t* slab = a.pool + (int64_t)head * kSlab;
-  const int k_off = (grp >> 1) * (kP * kHalfBytes) + col * kHalfBytes + (grp & 1) * 64;        // token col, dims 16 grp .. +15
-  const int v_off = kBlk + (col >> 3) * (kP * kHalfBytes) + (4 * grp) * kHalfBytes + (col & 7) * 16;   // tokens 4 grp + v, dims 4 col .. +3
+  // a page's address in scalar registers and the lane's offset in one of its own (left to itself the compiler keeps 64-bit sums
+  // and extended offsets, two registers each, through the loop, which has none to spare)
+  auto at = [&](int id, int part, uint32_t off) __attribute__((always_inline)) {
+    auto b = (const __attribute__((address_space(1))) uint8_t*)(slab + (int64_t)id * a.page_bytes + part);
+    asm("" : "+s"(b));
+    asm("" : "+v"(off));
+    return (const f32x4_t*)(b + off);
+  };
+  const uint32_t k_off = (grp >> 1) * (kP * kHalfBytes) + col * kHalfBytes + (grp & 1) * 64;        // token col, dims 16 grp .. +15
+  const uint32_t v_off = (col >> 3) * (kP * kHalfBytes) + (4 * grp) * kHalfBytes + (col & 7) * 16;   // tokens 4 grp + v, dims 4 col .. +3
   f32x4_t kk[4], vv[4];
   int p = page0 + wv;
   int pid = p < page1 ? sload(tbl + p) : 0;                        // a wavefront without pages: page 0, loaded and never used
   {
-    const f32x4_t* kp = (const f32x4_t*)(slab + (int64_t)pid * a.page_bytes + k_off);
+    const f32x4_t* kp = at(pid, 0, k_off);
 #pragma unroll
     for (int i = 0; i < 4; ++i) kk[i] = kp[i];
   }
+  bool odd = false;                                                // V elements of the tile's own tokens were left out
   for (; p < page1; p += kRowTileWaves) {
-    const uint8_t* base = slab + (int64_t)pid * a.page_bytes;
+    const f32x4_t* vp = at(pid, kBlk, v_off);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) vv[v] = *(const f32x4_t*)(base + v_off + v * kHalfBytes);
+    for (int v = 0; v < 4; ++v) vv[v] = vp[v * (kHalfBytes / 16)];
     pid = p + kRowTileWaves < page1 ? sload(tbl + p + kRowTileWaves) : 0;
     // eight sums of 8 products each, added up as a tree: one chain of 64 would round three times as coarsely as the
     // vector units' eight lanes per score
@@ -1937,20 +1948,28 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
       __builtin_amdgcn_sched_barrier(0);
     }
     {
-      const f32x4_t* kp = (const f32x4_t*)(slab + (int64_t)pid * a.page_bytes + k_off);
+      const f32x4_t* kp = at(pid, 0, k_off);
 #pragma unroll
       for (int i = 0; i < 4; ++i) kk[i] = kp[i];
     }
-    const int tok = p * kP + 4 * grp;                              // the lane's first token of the page
     if ((p + 1) * kP > vis0) {                                     // the causal edge of some row, or the end of the file
+      const int tok = p * kP + 4 * grp;                            // the lane's first token of the page
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) S[ct][v] = tok + v < vis[ct] ? S[ct][v] : -__builtin_inff();
-      // slots past the file's end may hold anything; their weight is 0, but 0 * NaN is NaN
+        for (int v = 0; v < 4; ++v) S[ct][v] = v < vis[ct] - tok ? S[ct][v] : -__builtin_inff();
+      // slots past the file's end may hold anything; their weight is 0, but 0 * NaN is NaN.  Likewise elements of the tile's own
+      // tokens that are not finite: V is the operand of all rows, and some don't see the token (added at the end to those that do)
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (tok + v >= kv_end) vv[v] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int v = 0; v < 4; ++v) {
+        if (v >= kv_end - tok) vv[v] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v >= vis0 - tok && !__builtin_isfinite(vv[v][e])) {
+            vv[v][e] = 0.f;
+            odd = true;
+          }
+      }
     }
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
@@ -1979,15 +1998,21 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
     }
   }
 
+  // (the thread's place again, from the register that brings it: nothing but the loop's own values lives through the loop)
+  int tid = threadIdx.x;
+  asm("" : "+v"(tid));
+  const int ecol = tid & 15, egrp = (tid >> 4) & 3;
   // combine the eight wavefronts: common maximum per row, everyone's accumulators rescaled to it, added up in two stages
 #pragma unroll
   for (int ct = 0; ct < 2; ++ct) {
     l[ct] = pair32_sum(pair16_sum(l[ct]));
-    if (grp == 0) {
-      stat[wv][ct * 16 + col][0] = m[ct];
-      stat[wv][ct * 16 + col][1] = l[ct];
+    if (egrp == 0) {
+      stat[wv][ct * 16 + ecol][0] = m[ct];
+      stat[wv][ct * 16 + ecol][1] = l[ct];
     }
   }
+  const bool any_odd = __builtin_amdgcn_ballot_w64(odd) != 0;
+  if ((tid & 63) == 0) left_out[wv] = any_odd;
   __syncthreads();
   auto row_max = [&](int row) {
     float M = stat[0][row][0];
@@ -1997,14 +2022,14 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
   };
 #pragma unroll
   for (int ct = 0; ct < 2; ++ct) {
-    const float f = __builtin_amdgcn_exp2f(m[ct] - row_max(ct * 16 + col));
+    const float f = __builtin_amdgcn_exp2f(m[ct] - row_max(ct * 16 + ecol));
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int v = 0; v < 4; ++v) O[ct][db][v] *= f;
   }
-  // lane's values of column tile ct, register v: dims 16 grp + 4 v .. +3 (one per dim block)
-  auto cell = [&](int w, int ct, int v) { return (f32x4_t*)&xch[w][ct * 16 + col][16 * grp + 4 * v]; };
+  // lane's values of column tile ct, register v: dims 16 egrp + 4 v .. +3 (one per dim block)
+  auto cell = [&](int w, int ct, int v) { return (f32x4_t*)&xch[w][ct * 16 + ecol][16 * egrp + 4 * v]; };
   if (wv >= kRowTileWaves / 2) {
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct)
@@ -2022,12 +2047,22 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
       }
   }
   __syncthreads();
-  const int row = threadIdx.x >> 4, d0 = (threadIdx.x & 15) * 4;   // 32 rows x 64 dims, four dims per thread
+  const int row = tid >> 4, d0 = ecol * 4;   // 32 rows x 64 dims, four dims per thread
   const int tl = row / G, h = row % G;
   if (tl >= count) return;
   f32x4_t o = *(const f32x4_t*)&xch[0][row][d0];
 #pragma unroll
   for (int w = 1; w < kRowTileWaves / 2; ++w) o = o + *(const f32x4_t*)&xch[w][row][d0];
+  bool add = false;
+#pragma unroll
+  for (int w = 0; w < kRowTileWaves; ++w) add |= left_out[w] != 0;
+  if (add)                                                         // rare: Inf and NaN are what they are at any weight
+    for (int t = max(vis0, page0 * kP); t < min(vis0 + tl, page1 * kP); ++t) {
+      const f32x4_t x = *(const f32x4_t*)(slab + (int64_t)sload(tbl + t / kP) * a.page_bytes + kBlk + (d0 >> 5) * (kP * kHalfBytes) + (t % kP) * kHalfBytes + (d0 & 31) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (!__builtin_isfinite(x[e])) o[e] += x[e];
+    }
   const float M = row_max(row);
   float L = 0.f;
 #pragma unroll

@@ -419,6 +419,31 @@ def test_infinite_values_of_visible_tokens(Hq, Hkv, D, dtype):
         sess.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 4), (8, 1), (1, 1)])
+def test_fp32_tokens_do_not_meet_later_tokens_values(Hq, Hkv):
+    """fp32 preds of several tokens: new token i >= 1 has an infinite (every second a NaN) V element in dim i % 64, which the
+    rows before it must not meet, whichever path computes them: drafts, tiles, tiles cut into key chunks, first pages that
+    hold old and new tokens."""
+    shape = synth.Shape(Hq, Hkv, 64, 16, synth.F32)
+
+    def edit(v, ranges):
+        for first, n, _ in ranges:
+            for i in range(1, n):
+                v[first + i, :, i % 64] = np.nan if i % 2 else -np.inf
+
+    for files, batch in (([5, 0, 129, 40], [4, 7, 33, 1]), ([3000], [40]), ([16, 31, 500], [70, 12, 3]), ([100] * 12, [9] * 12)):
+        wl = synth.custom("later_values", shape, [("new", n) for n in files], list(enumerate(batch)), 600, seed=9 + Hkv)
+        got, ref, sess, ranges = _run_with_values(wl, lambda V: None, edit)
+        for first, n, _ in ranges:
+            for i in range(1, n):
+                seen = ref[first + i:first + n, :, i % 64]
+                seen[...] = np.where(np.isnan(seen), np.nan, np.nan if i % 2 else -np.inf)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref)), (files, batch)
+        ok = np.isfinite(ref)
+        check_outputs(np.where(ok, got, 0.0), np.where(ok, ref, 0.0), tol=1e-5)
+        sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(32, 8), (64, 8), (8, 8)])
 def test_shared_prefix_groups(Hq, Hkv):
     """Forks of a prefix decode through the shared-prefix tiles (prefix pages read once per
