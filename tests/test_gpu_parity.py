@@ -331,6 +331,22 @@ def test_prefill_tiles_cut_into_key_chunks(Hq, Hkv):
     assert cut >= 3
 
 
+@pytest.mark.parametrize("Hq,Hkv,n,new", [(32, 8, 4000, 100), (8, 8, 3000, 64), (64, 8, 6000, 33)])
+def test_key_chunks_round_weights_to_nearest(Hq, Hkv, n, new):
+    """Weights are rounded to 11 bits, to nearest: their relative errors are evenly spread over +-2^-11 / x, x in [1, 2) the
+    weight's mantissa (density 1 / (x ln 2)), so over N(0, 1) values the relative 2-norm error is
+    2^-10 sqrt(E[x^-2] / 12) = 2.07e-4, with 4 % for the sample; cut off it is 2.19e-4 with one maximum per row and more
+    with one per chunk."""
+    shape = synth.Shape(Hq, Hkv, 128, 16, synth.BF16)
+    wl = synth.custom("chunk_rounding", shape, [("new", n)], [(0, new)], 600, seed=17)
+    got, sess, ref, osess = run_both(wl)
+    assert sess.ctx.get_stats()["last_batch_tiles"] > -(-new * Hq // Hkv // 256) * Hkv
+    err = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    print(f"error {err:.3e}", flush=True)
+    assert err <= 2.15e-4
+    sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,dtype", [(32, 8, 128, synth.BF16), (8, 8, 128, synth.BF16), (4, 1, 128, synth.BF16), (16, 8, 64, synth.F32)])
 def test_small_decode_batches(Hq, Hkv, D, dtype):
     """Decode batches around the lines of the planner's rules for small ones: ranges of fewer pages than wavefronts, of 24
