@@ -37,9 +37,9 @@ sym_tuning default_tuning(const sym_config* cfg) {
   sym_tuning t;
   t.decode_mfma = (bf16 && G == 8) ? 1 : 0;   // 8 query heads per kv head are bound by vector issue on the VALU path
   t.min_units = 4;
-  // fp32 has no rows of several tokens, so short drafts go to tiles too.  32 files of 500 tokens, 8 new ones each: 55 us per call
-  // as rows, 23 us as tiles; with 2 or 3 new tokens 21 against 17 us, but the rows' sums are slightly finer there (error
-  // against 64 bits 1.7e-7 against 2.0e-7; from 8 tokens on the tiles are as good or better), so those stay rows.
+  // fp32 has no rows of several tokens, so short drafts go to tiles too.  Error against 64 bits, tiles / rows, geometric mean over
+  // files of 0..8000 tokens and 1..8 heads per kv head: 0.92 with 4 new tokens, 0.91 with 6, 0.89 with 8; time of whole calls 0.80,
+  // 0.71, 0.66.  With 2 or 3 new tokens there is less to win (0.84), and on few short files the rows are faster.
   t.prefill_min = bf16 ? 16 : 4;
   t.share_min_lips = 4;
   t.share_min_pages = 8;

@@ -1852,17 +1852,23 @@ __global__ __launch_bounds__(128, 2) void decode_pair_kernel(DecodeArgs da) {
 // prompt of a few hundred tokens gives every compute unit a short chain.  Per page and wavefront, everything transposed as in
 // the bf16 kernels (a lane's column is its query row):
 //   S^T[16 tokens][16 rows] = K · Q^T     16 x v_mfma_f32_16x16x4_f32: step s, lane group g supplies dim 16 g + s, so a lane
-//                                          reads 64 consecutive bytes of one token's K row, and Q sits in 16 registers
+//                                          reads 64 consecutive bytes of one token's K row; Q comes from LDS
 //   O^T[64 dims][16 rows]  += V^T · P^T   4 steps x 4 dim blocks: step v, lane group g supplies token 4 g + v, which is the
 //                                          token whose score the lane holds in register v; block d holds dims 4 i + d, so a
 //                                          lane reads 16 consecutive bytes of V per token
-// Both operands come straight from global memory in whole 1 KiB wavefront loads: no LDS in the loop, no barrier, no transpose.
-// V of a page is requested before its scores are computed and K of the next page after them, so one set of registers each
-// is enough and four wavefronts fit on a SIMD (<= 128 registers).  Bound: fp32 matrix cores (a page costs a wavefront 64 MFMAs
-// of 32 cycles for 8 KiB of K/V).  All sums and weights are fp32.  A row must not meet what it does not see, also where that is
-// not finite (0 * Inf is NaN): such V elements of the tile's own tokens are left out of the products and added at the end.  Measured, whole calls: four prompts of 64..512 tokens on new
-// files, 8 heads: 543 -> 27 us (as rows of the vector-unit kernel: 67 us of kernel that re-read the file per token, and 0.6 ms of
-// planning for 13 500 ranges); 8 prompts of 400..500 tokens on 500, 16 query heads: 1232 -> 133 us (80 of 157 TFLOP/s).
+// K and V come straight from global memory in whole 1 KiB wavefront loads: no barrier in the loop, no transpose.  V of a page is
+// requested before its scores are computed and K of the next page after them, so one set of registers each is enough and four
+// wavefronts fit on a SIMD (<= 128 registers, which is why Q waits in LDS: 8 reads per page beside 128 MFMAs).  Bound: fp32 matrix
+// cores (a page costs a wavefront 64 MFMAs of 32 cycles per column tile for 8 KiB of K/V).
+// All sums and weights are fp32, and sums are short: a page's products are added up by themselves before they meet the
+// accumulator, one rounding per page at its size instead of 16, and so are four chunks in the merge.  Error against 64 bits, 4..200
+// new tokens on 0..8000, tiles / rows of the vector-unit kernel: 0.67..0.92 (products added to the accumulator one by one: 1.06
+// with 4 tokens, on 500 tokens up to 1.23; short sums cost nothing: 31.6 / 31.3 us for the prompts below).
+// A row must not meet what it does not see, also where that is not finite (0 * Inf is NaN): such V elements of the tile's own
+// tokens are left out of the products and added at the end.
+// Measured, whole calls: four prompts of 64..512 tokens on new files, 8 heads: 538 -> 31 us (as rows of the vector-unit kernel: 67 us
+// of kernel that re-read the file per token, and 0.5 ms of planning for 13 500 ranges); 8 prompts of 400..500 tokens on 500, 16
+// query heads: 1250 -> 138 us (77 of 157 TFLOP/s).
 // ---------------------------------------------------------------------------------------
 constexpr int kRowTileWaves = 8;
 constexpr int kRowTileRows = 32;
@@ -1883,21 +1889,13 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
   const int kv_end = vis0 + count - 1;                             // tokens the tile's last row sees
   const bool two = count * G > 16;                                 // the second column tile holds rows
 
-  float q[2][16];
+  // Q waits in the exchange buffer, where each wavefront reads it page by page: the loop has no registers to spare for it
+  const int rho = threadIdx.x >> 4;
+  const int64_t q_at = (int64_t)(qrow + min(rho / G, count - 1)) * a.Hq + head * G + rho % G;      // rows past the last token repeat it (never written)
+  const f32x4_t q_part = ((const f32x4_t*)((const uint8_t*)a.q + q_at * kRowBytes))[threadIdx.x & 15];
   int vis[2];
 #pragma unroll
-  for (int ct = 0; ct < 2; ++ct) {
-    const int rho = ct * 16 + col;
-    const int tl = min(rho / G, count - 1);                        // rows past the last token repeat it (never written)
-    vis[ct] = vis0 + tl;
-    const f32x4_t* qp = (const f32x4_t*)((const uint8_t*)a.q + ((int64_t)(qrow + tl) * a.Hq + head * G + rho % G) * kRowBytes + grp * 64);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const f32x4_t x = qp[i];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) q[ct][4 * i + e] = x[e];
-    }
-  }
+  for (int ct = 0; ct < 2; ++ct) vis[ct] = vis0 + min((ct * 16 + col) / G, count - 1);
   f32x4_t O[2][4];
   float m[2], l[2];
 #pragma unroll
@@ -1927,6 +1925,8 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
 #pragma unroll
     for (int i = 0; i < 4; ++i) kk[i] = kp[i];
   }
+  *(f32x4_t*)&xch[0][rho][(threadIdx.x & 15) * 4] = q_part;
+  __syncthreads();
   bool odd = false;                                                // V elements of the tile's own tokens were left out
   for (; p < page1; p += kRowTileWaves) {
     const f32x4_t* vp = at(pid, kBlk, v_off);
@@ -1938,11 +1938,14 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
     f32x4_t S[2];
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
-      auto part = [&](int u) __attribute__((always_inline)) {
-        f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1)], q[ct][2 * u], f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1) + 1], q[ct][2 * u + 1], x, 0, 0, 0);
-      };
       if (ct == 0 || two) {
+        f32x4_t q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] = *(const f32x4_t*)&xch[0][ct * 16 + col][grp * 16 + i * 4];
+        auto part = [&](int u) __attribute__((always_inline)) {
+          f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1)], q[u >> 1][2 * (u & 1)], f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+          return __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u >> 1][2 * (u & 1) + 1], q[u >> 1][2 * (u & 1) + 1], x, 0, 0, 0);
+        };
         S[ct] = (part(0) + part(1)) + (part(2) + part(3));
         __builtin_amdgcn_sched_barrier(0);       // (all eight at once would not fit the registers)
         S[ct] = S[ct] + ((part(4) + part(5)) + (part(6) + part(7)));
@@ -1995,10 +1998,15 @@ __global__ __launch_bounds__(64 * kRowTileWaves, 4) void row_tile_kernel(Prefill
         pw[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(S[ct][v], a.scale_log2e, -m[ct]));
         l[ct] += pw[v];
       }
+      // likewise: a page's products are added up by themselves, two sums of 8, before they meet the accumulator
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int db = 0; db < 4; ++db) O[ct][db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[v][db], pw[v], O[ct][db], 0, 0, 0);
+      for (int db = 0; db < 4; ++db) {
+        f32x4_t x = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[0][db], pw[0], f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        f32x4_t y = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[2][db], pw[2], f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        x = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[1][db], pw[1], x, 0, 0, 0);
+        y = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[3][db], pw[3], y, 0, 0, 0);
+        O[ct][db] = O[ct][db] + (x + y);
+      }
     }
   }
 
@@ -2130,13 +2138,17 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void tile_merge_kernel(MergeAr
         ls[h] = __builtin_fmaf(lv[u][h], w[u][h], ls[h]);
       }
     }
+    // the group's sum first: one rounding per group, not per chunk, at the size of the whole
+    float x[VL];
 #pragma unroll
-    for (int e = 0; e < VL; ++e) o[e] *= sc[(e * 64) / D];
+    for (int e = 0; e < VL; ++e) x[e] = t[0][e] * w[0][(e * 64) / D];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 1; u < 4; ++u)
       if (c0 + u < chunks)                           // a place to spare is left out: its weight is 0, but 0 * Inf is NaN
 #pragma unroll
-        for (int e = 0; e < VL; ++e) o[e] = __builtin_fmaf(t[u][e], w[u][(e * 64) / D], o[e]);
+        for (int e = 0; e < VL; ++e) x[e] = __builtin_fmaf(t[u][e], w[u][(e * 64) / D], x[e]);
+#pragma unroll
+    for (int e = 0; e < VL; ++e) o[e] = __builtin_fmaf(o[e], sc[(e * 64) / D], x[e]);
   }
   float* out = a.out + ((int64_t)qh + (int64_t)tl * a.Hq) * D + lane;
 #pragma unroll

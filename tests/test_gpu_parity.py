@@ -435,6 +435,23 @@ def test_infinite_values_of_visible_tokens(Hq, Hkv, D, dtype):
         sess.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (16, 8), (64, 8)])
+def test_fp32_row_tiles_are_no_coarser_than_rows(Hq, Hkv):
+    """The same preds as row tiles and as rows of the vector-unit kernel: the tiles' error against 64 bits is no larger, for
+    drafts and prompts, on files of a few pages per wavefront and on files cut into many key chunks."""
+    shape = synth.Shape(Hq, Hkv, 64, 16, synth.F32)
+    for files, new in (([500] * 12, 6), ([8000] * 2, 6), ([2000] * 3, 20)):
+        wl = synth.custom("fp32_error", shape, [("new", n) for n in files], [(i, new) for i in range(len(files))], 1200, seed=41)
+        ref, _ = run_oracle(wl, dtype=np.float64)
+        err = []
+        for prefill_min in (2, 4096):
+            got, sess = _hip().run_workload(wl, poison=True, tuning={"prefill_min": prefill_min})
+            err.append(float(np.linalg.norm(got - ref)))
+            sess.close()
+        print(f"[case] {files[0]} x {len(files)}, {new} new: tiles / rows {err[0] / err[1]:.3f}", flush=True)
+        assert err[0] <= err[1]
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 4), (8, 1), (1, 1)])
 def test_fp32_tokens_do_not_meet_later_tokens_values(Hq, Hkv):
     """fp32 preds of several tokens: new token i >= 1 has an infinite (every second a NaN) V element in dim i % 64, which the
