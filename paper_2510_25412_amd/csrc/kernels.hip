@@ -1135,8 +1135,8 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   // reads per flop but need ~510 registers, one wavefront per SIMD: measured 1.5x slower, also with
   // the pipelined block loop below.)
   constexpr int CT = 1;
-  // workgroups go round-robin over the 8 XCDs; the tile list comes in 8 shares of equal cost in which
-  // tiles that read the same K/V are neighbours (one L2 per XCD), longest first
+  // workgroups go round-robin over the 8 XCDs; the tile list comes in 8 shares in which tiles that read the same K/V are
+  // neighbours (one L2 per XCD): of equal cost, longest first, or, where all are about equal pieces of cut tiles, of equal count
   const int tile = sload(a.xcd_off + block % 8) + block / 8;
   if (tile >= sload(a.xcd_off + block % 8 + 1)) return;
   const int32_t* tw = a.tiles + (int64_t)(a.tile_first + tile) * 12;

@@ -713,6 +713,36 @@ def test_descriptor_key_chunks_cover_every_block_once(dtype, Hq, Hkv):
     assert cut >= 3
 
 
+@pytest.mark.parametrize("roots,members,prefix,prompts", [(16, 8, 256, [(8000, 512)]), (16, 16, 2048, [(4000, 512)]), (4, 16, 4096, [(30000, 64)]),
+                                                          (2, 64, 8192, [(3000, 32), (3000, 32)]), (0, 0, 0, [(8000, 512), (4000, 100)])])
+def test_descriptor_tile_shares_are_balanced_beside_key_chunks(roots, members, prefix, prompts):
+    """Forks of shared prefixes beside prompts whose tiles are cut into key chunks: the eight shares of the tile list (one per XCD) cost
+    about the same, in 32-token blocks, though the pieces and the prefix tiles have different lengths."""
+    c = host_ctx(1 << 17, decode_waves=8192)             # partial slots for prefixes and chunks
+    tables, lengths, n_tok, page = [], [], [], 0
+    for _ in range(roots):
+        shared = list(range(page, page + prefix // 16))
+        page += len(shared)
+        for _ in range(members):
+            tables.append(shared + [page])
+            lengths.append(prefix + 5)
+            n_tok.append(1)
+            page += 1
+    for old, new in prompts:
+        n = -(-(old + new) // 16)
+        tables.append(list(range(page, page + n)))
+        lengths.append(old + new)
+        n_tok.append(new)
+        page += n
+    off = np.concatenate([[0], np.cumsum([len(x) for x in tables])]).astype(np.int64)
+    w = c.build_desc(n_tok, np.concatenate(tables).astype(np.int32), off, lengths)
+    assert int(w[41]) > 0 and (int(w[17]) > 0) == (roots > 0)            # tiles are cut; prefixes are shared
+    xo, tiles = w[20:29], w[w[10]:w[10] + 12 * w[4]].reshape(-1, 12)
+    cost = [(int(t[8]) - int(t[7]) + 1) // 2 if t[6] else (int(t[1]) + int(t[5]) + int(t[3]) + 31) // 32 for t in tiles]
+    share = [sum(cost[xo[x]:xo[x + 1]]) for x in range(8)]
+    assert max(share) <= 1.1 * sum(share) / 8, share
+
+
 def test_truncate_errors_change_nothing():
     c = host_ctx(8)
     a, b = c.kv_open(), c.kv_open()
