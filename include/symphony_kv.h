@@ -68,8 +68,9 @@ typedef struct sym_tuning {
                               Hq/Hkv = 8, else 0                                          */
   int32_t min_units;       /* smallest piece, in pages, that a long range is cut into;
                               >= 1, default 4                                             */
-  int32_t prefill_min;     /* a pred of at least this many new tokens is computed by tiles;
-                              >= 2, default 16 (fp32: 4)                                  */
+  int32_t prefill_min;     /* a pred of at least this many new tokens is computed by tiles
+                              (SYM_F32 with 8 query heads per kv head: unless the batch is small
+                              and its files are long); >= 2, default 16 (fp32: 4)         */
   int32_t share_min_lips;  /* files of a batch that must share a page-list prefix before
                               the prefix is read once for all of them; 0 = never group,
                               default 4                                                   */

@@ -59,12 +59,29 @@ constexpr int64_t kTileStart = 6, kTileMerge = 11;
 // Most key chunks of a row tile: a token's chunks are merged one group of four after the other.  Kernel time over 525 shapes (4..200
 // new tokens on 0..8000) against 64: 0.985 (16: 0.986); one file of 8000 tokens, 8 new ones, 8 heads: 24.7 -> 18.5 us.
 constexpr int64_t kRowTileChunks = 32;
+// With 8 query heads per kv head: fewest (token, kv head, page) units of a batch that go to row tiles, if a file has more pages than this.
+constexpr int64_t kRowTileUnits = 2048, kRowTilePages = 24;
 }  // namespace
 
 int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, const int64_t* len_after,
                const int32_t* const* tables, BatchDesc* out) {
   const int32_t P = prm.page_tokens, H = prm.n_kv_heads, G = prm.n_q_heads / H;
-  auto is_rtile = [&](int32_t b) { return prm.row_tile_rows > 0 && n_tokens[b] >= prm.prefill_min; };
+  // Row tiles, unless there is little to do on long files with 8 heads per kv head: such a tile has 4 tokens in two column tiles, so a
+  // page costs it twice the matrix instructions for half the sharing, and few tiles leave the chip idle.  Whole calls, tiles /
+  // rows, 8 heads per kv head, files of 500 tokens on: 1.05..1.15 up to 2047 units (token, kv head, page), 0.92 from there to 16 000,
+  // then 0.7 and less; files of up to 250 tokens 0.85 (fewer heads: 0.9 and less at any size).
+  bool row_tiles = prm.row_tile_rows > 0;
+  if (row_tiles && G == 8) {
+    int64_t units = 0, longest = 0;
+    for (int32_t b = 0; b < n_lips; ++b)
+      if (n_tokens[b] >= prm.prefill_min) {
+        const int64_t pages = (len_after[b] + P - 1) / P;
+        units += std::min(pages, kRowTileUnits) * std::min<int64_t>(n_tokens[b], kRowTileUnits) * H;
+        longest = std::max(longest, pages);
+      }
+    row_tiles = units >= kRowTileUnits || longest <= kRowTilePages;
+  }
+  auto is_rtile = [&](int32_t b) { return row_tiles && n_tokens[b] >= prm.prefill_min; };
   auto is_prefill = [&](int32_t b) { return (prm.tile_tokens > 0 && n_tokens[b] >= prm.prefill_min) || is_rtile(b); };   // no decode rows
   // Tiles of a batch with prefill chunks have prm.tile_tokens new tokens (256 query rows by default:
   // eight wavefronts share one staging of K/V); a batch whose only tiles are shared prefixes (few

@@ -464,7 +464,7 @@ def test_fp32_tokens_do_not_meet_later_tokens_values(Hq, Hkv):
             for i in range(1, n):
                 v[first + i, :, i % 64] = np.nan if i % 2 else -np.inf
 
-    for files, batch in (([5, 0, 129, 40], [4, 7, 33, 1]), ([3000], [40]), ([16, 31, 500], [70, 12, 3]), ([100] * 12, [9] * 12)):
+    for files, batch in (([5, 0, 129, 40], [4, 7, 33, 1]), ([3000], [40]), ([16, 31, 500], [70, 12, 3]), ([100] * 12, [9] * 12), ([600], [8])):
         wl = synth.custom("later_values", shape, [("new", n) for n in files], list(enumerate(batch)), 600, seed=9 + Hkv)
         got, ref, sess, ranges = _run_with_values(wl, lambda V: None, edit)
         for first, n, _ in ranges:

@@ -713,6 +713,23 @@ def test_descriptor_key_chunks_cover_every_block_once(dtype, Hq, Hkv):
     assert cut >= 3
 
 
+@pytest.mark.parametrize("Hq,Hkv,lengths,n_tok,tiles", [
+    (8, 1, [508], [8], False), (64, 8, [504], [4], False), (8, 1, [384], [8], True), (8, 1, [385], [8], False),      # 24 pages, 25
+    (64, 8, [512], [7], False), (64, 8, [512], [8], True), (8, 1, [508] * 3, [8, 3, 20], False),                     # 32 pages x 8 heads x 7, 8
+    (8, 1, [508], [3], False), (32, 8, [508], [4], True), (8, 8, [8000], [4], True)])
+def test_descriptor_fp32_preds_by_tiles_or_rows(Hq, Hkv, lengths, n_tok, tiles):
+    """fp32 preds of 4 tokens on are row tiles, but with 8 heads per kv head and a file of more than 24 pages only from 2048
+    units on; tokens without tiles are rows of the decode kernel, and every token is one or the other."""
+    c = host_ctx(1 << 14, Hq=Hq, Hkv=Hkv, D=64, dtype="f32")
+    np_l = [-(-n // 16) for n in lengths]
+    off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+    w = c.build_desc(n_tok, np.arange(sum(np_l), dtype=np.int32), off, lengths)
+    assert int(w[0]) == sum(n_tok) and (int(w[39]) > 0) == tiles
+    rt = w[w[40]:w[40] + 8 * w[39]].reshape(-1, 8)
+    assert len({(int(x[2]) + i, int(x[4])) for x in rt for i in range(int(x[3]))}) == (sum(n for n in n_tok if n >= 4) * Hkv if tiles else 0)
+    assert (int(w[1]) > 0) == (not tiles or any(n < 4 for n in n_tok))
+
+
 @pytest.mark.parametrize("roots,members,prefix,prompts", [(16, 8, 256, [(8000, 512)]), (16, 16, 2048, [(4000, 512)]), (4, 16, 4096, [(30000, 64)]),
                                                           (2, 64, 8192, [(3000, 32), (3000, 32)]), (0, 0, 0, [(8000, 512), (4000, 100)])])
 def test_descriptor_tile_shares_are_balanced_beside_key_chunks(roots, members, prefix, prompts):
