@@ -2144,9 +2144,8 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void tile_merge_kernel(MergeAr
     for (int e = 0; e < VL; ++e) x[e] = t[0][e] * w[0][(e * 64) / D];
 #pragma unroll
     for (int u = 1; u < 4; ++u)
-      if (c0 + u < chunks)                           // a place to spare is left out: its weight is 0, but 0 * Inf is NaN
 #pragma unroll
-        for (int e = 0; e < VL; ++e) x[e] = __builtin_fmaf(t[u][e], w[u][(e * 64) / D], x[e]);
+      for (int e = 0; e < VL; ++e) x[e] = __builtin_fmaf(c0 + u < chunks ? t[u][e] : 0.f, w[u][(e * 64) / D], x[e]);      // (0 * Inf is NaN)
 #pragma unroll
     for (int e = 0; e < VL; ++e) o[e] = __builtin_fmaf(o[e], sc[(e * 64) / D], x[e]);
   }
@@ -2160,7 +2159,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void tile_merge_kernel(MergeAr
 //   out = sum_i acc_i 2^(m_i - M) / sum_i l_i 2^(m_i - M),  M = max_i m_i.
 // The G*D accumulator values of a piece form one flat list; lane owns entries e*64 + lane.  All
 // loads of a group of 4 pieces are issued before any is used (indices past the end re-read the
-// last piece and drop it), so the kernel costs one memory round trip per group after the entry.  A row that belongs
+// last piece and drop it: by a select, since under a branch the compiler moves the loads behind it, one round trip each), so the kernel costs one memory round trip per group after the entry.  A row that belongs
 // to a shared-prefix group has extra pieces: the partials the tile kernel left for the prefix.
 // S = wavefronts per entry.  1: four entries per workgroup.  4: wavefront w takes pieces w, w + 4, ..., so that up to 16 pieces
 // are one round trip, and the four are combined through LDS: for entries of many pieces (long files, and few files cut over
@@ -2232,9 +2231,8 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void merge_kernel(MergeArgs a)
         w[h] = (i0 + u * S < pieces) ? __builtin_amdgcn_exp2f(mv[u][h] - Mx[h]) : 0.f;
         ls[h] = __builtin_fmaf(lv[u][h], w[h], ls[h]);
       }
-      if (i0 + u * S < pieces)                       // a place to spare is left out: its weight is 0, but 0 * Inf is NaN
 #pragma unroll
-        for (int e = 0; e < VL; ++e) o[e] = __builtin_fmaf(t[u][e], w[(e * 64) / D], o[e]);
+      for (int e = 0; e < VL; ++e) o[e] = __builtin_fmaf(i0 + u * S < pieces ? t[u][e] : 0.f, w[(e * 64) / D], o[e]);      // (0 * Inf is NaN)
     }
   }
   if constexpr (S == 1) {
