@@ -1492,10 +1492,10 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
 
   // Results.  In the accumulators a lane holds 16 bytes at a time of a row of its own: stored like that, an instruction touches
   // 64 lines.  Each wavefront turns its 32 rows through LDS, 32 dims at a time (rows of 36 floats), and stores whole 128-byte
-  // lines, eight rows per instruction.  Whole calls: 16 prompts of 600..1000 tokens on nothing 204 -> 199 us, 8 of 100..600 52.7 ->
-  // 50.3, 8 x 512 tokens on U{0..8000} 320 -> 317.
-  if constexpr (!SPLIT) __syncthreads();               // everyone is done with the block buffers; a split tile uses one that is free
-  float* const stg = (float*)lds[SPLIT ? 2 : 0] + wvr * (32 * 36);
+  // lines, eight rows per instruction.  Whole calls: 16 prompts of 600..1000 tokens on nothing 204 -> 199 us, 8 x 512 tokens on
+  // U{0..8000} 320 -> 317.  A tile of at most two wavefronts' rows has few lines to store and would only wait for the turning: kernel
+  // time, straight / through LDS, 32 rows 0.89 (on nothing) .. 0.97 (on 1500), 64 rows 0.94 .. 0.98, 128 rows 1.02, 256 rows
+  // 1.05 .. 1.10 (420 shapes); fork trees, whose split tiles are always such, 0.97 .. 1.00.
   const float lt = l[0] + __shfl_xor(l[0], 32);
   const float inv = partial ? 1.0f : 1.0f / lt;
   // first partial slot of the tile, or its first q / out row
@@ -1505,6 +1505,19 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
     ml[0] = m[0];
     ml[1] = lt;
   }
+  if (SPLIT || count * G <= 64) {
+    if (tl[0] < count) {
+      float* o = (partial ? a.part_acc + ((row0 + tl[0]) * G + h[0]) * 128 : a.out + ((row0 + tl[0]) * a.Hq + g * G + h[0]) * 128) + 4 * hf;
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int vb = 0; vb < 4; ++vb)
+          *(float4*)(o + db * 32 + vb * 8) = make_float4(O[0][db][4 * vb] * inv, O[0][db][4 * vb + 1] * inv, O[0][db][4 * vb + 2] * inv, O[0][db][4 * vb + 3] * inv);
+    }
+    return;
+  }
+  __syncthreads();                                     // everyone is done with the block buffers
+  float* const stg = (float*)lds[0] + wvr * (32 * 36);
   const int r8 = lane >> 3, c4 = (lane & 7) * 4;
 #pragma unroll
   for (int db = 0; db < 4; ++db) {
