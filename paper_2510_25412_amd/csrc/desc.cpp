@@ -52,10 +52,9 @@ int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_
 // merge launch / without: 32 files of 100 tokens 13.6 / 9.1 us, sixteen of 200 12.8 / 9.7, eight of 300 12.5 / 10.6, one of 400
 // 12.1 / 12.2, one of 500 (32 pages) 12.0 / 13.0.
 constexpr int64_t kWholePages = 24;
-// bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch.  (A start of 10: of 3000
-// random prompt batches, 1..16 files, it changes the plan of 36, attention and merge of which take 1.10 times as long, 20 slower, 11
-// faster; a start of 14 another 1.13 of that.)
-constexpr int64_t kTileStart = 6, kTileMerge = 11;
+// bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch (a start of 6: three
+// prompts of 100..700 tokens on 200..4000 in two rounds of pieces, 78 us, instead of one, 74; 17 other shapes the same)
+constexpr int64_t kTileStart = 10, kTileMerge = 11;
 // Most key chunks of a row tile: a token's chunks are merged one group of four after the other.  Kernel time over 525 shapes (4..200
 // new tokens on 0..8000) against 64: 0.985 (16: 0.986); one file of 8000 tokens, 8 new ones, 8 heads: 24.7 -> 18.5 us.
 constexpr int64_t kRowTileChunks = 32;
