@@ -16,7 +16,10 @@ namespace {
 // bf16, 32 query / 8 kv heads, whole calls cut / whole: 512 tokens on 8000: 102 / 276 us; 64 on 60 000: 100 / 1820; 32 on
 // 2000: 25 / 61; three prompts of 100..700 on 200..4000: 76 / 117; 1024 on nothing: 43 / 53; 512 on nothing stays whole
 // (36.1 / 35.5).
-int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_t slots, int64_t start, int64_t merge, int64_t max_chunks, int64_t unit) {
+// beside: work of other kinds in the same launch, in steps: nothing ends before the chip has done all of it.  per_piece: partials that a piece
+// of a cut tile leaves at most; all pieces leave no more than `budget`.
+int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_t slots, int64_t start, int64_t merge, int64_t max_chunks, int64_t unit,
+                    int64_t beside, int64_t per_piece, int64_t budget) {
   int64_t n = 0, longest = 0, total = 0;
   for (auto& t : lens) {
     n += t.second;
@@ -26,21 +29,30 @@ int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_
   if (n == 0 || n > 3 * slots) return 0;
   const int64_t rounds0 = (n + slots - 1) / slots;
   int64_t best = rounds0 == 1 ? longest + start : std::max(longest + start, std::min(rounds0 * (longest + start), total / slots + rounds0 * start + longest / 2));
+  best = std::max(best, (total + beside) / slots);
   best -= best / 8;                              // a cut has to promise an eighth
   int64_t b_best = 0;
+  int64_t pieces = 0, partials = 0;
+  auto cut = [&](int64_t b) {
+    pieces = partials = 0;
+    for (auto& t : lens) {
+      const int64_t nc = (t.first + b - 1) / b;
+      pieces += nc * t.second;
+      if (nc > 1) partials += nc * t.second * per_piece;
+    }
+  };
   for (int64_t rounds = rounds0; rounds <= rounds0 + 2; ++rounds) {
     int64_t lo = (longest + max_chunks - 1) / max_chunks, hi = longest;       // smallest b in [lo, hi] whose pieces fit
     lo = std::max((lo + unit - 1) / unit, (int64_t)1);
     hi = std::max((hi + unit - 1) / unit, lo);
     while (lo < hi) {
       const int64_t mid = (lo + hi) / 2;
-      int64_t pieces = 0;
-      for (auto& t : lens) pieces += (t.first + mid * unit - 1) / (mid * unit) * t.second;
-      if (pieces <= rounds * slots) hi = mid;
+      cut(mid * unit);
+      if (pieces <= rounds * slots && partials <= budget) hi = mid;
       else lo = mid + 1;
     }
     if (lo * unit >= longest) continue;          // whole tiles
-    const int64_t est = rounds * (lo * unit + start) + merge;
+    const int64_t est = std::max(rounds * (lo * unit + start), (total + beside) / slots) + merge;
     if (est < best) {
       best = est;
       b_best = lo * unit;
@@ -52,9 +64,13 @@ int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_
 // merge launch / without: 32 files of 100 tokens 13.6 / 9.1 us, sixteen of 200 12.8 / 9.7, eight of 300 12.5 / 10.6, one of 400
 // 12.1 / 12.2, one of 500 (32 pages) 12.0 / 13.0.
 constexpr int64_t kWholePages = 24;
-// bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch (a start of 6: three
-// prompts of 100..700 tokens on 200..4000 in two rounds of pieces, 78 us, instead of one, 74; 17 other shapes the same)
-constexpr int64_t kTileStart = 10, kTileMerge = 11;
+// bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch.  196 random prompt batches
+// whose plan some setting changes, attention and merge together, against whole tiles: 0.82 of the time, one more than 4 % slower (6 %).  A
+// start of 6: 0.81, five slower, by up to 12 %; a merge of 8: 0.79, ten slower.
+// Units (token, kv head, page) of decode rows that take as long as a step: 111 batches of prompts beside 4..224 decode files 0.652 of
+// the time with whole tiles, three slower, by up to 12 % (3: 0.653, three; 6: 0.653, five; not counted: 0.654, thirteen, by up to 44 %: two
+// prompts of 64 tokens beside 200 files of 1000..3000 tokens 292 us whole, 421 cut).
+constexpr int64_t kTileStart = 10, kTileMerge = 11, kUnitsPerStep = 4;
 // Most key chunks of a row tile: a token's chunks are merged one group of four after the other.  Kernel time over 525 shapes (4..200
 // new tokens on 0..8000) against 64: 0.985 (16: 0.986); one file of 8000 tokens, 8 new ones, 8 heads: 24.7 -> 18.5 us.
 constexpr int64_t kRowTileChunks = 32;
@@ -265,12 +281,8 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     lens.clear();
     for (int32_t b : rorder)
       for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += RQ) lens.emplace_back((rpages(b, t0) + kRowTileWaves - 1) / kRowTileWaves, H);
-    rsteps = chunk_steps(lens, 2 * (int64_t)prm.cus, 4, 4, kRowTileChunks, 1);
+    rsteps = chunk_steps(lens, 2 * (int64_t)prm.cus, 4, 4, kRowTileChunks, 1, 0, RQ, chunk_budget);
     count_rtiles();
-    if (n_chunk_partials > chunk_budget) {
-      rsteps = 0;
-      count_rtiles();
-    }
     chunk_budget -= n_chunk_partials;
   }
 
@@ -301,12 +313,11 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       for (int32_t b = 0; b < n_lips; ++b)
         if (is_prefill(b) && !is_rtile(b))
           for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += TQ) lens.emplace_back(bblocks(b, t0), H);
-      bsteps = chunk_steps(lens, slots, kTileStart, kTileMerge, 64, 3);      // the block loop is unrolled by three
+      int64_t units = 0;                                   // decode work in the same launch (plain decode rows)
+      for (int32_t b = 0; b < n_lips; ++b)
+        if (!is_prefill(b)) units += ((len_after[b] + P - 1) / P - share_start[b]) * H * ((n_tokens[b] + RT - 1) / RT);
+      bsteps = chunk_steps(lens, slots, kTileStart, kTileMerge, 64, 3, units / kUnitsPerStep, TQ, chunk_budget);      // the block loop is unrolled by three
       count_btiles();
-      if (n_btile_partials > chunk_budget) {
-        bsteps = 0;
-        count_btiles();
-      }
     }
   }
 

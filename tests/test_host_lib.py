@@ -713,6 +713,29 @@ def test_descriptor_key_chunks_cover_every_block_once(dtype, Hq, Hkv):
     assert cut >= 3
 
 
+def test_descriptor_key_chunks_only_where_the_chip_would_idle():
+    """A few prompt tiles are cut into key chunks, but not beside so many decode rows that the chip is full without; and a cut that
+    the partial slots cannot hold becomes a coarser one, not none."""
+    rng = np.random.default_rng(3)
+
+    def desc(Hq, Hkv, prompts, decode, waves):
+        c = host_ctx(1 << 18, Hq=Hq, Hkv=Hkv, decode_waves=waves)
+        lengths, n_tok = [o + n for o, n in prompts] + decode, [n for _, n in prompts] + [1] * len(decode)
+        np_l = [-(-n // 16) for n in lengths]
+        off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+        return c.build_desc(n_tok, np.arange(sum(np_l), dtype=np.int32), off, lengths)
+
+    prompts, decode = [(1500, 64), (1900, 64)], rng.integers(1000, 3000, 200).tolist()
+    assert int(desc(32, 8, prompts, [], 8192)[41]) > 0 and int(desc(32, 8, prompts, decode[:4], 8192)[41]) > 0
+    assert int(desc(32, 8, prompts, decode, 8192)[41]) == 0
+    many = [(int(n), 512) for n in rng.integers(0, 8000, 16)]
+    fine, coarse = desc(8, 8, many, [], 1 << 16), desc(8, 8, many, [], 12288)
+    for w in (fine, coarse):
+        tm = w[w[42]:w[42] + 4 * w[41]].reshape(-1, 4)
+        assert len(tm) > 0 and int((tm[:, 0] + tm[:, 1] * tm[:, 2]).max()) <= int(w[2])
+    assert int(coarse[4]) < int(fine[4]) and int(coarse[2]) < int(fine[2])
+
+
 @pytest.mark.parametrize("Hq,Hkv,lengths,n_tok,tiles", [
     (8, 1, [508], [8], False), (64, 8, [504], [4], False), (8, 1, [384], [8], True), (8, 1, [385], [8], False),      # 24 pages, 25
     (64, 8, [512], [7], False), (64, 8, [512], [8], True), (8, 1, [508] * 3, [8, 3, 20], False),                     # 32 pages x 8 heads x 7, 8
