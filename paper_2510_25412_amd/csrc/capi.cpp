@@ -241,7 +241,7 @@ int stage_acquire(sym_ctx* c, int64_t words, int* idx) {
   return SYM_OK;
 }
 
-// Brackets a launch with a pair of events when the kernel id is being profiled.  attached = true: the
+// Brackets a launch (or the launches of one step, counted in `launches`) with a pair of events when the kernel id is being profiled.  attached = true: the
 // events are not recorded here but handed to the launch (start() / stop()), which attaches them to
 // the dispatch itself, so they bracket the kernel's execution and not its launch overhead.
 struct Timed {
@@ -251,8 +251,8 @@ struct Timed {
   bool on, attached;
   hipEvent_t start() const { return on && attached ? c->ev_start[id][c->ev_used[id]] : nullptr; }
   hipEvent_t stop() const { return on && attached ? c->ev_stop[id][c->ev_used[id]] : nullptr; }
-  Timed(sym_ctx* ctx, int kid, hipStream_t s, bool attach = false, bool allow = true) : c(ctx), id(kid), st(s), on(false), attached(attach) {
-    ++c->kernel_launches;
+  Timed(sym_ctx* ctx, int kid, hipStream_t s, bool attach = false, bool allow = true, int launches = 1) : c(ctx), id(kid), st(s), on(false), attached(attach) {
+    c->kernel_launches += launches;
     if (!allow || !((c->prof_mask >> id) & 1) || c->ev_used[id] >= kMaxTimed) return;
     if (c->prof_seen[id]++ % c->prof_stride != 0) return;          // every prof_stride-th launch is timed
     if ((int)c->ev_start[id].size() <= c->ev_used[id]) {
@@ -333,14 +333,14 @@ int launch_attention(sym_ctx* c, const Scratch& ws, int64_t blob_words, const vo
   pa.rtiles = dw + hdr[H_OFF_RTILES];
   pa.n_rtiles = d.n_rtiles;
   {
-    Timed t(c, SYM_K_ATTN, st, true, timed);
+    Timed t(c, SYM_K_ATTN, st, true, timed, (d.n_rtiles > 0) + (d.n_waves > 0 || d.n_tiles > 0));
     // rows that hold several new tokens exist for the matrix-core decode kernel only
     hipError_t e = launch_attn(a, pa, c->cfg.dtype, (c->decode_mode || d.max_row_tokens > 1) ? 1 : 0, st, t.start(), t.stop());
     if (e != hipSuccess) return fail_hip(c, e, "attention launch");
   }
   if (d.n_merge > 0 || d.n_tmerge > 0) {
     MergeArgs m{part_acc, part_ml, dw + hdr[H_OFF_MERGE], out, d.n_merge, d.merge_pieces, dw + hdr[H_OFF_TMERGE], d.n_tmerge, d.tmerge_tokens, c->cfg.n_q_heads};
-    Timed t(c, SYM_K_MERGE, st, false, timed);
+    Timed t(c, SYM_K_MERGE, st, false, timed, (d.n_tmerge > 0) + (d.n_merge > 0));
     hipError_t e = launch_merge(m, c->G, c->cfg.head_dim, st);
     if (e != hipSuccess) return fail_hip(c, e, "merge launch");
   }

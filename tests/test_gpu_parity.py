@@ -477,6 +477,22 @@ def test_fp32_tokens_do_not_meet_later_tokens_values(Hq, Hkv):
         sess.close()
 
 
+@pytest.mark.parametrize("shape,files,batch,launches", [
+    (synth.Shape(8, 8, 64, 16, synth.F32), [100, 50], [20, 1], 3),              # append, row tiles, decode bins
+    (synth.Shape(8, 8, 64, 16, synth.F32), [100], [20], 2),                      # append, row tiles
+    (synth.Shape(32, 8, 128, 16, synth.BF16), [3000, 2000], [16, 1], 4),         # append, tiles and bins, the merges of either
+    (synth.Shape(32, 8, 128, 16, synth.BF16), [100, 50], [1, 1], 2)])            # copy of the descriptor, bins
+def test_kernel_launches_are_counted(shape, files, batch, launches):
+    drv = _hip()
+    wl = synth.custom("launches", shape, [("new", n) for n in files], list(enumerate(batch)), 600, seed=3)
+    sess = drv.HipSession(shape, 600, max_lips=8, max_tokens=4096, max_entries=4096)
+    sess.setup(wl.setup_ops())
+    before = sess.ctx.get_stats()["kernel_launches"]
+    sess.pred(sess.upload_batch(wl.batch()))
+    assert sess.ctx.get_stats()["kernel_launches"] - before == launches
+    sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(32, 8), (64, 8), (8, 8)])
 def test_shared_prefix_groups(Hq, Hkv):
     """Forks of a prefix decode through the shared-prefix tiles (prefix pages read once per
