@@ -1028,7 +1028,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   out->n_tmerge = n_tmerge;
   out->tmerge_tokens = tmerge_tokens;
   out->merge_pieces = 0;
-  if (n_merge <= 512)                             // (more entries never use it)
+  if (n_merge <= kWideMergeItems)                 // (more entries never use it)
     for (int32_t i = 0; i < n_merge; ++i) out->merge_pieces = std::max(out->merge_pieces, merge[(int64_t)i * MERGE_WORDS + 1] + merge[(int64_t)i * MERGE_WORDS + 5]);
   w[H_N_WAVES] = (int32_t)nw;
   w[H_N_PARTIALS] = n_partials;

@@ -12,6 +12,7 @@
 #include <cstdint>
 #include <mutex>
 
+#include "desc.hpp"
 #include "kernels.hpp"
 
 namespace symkv {
@@ -2598,7 +2599,6 @@ hipError_t launch_attn(const DecodeArgs& da, const PrefillArgs& pa, int dtype, i
   return launch_attn_g<ElemBF16>(da, pa, decode_mode, st, ev0, ev1);
 }
 
-constexpr int kWideMergeItems = 512;       // (2040 entries of draft rows, 4 wavefronts each: 10.2 us instead of 8.9)
 hipError_t launch_merge(const MergeArgs& a, int G, int D, hipStream_t st) {
   if (a.n_tile_items > 0) {
     const dim3 tgrid((unsigned)a.n_tile_items, (unsigned)((a.tile_tokens + kWavesPerBlock - 1) / kWavesPerBlock));

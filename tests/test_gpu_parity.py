@@ -1038,6 +1038,35 @@ def test_layered_pred_layer_by_layer_against_the_oracle(Hq, Hkv, D, dtype, multi
     sess.close()
 
 
+@pytest.mark.parametrize("entry", ["layers", "static"])
+@pytest.mark.parametrize("shape,files,batch", [
+    (synth.Shape(32, 8, 128, 16, synth.BF16), [3000, 40], [70, 33]), (synth.Shape(32, 8, 128, 16, synth.BF16), [2000], [1]),
+    (synth.Shape(32, 8, 128, 16, synth.BF16), [300] * 4, [1] * 4), (synth.Shape(8, 8, 64, 16, synth.F32), [3000, 10], [9, 1])])
+def test_small_batches_through_every_entry(entry, shape, files, batch):
+    """Plans of small batches (tiles cut into key chunks, decode ranges spread over small workgroups, a workgroup per range) give through
+    sym_pred_begin / sym_pred_layer and through sym_pred_batch_static, bit for bit, what sym_pred_batch gives."""
+    drv = _hip()
+    wl = synth.custom("entries", shape, [("new", n) for n in files], list(enumerate(batch)), 400, seed=29)
+    want, sess = drv.run_workload(wl, poison=True)
+    sess.close()
+    layers = 2 if entry == "layers" else 1
+    sess = drv.HipSession(shape, 400, max_lips=8, max_tokens=4096, max_entries=4096, poison=True, n_layers=layers)
+    sess.setup(wl.setup_ops())
+    db = sess.upload_batch(wl.batch())
+    args = db["q"], db["k_new"], db["v_new"], db["out"], sess.stream
+    for layer in range(layers):
+        if entry == "static":
+            sess.ctx.pred_batch_static(db["kv"], db["n_tokens"], *args)
+        else:
+            if layer == 0:
+                sess.ctx.pred_begin(db["kv"], db["n_tokens"], sess.stream)
+            sess.ctx.pred_layer(layer, *args)
+        torch.cuda.synchronize()
+        assert np.array_equal(db["out"].cpu().numpy(), want), layer
+        db["out"].fill_(float("nan"))
+    sess.close()
+
+
 @pytest.mark.parametrize("how", ["truncate", "extract"])
 def test_copy_and_in_place_append_on_one_page_in_one_batch(how):
     """Two files share a partly filled page but see different numbers of its tokens (a fork that

@@ -592,6 +592,48 @@ def test_descriptor_bins_cover_every_unit_once_and_are_balanced(lengths, n_tok, 
         assert [seg_bin[i] for i in range(len(segs))] == sorted(seg_bin[i] for i in range(len(segs)))   # contiguous shares
 
 
+def _plain_desc(c, lengths):
+    np_l = [-(-n // 16) for n in lengths]
+    off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+    return c.build_desc([1] * len(lengths), np.arange(sum(np_l), dtype=np.int32) % (1 << 20), off, lengths)
+
+
+def test_descriptor_small_decode_batches():
+    """The planner's rules for small decode batches: up to 24 pages a workgroup of four wavefronts per range and no merge; from 25
+    on, or with more ranges than compute units (256 here), cut and merged; eight wavefronts past 4096 units (token, kv head,
+    page) and when the caller sets the wavefront slots."""
+    c = host_ctx(1 << 20)
+    head = lambda w: (int(w[34]), int(w[35]), int(w[14]))  # noqa: E731  bins, wavefronts, merge entries
+    for lengths in ([1], [384], [1, 16, 17, 40], [384] * 21, [256] * 32):
+        assert head(_plain_desc(c, lengths)) == (8 * len(lengths), 4, 0), lengths
+    for lengths in ([385], [2000], [384] * 19 + [385]):              # a range of 25 pages
+        n_bins, W, n_merge = head(_plain_desc(c, lengths))
+        assert W == 4 and n_merge > 0 and n_bins <= 256, lengths
+    assert head(_plain_desc(c, [16] * 33))[:2] == (17, 4)              # 264 ranges: packed, 16 units per bin
+    assert head(_plain_desc(c, [1024] * 8))[1] == 4                    # 4096 units
+    assert head(_plain_desc(c, [1024] * 7 + [1025]))[1] == 8           # 4104
+    assert head(_plain_desc(host_ctx(1 << 20, decode_waves=2048), [384]))[1] == 8
+
+
+@pytest.mark.parametrize("pages", [40, 30000])
+def test_descriptor_whole_ranges_go_to_the_least_loaded_bin(pages):
+    """Longest range first, each to the bin of least load, the lowest of equals: against a list of loads kept here, for loads that the
+    planner keeps in a table of bits and for loads beyond it, which it keeps in a heap."""
+    c = host_ctx(1 << 20, Hkv=1, Hq=1, tuning={"bin_tolerance": 1000})
+    lengths = (np.random.default_rng(pages).integers(pages // 2, pages, 800) * 16).tolist()
+    w = _plain_desc(c, lengths)
+    n_bins, cost = int(w[34]), [n // 16 + 3 for n in lengths]          # 3: the default range_cost
+    assert n_bins == 256
+    load, where = [0] * n_bins, {}
+    for row in sorted(range(800), key=lambda r: -cost[r]):
+        b = load.index(min(load))
+        load[b] += cost[row]
+        where[row] = b
+    segs, lm = w[w[33]:w[33] + 8 * w[32]].reshape(-1, 8), w[w[36]:w[36] + 32 * n_bins].reshape(-1, 32)
+    got = {int(segs[i, 5]): b for b in range(n_bins) for i in range(int(lm[b, 1]), int(lm[b, 2]))}
+    assert len(segs) == 800 and got == where
+
+
 def test_descriptor_rejects_bad_tables():
     c = host_ctx(64)
     with pytest.raises(binding.SymError):
