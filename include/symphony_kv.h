@@ -237,7 +237,10 @@ int64_t sym_last_swaps(sym_ctx* ctx, int32_t* out, int64_t cap);
  * LIP b attends to file tokens 0 .. len_before_b + i (the whole existing file plus the new
  * tokens up to itself).  T = sum n_tokens.  q: device [T][Hq][D]; k_new, v_new: device
  * [T][Hkv][D] (storage dtype, LIPs in batch order); out: device [T][Hq][D] float32.
- * kv, n_tokens: host.  If the pool cannot hold the batch: SYM_ENOSPC, nothing changes.   */
+ * kv, n_tokens: host.  If the pool cannot hold the batch: SYM_ENOSPC, nothing changes.
+ * Values that are not finite: an Inf or NaN element of a visible V row makes that element of the output Inf or NaN.
+ * With SYM_BF16, in a LIP of several new tokens, such an element of a new token may also reach the outputs of
+ * earlier new tokens of the same LIP (they share the V operand, at weight 0).             */
 int sym_pred_batch(sym_ctx* ctx, int32_t n_lips, const sym_kv* kv, const int32_t* n_tokens,
                    const void* q, const void* k_new, const void* v_new, float* out,
                    void* stream);

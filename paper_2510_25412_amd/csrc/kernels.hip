@@ -234,8 +234,8 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
   if (remaining > 0) {
   // Segment record: [0] page-table offset, [1] kv head, [2] first page, [3] end page (what the load side needs),
   // [4] tokens the row sees, [5] q row * Hq + first query head, [6] destination, [7] slot of the appended token or -1.
-  // compute cursor: the segment being accumulated.  The wave record carries the id of the first page, so the first
-  // K/V loads go out while the segment record (one more scalar round trip) is still on its way.
+  // compute cursor: the segment being accumulated.  The wave record carries the id of the first page: the first K/V loads wait for
+  // the segment record (the kv head and the end page are in it), not for the page table as well.
   int seg = sload(ww + 0), p = sload(ww + 1);
   const int pid_first = sload(ww + 4);
   const int32_t* sr = a.segs + (int64_t)seg * 8;
