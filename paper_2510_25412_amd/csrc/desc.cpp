@@ -62,8 +62,9 @@ int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_
 }
 // Longest range (pages) that a small decode batch leaves to one workgroup of four wavefronts.  Per layer, 32 query heads, with a
 // merge launch / without: 32 files of 100 tokens 13.6 / 9.1 us, sixteen of 200 12.8 / 9.7, eight of 300 12.5 / 10.6, one of 400
-// 12.1 / 12.2, one of 500 (32 pages) 12.0 / 13.0.
-constexpr int64_t kWholePages = 24;
+// 12.1 / 12.2, one of 500 (32 pages) 12.0 / 13.0.  Up to 32 pages one workgroup of eight: attention and merge of 1..14 files of 400..510
+// tokens 0.69..0.85 of the time that cut ranges of four take (which had cost up to 1.39 of the whole ranges before them).
+constexpr int64_t kWholePages = 24, kWholePagesWide = 32;
 // bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch.  196 random prompt batches
 // whose plan some setting changes, attention and merge together, against whole tiles: 0.82 of the time, one more than 4 % slower (6 %).  A
 // start of 6: 0.81, five slower, by up to 12 %; a merge of 8: 0.79, ten slower.
@@ -344,8 +345,10 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   const bool small_decode = bins && prm.spread_small && n_tiles == 0 && total_units <= (int64_t)prm.cus * 4 * prm.min_units_per_wave;
   // ... and if there are no more ranges than compute units and all are short, a workgroup per range: nothing is divided between
   // workgroups, so the merge launch is saved, which is worth about four pages of a wavefront's time.
-  const bool whole_small = small_decode && n_rows * H <= prm.cus && longest_range <= kWholePages;
-  const int32_t W = !bins ? 0 : n_tiles > 0 ? (TQ * G != 256 ? 4 : 8) : (prm.bin_waves == 4 || small_decode ? 4 : 8);
+  // (the longer of such ranges need eight wavefronts for it, four pages each)
+  const bool whole_wide = small_decode && prm.bin_waves == 8 && n_rows * H <= prm.cus && longest_range > kWholePages && longest_range <= kWholePagesWide;
+  const bool whole_small = whole_wide || (small_decode && n_rows * H <= prm.cus && longest_range <= kWholePages);
+  const int32_t W = !bins ? 0 : n_tiles > 0 ? (TQ * G != 256 ? 4 : 8) : (prm.bin_waves == 4 || (small_decode && !whole_wide) ? 4 : 8);
   const int64_t max_bins = std::max<int64_t>(1, prm.max_waves / std::max(W, 1));
   int64_t nw = (total_units + prm.min_units_per_wave - 1) / prm.min_units_per_wave;
   nw = std::max<int64_t>(1, std::min<int64_t>(nw, prm.max_waves));

@@ -96,7 +96,7 @@ struct BatchDesc {
   int32_t n_rtiles = 0;         // row tiles (fp32 storage)
   int32_t n_tmerge = 0, tmerge_tokens = 0;         // tiles cut into key chunks, and the most tokens such a tile holds
   int32_t n_bins = 0, bin_waves = 0, n_segs = 0;   // bins in use (0 = the global cut)
-  int32_t small_decode = 0;     // 1: the decode bins alone, of four wavefronts, spread over the chip (see build_desc)
+  int32_t small_decode = 0;     // 1: the decode bins alone, spread over the chip (see build_desc); those of four wavefronts load K/V plainly
   int32_t n_fused = 0;          // new tokens whose append the attention kernel carries out itself
   std::vector<uint8_t> fused;   // per LIP: 1 = its (single) new token is one of them
   // scratch of the builder, kept between calls

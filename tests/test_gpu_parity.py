@@ -350,11 +350,10 @@ def test_key_chunks_round_weights_to_nearest(Hq, Hkv, n, new):
 @pytest.mark.parametrize("Hq,Hkv,D,dtype", [(32, 8, 128, synth.BF16), (8, 8, 128, synth.BF16), (4, 1, 128, synth.BF16), (16, 8, 64, synth.F32)])
 def test_small_decode_batches(Hq, Hkv, D, dtype):
     """Decode batches around the lines of the planner's rules for small ones: ranges of fewer pages than wavefronts, of 24
-    pages (a workgroup each, no merge) and of 25 (cut, merged), more ranges than compute units, and a batch just past
-    "small"; the last
-    appended row is read back."""
+    pages (a workgroup of four each, no merge), of 25 and 32 (of eight) and of 33 (cut, merged), more ranges than compute units,
+    and a batch just past "small"; the last appended row is read back."""
     shape = synth.Shape(Hq, Hkv, D, 16, dtype)
-    for lens in ([0], [1, 15, 16, 40], [383], [384], [383] * 31, [100] * 33, [2000], [1000, 5], [240] * 40):
+    for lens in ([0], [1, 15, 16, 40], [383], [384], [511], [512], [383] * 31, [100] * 33, [2000], [1000, 5], [240] * 40):
         wl = synth.custom("small_decode", shape, [("new", n) for n in lens], [(i, 1) for i in range(len(lens))], 1500, seed=5 + len(lens))
         got, sess, ref, osess = run_both(wl)
         check_outputs(got, ref, tol=1e-5)          # weights and sums in fp32, as for the other single-token rows

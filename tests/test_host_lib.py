@@ -599,14 +599,16 @@ def _plain_desc(c, lengths):
 
 
 def test_descriptor_small_decode_batches():
-    """The planner's rules for small decode batches: up to 24 pages a workgroup of four wavefronts per range and no merge; from 25
-    on, or with more ranges than compute units (256 here), cut and merged; eight wavefronts past 4096 units (token, kv head,
+    """The planner's rules for small decode batches: up to 24 pages a workgroup of four wavefronts per range and no merge, up to
+    32 one of eight; with longer ones, or with more ranges than compute units (256 here), cut and merged; eight wavefronts past 4096 units (token, kv head,
     page) and when the caller sets the wavefront slots."""
     c = host_ctx(1 << 20)
     head = lambda w: (int(w[34]), int(w[35]), int(w[14]))  # noqa: E731  bins, wavefronts, merge entries
     for lengths in ([1], [384], [1, 16, 17, 40], [384] * 21, [256] * 32):
         assert head(_plain_desc(c, lengths)) == (8 * len(lengths), 4, 0), lengths
-    for lengths in ([385], [2000], [384] * 19 + [385]):              # a range of 25 pages
+    for lengths in ([385], [512], [384] * 19 + [385], [497] * 16):       # a range of 25..32 pages
+        assert head(_plain_desc(c, lengths)) == (8 * len(lengths), 8, 0), lengths
+    for lengths in ([513], [2000], [384] * 19 + [513]):              # a range of 33 pages
         n_bins, W, n_merge = head(_plain_desc(c, lengths))
         assert W == 4 and n_merge > 0 and n_bins <= 256, lengths
     assert head(_plain_desc(c, [16] * 33))[:2] == (17, 4)              # 264 ranges: packed, 16 units per bin
