@@ -72,6 +72,9 @@ constexpr int64_t kWholePages = 24, kWholePagesWide = 32;
 // the time with whole tiles, three slower, by up to 12 % (3: 0.653, three; 6: 0.653, five; not counted: 0.654, thirteen, by up to 44 %: two
 // prompts of 64 tokens beside 200 files of 1000..3000 tokens 292 us whole, 421 cut).
 constexpr int64_t kTileStart = 10, kTileMerge = 11, kUnitsPerStep = 4;
+// A segment record, and what is added to get from a kv head's to the next one's (plus G in S_QROW).
+typedef int32_t SegRecord __attribute__((vector_size(SEG_WORDS * sizeof(int32_t))));
+constexpr SegRecord kNextHead = {0, 1, 0, 0, 0, 0, 0, 0};
 // Most key chunks of a row tile: a token's chunks are merged one group of four after the other.  Kernel time over 525 shapes (4..200
 // new tokens on 0..8000) against 64: 0.985 (16: 0.986); one file of 8000 tokens, 8 new ones, 8 heads: 24.7 -> 18.5 us.
 constexpr int64_t kRowTileChunks = 32;
@@ -414,10 +417,18 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   auto trow_pages = [&](int64_t rr) { return (rows_tmp[rr * ROW_WORDS + 1] + trow_nt(rr) - 1 + P - 1) / P; };   // pages its last token sees
   auto trow_first = [&](int64_t rr) { return rows_tmp[rr * ROW_WORDS + 3] & ROW_PAGE_MASK; };
 
+  // record of kv head 0 of a row as one segment, destination the output
+  auto seg_record = [&](int64_t row) {
+    const int32_t* rw = rows_tmp.data() + row * ROW_WORDS;
+    const int32_t app = (!out->row_lip.empty() && out->fused[out->row_lip[row]]) ? (rw[1] - 1) % P : -1;
+    return SegRecord{rw[0], rw[3] & ~ROW_PAGE_MASK, trow_first(row), trow_pages(row), rw[1], rw[2] * prm.n_q_heads, -1, app};
+  };
+
   // ---- bins: segments (whole ranges, or pieces of ranges too long for a bin), handed to the bins longest first
   std::vector<int32_t>& seg_tmp = out->seg_tmp;          // SEG_WORDS per segment, in (row, head, page) order
   std::vector<int32_t>& item_bin = out->item_bin;        // bin of every segment
   int64_t n_segs = 0, n_split_partials = 0, n_split_merge = 0;
+  bool whole = false;                                    // every range is one segment, in the bin that item_bin says
   const int64_t alpha = prm.range_cost;
   if (bins) {
     const int64_t total_cost = total_units + alpha * n_rows * H;
@@ -426,144 +437,175 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     // no more segments than ranges and cuts at bin boundaries; the vectors only ever grow
     const size_t seg_cap = (size_t)(n_rows * H + n_bins + 1);
     if (seg_tmp.size() < seg_cap * SEG_WORDS) seg_tmp.resize(seg_cap * SEG_WORDS);
-    if (item_bin.size() < seg_cap) item_bin.resize(seg_cap);
-    auto emit = [&](int64_t row, int32_t g, int32_t pb, int32_t pe, int32_t np, int32_t dest, int32_t bin) {
-      const int32_t rec[SEG_WORDS] = {rows_tmp[row * ROW_WORDS + 0], g, pb, pe, rows_tmp[row * ROW_WORDS + 1], rows_tmp[row * ROW_WORDS + 2] * prm.n_q_heads + g * G, dest,
-                                      (pe == np && !out->row_lip.empty() && out->fused[out->row_lip[row]]) ? (rows_tmp[row * ROW_WORDS + 1] - 1) % P : -1};
-      std::memcpy(seg_tmp.data() + n_segs * SEG_WORDS, rec, sizeof rec);
-      item_bin[n_segs++] = bin;
+    if (item_bin.size() < (size_t)(n_rows * H)) item_bin.resize((size_t)(n_rows * H));
+    auto emit = [&](SegRecord rec, int32_t pb, int32_t pe) {
+      if (pe != rec[S_PE]) rec[S_APPEND] = -1;
+      rec[S_PB] = pb;
+      rec[S_PE] = pe;
+      std::memcpy(seg_tmp.data() + n_segs++ * SEG_WORDS, &rec, sizeof rec);
     };
     // Plan A, when there are several ranges per bin (short files, the members of forked prefixes): whole ranges, handed to
-    // the bins longest first; nothing is split, so no range leaves partials in device memory because of the bins.
+    // the bins longest first; nothing is split, so no range leaves partials in device memory because of the bins.  Only the
+    // bin of every range is found here; the records are written straight into the descriptor, bin by bin, further down (planning
+    // 256 files of 100..260 tokens, 8 kv heads: 35 -> 25 us; 16 x 16 forks 55 -> 44; one-page ranges of 147 files 15.6 -> 10).
     bool planned = false;
     if (whole_small || n_rows * H >= 3 * n_bins) {
-      n_segs = 0;
-      n_split_partials = n_split_merge = 0;
+      int32_t longest = 0, shortest = 0x7fffffff;
+      auto& own = out->row_pages;                              // pages of every row's own range
+      own.resize((size_t)n_rows);
       for (int64_t row = 0; row < n_rows; ++row) {
-        const int32_t np = trow_pages(row), p0 = trow_first(row);
-        for (int32_t g = 0; g < H; ++g) {
-          emit(row, g, p0, np, np, p0 > 0 ? (int32_t)n_split_partials : -1, 0);        // the members of a shared prefix always leave partials
-          if (p0 > 0) {
-            ++n_split_partials;
-            ++n_split_merge;
-          }
-        }
+        own[row] = trow_pages(row) - trow_first(row);
+        longest = std::max(longest, own[row]);
+        shortest = std::min(shortest, own[row]);
       }
-      // longest first by counting sort on the page count (rows come in, the H ranges of a row are equal)
-      int32_t longest = 0;
-      for (int64_t row = 0; row < n_rows; ++row) longest = std::max(longest, trow_pages(row) - trow_first(row));
-      order.assign((size_t)longest + 2, 0);                    // order[c] = rows with more than c pages, after the prefix sum
-      for (int64_t row = 0; row < n_rows; ++row) ++order[longest - (trow_pages(row) - trow_first(row)) + 1];
-      for (int32_t c = 0; c <= longest; ++c) order[c + 1] += order[c];
-      auto& sorted = out->tile_tmp;                            // rows, longest first (scratch that the tile list reuses later)
-      sorted.resize((size_t)n_rows);
-      for (int64_t row = 0; row < n_rows; ++row) sorted[order[longest - (trow_pages(row) - trow_first(row))]++] = (int32_t)row;
       int64_t worst = 0;
-      // The bin of least load, the lowest of equals, takes the next range.  Loads are small whole numbers: one bit per bin and
-      // load says which bins carry it, and the least load only rises.  (2048 ranges over 256 bins: 12 us; a heap of pairs, which
-      // serves loads too large for the table: 130 us.)
-      const int64_t max_load = total_cost / n_bins + longest + alpha + 1, wpl = (n_bins + 63) / 64;
-      if (max_load * wpl <= (1 << 16)) {
-        auto& bits = out->bin_bits;
-        auto& cnt = out->bin_count;
-        bits.assign((size_t)((max_load + 1) * wpl), 0);
-        cnt.assign((size_t)max_load + 1, 0);
-        for (int64_t b = 0; b < n_bins; ++b) bits[b >> 6] |= 1ull << (b & 63);
-        cnt[0] = (int32_t)n_bins;
-        int64_t lo = 0, word = 0;
-        for (int32_t row : sorted) {
-          const int64_t c = std::max<int64_t>(1, trow_pages(row) - trow_first(row) + alpha);
-          for (int32_t g = 0; g < H; ++g) {
-            if (cnt[lo] == 0) {
-              while (cnt[lo] == 0) ++lo;
-              word = 0;
-            }
-            uint64_t* from = bits.data() + lo * wpl;
-            while (!from[word]) ++word;
-            const uint64_t bit = from[word] & (~from[word] + 1);
-            from[word] ^= bit;
-            --cnt[lo];
-            bits[(lo + c) * wpl + word] |= bit;
-            ++cnt[lo + c];
-            item_bin[(size_t)row * H + g] = (int32_t)(word * 64 + __builtin_ctzll(bit));
-            worst = std::max(worst, lo + c);
-          }
-        }
+      if (longest == shortest) {                               // of one length: neighbours together, which is the cheapest to write down
+        const int64_t n = n_rows * H, per = n / n_bins, more = n % n_bins;      // `more` bins get one range more
+        int32_t* bin_of = item_bin.data();
+        for (int64_t b = 0; b < n_bins; ++b)
+          for (int64_t i = 0; i < per + (b < more); ++i) *bin_of++ = (int32_t)b;
+        worst = (per + (more > 0)) * std::max<int64_t>(1, longest + alpha);
       } else {
-        heap.clear();
-        for (int64_t b = 0; b < n_bins; ++b) heap.emplace_back(0, (int32_t)b);
-        auto worse = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) { return x > y; };   // min-heap on (load, bin)
-        for (int32_t row : sorted) {
-          const int64_t c = trow_pages(row) - trow_first(row) + alpha;
-          for (int32_t g = 0; g < H; ++g) {
-            std::pop_heap(heap.begin(), heap.end(), worse);
-            heap.back().first += c;
-            item_bin[(size_t)row * H + g] = heap.back().second;
-            worst = std::max(worst, heap.back().first);
-            std::push_heap(heap.begin(), heap.end(), worse);
+        // longest first by counting sort on the page count (rows come in, the H ranges of a row are equal)
+        order.assign((size_t)longest + 2, 0);                  // order[c] = rows with more than c pages, after the prefix sum
+        for (int64_t row = 0; row < n_rows; ++row) ++order[longest - own[row] + 1];
+        for (int32_t c = 0; c <= longest; ++c) order[c + 1] += order[c];
+        auto& sorted = out->tile_tmp;                            // rows, longest first (scratch that the tile list reuses later)
+        sorted.resize((size_t)n_rows);
+        for (int64_t row = 0; row < n_rows; ++row) sorted[order[longest - own[row]]++] = (int32_t)row;
+        // The bin of least load, the lowest of equals, takes the next range.  Loads are small whole numbers: one bit per bin and
+        // load says which bins carry it, and the least load only rises.  Ranges of one length come together, so where a word of
+        // bins has no more members than ranges are left, they are all served at once, lowest first.
+        const int64_t max_load = total_cost / n_bins + longest + alpha + 1, wpl = (n_bins + 63) / 64;
+        if (max_load * wpl <= (1 << 16)) {
+          auto& bits = out->bin_bits;
+          auto& cnt = out->bin_count;
+          bits.assign((size_t)((max_load + 1) * wpl), 0);
+          cnt.assign((size_t)max_load + 1, 0);
+          for (int64_t b = 0; b < n_bins; ++b) bits[b >> 6] |= 1ull << (b & 63);
+          cnt[0] = (int32_t)n_bins;
+          int64_t lo = 0, word = 0;
+          for (int64_t i = 0; i < n_rows;) {
+            const int32_t pages = own[sorted[i]];
+            const int64_t c = std::max<int64_t>(1, pages + alpha);
+            int64_t j = i + 1;                                   // rows i .. j are of one length
+            while (j < n_rows && own[sorted[j]] == pages) ++j;
+            int32_t row = sorted[i], g = 0;                      // the range that is next
+            for (int64_t left = (j - i) * H; left > 0;) {
+              if (cnt[lo] == 0) {
+                while (cnt[lo] == 0) ++lo;
+                word = 0;
+              }
+              uint64_t* from = bits.data() + lo * wpl;
+              while (!from[word]) ++word;
+              uint64_t set = from[word];
+              int32_t n = __builtin_popcountll(set);
+              if (n > left) {                                    // the lowest `left` of them
+                n = (int32_t)left;
+                uint64_t rest = set;
+                for (int32_t k = 0; k < n; ++k) rest &= rest - 1;
+                set ^= rest;
+              }
+              from[word] ^= set;
+              bits[(lo + c) * wpl + word] |= set;
+              cnt[lo] -= n;
+              cnt[lo + c] += n;
+              worst = std::max(worst, lo + c);
+              left -= n;
+              for (; set; set &= set - 1) {
+                item_bin[(size_t)row * H + g] = (int32_t)(word * 64 + __builtin_ctzll(set));
+                if (++g == H) {
+                  g = 0;
+                  if (++i < j) row = sorted[i];
+                }
+              }
+            }
+            i = j;
+          }
+        } else {
+          heap.clear();
+          for (int64_t b = 0; b < n_bins; ++b) heap.emplace_back(0, (int32_t)b);
+          auto worse = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) { return x > y; };   // min-heap on (load, bin)
+          for (int32_t row : sorted) {
+            const int64_t c = own[row] + alpha;
+            for (int32_t g = 0; g < H; ++g) {
+              std::pop_heap(heap.begin(), heap.end(), worse);
+              heap.back().first += c;
+              item_bin[(size_t)row * H + g] = heap.back().second;
+              worst = std::max(worst, heap.back().first);
+              std::push_heap(heap.begin(), heap.end(), worse);
+            }
           }
         }
       }
-      planned = whole_small || worst * n_bins * 100 <= total_cost * (100 + prm.bin_tolerance);
+      planned = whole = whole_small || worst * n_bins * 100 <= total_cost * (100 + prm.bin_tolerance);
+    }
+    // One bin (a small batch): every range is a segment of it, cut between its wavefronts only.
+    if (!planned && n_bins == 1) {
+      planned = whole = true;
+      std::fill(item_bin.begin(), item_bin.begin() + n_rows * H, 0);
+    }
+    if (whole) {
+      n_segs = n_rows * H;
+      for (int64_t row = 0; row < n_rows; ++row)
+        if (trow_first(row) > 0) n_split_partials += H;        // the members of a shared prefix always leave partials
+      n_split_merge = n_split_partials;
     }
     // Plan B: the units in (row, head, page) order are cut into n_bins * W contiguous ranges of equal cost, one per wavefront,
     // exactly like the global cut (on a virtual axis where every range occupies range_cost + pages, wavefront k starts at
     // total * k / (n_bins * W); a start inside the overhead part of a range snaps to its first page), and every W consecutive
     // wavefronts are a bin.  A range that a BIN boundary divides becomes one segment per part, each leaving a partial in
     // device memory (at most n_bins - 1 ranges); what the wavefront boundaries inside a bin divide is combined through LDS.
-    out->wave_pos.clear();
-    if (!planned && n_bins > 1) {
-      n_segs = 0;
-      n_split_partials = n_split_merge = 0;
-      auto& wpos = out->wave_pos;                        // (segment, page) where every wavefront starts
-      wpos.reserve((size_t)nw * 2);
-      int64_t k = 0, vstart = 0, cut = 0;                // cut: where wavefront k starts, total_cost * k / nw
-      int32_t bin = 0;
+    if (!planned) {
+      out->wave_pos.resize((size_t)nw * 3);              // (segment, page, units before it) where every wavefront starts
+      auto& seg_end = out->bin_first;                    // first segment of every bin
+      seg_end.assign((size_t)n_bins + 1, 0);
+      int32_t* wpos = out->wave_pos.data();
+      int64_t k = 0, vstart = 0, cut = 0;                // cut: where wavefront k starts, total_cost * k / nw ...
+      const int64_t step = total_cost / nw, over = total_cost % nw;
+      int64_t rem = 0, units_before = 0;                 // ... and what that leaves: total_cost * k % nw
+      SegRecord next_head = kNextHead;
+      next_head[S_QROW] = G;
       for (int64_t row = 0; row < n_rows; ++row) {
-        const int32_t np = trow_pages(row), p0 = trow_first(row);
-        for (int32_t g = 0; g < H; ++g) {
+        SegRecord rec = seg_record(row);
+        const int32_t np = rec[S_PE], p0 = rec[S_PB];
+        for (int32_t g = 0; g < H; ++g, rec += next_head) {
           const int64_t vend = vstart + alpha + (np - p0);
           const size_t first_seg = (size_t)n_segs;
           int32_t pb = p0;
-          for (; k < nw && cut < vend; ++k, cut = total_cost * k / nw) {
+          while (k < nw && cut < vend) {
             const int32_t at = p0 + (int32_t)std::max<int64_t>(0, cut - vstart - alpha);
             if (k % W == 0) {                            // a bin begins here
               if (at > pb) {
-                emit(row, g, pb, at, np, 0, bin);
+                emit(rec, pb, at);
                 pb = at;
               }
-              bin = (int32_t)(k / W);
+              seg_end[k / W] = (int32_t)n_segs;
             }
-            wpos.push_back((int32_t)n_segs);      // the segment that is emitted next holds page `at`
-            wpos.push_back(at);
+            wpos[0] = (int32_t)n_segs;                   // the segment that is emitted next holds page `at`
+            wpos[1] = at;
+            wpos[2] = (int32_t)(uint32_t)(units_before + at - p0);      // (differences of neighbours count, modulo 2^32)
+            wpos += 3;
+            ++k;
+            cut += step;
+            if ((rem += over) >= nw) {
+              rem -= nw;
+              ++cut;
+            }
           }
-          emit(row, g, pb, np, np, 0, bin);
+          emit(rec, pb, np);
           const size_t n_here = (size_t)n_segs - first_seg;
-          const bool partial = n_here > 1 || p0 > 0;
-          for (size_t i = 0; i < n_here; ++i) seg_tmp[(first_seg + i) * SEG_WORDS + S_DEST] = partial ? (int32_t)(n_split_partials + i) : -1;
-          if (partial) {
-            n_split_partials += (int64_t)n_here;
-            ++n_split_merge;
+          if (n_here > 1 || p0 > 0) {
+            const int32_t nt = trow_nt(row);             // a part leaves one partial per token of the row
+            for (size_t i = 0; i < n_here; ++i) seg_tmp[(first_seg + i) * SEG_WORDS + S_DEST] = (int32_t)(n_split_partials + i * nt);
+            n_split_partials += (int64_t)n_here * nt;
+            n_split_merge += nt;
           }
           vstart = vend;
+          units_before += np - p0;
         }
       }
-      planned = true;
-    }
-    // One bin (a small batch): every range is a segment of it, cut between its wavefronts only.
-    if (!planned) {
-      n_segs = 0;
-      n_split_partials = n_split_merge = 0;
-      for (int64_t row = 0; row < n_rows; ++row) {
-        const int32_t np = trow_pages(row), p0 = trow_first(row);
-        for (int32_t g = 0; g < H; ++g) {
-          emit(row, g, p0, np, np, p0 > 0 ? (int32_t)n_split_partials : -1, 0);
-          if (p0 > 0) {
-            ++n_split_partials;
-            ++n_split_merge;
-          }
-        }
-      }
+      seg_end[n_bins] = (int32_t)n_segs;
     }
   }
 
@@ -683,27 +725,56 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     int32_t* lmerge = w + off_lmerge;
     std::memset(lmerge, 0, (size_t)n_bins * LMERGE_WORDS * sizeof(int32_t));
     auto& first = out->bin_first;                         // first segment of every bin in the final order
-    first.assign((size_t)n_bins + 1, 0);
-    for (int64_t i = 0; i < n_segs; ++i) ++first[item_bin[i] + 1];
-    for (int64_t b = 0; b < n_bins; ++b) first[b + 1] += first[b];
-    auto& pos = out->item_order;                          // reused: next free place of every bin
-    pos.assign(first.begin(), first.end() - 1);
-    for (int64_t i = 0; i < n_segs; ++i)                  // (row, head, page) order is kept inside a bin
-      std::memcpy(segs + (int64_t)pos[item_bin[i]]++ * SEG_WORDS, seg_tmp.data() + i * SEG_WORDS, SEG_WORDS * sizeof(int32_t));
+    auto& bin_units = out->bin_units;                     // units of every bin of whole ranges
+    if (whole) {                                          // (row, head, page) order is kept inside a bin
+      first.assign((size_t)n_bins + 1, 0);
+      for (int64_t i = 0; i < n_segs; ++i) ++first[item_bin[i] + 1];
+      for (int64_t b = 0; b < n_bins; ++b) first[b + 1] += first[b];
+      auto& pos = out->item_order;                        // reused: next free place of every bin
+      pos.assign(first.begin(), first.end() - 1);
+      bin_units.assign((size_t)n_bins, 0);
+      for (int64_t row = 0; row < n_rows; ++row) {
+        SegRecord rec = seg_record(row);
+        const int32_t units = rec[S_PE] - rec[S_PB], qh = rec[S_QROW];
+        const int32_t dest = rec[S_PB] > 0 ? n_merge : -1;      // a member of a shared prefix leaves a partial and has a merge entry
+        rec[S_DEST] = dest;
+        SegRecord next_head = kNextHead;
+        next_head[S_QROW] = G;
+        next_head[S_DEST] = dest < 0 ? 0 : 1;
+        const int32_t* bin_of = item_bin.data() + (size_t)row * H;
+        for (int32_t g = 0; g < H; ++g, rec += next_head) {
+          const int32_t bin = bin_of[g];
+          bin_units[bin] += units;
+          std::memcpy(segs + (int64_t)pos[bin]++ * SEG_WORDS, &rec, sizeof rec);
+        }
+        for (int32_t g = 0; g < H && dest >= 0; ++g) {
+          int32_t* it = merge + (int64_t)n_merge++ * MERGE_WORDS;
+          std::memset(it, 0, MERGE_WORDS * sizeof(int32_t));
+          it[0] = dest + g;
+          it[1] = 1;
+          it[2] = qh + g * G;
+          it[6] = 1;
+        }
+      }
+    } else {
+      std::memcpy(segs, seg_tmp.data(), (size_t)n_segs * SEG_WORDS * sizeof(int32_t));      // bins are contiguous
+    }
     std::memset(segs + n_segs * SEG_WORDS, 0, 2 * SEG_WORDS * sizeof(int32_t));
     // merge entries of the ranges that leave partials, in (row, head) order = the order of their partial numbers
-    for (int64_t i = 0; i < n_segs; ++i) {
+    for (int64_t i = 0; i < n_segs && !whole; ++i) {
       const int32_t* sg = seg_tmp.data() + i * SEG_WORDS;
       if (sg[S_DEST] < 0) continue;
       const bool first_piece = i == 0 || sg[-SEG_WORDS + S_DEST] < 0 || sg[-SEG_WORDS + S_QROW] != sg[S_QROW];
-      if (first_piece) {
-        int32_t* it = merge + (int64_t)n_merge++ * MERGE_WORDS;
-        std::memset(it, 0, MERGE_WORDS * sizeof(int32_t));
-        it[0] = sg[S_DEST];
-        it[2] = sg[S_QROW];
-        it[6] = 1;
-      }
-      ++merge[(int64_t)(n_merge - 1) * MERGE_WORDS + 1];
+      const int32_t nt = (sg[S_HEAD] >> ROW_NT_SHIFT) + 1;
+      if (first_piece)
+        for (int32_t t = 0; t < nt; ++t) {
+          int32_t* it = merge + (int64_t)n_merge++ * MERGE_WORDS;
+          std::memset(it, 0, MERGE_WORDS * sizeof(int32_t));
+          it[0] = sg[S_DEST] + t;
+          it[2] = sg[S_QROW] + t * prm.n_q_heads;
+          it[6] = nt;                                     // distance between the token's pieces
+        }
+      for (int32_t t = 0; t < nt; ++t) ++merge[(int64_t)(n_merge - 1 - t) * MERGE_WORDS + 1];
     }
     part = (int32_t)n_split_partials;
     // Inside a bin the wavefronts cut the bin's segments like the global cut does the batch: on a virtual axis where every
@@ -714,66 +785,62 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     // slot of the first piece, its wavefront, pieces) tells the workgroup what to combine when all are done.
     for (int64_t b = 0; b < n_bins; ++b) {
       const int64_t s0 = first[b], s1 = first[b + 1];
-      int64_t pages = 0;
-      for (int64_t i = s0; i < s1; ++i) pages += segs[i * SEG_WORDS + S_PE] - segs[i * SEG_WORDS + S_PB];
-      const int64_t vt = pages + alpha * (s1 - s0);
-      const int64_t Wb = out->wave_pos.empty() ? std::min<int64_t>(W, pages) : W;
       int32_t* bw = waves + b * W * WAVE_WORDS;
       std::memset(bw, 0, (size_t)W * WAVE_WORDS * sizeof(int32_t));
       int32_t* lm = lmerge + b * LMERGE_WORDS;
-      lm[1] = (int32_t)s0;                              // the bin's segments (the kernel walks them for the appends that ride along)
+      lm[1] = (int32_t)s0;                              // the bin's segments
       lm[2] = (int32_t)s1;
-      int64_t k = 0, vstart = 0, cut = 0;               // cut: where wavefront k starts, vt * k / Wb
-      if (!out->wave_pos.empty()) {                     // the wavefronts' starts come from the cut of the whole batch
-        for (; k < W; ++k) {
-          bw[k * WAVE_WORDS + 0] = out->wave_pos[(size_t)(b * W + k) * 2];
-          bw[k * WAVE_WORDS + 1] = out->wave_pos[(size_t)(b * W + k) * 2 + 1];
-        }
-      }
-      for (int64_t i = s0; i < s1 && k < Wb; ++i) {
-        const int32_t pb = segs[i * SEG_WORDS + S_PB], pe = segs[i * SEG_WORDS + S_PE];
-        const int64_t vend = vstart + alpha + (pe - pb);
-        for (; k < Wb && cut < vend; ++k, cut = vt * k / Wb) {
-          int32_t* ww = bw + k * WAVE_WORDS;
-          ww[0] = (int32_t)i;
-          ww[1] = pb + (int32_t)std::max<int64_t>(0, cut - vstart - alpha);
-        }
-        vstart = vend;
-      }
-      for (int64_t kk = 0; kk < Wb; ++kk) {
-        int32_t* ww = bw + kk * WAVE_WORDS;
-        int64_t i = ww[0];
-        int32_t p = ww[1];
-        const int64_t ei = kk + 1 < Wb ? ww[WAVE_WORDS + 0] : s1;
-        const int32_t ep = kk + 1 < Wb ? ww[WAVE_WORDS + 1] : 0;
-        {                                   // ids of the first pages: their loads need no table lookup
-          const int32_t* sg = segs + i * SEG_WORDS;
-          for (int t = 0; t < 3; ++t) ww[4 + t] = pt[sg[S_TBL] + std::min(p + t, sg[S_PE] - 1)];
-        }
-        int64_t units = 0;
-        int32_t piece = 0;
-        while (i < s1) {
-          const int32_t* sg = segs + i * SEG_WORDS;
-          const int32_t end = (i == ei) ? ep : sg[S_PE];      // the next wavefront may start inside this segment
-          if (end > p) {
-            if (!(p == sg[S_PB] && end == sg[S_PE])) {        // a piece of a cut segment
-              if (p == sg[S_PB]) {                             // its first piece: a new entry
-                int32_t* en = lm + 4 + 4 * lm[0]++;
-                en[0] = (int32_t)i;
-                en[1] = (int32_t)(piece == 0 ? 2 * kk : 2 * kk + 1);
-                en[2] = (int32_t)kk;
-                en[3] = 0;
-              }
-              ++lm[4 + 4 * (lm[0] - 1) + 3];
+      int64_t Wb = W, total;                            // wavefronts that get work; units of the bin (plan B: of the batch up to its end)
+      if (whole) {
+        total = bin_units[b];
+        Wb = std::min<int64_t>(W, total);
+        if (Wb == 0) continue;
+        const int64_t vt = total + alpha * (s1 - s0), step = vt / Wb, over = vt - step * Wb;
+        int64_t k = 0, vstart = 0, units = 0, cut = 0, rem = 0;      // wavefront k starts at cut = vt * k / Wb, rem = vt * k % Wb
+        for (int64_t i = s0; i < s1 && k < Wb; ++i) {
+          const int32_t pb = segs[i * SEG_WORDS + S_PB], n = segs[i * SEG_WORDS + S_PE] - pb;
+          const int64_t vend = vstart + alpha + n;
+          while (k < Wb && cut < vend) {
+            int32_t* ww = bw + k * WAVE_WORDS;
+            const int32_t in = (int32_t)std::max<int64_t>(0, cut - vstart - alpha);
+            ww[0] = (int32_t)i;
+            ww[1] = pb + in;
+            ww[2] = (int32_t)(uint32_t)(units + in);    // units before it, for now
+            ++k;
+            cut += step;
+            if ((rem += over) >= Wb) {
+              rem -= Wb;
+              ++cut;
             }
-            units += end - p;
-            ++piece;
           }
-          if (i == ei) break;
-          ++i;
-          p = i < s1 ? segs[i * SEG_WORDS + S_PB] : 0;
+          vstart = vend;
+          units += n;
         }
-        ww[2] = (int32_t)units;
+      } else {                                          // the wavefronts' starts come from the cut of the whole batch
+        const int32_t* wp = out->wave_pos.data() + b * W * 3;
+        for (int64_t k = 0; k < W; ++k) std::memcpy(bw + k * WAVE_WORDS, wp + 3 * k, 3 * sizeof(int32_t));
+        total = b + 1 < n_bins ? (uint32_t)wp[3 * W + 2] : total_units;
+      }
+      for (int64_t k = 0; k < Wb; ++k) {
+        int32_t* ww = bw + k * WAVE_WORDS;
+        const int32_t* sg = segs + (int64_t)ww[0] * SEG_WORDS;
+        const int32_t p = ww[1], last = sg[S_PE] - 1;
+        const int32_t* ids = pt + sg[S_TBL];            // of the first pages: their loads need no table lookup
+        for (int t = 0; t < 3; ++t) ww[4 + t] = ids[std::min(p + t, last)];
+        ww[2] = (int32_t)((k + 1 < Wb ? (uint32_t)ww[WAVE_WORDS + 2] : (uint32_t)total) - (uint32_t)ww[2]);
+        if (p == sg[S_PB]) continue;
+        // it continues a segment: of the wavefront before it, whose last piece is either the segment's first or continues it too
+        const int32_t* wb = ww - WAVE_WORDS;
+        if (wb[0] != ww[0] || wb[1] == sg[S_PB]) {
+          int32_t* en = lm + 4 + 4 * lm[0]++;
+          en[0] = ww[0];
+          en[1] = (int32_t)(wb[0] == ww[0] ? 2 * (k - 1) : 2 * (k - 1) + 1);
+          en[2] = (int32_t)(k - 1);
+          en[3] = 1;
+        }
+        int32_t* en = lm + 4 + 4 * (lm[0] - 1);
+        ++en[3];
+        ++bw[en[2] * WAVE_WORDS + 3];                   // wavefronts that continue that one's last segment
       }
     }
   } else {
