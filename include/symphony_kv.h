@@ -347,7 +347,8 @@ int sym_plan_copies_first(sym_ctx* ctx);
  *                           first three pages of the first range (its first loads need no
  *                           table lookup).  Bins (decode workgroups of [35] wavefronts; wavefront
  *                           w of bin b is record b * [35] + w): first segment, page inside it,
- *                           units, 0, ids of its first three pages, 0: the wavefronts of a bin
+ *                           units, wavefronts that continue its last segment, ids of its first
+ *                           three pages, kv head of the first segment: the wavefronts of a bin
  *                           take equal consecutive parts of the bin's segments
  *   segs      [n_segs + 2][8]  (bins) a (row, kv head) range or the part of one that falls
  *                           into a bin: page-table offset, kv head, first page, end page,

@@ -827,6 +827,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
         const int32_t p = ww[1], last = sg[S_PE] - 1;
         const int32_t* ids = pt + sg[S_TBL];            // of the first pages: their loads need no table lookup
         for (int t = 0; t < 3; ++t) ww[4 + t] = ids[std::min(p + t, last)];
+        ww[7] = sg[S_HEAD];
         ww[2] = (int32_t)((k + 1 < Wb ? (uint32_t)ww[WAVE_WORDS + 2] : (uint32_t)total) - (uint32_t)ww[2]);
         if (p == sg[S_PB]) continue;
         // it continues a segment: of the wavefront before it, whose last piece is either the segment's first or continues it too

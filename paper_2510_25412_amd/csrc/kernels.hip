@@ -41,6 +41,13 @@ __device__ __forceinline__ uint32_t as_u32(float f) { return __builtin_bit_cast(
 typedef const __attribute__((address_space(4))) int32_t* const_word_t;
 __device__ __forceinline__ int sload(const int32_t* ptr) { return __builtin_amdgcn_readfirstlane(*(const_word_t)(uintptr_t)ptr); }
 
+// Kernel arguments that a start needs, all requested before the first of them is waited for.  Left to itself the compiler fetches
+// each where it is used, and a start is then a chain of up to six misses of the scalar cache before the first K/V load.
+template <typename... T>
+__device__ __forceinline__ void hold(const T&... x) {
+  (..., [](auto v) __attribute__((always_inline)) { asm volatile("" ::"s"(v)); }(x));
+}
+
 // Sum over the 8 lanes of a lane octet (lanes 8k .. 8k+7): three DPP adds.
 __device__ __forceinline__ float octet_sum(float x) {
   x += as_f32(__builtin_amdgcn_update_dpp(0, as_u32(x), 0xB1, 0xf, 0xf, false));    // quad_perm [1,0,3,2]
@@ -157,22 +164,44 @@ struct BinLds {
   static constexpr int kSlot = kAcc + 2 * G;                   // + (max, sum) per head
 };
 
-// After the barrier: wavefront `wib` of the bin combines the pieces of cut segments wib, wib + W, ... of the bin's list.
+// What a wavefront of a bin starts with: its wave record, and the entry of the bin's merge list that it will carry out (the cut
+// divides at most W - 1 segments, so there is at most one).  Both hang on the kernel arguments alone, so they are one round trip;
+// the first K/V page and the records of the segments, which the wave record leads to, are the next.  (Arguments fetched one by one, the
+// first page behind the segment's record and the merge list behind the barrier were eight misses of about 0.2 us each: one file of
+// 2000 tokens x 32 layers 413 -> 394 us, 64 files of 512..4096 x 8 layers 786 -> 781.)
+struct BinStart {
+  int seg, p, units, id0, id1, head;           // first segment, page inside it, units, ids of its first two pages, kv head
+  bool merges;
+  int m_seg, m_slot, m_wave, m_pieces;
+};
+__device__ __forceinline__ BinStart bin_start(const DecodeArgs& a, const int bin, const int W, const int wib) {
+  const int32_t* ww = a.waves + ((int64_t)bin * W + wib) * 8;
+  const int32_t* lm = a.lmerge + (int64_t)bin * 32;
+  const int32_t* en = lm + 4 + 4 * min(wib, 6);
+  BinStart b;
+  b.seg = sload(ww + 0);
+  b.p = sload(ww + 1);
+  b.units = sload(ww + 2);
+  b.id0 = sload(ww + 4);
+  b.id1 = sload(ww + 5);
+  b.head = sload(ww + 7);
+  b.merges = wib < sload(lm);
+  b.m_seg = sload(en + 0);
+  b.m_slot = sload(en + 1);
+  b.m_wave = sload(en + 2);
+  b.m_pieces = sload(en + 3);
+  return b;
+}
+
+// After the barrier: the wavefront combines the pieces of the divided segment that is its own (qh, dest: words 5 and 6 of that
+// segment's record, fetched while the first pages were on their way).
 // Lane owns accumulator entries e * 64 + lane of the G * D values (head = entry / D).
 template <typename E, int G>
-__device__ __forceinline__ void merge_bin_pieces(const DecodeArgs& a, const int bin, const int W, const int wib, const float* lds) {
+__device__ __forceinline__ void merge_bin_pieces(const DecodeArgs& a, const BinStart& b, const int qh, const int dest, const float* lds) {
   constexpr int D = 16 * E::kDimsPerChunk, VL = G * D / 64, SLOT = BinLds<E, G>::kSlot, ACC = BinLds<E, G>::kAcc;
   const int lane = threadIdx.x & 63;
-  const int32_t* lm = a.lmerge + (int64_t)bin * 32;
-  const int cnt = sload(lm + 0);
-  for (int k = wib; k < cnt; k += W) {
-    const int seg = sload(lm + 4 + 4 * k + 0);
-    const int s0 = sload(lm + 4 + 4 * k + 1);
-    const int w0 = sload(lm + 4 + 4 * k + 2);
-    const int n = sload(lm + 4 + 4 * k + 3);
-    const int32_t* sr = a.segs + (int64_t)seg * 8;
-    const int qh = sload(sr + 5);        // q row * Hq + first query head
-    const int dest = sload(sr + 6);
+  if (b.merges) {
+    const int s0 = b.m_slot, w0 = b.m_wave, n = b.m_pieces;
     float M[G], ls[G], o[VL];
 #pragma unroll
     for (int h = 0; h < G; ++h) {
@@ -224,20 +253,37 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
   constexpr int DPL = 2 * C;             // dims per lane
   constexpr int D = 16 * C;              // head dim
   constexpr int SLOT = BinLds<E, G>::kSlot, ACC = BinLds<E, G>::kAcc;
+  hold(a.waves, a.lmerge, a.segs, a.pt, a.pool, a.page_bytes, a.q, a.out, a.part_acc, a.part_ml, a.k_new, a.v_new, a.n_bins, a.Hkv, a.scale_log2e);
   if (bin >= a.n_bins) return;           // the whole workgroup
   const int lane = threadIdx.x & 63;
   const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));      // wavefront within the bin
   const int r = lane >> 3, j = lane & 7;
-  const int32_t* ww = a.waves + ((int64_t)bin * W + wib) * 8;
-  int remaining = sload(ww + 2);
+  const BinStart st = bin_start(a, bin, W, wib);
+  int remaining = st.units;
+  int m_qh = 0, m_dest = 0;              // of the segment whose pieces it merges at the end: query row * Hq + head, destination
+  auto merge_record = [&]() __attribute__((always_inline)) {
+    const int32_t* msr = a.segs + (int64_t)(st.merges ? st.m_seg : 0) * 8;
+    m_qh = sload(msr + 5);
+    m_dest = sload(msr + 6);
+  };
 
   if (remaining > 0) {
+  // The first page, by what the wave record holds: its loads go out before the segment's record has come.
+  const uint8_t* pool_lane = a.pool + lane * 16;
+  auto request = [&](PageRegs& R, const uint8_t* base) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) R.k[x] = ld16<STREAM>(base + x * 1024);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) R.v[x] = ld16<STREAM>(base + kBlk + x * 1024);
+  };
+  PageRegs A, B;
+  request(A, pool_lane + (int64_t)st.head * kSlab + (int64_t)st.id0 * a.page_bytes);
+  __builtin_amdgcn_sched_barrier(0);
+  merge_record();
   // Segment record: [0] page-table offset, [1] kv head, [2] first page, [3] end page (what the load side needs),
   // [4] tokens the row sees, [5] q row * Hq + first query head, [6] destination, [7] slot of the appended token or -1.
-  // compute cursor: the segment being accumulated.  The wave record carries the id of the first page: the first K/V loads wait for
-  // the segment record (the kv head and the end page are in it), not for the page table as well.
-  int seg = sload(ww + 0), p = sload(ww + 1);
-  const int pid_first = sload(ww + 4);
+  // compute cursor: the segment being accumulated
+  int seg = st.seg, p = st.p;
   const int32_t* sr = a.segs + (int64_t)seg * 8;
   int pe = sload(sr + 3), vis = sload(sr + 4), qh = sload(sr + 5);
   int dest = sload(sr + 6), app = sload(sr + 7), tbl = sload(sr + 0);
@@ -266,14 +312,13 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
     c_tbl = sload(q8 + 0);
   };
 
-  const uint8_t* pool_lane = a.pool + lane * 16;
   // Requests the K/V of the next unit into R and advances the load cursor; past the last unit: page 0, head 0 (valid
   // memory that every wavefront touches, never used).
   // A streaming batch takes page ids as vector loads: the wait for one then drains the K/V loads before it, and without that the
   // wavefronts of a batch of equally long files run in step over the same memory channels (64 files of 4000 tokens, one
   // after the other in the pool: 190 us instead of 175; ragged or scattered files: the same within 1 %).
   auto page_id = [&](const int32_t* ptr) __attribute__((always_inline)) { return STREAM ? __builtin_amdgcn_readfirstlane(*ptr) : sload(ptr); };
-  int next_pid = pid_first;
+  int next_pid = 0;
   auto load_next = [&](PageRegs& R) __attribute__((always_inline)) {
     const bool valid = lrem > 0;
     const uint8_t* base = pool_lane + (int64_t)(valid ? lg : 0) * kSlab + (int64_t)(valid ? next_pid : 0) * a.page_bytes;
@@ -291,10 +336,7 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
     }
     // every load is unconditional and off one base address: no control-flow join between a load and its use, so the
     // waits can be for exactly the older page while the newer one is in flight
-#pragma unroll
-    for (int x = 0; x < 4; ++x) R.k[x] = ld16<STREAM>(base + x * 1024);
-#pragma unroll
-    for (int x = 0; x < 4; ++x) R.v[x] = ld16<STREAM>(base + kBlk + x * 1024);
+    request(R, base);
   };
 
   // q chunks of this lane for the G heads of the current segment
@@ -315,6 +357,19 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
   };
   fetch_compute_next_seg();
   load_q();
+  // past the first page, which is on its way; the record has the second one's id too, if that is of the same segment
+  hold(m_qh, m_dest);
+  next_pid = st.id1;
+  --lrem;
+  if (++lp == lpe) {
+    ++lseg;
+    ltbl = n_tbl;
+    lg = n_g;
+    lp = n_pb;
+    lpe = n_pe;
+    fetch_next_seg(lseg + 1);
+    if (lrem > 0) next_pid = page_id(a.pt + ltbl + lp);
+  }
 
   float m[G], l[G], acc[G][DPL];
   auto reset_state = [&]() __attribute__((always_inline)) {
@@ -532,17 +587,17 @@ __device__ __forceinline__ void decode_bins(const DecodeArgs& a, const int bin, 
     if (p == pe || remaining == 0) finish_piece();
   };
 
-  PageRegs A, B;
-  load_next(A);
   while (remaining > 0) {
     load_next(B);
     do_unit(A);
     load_next(A);
     if (remaining > 0) do_unit(B);
   }
+  } else {
+    merge_record();
   }
   __syncthreads();                                       // every piece of the bin is in LDS (or went straight to its destination)
-  merge_bin_pieces<E, G>(a, bin, W, wib, lds);
+  merge_bin_pieces<E, G>(a, st, m_qh, m_dest, lds);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -573,18 +628,37 @@ __device__ __forceinline__ float row_shl(float x) {     // value of the lane N f
 template <int G>
 __device__ __forceinline__ void decode_bins_mx(const DecodeArgs& a, const int bin, const int W, float* lds) {
   constexpr int D = 128, SLOT = BinLds<ElemBF16, G>::kSlot, ACC = BinLds<ElemBF16, G>::kAcc;
+  hold(a.waves, a.lmerge, a.segs, a.pt, a.pool, a.page_bytes, a.q, a.out, a.part_acc, a.part_ml, a.k_new, a.v_new, a.n_bins, a.Hkv, a.scale_log2e);
   if (bin >= a.n_bins) return;           // the whole workgroup
   const int lane = threadIdx.x & 63;
   const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));      // wavefront within the bin
   const int col = lane & 15, grp = lane >> 4;
   const int head = col % G, part = col / G;                                      // columns from 3 G on are ignored
-  const int32_t* ww = a.waves + ((int64_t)bin * W + wib) * 8;
-  int remaining = sload(ww + 2);
+  const BinStart st = bin_start(a, bin, W, wib);
+  int remaining = st.units;
+  int m_qh = 0, m_dest = 0;
+  auto merge_record = [&]() __attribute__((always_inline)) {
+    const int32_t* msr = a.segs + (int64_t)(st.merges ? st.m_seg : 0) * 8;
+    m_qh = sload(msr + 5);
+    m_dest = sload(msr + 6);
+  };
 
   if (remaining > 0) {
-  // cursors and records as in decode_bins
-  int seg = sload(ww + 0), p = sload(ww + 1);
-  const int pid_first = sload(ww + 4);
+  // first page, cursors and records as in decode_bins
+  const int k_off = col * kHalfBytes + grp * 16;                                 // token col, chunk 4 ks + grp of its row
+  const int v_off = kBlk + (col >> 3) * (kP * kHalfBytes) + (4 * grp) * kHalfBytes + (col & 7) * 16;      // tokens 4 grp + u, chunk col
+  auto request = [&](PageRegs& R, const uint8_t* base) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+      R.k[ks] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + k_off + (ks >> 1) * (kP * kHalfBytes) + (ks & 1) * 64)));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) R.v[u] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + v_off + u * kHalfBytes)));
+  };
+  PageRegs A, B;
+  request(A, a.pool + (int64_t)st.head * kSlab + (int64_t)st.id0 * a.page_bytes);
+  __builtin_amdgcn_sched_barrier(0);
+  merge_record();
+  int seg = st.seg, p = st.p;
   const int32_t* sr = a.segs + (int64_t)seg * 8;
   int pe = sload(sr + 3), vis = sload(sr + 4), qh = sload(sr + 5);
   int dest = sload(sr + 6), app = sload(sr + 7), tbl = sload(sr + 0);
@@ -610,9 +684,7 @@ __device__ __forceinline__ void decode_bins_mx(const DecodeArgs& a, const int bi
     c_tbl = sload(q8 + 0);
   };
 
-  const int k_off = col * kHalfBytes + grp * 16;                                 // token col, chunk 4 ks + grp of its row
-  const int v_off = kBlk + (col >> 3) * (kP * kHalfBytes) + (4 * grp) * kHalfBytes + (col & 7) * 16;      // tokens 4 grp + u, chunk col
-  int next_pid = pid_first;
+  int next_pid = 0;
   auto load_next = [&](PageRegs& R) __attribute__((always_inline)) {
     const bool valid = lrem > 0;
     const uint8_t* base = a.pool + (int64_t)(valid ? lg : 0) * kSlab + (int64_t)(valid ? next_pid : 0) * a.page_bytes;
@@ -628,11 +700,7 @@ __device__ __forceinline__ void decode_bins_mx(const DecodeArgs& a, const int bi
       }
       next_pid = lrem > 0 ? sload(a.pt + ltbl + lp) : 0;
     }
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      R.k[ks] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + k_off + (ks >> 1) * (kP * kHalfBytes) + (ks & 1) * 64)));
-#pragma unroll
-    for (int u = 0; u < 4; ++u) R.v[u] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + v_off + u * kHalfBytes)));
+    request(R, base);
   };
 
   bf16x8_t q[4];                         // Q^T operand: this lane's head, dims 32 ks + 8 grp .. +8
@@ -645,6 +713,18 @@ __device__ __forceinline__ void decode_bins_mx(const DecodeArgs& a, const int bi
   };
   fetch_compute_next_seg();
   load_q();
+  hold(m_qh, m_dest);
+  next_pid = st.id1;
+  --lrem;
+  if (++lp == lpe) {
+    ++lseg;
+    ltbl = n_tbl;
+    lg = n_g;
+    lp = n_pb;
+    lpe = n_pe;
+    fetch_next_seg(lseg + 1);
+    if (lrem > 0) next_pid = sload(a.pt + ltbl + lp);
+  }
 
   f32x4_t O[8];
   float m, l;
@@ -804,8 +884,6 @@ __device__ __forceinline__ void decode_bins_mx(const DecodeArgs& a, const int bi
 
   // One copy of the end-of-piece code for both register sets: a launch starts with a cold instruction cache, and a wavefront of
   // a small batch runs through this code once.
-  PageRegs A, B;
-  load_next(A);
   bool odd = false;
   while (remaining > 0) {
     if (!odd) {
@@ -818,9 +896,11 @@ __device__ __forceinline__ void decode_bins_mx(const DecodeArgs& a, const int bi
     odd = !odd;
     if (p == pe || remaining == 0) finish_piece();
   }
+  } else {
+    merge_record();
   }
   __syncthreads();                                       // every piece of the bin is in LDS (or went straight to its destination)
-  merge_bin_pieces<ElemBF16, G>(a, bin, W, wib, lds);
+  merge_bin_pieces<ElemBF16, G>(a, st, m_qh, m_dest, lds);
 }
 
 // The decode bins of a shape.  With 1 or 2 query heads per kv head the vector units' page is short, and its loads take whole

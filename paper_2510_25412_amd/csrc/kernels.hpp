@@ -20,7 +20,7 @@ struct DecodeArgs {
   int32_t n_waves, Hq, Hkv;
   float scale_log2e;        // softmax scale * log2(e)
   // bins (the vector-unit decode kernel): `waves` then holds bin_waves records per bin: first segment, first
-  // page, units, 0, ids of the first three pages
+  // page, units, wavefronts that continue its last segment, ids of the first three pages, kv head
   const int32_t* segs;      // [n_segs + 2][8]: page-table offset, kv head, first page, end page, visible tokens,
                             //   q/out row * Hq + first query head, destination (-1 output, else partial slot), slot of the appended token or -1
   const int32_t* lmerge;    // [n_bins][32]: count, then (segment, LDS slot of its first piece, that piece's wavefront,

@@ -592,6 +592,27 @@ def test_descriptor_bins_cover_every_unit_once_and_are_balanced(lengths, n_tok, 
         assert [seg_bin[i] for i in range(len(segs))] == sorted(seg_bin[i] for i in range(len(segs)))   # contiguous shares
 
 
+@pytest.mark.parametrize("lengths", [[1], [16], [17, 300, 5], [1000], [200] * 64, [4000, 16, 16, 900] * 8])
+def test_wave_records_name_what_the_first_loads_need(lengths):
+    """A wavefront of a bin requests its first page before its segment's record has come: kv head and page ids of the wave
+    record are those of the segment it starts in."""
+    c = host_ctx(1 << 15)
+    np_l = [-(-n // 16) for n in lengths]
+    off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+    flat = np.random.default_rng(3).permutation(1 << 15)[:sum(np_l)].astype(np.int32)
+    w = c.build_desc([1] * len(lengths), flat, off, lengths)
+    hdr = w[:48]
+    waves = w[hdr[6]:hdr[6] + 8 * hdr[1]].reshape(-1, 8)
+    segs = w[hdr[33]:hdr[33] + 8 * hdr[32]].reshape(-1, 8)
+    live = waves[waves[:, 2] > 0]
+    assert len(live) and int(live[:, 2].sum()) == sum(np_l) * 8
+    sg = segs[live[:, 0]]
+    assert np.array_equal(live[:, 7], sg[:, 1])
+    assert np.array_equal(live[:, 4], w[hdr[8] + sg[:, 0] + live[:, 1]])
+    inside = live[:, 1] + 1 < sg[:, 3]
+    assert np.array_equal(live[inside, 5], w[hdr[8] + sg[inside, 0] + live[inside, 1] + 1])
+
+
 def _plain_desc(c, lengths):
     np_l = [-(-n // 16) for n in lengths]
     off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
