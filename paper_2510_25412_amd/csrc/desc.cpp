@@ -358,7 +358,16 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   if (total_units == 0) nw = 0;
   int64_t n_bins = 0;
   if (bins) {
-    n_bins = (total_units + (int64_t)prm.min_units_per_wave * W - 1) / ((int64_t)prm.min_units_per_wave * W);
+    // A small batch with long ranges: a wavefront takes as few pages as give every compute unit one workgroup (both of two are in
+    // flight from the start), but two at least where one would leave a range in more than the 16 pieces that a merge reads in one
+    // round trip.  32 layers, four pages per wavefront / by this rule: a file of 600 tokens 362 / 298 us, of 1000 361 / 299, of 2000
+    // 389 / 354, of 4000 414 / 390, of 6000 443 / 425; four of 800..1200 400 / 360, eight of 400..700 397 / 381; 2000 tokens with 16
+    // query heads 293 / 272, 8000 with 4 heads of one kv head 377 / 370 (one page each: 472).  Short ranges in more than one per
+    // compute unit stay at four: there is no latency of a long range to divide.
+    int64_t upw = prm.min_units_per_wave;
+    if (small_decode && longest_range > kWholePagesWide)
+      upw = std::min(upw, std::max<int64_t>(longest_range <= 16 * W ? 1 : 2, (total_units + prm.cus * 4 - 1) / (prm.cus * 4)));
+    n_bins = (total_units + upw * W - 1) / (upw * W);
     n_bins = std::max<int64_t>(1, std::min<int64_t>(n_bins, max_bins));
     if (whole_small) n_bins = n_rows * H;
     nw = n_bins * W;

@@ -619,6 +619,22 @@ def _plain_desc(c, lengths):
     return c.build_desc([1] * len(lengths), np.arange(sum(np_l), dtype=np.int32) % (1 << 20), off, lengths)
 
 
+@pytest.mark.parametrize("Hkv,G,lengths,units", [
+    (8, 4, [513], 1), (8, 4, [1024], 1), (8, 4, [1025], 2), (8, 4, [4096], 2), (8, 4, [4097], 3), (8, 4, [6144], 3), (8, 4, [6145], 4), (8, 4, [8192], 4),
+    (1, 4, [529], 1), (1, 4, [1024], 1), (1, 4, [1025], 2), (1, 4, [65536], 4), (2, 1, [1000, 16, 17], 1), (8, 2, [600, 700], 1), (8, 4, [900] * 3, 2)])
+def test_descriptor_small_batches_of_long_ranges_are_spread(Hkv, G, lengths, units):
+    """The fewest pages per wavefront of a small batch with ranges of more than 32 pages: what gives each of 256 compute units one
+    workgroup of four, at least two where a range has more than 64 pages; every page is covered once, also where wavefronts get none."""
+    c = host_ctx(1 << 16, Hq=Hkv * G, Hkv=Hkv)
+    np_l = [-(-n // 16) for n in lengths]
+    off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+    w = c.build_desc([1] * len(lengths), np.arange(sum(np_l), dtype=np.int32), off, lengths)
+    total = sum(np_l) * Hkv
+    assert (int(w[34]), int(w[35])) == (-(-total // (4 * units)), 4) and int(w[14]) > 0
+    segs, cover, seg_bin, loads, n_bins, W = _walk_bins(w)
+    assert len(cover) == total == sum(loads)
+
+
 def test_descriptor_small_decode_batches():
     """The planner's rules for small decode batches: up to 24 pages a workgroup of four wavefronts per range and no merge, up to
     32 one of eight; with longer ones, or with more ranges than compute units (256 here), cut and merged; eight wavefronts past 4096 units (token, kv head,
