@@ -377,7 +377,7 @@ int sym_plan_copies_first(sym_ctx* ctx);
  *                           in the tile, kv head, token offset in the chunk (shared: first
  *                           partial slot), kind (0 prefill chunk, 1 shared prefix, 2 prefill chunk over
  *                           part of its keys), first page, end page, first partial slot of
- *                           kind 2, 0, 0; ordered share by share
+ *                           kind 2, ids of the first two pages it walks; ordered share by share
  *   members   [n_members]   q rows of the members of shared-prefix tiles
  *   rtiles    [n_rtiles][8]  (fp32) page-table offset, tokens the tile's first row sees, its q/out
  *                           row, tokens, kv head, first page, end page, first partial slot (-1: the

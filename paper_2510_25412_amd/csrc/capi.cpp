@@ -319,9 +319,8 @@ int launch_attention(sym_ctx* c, const Scratch& ws, int64_t blob_words, const vo
   pa.members = dw + hdr[H_OFF_MEMBERS];
   pa.part_acc = part_acc;
   pa.part_ml = part_ml;
-  pa.tile_first = 0;
   pa.n_tiles = d.n_tiles;
-  pa.xcd_off = dw + H_XCD_OFF;
+  for (int x = 0; x <= 8; ++x) pa.xcd_off[x] = hdr[H_XCD_OFF + x];
   pa.tile_blocks = d.tile_blocks;
   pa.tile_rows = d.tile_rows;
   pa.Hq = c->cfg.n_q_heads;

@@ -992,6 +992,15 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       }
     }
   }
+  // ---- ids of the pages of a tile's first block (the page after its last one stands in by the last)
+  for (int64_t i = 0; i < n_tiles; ++i) {
+    int32_t* t = tiles + i * TILE_WORDS;
+    const int32_t p0 = t[T_KIND] == TILE_PREFILL ? 0 : t[T_PAGE0];
+    const int64_t rows_end = ((int64_t)t[T_LEN] + t[T_AUX] + t[T_COUNT] + P - 1) / P;      // pages the tile's last row sees
+    const int32_t end = t[T_KIND] == TILE_SHARED ? t[T_PAGE1] : t[T_KIND] == TILE_CHUNK ? (int32_t)std::min<int64_t>(rows_end, t[T_PAGE1]) : (int32_t)rows_end;
+    t[T_ID0] = pt[t[T_TBL] + std::min(p0, std::max(end - 1, 0))];
+    t[T_ID1] = pt[t[T_TBL] + std::min(p0 + 1, std::max(end - 1, 0))];
+  }
   // ---- the tile list in 8 shares of equal cost, one per XCD
   int32_t tile_blocks = 0;
   {

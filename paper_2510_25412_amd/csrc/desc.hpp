@@ -65,7 +65,7 @@ enum {
 // page that receives the row's new token (-1 = the token is not appended by the attention kernel)
 enum { S_TBL = 0, S_HEAD, S_PB, S_PE, S_VIS, S_QROW, S_DEST, S_APPEND };
 // tile words
-enum { T_TBL = 0, T_LEN, T_QROW, T_COUNT, T_HEAD, T_AUX, T_KIND, T_PAGE0, T_PAGE1, T_DEST };
+enum { T_TBL = 0, T_LEN, T_QROW, T_COUNT, T_HEAD, T_AUX, T_KIND, T_PAGE0, T_PAGE1, T_DEST, T_ID0, T_ID1 };
 enum { TILE_PREFILL = 0, TILE_SHARED = 1, TILE_CHUNK = 2 };      // TILE_CHUNK: a prefill tile over part of its keys, which leaves partials
 // row tile words: page-table offset, tokens the tile's first row sees, its q / out row, tokens in the tile, kv head, first
 // page, end page, partial slot of the chunk's first token (-1 = the final output rows)

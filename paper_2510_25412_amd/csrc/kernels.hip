@@ -1223,12 +1223,26 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   constexpr int CT = 1;
   // workgroups go round-robin over the 8 XCDs; the tile list comes in 8 shares in which tiles that read the same K/V are
   // neighbours (one L2 per XCD): of equal cost, longest first, or, where all are about equal pieces of cut tiles, of equal count
-  const int tile = sload(a.xcd_off + block % 8) + block / 8;
-  if (tile >= sload(a.xcd_off + block % 8 + 1)) return;
-  const int32_t* tw = a.tiles + (int64_t)(a.tile_first + tile) * 12;
-  const int tbl_off = sload(tw + 0), g = sload(tw + 4), count = sload(tw + 3);
-  const bool shared = sload(tw + 6) == 1;
-  const bool partial = sload(tw + 6) != 0;               // shared prefixes and key chunks leave partials
+  // A start is the order table, the tile's record, then everything else at once: the offsets of the shares are kernel arguments,
+  // and the record names the first block's pages, whose loads need no table lookup.  (As a chain of about ten scalar loads, 0.2 us
+  // each: fork tree of 16 x 16 81.5 -> 80.7 us, three ragged prompts 72.0 -> 71.3, the mixed batch the same.)
+  int tile = a.xcd_off[0], tile_end = a.xcd_off[1];
+#pragma unroll
+  for (int x = 1; x < 8; ++x)
+    if (block % 8 == x) {
+      tile = a.xcd_off[x];
+      tile_end = a.xcd_off[x + 1];
+    }
+  tile += block / 8;
+  if (tile >= tile_end) return;
+  const int32_t* tw = a.tiles + (int64_t)tile * 12;
+  int rec[12];
+#pragma unroll
+  for (int i = 0; i < 12; ++i) rec[i] = sload(tw + i);
+  hold(rec[0], rec[1], rec[2], rec[3], rec[4], rec[5], rec[6], rec[7], rec[8], rec[9], rec[10], rec[11]);
+  const int tbl_off = rec[0], g = rec[4], count = rec[3];
+  const bool shared = rec[6] == 1;
+  const bool partial = rec[6] != 0;               // shared prefixes and key chunks leave partials
   const int32_t* tbl = a.pt + tbl_off;
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -1236,12 +1250,12 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   // prefill chunk: `count` new tokens from chunk offset t0 on a file of L tokens; row tl sees
   // tokens 0 .. L + t0 + tl.  shared prefix: `count` decode rows (q rows in the member list) that
   // all see the same full pages [page0, page1) of the group's first file.
-  const int L = sload(tw + 1), t0 = sload(tw + 5);
+  const int L = rec[1], t0 = rec[5];
   // key chunk of a prefill tile: the same rows over the blocks of pages [page0, page1) only (some rows may see none of them)
-  const int lim = partial ? sload(tw + 8) * kP : 0x7fffffff;
+  const int lim = partial ? rec[8] * kP : 0x7fffffff;
   const int kv_end = shared ? lim : min(L + t0 + count, lim);    // tokens the tile's last row sees
   const int mask_from = shared ? lim : min(L + t0 + 1, lim);     // first token some row may not see
-  const int kb0 = partial ? sload(tw + 7) / 2 : 0;                       // first 32-token block (page0 is even)
+  const int kb0 = partial ? rec[7] / 2 : 0;                       // first 32-token block (page0 is even)
   const int nblk = (kv_end + kKvBlock - 1) / kKvBlock;
   const int last_page = max((kv_end + kP - 1) / kP - 1, 0);
   // A shared-prefix tile of four wavefronts with at most 64 live rows would keep two of them busy, each alone
@@ -1257,21 +1271,6 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   const int pair = split ? (wv >> 1) : 0;
   const int wvr = split ? (wv & 1) : wv;                         // which 32 rows of the tile
   const bool wave_live = wvr * 32 * CT < count * G;              // a wavefront whose rows are all padding only stages
-
-  int tl[CT], h[CT], qrow[CT], vis[CT];
-  bf16x8_t q[CT][8];             // Q of this lane's rows: 8 k-steps of 16 dims, this lane supplies dims 16*ks + 8*hf .. +8
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const int rho = (wvr * CT + ct) * 32 + col;    // query row of this lane inside the tile
-    tl[ct] = rho / G;                              // token (prefill) or member (shared prefix) of the row
-    h[ct] = rho % G;
-    const int tlc = min(tl[ct], count - 1);        // rows past the tile's last token/member repeat it (never written)
-    qrow[ct] = shared ? a.members[sload(tw + 2) + tlc] : sload(tw + 2) + tlc;
-    vis[ct] = shared ? kv_end : min(L + t0 + tlc + 1, lim);   // tokens this row sees
-    const uint8_t* qp = (const uint8_t*)a.q + ((int64_t)qrow[ct] * a.Hq + g * G + h[ct]) * kRowBytes + hf * 16;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) q[ct][ks] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + ks * 32));
-  }
 
   // ---- staging roles
   // K: thread copies chunk c = tid (and tid + 256 with four wavefronts) of the block: token c/16, dim chunk c%16
@@ -1291,12 +1290,12 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   const int k_off = (kdc >> 3) * (kP * kHalfBytes) + kt * kHalfBytes + (kdc & 7) * 16;
   const int dbyte = vc * VD * 2;                            // byte offset of the thread's dims in the 256-byte row
   const int v_off = kBlk + (dbyte >> 7) * (kP * kHalfBytes) + (4 * q4 + 2 * up) * kHalfBytes + (dbyte & 127);
-  auto page_base = [&](int pi) {
-    const int pid = sload(tbl + min(pi, last_page));
-    return slab + (int64_t)pid * a.page_bytes;
-  };
-  auto issue_loads = [&](int kb, uint4& k0, uint4& k1, uint4& v0, uint4& v1) {
-    const uint8_t* pk = page_base(2 * kb + k_page);
+  auto page_id = [&](int pi) { return sload(tbl + min(pi, last_page)); };
+  // K/V of a block, its two pages by their ids (eight wavefronts: a wavefront needs one of them)
+  auto issue_pages = [&](int id0, int id1, uint4& k0, uint4& k1, uint4& v0, uint4& v1) {
+    const uint8_t* p0 = slab + (int64_t)id0 * a.page_bytes;
+    const uint8_t* p1 = slab + (int64_t)id1 * a.page_bytes;
+    const uint8_t* pk = k_page ? p1 : p0;
     // four-wavefront tiles are shared-prefix tiles, and each of those streams K/V of its own (nobody reads a
     // line twice): nontemporal loads.  Prefill tiles share their stream with seven neighbours through L2.
     auto ld16 = [&](const uint8_t* q16) {
@@ -1304,8 +1303,8 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
       else return *(const uint4*)q16;
     };
     k0 = ld16(pk + k_off);
-    if constexpr (TW == 4) k1 = ld16(page_base(2 * kb + 1) + k_off);
-    const uint8_t* p = (TW == 4 ? page_base(2 * kb + v_page) : pk) + v_off;
+    if constexpr (TW == 4) k1 = ld16(p1 + k_off);
+    const uint8_t* p = (v_page ? p1 : p0) + v_off;
     if constexpr (TW == 4) {
       v0 = ld16(p);
       v1 = ld16(p + kHalfBytes);
@@ -1315,6 +1314,44 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
       v1.x = x1.x; v1.y = x1.y;
     }
   };
+  auto issue_loads = [&](int kb, uint4& k0, uint4& k1, uint4& v0, uint4& v1) {
+    if constexpr (TW == 4) {
+      issue_pages(page_id(2 * kb), page_id(2 * kb + 1), k0, k1, v0, v1);
+    } else {
+      const int id = page_id(2 * kb + k_page);
+      issue_pages(id, id, k0, k1, v0, v1);
+    }
+  };
+  int tl[CT], h[CT], qrow[CT], vis[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const int rho = (wvr * CT + ct) * 32 + col;    // query row of this lane inside the tile
+    tl[ct] = rho / G;                              // token (prefill) or member (shared prefix) of the row
+    h[ct] = rho % G;
+    const int tlc = min(tl[ct], count - 1);        // rows past the tile's last token/member repeat it (never written)
+    qrow[ct] = shared ? a.members[rec[2] + tlc] : rec[2] + tlc;
+    vis[ct] = shared ? kv_end : min(L + t0 + tlc + 1, lim);   // tokens this row sees
+  }
+  // the first block by the record's ids; those of the blocks behind it are on their way meanwhile, all in one round trip
+  constexpr int kAhead = SPLIT ? 3 : 2;
+  int ids[kAhead][2];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) {
+    ids[i][0] = page_id(2 * (kb0 + 1 + i) + (TW == 4 ? 0 : k_page));
+    ids[i][1] = TW == 4 ? page_id(2 * (kb0 + 1 + i) + 1) : ids[i][0];
+  }
+  issue_pages(rec[10], rec[11], ka0, ka1, va0, va1);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) hold(ids[i][0], ids[i][1]);
+  bf16x8_t q[CT][8];             // Q of this lane's rows: 8 k-steps of 16 dims, this lane supplies dims 16*ks + 8*hf .. +8
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const uint8_t* qp = (const uint8_t*)a.q + ((int64_t)qrow[ct] * a.Hq + g * G + h[ct]) * kRowBytes + hf * 16;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) q[ct][ks] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + ks * 32));
+  }
+
   auto k_dst = [&](uint8_t* base, int c) {
     const int t = c >> 4, dc = c & 15;
     return base + (t * 16 + (dc ^ (t & 15))) * 16;
@@ -1517,10 +1554,9 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
     // the loop unrolled by four addresses them statically) puts the loads four blocks ahead of their use.
     // These tiles each stream K/V of their own, and what bounds them is the bytes in flight.
     uint4 kd0, kd1, vd0, vd1;
-    issue_loads(kb0, ka0, ka1, va0, va1);
-    issue_loads(kb0 + 1, kb0r, kb1r, vb0, vb1);
-    issue_loads(kb0 + 2, kc0, kc1, vc0, vc1);
-    issue_loads(kb0 + 3, kd0, kd1, vd0, vd1);
+    issue_pages(ids[0][0], ids[0][1], kb0r, kb1r, vb0, vb1);
+    issue_pages(ids[1][0], ids[1][1], kc0, kc1, vc0, vc1);
+    issue_pages(ids[2][0], ids[2][1], kd0, kd1, vd0, vd1);
     store_lds(kb0, lds[0], ka0, ka1, va0, va1);
     __syncthreads();
     issue_loads(kb0 + 4, ka0, ka1, va0, va1);
@@ -1557,9 +1593,8 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
       m[0] = mn;
     }
   } else {
-  issue_loads(kb0, ka0, ka1, va0, va1);
-  issue_loads(kb0 + 1, kb0r, kb1r, vb0, vb1);
-  issue_loads(kb0 + 2, kc0, kc1, vc0, vc1);
+  issue_pages(ids[0][0], ids[0][1], kb0r, kb1r, vb0, vb1);
+  issue_pages(ids[1][0], ids[1][1], kc0, kc1, vc0, vc1);
   store_lds(kb0, lds[0], ka0, ka1, va0, va1);
   __syncthreads();
   issue_loads(kb0 + 3, ka0, ka1, va0, va1);
@@ -1585,7 +1620,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   const float lt = l[0] + __shfl_xor(l[0], 32);
   const float inv = partial ? 1.0f : 1.0f / lt;
   // first partial slot of the tile, or its first q / out row
-  const int64_t row0 = partial ? (int64_t)(shared ? t0 : sload(tw + 9)) : (int64_t)sload(tw + 2);
+  const int64_t row0 = partial ? (int64_t)(shared ? t0 : rec[9]) : (int64_t)rec[2];
   if (partial && hf == 0 && tl[0] < count) {           // partials: unnormalised accumulator, max, sum, for the merge kernel
     float* ml = a.part_ml + ((row0 + tl[0]) * G + h[0]) * 2;
     ml[0] = m[0];
@@ -1911,6 +1946,9 @@ __global__ __launch_bounds__(64 * TW, 8 / TW) void attn_kernel(DecodeArgs da, Pr
   // the matrix cores busy: the two kinds of work are bound by different units.  (Measured on the mixed batch:
   // 1.85 ms against 1.91 ms with all tiles first; spread over the whole grid: 2.02 ms.  A CU that runs decode
   // ranges alone has only its eight wavefronts' loads in flight, so the gain is small.)
+  if constexpr (E::kDimsPerChunk == 8)
+    hold(pa.group_map, pa.tiles, pa.pt, pa.pool, pa.page_bytes, pa.q, pa.members, pa.Hq, pa.scale_log2e, pa.xcd_off[0], pa.xcd_off[1], pa.xcd_off[2], pa.xcd_off[3],
+         pa.xcd_off[4], pa.xcd_off[5], pa.xcd_off[6], pa.xcd_off[7], pa.xcd_off[8], da.waves, da.lmerge, da.segs, da.n_bins);
   const uint32_t j = blockIdx.x >> 3, x = blockIdx.x & 7;
   const int32_t g = pa.group_map ? sload(pa.group_map + j) : (int32_t)j;   // no table: tiles only
   const bool is_decode = g < 0;
@@ -2563,7 +2601,6 @@ hipError_t launch_attn_g(const DecodeArgs& da, const PrefillArgs& pa, int decode
   // VALU kernel fused into the tile launch (mode 0)
   const int mode = (E::kDimsPerChunk == 8 && decode_mode == 1) ? 1 : (G == 8 ? 2 : 0);
   PrefillArgs ps = pa;
-  ps.tile_first = 0;
   const int tile_blocks = ps.n_tiles > 0 ? ps.tile_blocks : 0;
   // eight-wavefront workgroups when the tiles have 256 query rows (and no tile is there: four)
   const int tw = (ps.n_tiles > 0 && ps.tile_rows == 256) ? 8 : 4;

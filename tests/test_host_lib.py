@@ -619,6 +619,29 @@ def _plain_desc(c, lengths):
     return c.build_desc([1] * len(lengths), np.arange(sum(np_l), dtype=np.int32) % (1 << 20), off, lengths)
 
 
+@pytest.mark.parametrize("lengths,n_tok", [([16], [16]), ([17], [16]), ([40, 300], [40, 64]), ([6000], [100]), ([1300] * 6, [1] * 6), ([900, 1300, 1300, 1300, 1300], [300, 1, 1, 1, 1])])
+def test_tile_records_name_the_pages_of_the_first_block(lengths, n_tok):
+    """Whole tiles, key chunks and shared prefixes: words 10 and 11 are the ids of the first two pages a tile walks, the last
+    page standing in for one past it."""
+    c = host_ctx(1 << 14)
+    np_l = [-(-n // 16) for n in lengths]
+    rng, tables = np.random.default_rng(4), []
+    ids = rng.permutation(1 << 14)
+    for b, n in enumerate(np_l):                                     # files of equal length share their first 64 pages
+        own = ids[b * 400:b * 400 + n].copy()
+        if lengths.count(lengths[b]) > 1:
+            own[:64] = ids[8000:8064]
+        tables.append(own)
+    off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+    w = c.build_desc(n_tok, np.concatenate(tables).astype(np.int32), off, lengths)
+    tiles = w[w[10]:w[10] + 12 * w[4]].reshape(-1, 12)
+    assert len(tiles)
+    for t in tiles.tolist():
+        end = -(-(t[1] + t[5] + t[3]) // 16)
+        p0, end = (0, end) if t[6] == 0 else (t[7], t[8] if t[6] == 1 else min(end, t[8]))
+        assert t[10:12] == [int(w[w[8] + t[0] + min(p, end - 1)]) for p in (p0, p0 + 1)], t
+
+
 @pytest.mark.parametrize("Hkv,G,lengths,units", [
     (8, 4, [513], 1), (8, 4, [1024], 1), (8, 4, [1025], 2), (8, 4, [4096], 2), (8, 4, [4097], 3), (8, 4, [6144], 3), (8, 4, [6145], 4), (8, 4, [8192], 4),
     (1, 4, [529], 1), (1, 4, [1024], 1), (1, 4, [1025], 2), (1, 4, [65536], 4), (2, 1, [1000, 16, 17], 1), (8, 2, [600, 700], 1), (8, 4, [900] * 3, 2)])
