@@ -333,8 +333,9 @@ int sym_plan_copies_first(sym_ctx* ctx);
  * [18] workgroups of the tile part of the launch; [20..28] the 9 offsets that cut the tile list
  * into 8 shares of equal cost, one per XCD (workgroup b runs tile b / 8 of share b % 8);
  * [32] n_segs, [33] offset of the segments, [34] n_bins, [35] wavefronts of a bin,
- * [36] offset of the in-bin merge lists (all five 0 when ranges are cut globally, as the
- * matrix-core decode kernel wants: wave_work is then one record per wavefront slot);
+ * [36] offset of the in-bin merge lists (n_segs, n_bins 0 when ranges are cut globally: the
+ * matrix-core decode kernel beside tiles, or with decode_waves set: wave_work is then one record
+ * per wavefront slot);
  * [37] n_groups, [38] offset of the order table (0 unless the launch holds tiles and bins);
  * [39] n_rtiles, [40] offset of the row tiles (fp32 storage), [41] n_tmerge, [42] offset of the
  * merge list of tiles cut into key chunks}, then the sections (the rows of row tiles count in
@@ -351,7 +352,8 @@ int sym_plan_copies_first(sym_ctx* ctx);
  *                           three pages, kv head of the first segment: the wavefronts of a bin
  *                           take equal consecutive parts of the bin's segments
  *   segs      [n_segs + 2][8]  (bins) a (row, kv head) range or the part of one that falls
- *                           into a bin: page-table offset, kv head, first page, end page,
+ *                           into a bin: page-table offset, kv head | (tokens in the row - 1)
+ *                           << 28, first page, end page,
  *                           tokens the row sees, q row * Hq + first query head, destination
  *                           (-1: the output rows; else the partial slot of its first piece),
  *                           pool slot (page * 16 + token) that receives the row's new K/V

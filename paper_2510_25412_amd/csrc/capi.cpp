@@ -187,7 +187,8 @@ DescParams desc_params(const sym_ctx* c, int64_t partials, int64_t max_words, bo
   // the vector-unit decode kernel (up to 4 query heads per kv head, unless the matrix cores are asked for) works on bins
   p.bin_waves = (c->G < 8 && !c->decode_mode) ? c->bin_waves : 0;
   p.fuse_append = (fuse_append && p.bin_waves && c->fuse_append) ? 1 : 0;
-  p.spread_small = c->cfg.decode_waves <= 0 ? 1 : 0;
+  p.spread_small = p.mfma_bins = c->cfg.decode_waves <= 0 ? 1 : 0;
+  p.decode_mfma = c->decode_mode;
   p.bin_tolerance = c->bin_tolerance;
   p.mix_lead = c->mix_lead;
   p.mix_spread = c->mix_spread;

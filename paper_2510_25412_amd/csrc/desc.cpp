@@ -336,9 +336,10 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       longest_range = std::max(longest_range, pages);
     }
   }
-  // bins (whole ranges per workgroup, pieces combined through LDS) for the vector-unit kernel; the global
-  // cut for the matrix-core decode kernel, which rows of several tokens need
-  const bool bins = prm.bin_waves > 0 && max_nt == 1 && total_units > 0;
+  // bins (whole ranges per workgroup, pieces combined through LDS) for the vector-unit kernel, and for the matrix-core decode
+  // kernel (which rows of several tokens need) in a batch without tiles; otherwise its launch takes the global cut
+  const bool mfma_bins = prm.mfma_bins && (prm.decode_mfma || max_nt > 1) && n_tiles == 0 && total_units > 0;
+  const bool bins = mfma_bins || (prm.bin_waves > 0 && max_nt == 1 && total_units > 0);
   // a bin is a workgroup: eight wavefronts, or four when the launch has tiles of 128 query rows (four-wavefront workgroups)
   // A batch that gives no compute unit more than a workgroup of four: workgroups of four instead of eight, so that twice as many
   // compute units share it, and plain loads.  One compute unit draws about 40 GB/s with nontemporal loads, 60 with plain ones, and
@@ -366,7 +367,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     // compute unit stay at four: there is no latency of a long range to divide.
     int64_t upw = prm.min_units_per_wave;
     if (small_decode && longest_range > kWholePagesWide)
-      upw = std::min(upw, std::max<int64_t>(longest_range <= 16 * W ? 1 : 2, (total_units + prm.cus * 4 - 1) / (prm.cus * 4)));
+      upw = std::min(upw, std::max<int64_t>(longest_range <= 16 * W && !mfma_bins ? 1 : 2, (total_units + prm.cus * 4 - 1) / (prm.cus * 4)));
     n_bins = (total_units + upw * W - 1) / (upw * W);
     n_bins = std::max<int64_t>(1, std::min<int64_t>(n_bins, max_bins));
     if (whole_small) n_bins = n_rows * H;
@@ -407,7 +408,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
           rows_tmp[r * ROW_WORDS + 3] = share_start[b] | ((nt - 1) << ROW_NT_SHIFT);      // first page of the row's own range; tokens - 1
         }
         // the attention kernel can append a LIP's token itself when it is the LIP's only one (nobody else reads it in this launch)
-        if (bins && prm.fuse_append && n_tokens[b] == 1) {
+        if (bins && !mfma_bins && prm.fuse_append && n_tokens[b] == 1) {
           out->fused[b] = 1;
           ++n_fused;
         }

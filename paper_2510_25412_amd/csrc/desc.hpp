@@ -22,12 +22,12 @@
 // The work of the decode kernel is measured in units of one (page, kv head) = one 8 KiB K+V
 // slab.  Two ways of handing the units to wavefronts:
 //  * the global cut (matrix-core decode kernel: 8 query heads per kv head, rows of several draft
-//    tokens): the units of all rows, ordered (row, kv head, page), are cut into n_waves contiguous
+//    tokens; beside tiles, or when the caller sets the wavefront slots): the units of all rows, ordered (row, kv head, page), are cut into n_waves contiguous
 //    ranges of equal cost, one per wavefront, whatever the raggedness of the files.  A range
 //    that covers only part of a (row, kv head) produces a partial result (running max, sum,
 //    unnormalised accumulator) in device memory and an entry in the merge list (a kernel of its
 //    own combines them); a range covering a whole (row, kv head) writes the final output directly.
-//  * bins (the vector-unit decode kernel): every workgroup of bin_waves wavefronts is a bin that
+//  * bins (the vector-unit decode kernel; the matrix-core one in a batch without tiles): every workgroup of bin_waves wavefronts is a bin that
 //    receives WHOLE (row, kv head) ranges, as "segments", balanced over the bins longest first; only a
 //    range longer than a bin's share (or ranges too few to balance) is split into several segments,
 //    each of which leaves a partial result in device memory like above.  Inside a bin the
@@ -60,7 +60,7 @@ enum {
   // row tiles (fp32 storage): LIPs with several new tokens; and the tiles whose key range is cut into chunks
   H_N_RTILES = 39, H_OFF_RTILES, H_N_TMERGE, H_OFF_TMERGE
 };
-// segment words: page-table offset, kv head, first page, end page | tokens the row sees, q/out row * Hq + first
+// segment words: page-table offset, kv head | (new tokens in the row - 1) << 28, first page, end page | tokens the row sees, q/out row * Hq + first
 // query head of the kv head, destination (-1 = the final output rows; otherwise a partial slot in device memory), slot of the row's last
 // page that receives the row's new token (-1 = the token is not appended by the attention kernel)
 enum { S_TBL = 0, S_HEAD, S_PB, S_PE, S_VIS, S_QROW, S_DEST, S_APPEND };
@@ -128,6 +128,8 @@ struct DescParams {
   int32_t bin_waves = 0;      // != 0: bins (the vector-unit decode kernel) unless a row holds several tokens; as many bins as
                               //   max_waves fills with workgroups of 8 wavefronts (4 beside tiles of 128 query rows; a batch
                               //   without tiles: 4 if this is 4, else 8)
+  int32_t decode_mfma = 0;    // 1: every decode row goes to the matrix-core kernel (rows of several tokens always do)
+  int32_t mfma_bins = 0;      // 1: bins for that kernel too, in a batch without tiles (not when the caller set the wavefront slots)
   int32_t spread_small = 0;   // 1: a small decode batch is spread over more, smaller workgroups (not when the caller set the wavefront slots)
   int32_t bin_tolerance = 3;  // percent by which the fullest bin may exceed the mean before ranges are split finer
   int32_t fuse_append = 0;    // 1: single-token LIPs are appended by the attention kernel (bins only)

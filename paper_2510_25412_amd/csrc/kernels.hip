@@ -1681,11 +1681,26 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
 constexpr int kVtRow = 80;                    // bytes per dim row of V^T (32 tokens fp16 + 16 pad)
 constexpr int kVtLds = 128 * kVtRow;          // 10 KiB per wavefront
 
-template <int GT>
-__device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const int block, uint8_t* vlds) {
+// Two plans (see the descriptor): the global cut (BINS = false: a wavefront per range of the cut, every piece of a divided range a
+// partial in device memory), and bins (BINS = true), as in decode_bins: what the wavefronts of a workgroup divide is combined
+// through LDS when they are done.  A row of four draft tokens leaves 8 KiB per piece, so with the global cut a batch of drafts
+// wrote and read again 21 MB beside 604 MB of K/V.  Bins in a launch of their own, i.e. in batches without tiles.  Before / after:
+// drafts of 4 on 64 files of 512..4096 tokens 134.3 / 121.1 us, 8 query heads per kv head on 16 files of 32 k..131 k 709 / 694; per layer,
+// 64 query heads: one file of 2000 tokens 18.3 / 15.6, four of 100..300 17.1 / 12.2, 64 of 512..4096 120.7 / 113.1; drafts of 3 on 64 files of
+// 500..900 52.3 / 46.3.  Eight wavefronts in 150 KiB of LDS, one workgroup per compute unit: with two of four a cut divides twice as
+// many ranges (drafts 133, short drafts 55.5 against 53.5).
+constexpr int kMxRow = 132;                                    // floats per query column of a piece in LDS: 128 dims, max, sum, 2 spare
+constexpr int kMxSlot = 16 * kMxRow * 4;                       // a piece: 16 columns
+constexpr int kMxWave = kVtLds + kMxSlot;                      // LDS of a wavefront: its V buffer, where its last piece goes when it is done, and its first piece
+static_assert(kMxSlot <= kVtLds, "the last piece takes the V buffer's place");
+
+template <int GT, bool BINS, bool STREAM>
+__device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const int block, const int W, uint8_t* lds) {
   const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(block * kWavesPerBlock + (int)(threadIdx.x >> 6));
-  if (wv >= a.n_waves) return;
+  const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wv = block * W + wib;
+  if (BINS ? block >= a.n_bins : wv >= a.n_waves) return;        // (bins: the whole workgroup)
+  uint8_t* const vlds = lds + wib * (BINS ? kMxWave : kVtLds);
   const int col = lane & 15, grp = lane >> 4;        // query column, lane group (tokens 4*grp .. 4*grp+3 of a page)
   const int head = col % GT;                          // columns past nt * GT repeat earlier ones; their results are ignored
   const int vq4 = lane >> 4, vc = lane & 15;          // V staging role: tokens 4*vq4 .. +3 of a page, dim chunk vc
@@ -1694,35 +1709,68 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
   // cursor through the same sequence of (row, kv head) ranges, in steps of a pair of pages (a pair never
   // straddles two ranges: the last pair of a range with an odd number of pages has one page), so the
   // K/V loads of the next range are in flight while the current one is finished and written out.
-  const int32_t* ww = a.waves + wv * 8;
-  // compute cursor: the range being accumulated
-  int row = sload(ww + 0), g = sload(ww + 1), p = sload(ww + 2);
-  int remaining = sload(ww + 3);
-  int part = sload(ww + 4);
-  const int tbl0 = sload(a.rows + row * 4 + 0);
-  int vis = sload(a.rows + row * 4 + 1), qrow = sload(a.rows + row * 4 + 2);
-  int pstart = sload(a.rows + row * 4 + 3);
-  int nt = (pstart >> 28) + 1;                        // new tokens in the row
-  pstart &= 0x0fffffff;
-  int np = (vis + nt - 1 + kP - 1) / kP;              // pages the row's last token sees
+  const BinStart st = BINS ? bin_start(a, block, W, wib) : BinStart{};
+  const int32_t* ww = a.waves + (int64_t)wv * 8;
+  // compute cursor: the range (bins: segment, number `row`) being accumulated: pages [pstart, np), tokens its first token sees,
+  // q row * Hq + first head, new tokens
+  int row = BINS ? st.seg : sload(ww + 0), g = BINS ? 0 : sload(ww + 1), p = BINS ? st.p : sload(ww + 2);
+  int remaining = BINS ? st.units : sload(ww + 3);
+  int part = BINS ? 0 : sload(ww + 4);                // global cut: the next partial; bins: the segment's destination
+  int m_g = 0, m_qh = 0, m_dest = 0;                  // of the segment whose pieces it merges at the end
+  auto merge_record = [&]() __attribute__((always_inline)) {
+    const int32_t* msr = a.segs + (int64_t)(st.merges ? st.m_seg : 0) * 8;
+    m_g = sload(msr + 1);
+    m_qh = sload(msr + 5);
+    m_dest = sload(msr + 6);
+  };
+  if constexpr (BINS) merge_record();
+  if (!BINS || remaining > 0) {
+  const int32_t* sr = a.segs + (int64_t)row * 8;
+  const int tbl0 = BINS ? sload(sr + 0) : sload(a.rows + row * 4 + 0);
+  int vis = BINS ? sload(sr + 4) : sload(a.rows + row * 4 + 1);
+  int qh = BINS ? sload(sr + 5) : sload(a.rows + row * 4 + 2) * a.Hq + g * GT;
+  const int ps0 = BINS ? sload(sr + 1) : sload(a.rows + row * 4 + 3);      // (tokens - 1) << 28 | kv head (bins) or first page
+  int pstart = BINS ? sload(sr + 2) : ps0 & 0x0fffffff;
+  int nt = (ps0 >> 28) + 1;                           // new tokens in the row
+  int np = BINS ? sload(sr + 3) : (vis + nt - 1 + kP - 1) / kP;              // bins: the segment's end; else the pages the row's last token sees
+  if constexpr (BINS) part = sload(sr + 6);
   // load cursor: the pair whose K/V is requested next
-  int lg = g, lrow = row, lp = p, lnp = np, ltbl = tbl0, lpstart = pstart, lrem = remaining;
-  int id0 = sload(ww + 5), id1 = sload(ww + 6);       // page ids of that pair (the first pair's come with the wave record)
-  // record of the row after the load cursor's, fetched a whole row ahead (one past the last row: valid words, never used)
-  int n_tbl = 0, n_np = 0, n_pstart = 0;
+  int lg = BINS ? ps0 & 0x0fffffff : g, lrow = row, lp = p, lnp = np, ltbl = tbl0, lpstart = pstart, lrem = remaining;
+  // page ids of that pair (the first pair's come with the wave record; a pair of one page: the second is not used)
+  int id0 = BINS ? st.id0 : sload(ww + 5), id1 = BINS ? st.id1 : sload(ww + 6);
+  // record of the row (bins: segment) after the load cursor's, fetched a whole row ahead (one past the last row: valid words, never used)
+  int n_tbl = 0, n_np = 0, n_pstart = 0, n_g = 0;
   auto fetch_next_row = [&](int rr) __attribute__((always_inline)) {
-    n_tbl = sload(a.rows + rr * 4 + 0);
-    const int v = sload(a.rows + rr * 4 + 1), ps = sload(a.rows + rr * 4 + 3);
-    n_pstart = ps & 0x0fffffff;
-    n_np = (v + (ps >> 28) + kP - 1) / kP;
+    if constexpr (BINS) {
+      const int32_t* q4 = a.segs + (int64_t)rr * 8;
+      n_tbl = sload(q4 + 0);
+      n_g = sload(q4 + 1) & 0x0fffffff;
+      n_pstart = sload(q4 + 2);
+      n_np = sload(q4 + 3);
+    } else {
+      n_tbl = sload(a.rows + rr * 4 + 0);
+      const int v = sload(a.rows + rr * 4 + 1), ps = sload(a.rows + rr * 4 + 3);
+      n_pstart = ps & 0x0fffffff;
+      n_np = (v + (ps >> 28) + kP - 1) / kP;
+    }
   };
   fetch_next_row(row + 1);
   // record of row + 1 as the compute side needs it
-  int c_nvis = 0, c_nqrow = 0, c_nps = 0;
+  int c_nvis = 0, c_nqrow = 0, c_nps = 0, c_pb = 0, c_pe = 0, c_dest = 0;
   auto fetch_compute_next_row = [&]() __attribute__((always_inline)) {
-    c_nvis = sload(a.rows + (row + 1) * 4 + 1);
-    c_nqrow = sload(a.rows + (row + 1) * 4 + 2);
-    c_nps = sload(a.rows + (row + 1) * 4 + 3);
+    if constexpr (BINS) {
+      const int32_t* q8 = a.segs + (int64_t)(row + 1) * 8;
+      c_nps = sload(q8 + 1);
+      c_pb = sload(q8 + 2);
+      c_pe = sload(q8 + 3);
+      c_nvis = sload(q8 + 4);
+      c_nqrow = sload(q8 + 5);
+      c_dest = sload(q8 + 6);
+    } else {
+      c_nvis = sload(a.rows + (row + 1) * 4 + 1);
+      c_nqrow = sload(a.rows + (row + 1) * 4 + 2);
+      c_nps = sload(a.rows + (row + 1) * 4 + 3);
+    }
   };
   fetch_compute_next_row();
 
@@ -1733,11 +1781,9 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
   auto load_page = [&](uint4 (&kk)[4], uint4 (&vv)[4], const uint8_t* slab, int pid) __attribute__((always_inline)) {
     const uint8_t* base = slab + (int64_t)pid * a.page_bytes;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      kk[ks] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + k_off + (ks >> 1) * (kP * kHalfBytes) + (ks & 1) * 64)));
+    for (int ks = 0; ks < 4; ++ks) kk[ks] = ld16<STREAM>(base + k_off + (ks >> 1) * (kP * kHalfBytes) + (ks & 1) * 64);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      vv[u] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_t*)(base + v_off + u * kHalfBytes)));
+    for (int u = 0; u < 4; ++u) vv[u] = ld16<STREAM>(base + v_off + u * kHalfBytes);
   };
   // Requests the next pair and moves the load cursor; every load is unconditional (a page that does not
   // exist, also past the end of the wavefront's work, is page 0 of the pool and is never used).
@@ -1749,9 +1795,9 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
     if (take > 0) {
       lrem -= take;
       lp += take;
-      if (lp == lnp) {                                 // the range after: next head of the row, or the next row
-        if (++lg == a.Hkv) {
-          lg = 0;
+      if (lp == lnp) {                                 // the range after: next head of the row, or the next row; bins: the next segment
+        if (BINS || ++lg == a.Hkv) {
+          lg = BINS ? n_g : 0;
           ++lrow;
           ltbl = n_tbl;
           lnp = n_np;
@@ -1771,7 +1817,7 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
   bf16x8_t q[4];                                      // Q^T operand: this lane's (token, head), dims 32*ks + 8*grp .. +8
   auto load_q = [&]() __attribute__((always_inline)) {
     tok = min(col / GT, nt - 1);
-    const uint8_t* qp = (const uint8_t*)a.q + ((int64_t)(qrow + tok) * a.Hq + g * GT + head) * kRowBytes + grp * 16;
+    const uint8_t* qp = (const uint8_t*)a.q + ((int64_t)qh + tok * a.Hq + head) * kRowBytes + grp * 16;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) q[ks] = __builtin_bit_cast(bf16x8_t, *(const uint4*)(qp + ks * 64));
   };
@@ -1786,6 +1832,7 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
   reset_state();
   load_q();
   int p_first = p;                                    // first page of the piece being accumulated
+  int piece = 0;                                      // pieces this wavefront has finished
 
   // scores of one page: 4 tokens (4*grp + v) x this lane's head; tokens past nvalid masked
   auto scores = [&](const uint4 (&kk)[4], int nvalid, float (&sc)[4]) __attribute__((always_inline)) {
@@ -1863,29 +1910,44 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
   // End of a piece: the four lane groups of a head add up their sums, O^T is complete; the compute cursor
   // moves to the next range first, so that its query rows are on their way while this piece is written.
   auto finish_piece = [&]() __attribute__((always_inline)) {
-    const bool whole = (p_first == 0 && p == np);
-    const int64_t o_row = (int64_t)(qrow + tok) * a.Hq + g * GT + head;
+    const bool whole = p_first == (BINS ? pstart : 0) && p == np;
+    const int64_t o_row = (int64_t)qh + tok * a.Hq + head;
     const int64_t o_slot = (int64_t)(part + tok) * GT + head;     // a piece leaves one partial per token of the row
     const bool o_live = col < nt * GT;
-    if (!whole) part += nt;
+    const bool o_final = BINS ? part < 0 : true;                   // what a whole piece writes: the output, or (bins) a partial
+    if (!BINS && !whole) part += nt;
     const bool more = remaining > 0;
     if (more) {
-      if (++g == a.Hkv) {
+      if (BINS || ++g == a.Hkv) {
         g = 0;
         ++row;
         vis = c_nvis;
-        qrow = c_nqrow;
         nt = (c_nps >> 28) + 1;
-        pstart = c_nps & 0x0fffffff;
-        np = (vis + nt - 1 + kP - 1) / kP;
+        if constexpr (BINS) {
+          qh = c_nqrow;
+          pstart = c_pb;
+          np = c_pe;
+          part = c_dest;
+        } else {
+          qh = c_nqrow * a.Hq;
+          pstart = c_nps & 0x0fffffff;
+          np = (vis + nt - 1 + kP - 1) / kP;
+        }
         fetch_compute_next_row();
+      } else {
+        qh += GT;
       }
       load_q();
     }
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
     if (o_live) {
-      if (whole) {
+      if (BINS && !whole) {
+        float* o = (float*)(piece == 0 ? vlds + kVtLds : vlds) + col * kMxRow + 4 * grp;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) *(float4*)(o + db * 16) = make_float4(O[db][0], O[db][1], O[db][2], O[db][3]);
+        if (grp == 0) *(float2*)(o + 128) = make_float2(m, l);
+      } else if (whole && o_final) {
         const float inv = 1.0f / l;
         float* o = a.out + o_row * 128 + 4 * grp;
 #pragma unroll
@@ -1900,6 +1962,7 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
         }
       }
     }
+    ++piece;
     if (more) {
       p = pstart;
       p_first = p;
@@ -1925,12 +1988,56 @@ __device__ __forceinline__ void decode_mfma_ranges(const DecodeArgs& a, const in
     if (remaining > 0) do_pair(kC, vC, kD, vD);
     load_next_pair(kC, vC, kD, vD);
   }
+  }
+  if constexpr (!BINS) return;
+  __syncthreads();                                       // every piece of the bin is in LDS (or went straight to its destination)
+  if (!st.merges) return;
+  // four columns at a time: lane group `grp` has one, its lanes dims 4 (lane % 16) .. +3 and the same plus 64
+  const int m_cols = ((m_g >> 28) + 1) * GT, d0 = 4 * (lane & 15);
+#pragma unroll
+  for (int c0 = 0; c0 < 16; c0 += 4) {
+    const int c = c0 + grp;
+    if (c >= m_cols) continue;
+    float M = -__builtin_inff(), ls = 0.f;
+    f32x4_t x = {0.f, 0.f, 0.f, 0.f}, y = x;
+    for (int i = 0; i < st.m_pieces; ++i) {
+      const int slot = i == 0 ? st.m_slot : 2 * (st.m_wave + i);
+      const float* pc = (const float*)(lds + (slot >> 1) * kMxWave + (slot & 1 ? 0 : kVtLds)) + c * kMxRow;
+      const float mi = pc[128], li = pc[129], mn = fmaxf(M, mi);
+      const float sc = __builtin_amdgcn_exp2f(M - mn), wt = __builtin_amdgcn_exp2f(mi - mn);      // sc: 0 for the first piece
+      ls = ls * sc + li * wt;
+      M = mn;
+      x = x * sc + *(const f32x4_t*)(pc + d0) * wt;
+      y = y * sc + *(const f32x4_t*)(pc + d0 + 64) * wt;
+    }
+    const int t = c / GT, h = c % GT;
+    if (m_dest < 0) {
+      const float inv = 1.0f / ls;
+      float* o = a.out + ((int64_t)m_qh + t * a.Hq + h) * 128 + d0;
+      *(f32x4_t*)o = x * inv;
+      *(f32x4_t*)(o + 64) = y * inv;
+    } else {
+      const int64_t o_slot = (int64_t)(m_dest + t) * GT + h;
+      float* o = a.part_acc + o_slot * 128 + d0;
+      *(f32x4_t*)o = x;
+      *(f32x4_t*)(o + 64) = y;
+      if ((lane & 15) == 0) {
+        a.part_ml[o_slot * 2 + 0] = M;
+        a.part_ml[o_slot * 2 + 1] = ls;
+      }
+    }
+  }
 }
 
 template <int GT>
 __global__ __launch_bounds__(256, 2) void decode_mfma_kernel(DecodeArgs da) {
-  __shared__ __align__(16) uint8_t vlds[kWavesPerBlock][kVtLds];
-  decode_mfma_ranges<GT>(da, blockIdx.x, vlds[threadIdx.x >> 6]);
+  __shared__ __align__(16) uint8_t vlds[kWavesPerBlock * kVtLds];
+  decode_mfma_ranges<GT, false, true>(da, blockIdx.x, kWavesPerBlock, vlds);
+}
+template <int GT, int W, bool STREAM>
+__global__ __launch_bounds__(64 * W, 8 / W) void decode_mfma_bins_kernel(DecodeArgs da) {
+  __shared__ __align__(16) uint8_t lds[W * kMxWave];
+  decode_mfma_ranges<GT, true, STREAM>(da, blockIdx.x, W, lds);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2615,6 +2722,7 @@ hipError_t launch_attn_g(const DecodeArgs& da, const PrefillArgs& pa, int decode
   if (tile_groups > 0 && decode_groups > 0 && (!ps.group_map || ps.n_groups != tile_groups + decode_groups)) return hipErrorInvalidValue;
   if (decode_groups == 0) ps.group_map = nullptr;
   if (ps.n_tiles > 0 && ps.tile_rows != 128 && ps.tile_rows != 256) return hipErrorInvalidValue;
+  if (mode == 2 && da.n_bins > 0) return hipErrorInvalidValue;      // no kernel
   const bool second = da.n_waves > 0 && mode != 0;          // decode ranges in a launch of their own
   const hipEvent_t e_first = second ? nullptr : ev1;
   const hipEvent_t s_second = grid.x > 0 ? nullptr : ev0;
@@ -2645,7 +2753,21 @@ hipError_t launch_attn_g(const DecodeArgs& da, const PrefillArgs& pa, int decode
   }
 #undef SYM_ATTN_CASE
   if (da.n_waves > 0 && mode == 2) launch(decode_pair_kernel<E>, dim3(da.n_waves), dim3(128), s_second, ev1, da);
-  if (da.n_waves > 0 && mode == 1) {
+  if (da.n_bins > 0 && mode == 1) {
+    if (da.bin_waves != 4 && da.bin_waves != 8) return hipErrorInvalidValue;
+    const dim3 dgrid(da.n_bins), dblock(64 * da.bin_waves);
+#define SYM_DECODE_CASE(GG) \
+  case GG: \
+    if (da.bin_waves == 8) launch(decode_mfma_bins_kernel<GG, 8, true>, dgrid, dblock, s_second, ev1, da); \
+    else if (da.cached) launch(decode_mfma_bins_kernel<GG, 4, false>, dgrid, dblock, s_second, ev1, da); \
+    else launch(decode_mfma_bins_kernel<GG, 4, true>, dgrid, dblock, s_second, ev1, da); \
+    break;
+    switch (G) {
+      SYM_DECODE_CASE(1) SYM_DECODE_CASE(2) SYM_DECODE_CASE(4) SYM_DECODE_CASE(8)
+      default: return hipErrorInvalidValue;
+    }
+#undef SYM_DECODE_CASE
+  } else if (da.n_waves > 0 && mode == 1) {
     const dim3 dgrid((da.n_waves + kWavesPerBlock - 1) / kWavesPerBlock);
     switch (G) {
       case 1: launch(decode_mfma_kernel<1>, dgrid, block, s_second, ev1, da); break;

@@ -366,6 +366,25 @@ def test_small_decode_batches(Hq, Hkv, D, dtype):
         sess.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv,new", [(64, 8, 1), (8, 1, 1), (64, 8, 2), (32, 8, 4), (32, 8, 7), (8, 4, 3), (8, 8, 2)])
+def test_matrix_core_decode_bins(Hq, Hkv, new):
+    """Rows of 8 heads per kv head and rows of several draft tokens, in bins: fewer pages than wavefronts, odd page counts, whole
+    ranges of 24 pages and cut ones of 25 and more, ranges that wavefronts and bins divide, many short ranges, single tokens beside
+    drafts.  Against the oracle at the bar of the matrix-core kernels; the global cut (the caller's wavefront slots) too.  The two are
+    not compared with each other: a weight is cut to 11 bits at its size relative to its piece's maximum (relative error below 2^-10,
+    of which the mean cancels in the division by the sum), and their pieces differ."""
+    shape = synth.Shape(Hq, Hkv, 128, 16, synth.BF16)
+    for lens in ([0], [5, 16, 30], [383], [400], [2000, 33], [640] * 12, [60] * 80, [1500, 200, 90, 3000] * 6):
+        wl = synth.custom("mx_bins", shape, [("new", n) for n in lens], [(i, new if i % 3 == 0 else 1) for i in range(len(lens))], 2600, seed=len(lens))
+        got, sess, ref, osess = run_both(wl)
+        check_outputs(got, ref)
+        check_state(wl, sess, osess)
+        sess.close()
+        cut, sess = _hip().run_workload(wl, poison=True, decode_waves=512)
+        check_outputs(cut, ref)
+        sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 4), (8, 2), (8, 1), (1, 1)])
 def test_fp32_row_tiles(Hq, Hkv):
     """Several new tokens per LIP in fp32 storage (row tiles: 32 / G tokens x one kv head, every eighth page per

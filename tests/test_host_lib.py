@@ -619,6 +619,46 @@ def _plain_desc(c, lengths):
     return c.build_desc([1] * len(lengths), np.arange(sum(np_l), dtype=np.int32) % (1 << 20), off, lengths)
 
 
+@pytest.mark.parametrize("Hkv,G,lengths,n_tok", [
+    (8, 8, [16], [1]), (8, 8, [384], [1]), (8, 8, [385], [1]), (8, 8, [9000, 40], [1, 1]), (8, 8, [100] * 100, [1] * 100), (8, 8, [3000, 17, 900] * 20, [1, 2, 1] * 20),
+    (8, 4, [400], [4]), (8, 4, [33, 2000, 515], [8, 3, 1]), (8, 4, [2500, 1000, 64] * 20, [4, 1, 7] * 20), (2, 1, [1000] * 300, [5] * 300), (1, 2, [5], [5])])
+def test_descriptor_bins_of_the_matrix_core_kernel(Hkv, G, lengths, n_tok):
+    """Rows of 8 heads per kv head or of several draft tokens in a batch without tiles: bins.  Segments tile the pages of every
+    (row, head), each page is covered once, a divided range leaves a partial per part and token, numbered as its merge entries
+    say.  With the wavefront slots set by the caller: the global cut."""
+    Hq = Hkv * G
+    np_l = [-(-n // 16) for n in lengths]
+    off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+    flat = np.arange(sum(np_l), dtype=np.int32) % (1 << 15)
+    w = host_ctx(1 << 15, Hq=Hq, Hkv=Hkv).build_desc(n_tok, flat, off, lengths)
+    assert int(w[4]) == 0 and int(w[34]) > 0
+    rows = w[w[5]:w[5] + 4 * w[0]].reshape(-1, 4)
+    nts = (rows[:, 3] >> 28) + 1
+    pages = -(-(rows[:, 1] + nts - 1) // 16)
+    segs, cover, seg_bin, loads, n_bins, W = _walk_bins(w)
+    assert W in (4, 8) and len(cover) == int(pages.sum()) * Hkv
+    items = {int(m[2]): m for m in w[w[7]:w[7] + 8 * w[14]].reshape(-1, 8)}
+    by_range, parts = {}, []
+    for tbl, hd, pb, pe, vis, qh, dest, app in segs.tolist():
+        by_range.setdefault(qh, []).append((pb, pe, dest, hd, vis, tbl, app))
+    assert len(by_range) == len(rows) * Hkv
+    for r, row in enumerate(rows.tolist()):
+        for g in range(Hkv):
+            key = row[2] * Hq + g * G
+            ps = sorted(by_range[key])
+            assert ps[0][0] == 0 and ps[-1][1] == pages[r] and all(a[1] == b[0] for a, b in zip(ps, ps[1:]))
+            assert all(p[3:] == (g | (int(nts[r]) - 1) << 28, row[1], row[0], -1) for p in ps)
+            for t in range(nts[r]):
+                if len(ps) == 1:
+                    assert ps[0][2] == -1 and key + t * Hq not in items
+                else:
+                    m = items.pop(key + t * Hq)
+                    assert [p[2] + t for p in ps] == [int(m[0]) + i * int(m[6]) for i in range(int(m[1]))] and int(m[6]) == nts[r]
+                    parts += [p[2] + t for p in ps]
+    assert not items and sorted(parts) == list(range(int(w[2])))
+    assert int(host_ctx(1 << 15, Hq=Hq, Hkv=Hkv, decode_waves=256).build_desc(n_tok, flat, off, lengths)[34]) == 0
+
+
 @pytest.mark.parametrize("lengths,n_tok", [([16], [16]), ([17], [16]), ([40, 300], [40, 64]), ([6000], [100]), ([1300] * 6, [1] * 6), ([900, 1300, 1300, 1300, 1300], [300, 1, 1, 1, 1])])
 def test_tile_records_name_the_pages_of_the_first_block(lengths, n_tok):
     """Whole tiles, key chunks and shared prefixes: words 10 and 11 are the ids of the first two pages a tile walks, the last
