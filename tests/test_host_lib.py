@@ -659,6 +659,37 @@ def test_descriptor_bins_of_the_matrix_core_kernel(Hkv, G, lengths, n_tok):
     assert int(host_ctx(1 << 15, Hq=Hq, Hkv=Hkv, decode_waves=256).build_desc(n_tok, flat, off, lengths)[34]) == 0
 
 
+@pytest.mark.parametrize("Hkv,G,n_tok,len0", [(8, 1, [300, 100], 0), (8, 1, [491, 150, 440, 478], 0), (8, 4, [400, 90, 333], 70), (1, 4, [2000], 0), (2, 8, [100] * 30, 5), (8, 1, [600] * 6, 0), (8, 2, [700, 20], 20000)])
+def test_descriptor_order_of_row_tiles(Hkv, G, n_tok, len0):
+    """More row tiles than compute units (256): longest piece first, heads of a piece together; up to twice as many, those past the
+    first 256 shortest first.  No piece is lost and none comes twice."""
+    c = host_ctx(1 << 15, Hq=Hkv * G, Hkv=Hkv, D=64, dtype="f32")
+    lengths = [n + len0 for n in n_tok]
+    np_l = [-(-n // 16) for n in lengths]
+    off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+    w = c.build_desc(n_tok, np.arange(sum(np_l), dtype=np.int32) % (1 << 15), off, lengths)
+    n = int(w[39])
+    rt = w[w[40]:w[40] + 8 * n].reshape(-1, Hkv, 8)
+    assert n and (rt[:, :, 4] == np.arange(Hkv)).all() and (np.delete(rt, [4, 7], 2) == np.delete(rt, [4, 7], 2)[:, :1]).all()
+    pages = (rt[:, 0, 6] - rt[:, 0, 5]).tolist()
+    if n > 256:
+        alone = len(pages) if n > 512 else 256 // Hkv
+        assert pages[:alone] == sorted(pages, reverse=True)[:alone] and pages[alone:] == sorted(pages[alone:])
+    cover = set()
+    for tbl, vis, qrow, count, head, pb, pe, dest in rt[:, 0].tolist():
+        for t in range(count):
+            for p in range(pb, pe):
+                assert (qrow + t, p) not in cover
+                cover.add((qrow + t, p))
+    last = {}
+    for row, p in cover:
+        last[row] = max(last.get(row, -1), p)
+    q0 = 0
+    for nt, L in zip(n_tok, lengths):
+        assert all(last[q0 + t] >= (L - nt + t) // 16 for t in range(nt))
+        q0 += nt
+
+
 @pytest.mark.parametrize("lengths,n_tok", [([16], [16]), ([17], [16]), ([40, 300], [40, 64]), ([6000], [100]), ([1300] * 6, [1] * 6), ([900, 1300, 1300, 1300, 1300], [300, 1, 1, 1, 1])])
 def test_tile_records_name_the_pages_of_the_first_block(lengths, n_tok):
     """Whole tiles, key chunks and shared prefixes: words 10 and 11 are the ids of the first two pages a tile walks, the last
