@@ -151,6 +151,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   // of the row; the rest is split between the prefix partials of sharing groups and the
   // members' own ranges (one partial per (member, head), never more than the former).
   const int64_t shared_budget = std::max<int64_t>(0, ((int64_t)prm.max_partials - 2 * (int64_t)RT * prm.max_waves) / 2);
+  int64_t one_round = 0;                                    // workgroups that tiles and bins together may have (0: no matter)
   const int32_t tile_lips = TQ;                             // members of a shared-prefix tile (rows = members x G)
   if (prm.share_min_lips > 0 && tile_lips > 0) {
     auto& cand = out->by_first_page;
@@ -222,7 +223,32 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       lo = hi;
     }
     if (!groups.empty()) {
-      const int64_t target = std::max(1, prm.share_tiles);    // default 512: about two workgroups per CU
+      int64_t target = std::max(1, prm.share_tiles);          // default 512: about two workgroups per CU
+      // Tiles and the bins of the members' own pages (workgroups of four, two per compute unit) in one round, where whole chunks
+      // leave neither of them more than 15 % above its share: a second round starts with a memory latency of its own.  512 tiles
+      // and 512 bins / in one round: 16 roots x 16 members, 2048 tokens shared and up to 256 own, 80.0 / 70.0 us (1 head per kv head
+      // 67.8 / 61.0); 8 x 24 on 1000 51.4 / 44.5; 9 x 24 on 2200 79.9 / 61.7; 10 x 20 on 4000 89.3 / 74.0.  At 25..31 % of imbalance, 16 query
+      // heads, 4 to 7 % slower.
+      int64_t tile_units = 0, own_units = 0;
+      for (size_t gi = 0; gi < groups.size(); gi += 3) {
+        tile_units += (int64_t)((groups[gi + 1] + tile_lips - 1) / tile_lips) * groups[gi + 2] * H;
+        own_units -= (int64_t)groups[gi + 1] * groups[gi + 2] * H;
+      }
+      bool prompts = false;
+      for (int32_t b = 0; b < n_lips; ++b) {
+        prompts |= is_prefill(b);
+        own_units += (len_after[b] + P - 1) / P * H;
+      }
+      const int64_t round = 2 * (int64_t)prm.cus, bins_then = std::min<int64_t>(own_units / (4 * (int64_t)prm.min_units_per_wave) + 1, prm.max_waves / 4);
+      if (prm.spread_small && prm.bin_waves > 0 && max_nt == 1 && !prompts && own_units > 0 &&
+          (target + base_tiles - 1) / base_tiles * base_tiles + bins_then > round) {
+        const int64_t tiles = std::max<int64_t>(1, (round * tile_units / (tile_units + own_units) + base_tiles / 2) / base_tiles) * base_tiles;
+        const int64_t most = (tile_units + own_units) * 115 / 100;      // x 1 / round
+        if (tiles < round && tile_units * round <= most * tiles && own_units * round <= most * (round - tiles)) {
+          target = std::min(target, tiles);
+          one_round = round;
+        }
+      }
       int32_t nc_want = (int32_t)std::max<int64_t>(1, std::min<int64_t>(8, (target + base_tiles - 1) / base_tiles));
       // every member leaves one partial per kv head and key chunk: the same number of chunks for all groups
       // that the partial slots can hold (not the wanted number for the first groups and none for the last)
@@ -353,7 +379,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   const bool whole_wide = small_decode && prm.bin_waves == 8 && n_rows * H <= prm.cus && longest_range > kWholePages && longest_range <= kWholePagesWide;
   const bool whole_small = whole_wide || (small_decode && n_rows * H <= prm.cus && longest_range <= kWholePages);
   const int32_t W = !bins ? 0 : n_tiles > 0 ? (TQ * G != 256 ? 4 : 8) : (prm.bin_waves == 4 || (small_decode && !whole_wide) ? 4 : 8);
-  const int64_t max_bins = std::max<int64_t>(1, prm.max_waves / std::max(W, 1));
+  const int64_t max_bins = std::max<int64_t>(1, std::min<int64_t>(prm.max_waves / std::max(W, 1), one_round > 0 && W == 4 ? one_round - n_tiles : prm.max_waves));
   int64_t nw = (total_units + prm.min_units_per_wave - 1) / prm.min_units_per_wave;
   nw = std::max<int64_t>(1, std::min<int64_t>(nw, prm.max_waves));
   if (total_units == 0) nw = 0;

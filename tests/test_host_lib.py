@@ -659,6 +659,30 @@ def test_descriptor_bins_of_the_matrix_core_kernel(Hkv, G, lengths, n_tok):
     assert int(host_ctx(1 << 15, Hq=Hq, Hkv=Hkv, decode_waves=256).build_desc(n_tok, flat, off, lengths)[34]) == 0
 
 
+@pytest.mark.parametrize("roots,children,shared,own,one_round", [(16, 16, 128, 9, True), (8, 24, 62, 3, True), (16, 16, 128, 60, False), (16, 16, 40, 1, True), (2, 8, 128, 9, False)])
+def test_descriptor_forks_in_one_round(roots, children, shared, own, one_round):
+    """Shared-prefix tiles and the bins of the members' own pages: together as many workgroups as start at once (two per compute unit of
+    256) where their work divides so, else by their own rules; the tiles of every (group, head) cover the shared pages once."""
+    c = host_ctx(1 << 17)
+    n, ids = roots * children, iter(range(1 << 17))
+    prefix = [[next(ids) for _ in range(shared)] for _ in range(roots)]
+    tables = [prefix[b // children] + [next(ids) for _ in range(own)] for b in range(n)]
+    off = np.arange(n + 1, dtype=np.int64) * (shared + own)
+    w = c.build_desc([1] * n, np.concatenate(tables).astype(np.int32), off, [(shared + own) * 16] * n)
+    n_tiles, n_bins = int(w[4]), int(w[34])
+    assert n_tiles == int(w[17]) > 0 and int(w[35]) == 4
+    assert (n_tiles + n_bins <= 512 and n_tiles + n_bins > 400) == one_round, (n_tiles, n_bins)
+    spans = {}
+    for t in w[w[10]:w[10] + 12 * n_tiles].reshape(-1, 12).tolist():
+        spans.setdefault((t[0], t[4]), []).append((t[7], t[8]))
+    for sp in spans.values():
+        sp.sort()
+        assert sp[0][0] == 0 and sp[-1][1] == shared // 2 * 2 and all(x[1] == y[0] for x, y in zip(sp, sp[1:]))
+    assert len(spans) == roots * 8
+    _, cover, _, loads, _, _ = _walk_bins(w)
+    assert len(cover) == sum(loads) == n * 8 * (shared + own - shared // 2 * 2)
+
+
 @pytest.mark.parametrize("Hkv,G,n_tok,len0", [(8, 1, [300, 100], 0), (8, 1, [491, 150, 440, 478], 0), (8, 4, [400, 90, 333], 70), (1, 4, [2000], 0), (2, 8, [100] * 30, 5), (8, 1, [600] * 6, 0), (8, 2, [700, 20], 20000)])
 def test_descriptor_order_of_row_tiles(Hkv, G, n_tok, len0):
     """More row tiles than compute units (256): longest piece first, heads of a piece together; up to twice as many, those past the
