@@ -394,7 +394,9 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     int64_t upw = prm.min_units_per_wave;
     if (small_decode && longest_range > kWholePagesWide)
       upw = std::min(upw, std::max<int64_t>(longest_range <= 16 * W && !mfma_bins ? 1 : 2, (total_units + prm.cus * 4 - 1) / (prm.cus * 4)));
-    n_bins = (total_units + upw * W - 1) / (upw * W);
+    // No more wavefronts than the batch's cost has steps: the starts of the cut (plan B) are then apart, and no wavefront without a
+    // page begins inside a range.  (With the default settings a wavefront's share never falls below one.)
+    n_bins = std::min((total_units + upw * W - 1) / (upw * W), (total_units + (int64_t)prm.range_cost * n_rows * H) / W);
     n_bins = std::max<int64_t>(1, std::min<int64_t>(n_bins, max_bins));
     if (whole_small) n_bins = n_rows * H;
     nw = n_bins * W;

@@ -990,6 +990,23 @@ def test_every_planner_setting_gives_the_oracles_outputs(with_chunk):
         print(f"  worst scaled error {worst:.2e}")
 
 
+@pytest.mark.parametrize("Hq,Hkv,files,new", [
+    (4, 1, [("new", 512)], [1]), (4, 1, [("new", 528)], [1]), (8, 1, [("new", 16392)], [1]), (4, 2, [("new", 83), ("new", 998)], [1, 1]),
+    (32, 8, [("new", n) for n in (600, 31, 1500, 257, 2200, 64)], [4, 1, 3, 1, 2, 7]),
+    (32, 8, [("new", 512)] * 8 + [("fork", r, 47 + i) for r in range(8) for i in range(8)], [0] * 8 + [1] * 64)])
+def test_every_planner_setting_with_the_chips_own_wavefront_slots(Hq, Hkv, files, new):
+    """As above on the plans that a batch gets when the caller leaves the wavefront slots to the library: few pages per wavefront
+    (small batches of long files), drafts in bins, forks whose tiles and bins are one round of workgroups."""
+    wl = synth.custom(f"slots_{Hq}_{Hkv}_{len(files)}", synth.Shape(Hq, Hkv, 128, 16, synth.BF16), files, [(f, n) for f, n in enumerate(new) if n], 2048, seed=Hq + len(files))
+    ref, osess = run_oracle(wl, dtype=np.float64)
+    for tuning in [None] + _SETTINGS + [{"range_cost": 0}, {"range_cost": 1}, {"min_units": 1}, {"share_tiles": 64}, {"share_tiles": 1024}]:
+        print(f"[case] {wl.name} tuning={tuning}", flush=True)
+        got, sess = _hip().run_workload(wl, poison=True, tuning=tuning)
+        check_outputs(got, ref)
+        check_state(wl, sess, osess)
+        sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,dtype,multi", [(32, 8, 128, synth.BF16, 1), (32, 8, 128, synth.BF16, 3), (8, 8, 64, synth.F32, 3),
                                                   (64, 8, 128, synth.BF16, 1), (16, 8, 128, synth.BF16, 1)])
 def test_layered_pred_layer_by_layer_against_the_oracle(Hq, Hkv, D, dtype, multi):

@@ -592,6 +592,48 @@ def test_descriptor_bins_cover_every_unit_once_and_are_balanced(lengths, n_tok, 
         assert [seg_bin[i] for i in range(len(segs))] == sorted(seg_bin[i] for i in range(len(segs)))   # contiguous shares
 
 
+def _check_bin_lists(words):
+    """What the kernels take for granted of a bin: the wavefronts' units are the pages between their starts, and the pieces of a
+    divided segment, n of them from the listed wavefront on, each hold a page (each writes the LDS slot that is read for it)."""
+    hdr = words[:48]
+    n_segs, n_bins, W = int(hdr[32]), int(hdr[34]), int(hdr[35])
+    segs = words[hdr[33]:hdr[33] + 8 * (n_segs + 1)].reshape(-1, 8)
+    waves = words[hdr[6]:hdr[6] + 8 * n_bins * W].reshape(n_bins, W, 8)
+    lm = words[hdr[36]:hdr[36] + 32 * n_bins].reshape(n_bins, 32)
+    pages = (segs[:n_segs, 3] - segs[:n_segs, 2]).astype(np.int64)
+    before = np.concatenate([[0], np.cumsum(pages)])
+    start = before[waves[:, :, 0]] + waves[:, :, 1] - segs[waves[:, :, 0], 2]
+    live = waves[:, :, 2] > 0
+    at, n = start[live], waves[:, :, 2][live]
+    order = np.argsort(at)
+    assert (np.concatenate([[0], np.cumsum(n[order])])[:-1] == at[order]).all() and int(n.sum()) == before[-1]
+    inside = live & (waves[:, :, 1] > segs[waves[:, :, 0], 2])       # wavefronts that continue a segment
+    assert int(inside.sum()) == int(sum(lm[b, 7:4 + 4 * lm[b, 0]:4].sum() - lm[b, 0] for b in range(n_bins)))
+    for b in np.flatnonzero(lm[:, 0]):
+        assert lm[b, 0] < W
+        for seg, slot, w, cnt in lm[b, 4:4 + 4 * lm[b, 0]].reshape(-1, 4).tolist():
+            assert cnt >= 2 and slot in (2 * w, 2 * w + 1) and w + cnt <= W and live[b, w:w + cnt].all(), (b, seg, slot, w, cnt)
+            assert (waves[b, w + 1:w + cnt, 0] == seg).all() and inside[b, w + 1:w + cnt].all()
+
+
+@pytest.mark.parametrize("range_cost", [0, 1, 2, 3])
+@pytest.mark.parametrize("min_units", [1, 2, 4])
+def test_descriptor_every_piece_of_a_divided_range_has_a_page(range_cost, min_units):
+    """No setting makes two wavefronts of a bin start on one page inside a range, however few pages there are per wavefront: the
+    first of them would have no page, and the piece that the merge reads for it would be one that nobody wrote."""
+    rng = np.random.default_rng(10 * range_cost + min_units)
+    fixed = [[513], [529], [641], [769], [897], [84, 999], [1000], [16393], [40], [8193, 17]]
+    for Hkv, G in [(1, 1), (1, 4), (1, 8), (2, 2), (2, 8), (8, 1), (8, 4)]:
+        c = host_ctx(1 << 16, Hq=Hkv * G, Hkv=Hkv, tuning={"range_cost": range_cost, "min_units": min_units})
+        drawn = [np.exp(rng.uniform(0, np.log(20000 if n == 1 else 3000), n)).astype(int).tolist() for n in (1, 1, 1, 1, 1, 1, 1, 1, 2, 2, 3, 5, 9, 30)]
+        for i, lengths in enumerate(fixed + drawn):
+            n_tok = [1] * len(lengths) if i % 2 == 0 else [min(n, 3) for n in lengths]
+            np_l = [-(-n // 16) for n in lengths]
+            w = c.build_desc(n_tok, np.arange(sum(np_l), dtype=np.int32), np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64), lengths)
+            assert int(w[34]) > 0
+            _check_bin_lists(w)
+
+
 @pytest.mark.parametrize("lengths", [[1], [16], [17, 300, 5], [1000], [200] * 64, [4000, 16, 16, 900] * 8])
 def test_wave_records_name_what_the_first_loads_need(lengths):
     """A wavefront of a bin requests its first page before its segment's record has come: kv head and page ids of the wave
