@@ -95,7 +95,8 @@ typedef struct sym_tuning {
                               tile workgroups follow                                      */
   int32_t share_tiles;     /* shared prefixes are cut by key chunk (at most 8 chunks each) until
                               the batch has about this many tiles; >= 1, default 512 (two
-                              workgroups per CU)                                          */
+                              workgroups per CU; at the default, fewer where the tiles and
+                              the members' decode workgroups then all start at once)      */
 } sym_tuning;
 
 typedef struct sym_config {

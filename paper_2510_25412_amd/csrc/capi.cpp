@@ -30,6 +30,7 @@ inline int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 inline void copy_bytes(void* dst, const void* src, size_t bytes) {
   if (bytes) std::memcpy(dst, src, bytes);
 }
+constexpr int32_t kShareTiles = 512;                 // default share_tiles: two workgroups per compute unit
 // The planner settings of a shape when the caller gives none.
 sym_tuning default_tuning(const sym_config* cfg) {
   const int G = cfg->n_q_heads / cfg->n_kv_heads;
@@ -51,7 +52,7 @@ sym_tuning default_tuning(const sym_config* cfg) {
   t.fuse_append = 1;
   t.mix_lead = 0;
   t.mix_spread = 50;
-  t.share_tiles = 512;
+  t.share_tiles = kShareTiles;
   return t;
 }
 }  // namespace
@@ -84,7 +85,7 @@ struct sym_ctx {
   int32_t row_tokens = 1;                      // new tokens of one LIP per decode row (bf16: up to 16 / G, at most 4)
   int32_t fuse_append = 1;                     // 1: the attention kernel appends the tokens of single-token LIPs itself
   int32_t mix_lead = 0, mix_spread = 50;       // where decode workgroups sit among the tile workgroups of a launch (percent)
-  int32_t share_tiles = 512;                   // shared-prefix tiles a batch is cut into (by key chunk), about
+  int32_t share_tiles = kShareTiles;           // shared-prefix tiles a batch is cut into (by key chunk), about
   int32_t bin_waves = 8;                       // wavefronts per decode bin (workgroup) of a batch without tiles: 4 or 8
   int32_t bin_tolerance = 3;                   // percent of imbalance between the decode bins that is accepted before ranges are split
   std::mutex mu;
@@ -193,6 +194,7 @@ DescParams desc_params(const sym_ctx* c, int64_t partials, int64_t max_words, bo
   p.mix_lead = c->mix_lead;
   p.mix_spread = c->mix_spread;
   p.share_tiles = c->share_tiles;
+  p.one_round = (c->cfg.decode_waves <= 0 && c->share_tiles == kShareTiles) ? 1 : 0;
   p.row_tile_rows = c->cfg.dtype == SYM_F32 ? 32 : 0;
   p.cus = c->cus;
   p.max_words = max_words;

@@ -240,12 +240,12 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
         own_units += (len_after[b] + P - 1) / P * H;
       }
       const int64_t round = 2 * (int64_t)prm.cus, bins_then = std::min<int64_t>(own_units / (4 * (int64_t)prm.min_units_per_wave) + 1, prm.max_waves / 4);
-      if (prm.spread_small && prm.bin_waves > 0 && max_nt == 1 && !prompts && own_units > 0 &&
+      if (prm.one_round && prm.bin_waves > 0 && max_nt == 1 && !prompts && own_units > 0 &&
           (target + base_tiles - 1) / base_tiles * base_tiles + bins_then > round) {
         const int64_t tiles = std::max<int64_t>(1, (round * tile_units / (tile_units + own_units) + base_tiles / 2) / base_tiles) * base_tiles;
         const int64_t most = (tile_units + own_units) * 115 / 100;      // x 1 / round
         if (tiles < round && tile_units * round <= most * tiles && own_units * round <= most * (round - tiles)) {
-          target = std::min(target, tiles);
+          target = std::min(target, tiles);                   // fewer tiles than share_tiles, never more
           one_round = round;
         }
       }

@@ -140,6 +140,7 @@ struct DescParams {
   int32_t cus = 256;          // compute units: what the tiles of a small batch should fill
   int64_t max_words = 0x7fffffff;   // words the descriptor may take; tiles are not cut into key chunks beyond it
   int32_t share_tiles = 512;  // shared prefixes are cut by key chunk (up to 8 chunks) until the batch has about this many tiles
+  int32_t one_round = 0;      // 1: fewer tiles and bins where both then start in one round (not when the caller set share_tiles or the wavefront slots)
 };
 
 // n_tokens[b] new tokens of LIP b; len_after[b] = file length including them; LIP b's page

@@ -725,6 +725,18 @@ def test_descriptor_forks_in_one_round(roots, children, shared, own, one_round):
     assert len(cover) == sum(loads) == n * 8 * (shared + own - shared // 2 * 2)
 
 
+@pytest.mark.parametrize("share_tiles,n_tiles", [(1, 128), (128, 128), (129, 256), (256, 256), (511, 512), (513, 640), (1024, 640), (2048, 640)])
+def test_descriptor_keeps_the_callers_number_of_shared_tiles(share_tiles, n_tiles):
+    """share_tiles other than the default: the fewest equal chunks of every group that give so many tiles, as far as the partial
+    slots go (5 chunks here), and the bins as many as the wavefront slots fill, whether or not fewer would start at once."""
+    c = host_ctx(1 << 17, tuning={"share_tiles": share_tiles})
+    ids = iter(range(1 << 17))
+    prefix = [[next(ids) for _ in range(128)] for _ in range(16)]
+    tables = [prefix[b // 16] + [next(ids) for _ in range(9)] for b in range(256)]
+    w = c.build_desc([1] * 256, np.concatenate(tables).astype(np.int32), np.arange(257, dtype=np.int64) * 137, [137 * 16] * 256)
+    assert (int(w[4]), int(w[34])) == (n_tiles, 512)
+
+
 @pytest.mark.parametrize("Hkv,G,n_tok,len0", [(8, 1, [300, 100], 0), (8, 1, [491, 150, 440, 478], 0), (8, 4, [400, 90, 333], 70), (1, 4, [2000], 0), (2, 8, [100] * 30, 5), (8, 1, [600] * 6, 0), (8, 2, [700, 20], 20000)])
 def test_descriptor_order_of_row_tiles(Hkv, G, n_tok, len0):
     """More row tiles than compute units (256): longest piece first, heads of a piece together; up to twice as many, those past the
