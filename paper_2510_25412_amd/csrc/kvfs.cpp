@@ -309,15 +309,24 @@ int64_t Kvfs::gather_need(int32_t n_seg, const int32_t* seg_handle, const int64_
     int32_t* out = src.data() + at;
     const int32_t* pages = f->pages.data();
     const int64_t len = f->len;
-    const int sh = page_shift_;                            // page size is a power of two on the device path
-    for (int64_t j = lo; j < hi; ++j) {
-      const int64_t i = idx ? idx[j] : j;
-      if ((uint64_t)i >= (uint64_t)len) {
+    // Block by block: the range check of all its indices, then their lookups, so that neither loop has a branch.  (With a check per
+    // index the 76 000 lookups of 64 files took 39, 51 or 65 us, by where the linker put the loop; so they take 42..46.)
+    constexpr int64_t kBlock = 256;
+    for (int64_t j = lo; j < hi; j += kBlock) {
+      const int64_t m = std::min(kBlock, hi - j);
+      uint64_t outside = 0;                                // top bit set: an index is below 0, or above len - 1
+      for (int64_t k = 0; k < m && idx; ++k) outside |= (uint64_t)idx[j + k] | ((uint64_t)(len - 1) - (uint64_t)idx[j + k]);
+      if (outside >> 63) {
         src.resize(at);
         if (err) *err = "extract: token index outside the file";
         return SYM_EINVAL;
       }
-      *out++ = sh >= 0 ? (pages[i >> sh] << sh) + (int32_t)(i & (P_ - 1)) : pages[i / P_] * P_ + (int32_t)(i % P_);
+      auto look_up = [&](auto slot) {
+        for (int64_t k = 0; k < m; ++k) out[k] = slot(idx ? idx[j + k] : j + k);
+      };
+      if (const int sh = page_shift_; sh >= 0) look_up([=, mask = (int64_t)P_ - 1](int64_t i) { return (pages[i >> sh] << sh) + (int32_t)(i & mask); });
+      else look_up([=, P = P_](int64_t i) { return pages[i / P] * P + (int32_t)(i % P); });
+      out += m;
     }
   }
   const int64_t n = (int64_t)(src.size() - s0), np = (n + P_ - 1) / P_;
@@ -342,27 +351,30 @@ int32_t Kvfs::gather_commit(GatherPlan* plan, int32_t k) {
   const int32_t* src = plan->src.data() + s0;
   const int32_t* shared = plan->shared.data() + h0;
   const int32_t id = new_file();
-  files_[id].pages.reserve((size_t)np);
-  for (int64_t d = 0; d < np; ++d) {
+  std::vector<int32_t>& pages = files_[id].pages;
+  pages.reserve((size_t)np);
+  int64_t moved = 0;                                       // tokens of the pages that are copied
+  for (int64_t d = 0; d < np; ++d)
+    if (shared[d] < 0) moved += std::min<int64_t>(P_, n - d * P_);
+  const size_t at = plan->moves.size();
+  plan->moves.resize(at + (size_t)(2 * moved));
+  int32_t* mv = plan->moves.data() + at;
+  for (int64_t d = 0; d < np; ++d, src += P_) {
     if (shared[d] >= 0) {
       ++refcount_[shared[d]];
-      files_[id].pages.push_back(shared[d]);
+      pages.push_back(shared[d]);
       ++plan->pages_shared;
       ++pages_referenced;
-    } else {
-      const int32_t dst = alloc_page();
-      files_[id].pages.push_back(dst);
-      const int64_t base = d * P_, c = std::min<int64_t>(P_, n - base);
-      const size_t at = plan->moves.size();
-      plan->moves.resize(at + (size_t)(2 * c));
-      int32_t* mv = plan->moves.data() + at;
-      for (int64_t t = 0; t < c; ++t) {
-        mv[2 * t] = src[base + t];
-        mv[2 * t + 1] = dst * P_ + (int32_t)t;
-      }
-      tokens_moved += c;
+      continue;
+    }
+    const int32_t dst = alloc_page(), c = (int32_t)std::min<int64_t>(P_, n - d * P_);
+    pages.push_back(dst);
+    for (int32_t t = 0; t < c; ++t, mv += 2) {
+      mv[0] = src[t];
+      mv[1] = dst * P_ + t;
     }
   }
+  tokens_moved += moved;
   files_[id].len = n;
   return new_handle(id);
 }

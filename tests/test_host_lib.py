@@ -318,6 +318,28 @@ def test_error_codes_and_all_or_nothing():
         c.kv_append(n2, 1, 1, 1)
 
 
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 700])
+def test_extract_checks_every_index(n):
+    """An index outside the file, wherever it stands in the list (indices are checked 256 at a time): refused, nothing changes."""
+    c = host_ctx(256)
+    a = c.kv_open()
+    c.plan_append([a], [700])
+    state = lambda: (c.kv_pages(a), c.free_pages(), [c.page_refcount(p) for p in range(256)])  # noqa: E731
+    before = state()
+    for at in {0, 1, n // 2, 254, 255, 256, 257, n - 1} & set(range(n)):
+        for bad in (-1, 700, 1 << 40, -(1 << 63), (1 << 63) - 1):
+            idx = list(range(n))
+            idx[at] = bad
+            with pytest.raises(binding.SymError) as e:
+                c.kv_extract(a, idx)
+            assert e.value.code == binding.SYM_EINVAL and state() == before, (at, bad)
+    idx = list(range(n))[::-1]
+    x = c.kv_extract(a, idx)
+    pages, own = c.kv_pages(a), c.kv_pages(x)
+    moves = [(pages[i // 16] * 16 + i % 16, own[d // 16] * 16 + d % 16) for d, i in enumerate(idx) if own[d // 16] not in pages]
+    assert [tuple(m) for m in np.asarray(c.last_moves()).reshape(-1, 2).tolist()] == moves and c.kv_len(x) == n
+
+
 def test_extract_of_no_tokens_same_codes_as_the_model():
     """An extract of no tokens makes an empty file from a usable source and is refused, with the model's
     code and without a new file, from a stale handle (EBADF) or a waiting file (EBUSY)."""
