@@ -66,8 +66,8 @@ typedef struct sym_tuning {
   int32_t decode_mfma;     /* ranges of single tokens and short drafts on the matrix cores (1)
                               or on the vector ALUs (0); bf16 only.  Default: 1 when
                               Hq/Hkv = 8, else 0                                          */
-  int32_t min_units;       /* smallest piece, in pages, that a long range is cut into;
-                              >= 1, default 4                                             */
+  int32_t min_units;       /* smallest piece, in pages, that a long range is cut into (the
+                              long ranges of a small decode batch: down to 1); >= 1, default 4 */
   int32_t prefill_min;     /* a pred of at least this many new tokens is computed by tiles
                               (SYM_F32 with 8 query heads per kv head: unless the batch is small
                               and its files are long); >= 2, default 16 (fp32: 4)         */

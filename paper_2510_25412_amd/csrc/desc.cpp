@@ -386,14 +386,21 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   int64_t n_bins = 0;
   if (bins) {
     // A small batch with long ranges: a wavefront takes as few pages as give every compute unit one workgroup (both of two are in
-    // flight from the start), but two at least where one would leave a range in more than the 16 pieces that a merge reads in one
-    // round trip.  32 layers, four pages per wavefront / by this rule: a file of 600 tokens 362 / 298 us, of 1000 361 / 299, of 2000
-    // 389 / 354, of 4000 414 / 390, of 6000 443 / 425; four of 800..1200 400 / 360, eight of 400..700 397 / 381; 2000 tokens with 16
-    // query heads 293 / 272, 8000 with 4 heads of one kv head 377 / 370 (one page each: 472).  Short ranges in more than one per
-    // compute unit stay at four: there is no latency of a long range to divide.
+    // flight from the start), but no fewer than leave a range in the pieces that a merge of four wavefronts reads in one round trip
+    // (16), in two where a piece has more than one page and its merge is short (the vector-unit kernel); and two at least on the
+    // matrix cores.  32 layers, four pages per wavefront / by this rule: a file of 600 tokens 362 / 298 us, of 1000 361 / 299, of
+    // 2000 389 / 354, of 4000 414 / 390; four of 800..1200 400 / 360, eight of 400..700 397 / 381; 2000 tokens with 16 query heads
+    // 293 / 272.  Per layer, 4 heads of one kv head, a file of 2000 tokens 12.1 / 10.6, of 4800 12.0 / 11.8; 8 heads of one, 2000
+    // tokens 15.1 / 13.8, 2550 tokens 15.1 / 14.2.  Past these lines, two pages against four: 4 heads of one kv head, 8000 tokens
+    // 12.6 / 12.2, 24 000 19.6 / 16.5; 8 heads of one, 8000 tokens 18.5 / 16.0, 20 000 26.2 / 19.8; 3 tokens on 20 000 22.2 / 18.0.
+    // Short ranges in more than one per compute unit stay at four: there is no latency of a long range to divide.
     int64_t upw = prm.min_units_per_wave;
-    if (small_decode && longest_range > kWholePagesWide)
-      upw = std::min(upw, std::max<int64_t>(longest_range <= 16 * W && !mfma_bins ? 1 : 2, (total_units + prm.cus * 4 - 1) / (prm.cus * 4)));
+    if (small_decode && longest_range > kWholePagesWide) {
+      const int64_t trip = 16 * W, most = mfma_bins ? trip : 2 * trip;
+      int64_t fewest = (longest_range + most - 1) / most;
+      if (mfma_bins || longest_range > trip) fewest = std::max<int64_t>(fewest, 2);
+      upw = std::min(upw, std::max(fewest, (total_units + prm.cus * 4 - 1) / (prm.cus * 4)));
+    }
     // No more wavefronts than the batch's cost has steps: the starts of the cut (plan B) are then apart, and no wavefront without a
     // page begins inside a range.  (With the default settings a wavefront's share never falls below one.)
     n_bins = std::min((total_units + upw * W - 1) / (upw * W), (total_units + (int64_t)prm.range_cost * n_rows * H) / W);

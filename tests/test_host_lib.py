@@ -829,6 +829,19 @@ def test_descriptor_small_batches_of_long_ranges_are_spread(Hkv, G, lengths, uni
     assert len(cover) == total == sum(loads)
 
 
+@pytest.mark.parametrize("Hkv,G,lengths,new,units", [
+    (1, 4, [4096], 1, 2), (1, 4, [4097], 1, 3), (1, 4, [6144], 1, 3), (1, 4, [6145], 1, 4), (1, 1, [20000], 1, 4), (2, 4, [8000], 1, 4), (4, 4, [8000], 1, 4), (1, 4, [8000] * 4, 1, 4),
+    (1, 8, [600], 1, 2), (1, 8, [2048], 1, 2), (1, 8, [2049], 1, 3), (1, 8, [3072], 1, 3), (1, 8, [3073], 1, 4), (1, 4, [2048], 3, 2), (1, 4, [2560], 3, 3), (2, 4, [20000], 3, 4)])
+def test_descriptor_small_batches_leave_no_more_pieces_than_a_merge_reads_at_once(Hkv, G, lengths, new, units):
+    """Fewest pages per wavefront of a small batch: a range in 32 pieces at most (on the matrix cores 16: 8 heads per kv head, rows
+    of several tokens), until a wavefront has min_units pages."""
+    np_l = [-(-n // 16) for n in lengths]
+    off = np.concatenate([[0], np.cumsum(np_l)]).astype(np.int64)
+    w = host_ctx(1 << 16, Hq=Hkv * G, Hkv=Hkv).build_desc([new] * len(lengths), np.arange(sum(np_l), dtype=np.int32), off, lengths)
+    assert (int(w[34]), int(w[35])) == (-(-sum(np_l) * Hkv // (4 * units)), 4)
+    _check_bin_lists(w)
+
+
 def test_descriptor_small_decode_batches():
     """The planner's rules for small decode batches: up to 24 pages a workgroup of four wavefronts per range and no merge, up to
     32 one of eight; with longer ones, or with more ranges than compute units (256 here), cut and merged; eight wavefronts past 4096 units (token, kv head,
