@@ -775,19 +775,17 @@ def test_descriptor_order_of_row_tiles(Hkv, G, n_tok, len0):
     if n > 256:
         alone = len(pages) if n > 512 else 256 // Hkv
         assert pages[:alone] == sorted(pages, reverse=True)[:alone] and pages[alone:] == sorted(pages[alone:])
-    cover = set()
+    cover = {}
     for tbl, vis, qrow, count, head, pb, pe, dest in rt[:, 0].tolist():
         for t in range(count):
-            for p in range(pb, pe):
-                assert (qrow + t, p) not in cover
-                cover.add((qrow + t, p))
-    last = {}
-    for row, p in cover:
-        last[row] = max(last.get(row, -1), p)
-    q0 = 0
+            cover.setdefault(qrow + t, []).extend(range(pb, pe))
+    q0, RQ = 0, 32 // G
     for nt, L in zip(n_tok, lengths):
-        assert all(last[q0 + t] >= (L - nt + t) // 16 for t in range(nt))
+        for t in range(nt):                                          # every page up to the last that the token's tile sees, once
+            seen = L - nt + min(t // RQ * RQ + RQ, nt)
+            assert sorted(cover.pop(q0 + t)) == list(range(-(-seen // 16))), (nt, t)
         q0 += nt
+    assert not cover
 
 
 @pytest.mark.parametrize("lengths,n_tok", [([16], [16]), ([17], [16]), ([40, 300], [40, 64]), ([6000], [100]), ([1300] * 6, [1] * 6), ([900, 1300, 1300, 1300, 1300], [300, 1, 1, 1, 1])])
