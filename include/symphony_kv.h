@@ -84,7 +84,8 @@ typedef struct sym_tuning {
                               then holds at most this many percent more than the mean;
                               otherwise ranges are cut at equal cost; >= 0, default 3     */
   int32_t bin_waves;       /* wavefronts of a decode workgroup: 8 (default; 4 for a batch so small
-                              that this gives every compute unit at most one) or 4        */
+                              that this gives every compute unit at most one) or 4.  With
+                              decode_mfma = 1 single tokens always have the default        */
   int32_t fuse_append;     /* 1 (default): the K/V row of a single new token is written by
                               the wavefront that reads the row's last page; 0: by a launch
                               of its own before attention                                 */
@@ -349,9 +350,9 @@ int sym_plan_copies_first(sym_ctx* ctx);
  *                           first three pages of the first range (its first loads need no
  *                           table lookup).  Bins (decode workgroups of [35] wavefronts; wavefront
  *                           w of bin b is record b * [35] + w): first segment, page inside it,
- *                           units, wavefronts that continue its last segment, ids of its first
- *                           three pages, kv head of the first segment: the wavefronts of a bin
- *                           take equal consecutive parts of the bin's segments
+ *                           units, 0, ids of its first three pages, word 1 of the first segment
+ *                           (kv head): the wavefronts of a bin take equal consecutive parts of
+ *                           the bin's segments
  *   segs      [n_segs + 2][8]  (bins) a (row, kv head) range or the part of one that falls
  *                           into a bin: page-table offset, kv head | (tokens in the row - 1)
  *                           << 28, first page, end page,

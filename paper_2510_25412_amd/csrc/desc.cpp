@@ -60,10 +60,11 @@ int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_
   }
   return b_best;
 }
-// Longest range (pages) that a small decode batch leaves to one workgroup of four wavefronts.  Per layer, 32 query heads, with a
-// merge launch / without: 32 files of 100 tokens 13.6 / 9.1 us, sixteen of 200 12.8 / 9.7, eight of 300 12.5 / 10.6, one of 400
-// 12.1 / 12.2, one of 500 (32 pages) 12.0 / 13.0.  Up to 32 pages one workgroup of eight: attention and merge of 1..14 files of 400..510
-// tokens 0.69..0.85 of the time that cut ranges of four take (which had cost up to 1.39 of the whole ranges before them).
+// Longest range (pages) that a small decode batch leaves to one workgroup of four wavefronts, and to one of eight.  Per layer, 32 query
+// heads, cut at four pages per wavefront and merged / whole: 32 files of 100 tokens 13.6 / 9.1 us, sixteen of 200 12.8 / 9.7, eight of
+// 300 12.5 / 10.6, one of 400 12.1 / 12.2; whole ranges of eight wavefronts, 1..14 files of 400..510 tokens, 0.69..0.85 of such a cut.
+// Against a cut at one or two pages per wavefront, as longer ranges have it, a single file of 500 tokens is slower whole (13.6 / 9.2 us):
+// the lines are where they were for the coarser cut, and have not been weighed against the finer one over numbers of files and heads.
 constexpr int64_t kWholePages = 24, kWholePagesWide = 32;
 // bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch.  196 random prompt batches
 // whose plan some setting changes, attention and merge together, against whole tiles: 0.82 of the time, one more than 4 % slower (6 %).  A
@@ -884,9 +885,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
           en[2] = (int32_t)(k - 1);
           en[3] = 1;
         }
-        int32_t* en = lm + 4 + 4 * (lm[0] - 1);
-        ++en[3];
-        ++bw[en[2] * WAVE_WORDS + 3];                   // wavefronts that continue that one's last segment
+        ++lm[4 + 4 * (lm[0] - 1) + 3];
       }
     }
   } else {
@@ -980,8 +979,9 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
         }
     }
   }
-  // ---- row tiles, files of the longest first, from their last tokens down; the kv heads of a token tile are neighbours, so that with 8 of them (workgroup b runs on
-  // XCD b % 8) the tiles that read one (file, kv head) share an L2
+  // ---- row tiles: the longest file first, from its last tokens down (more than the compute units hold at once: the longest piece
+  // first, below); the kv heads of a token tile are neighbours, so that with 8 of them (workgroup b runs on XCD b % 8) the tiles that
+  // read one (file, kv head) share an L2
   if (n_btile_partials > 0) {                            // the partials of the prefill tiles' chunks follow those of the shared prefixes
     const int32_t first = shared_base + (int32_t)n_shared_partials;
     for (int64_t i = 0; i < n_tiles; ++i)

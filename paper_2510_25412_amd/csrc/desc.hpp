@@ -22,13 +22,14 @@
 // The work of the decode kernel is measured in units of one (page, kv head) = one 8 KiB K+V
 // slab.  Two ways of handing the units to wavefronts:
 //  * the global cut (matrix-core decode kernel: 8 query heads per kv head, rows of several draft
-//    tokens; beside tiles, or when the caller sets the wavefront slots): the units of all rows, ordered (row, kv head, page), are cut into n_waves contiguous
+//    tokens; beside tiles, or when the caller sets the wavefront slots): the units of all rows,
+//    ordered (row, kv head, page), are cut into n_waves contiguous
 //    ranges of equal cost, one per wavefront, whatever the raggedness of the files.  A range
 //    that covers only part of a (row, kv head) produces a partial result (running max, sum,
 //    unnormalised accumulator) in device memory and an entry in the merge list (a kernel of its
 //    own combines them); a range covering a whole (row, kv head) writes the final output directly.
-//  * bins (the vector-unit decode kernel; the matrix-core one in a batch without tiles): every workgroup of bin_waves wavefronts is a bin that
-//    receives WHOLE (row, kv head) ranges, as "segments", balanced over the bins longest first; only a
+//  * bins (the vector-unit decode kernel; the matrix-core one in a batch without tiles): every
+//    workgroup of bin_waves wavefronts is a bin that receives WHOLE (row, kv head) ranges, as "segments", balanced over the bins longest first; only a
 //    range longer than a bin's share (or ranges too few to balance) is split into several segments,
 //    each of which leaves a partial result in device memory like above.  Inside a bin the
 //    wavefronts cut the bin's segments into equal contiguous parts and combine the pieces of a cut
@@ -125,9 +126,9 @@ struct DescParams {
   int32_t share_min_pages;    // common full pages a group must have
   int32_t max_partials;       // partial-result slots the workspace holds
   int32_t row_tokens;         // new tokens of one LIP a decode row may hold (1 = a row per token)
-  int32_t bin_waves = 0;      // != 0: bins (the vector-unit decode kernel) unless a row holds several tokens; as many bins as
+  int32_t bin_waves = 0;      // != 0: bins for the vector-unit decode kernel (no row holds several tokens); as many bins as
                               //   max_waves fills with workgroups of 8 wavefronts (4 beside tiles of 128 query rows; a batch
-                              //   without tiles: 4 if this is 4, else 8)
+                              //   without tiles, also in mfma_bins: 4 if this is 4 or the batch is small, else 8)
   int32_t decode_mfma = 0;    // 1: every decode row goes to the matrix-core kernel (rows of several tokens always do)
   int32_t mfma_bins = 0;      // 1: bins for that kernel too, in a batch without tiles (not when the caller set the wavefront slots)
   int32_t spread_small = 0;   // 1: a small decode batch is spread over more, smaller workgroups (not when the caller set the wavefront slots)

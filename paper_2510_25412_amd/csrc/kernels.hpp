@@ -19,10 +19,10 @@ struct DecodeArgs {
   const int32_t* pt;        // flattened page tables
   int32_t n_waves, Hq, Hkv;
   float scale_log2e;        // softmax scale * log2(e)
-  // bins (the vector-unit decode kernel): `waves` then holds bin_waves records per bin: first segment, first
-  // page, units, wavefronts that continue its last segment, ids of the first three pages, kv head
-  const int32_t* segs;      // [n_segs + 2][8]: page-table offset, kv head, first page, end page, visible tokens,
-                            //   q/out row * Hq + first query head, destination (-1 output, else partial slot), slot of the appended token or -1
+  // bins: `waves` then holds bin_waves records per bin: first segment, first page, units, 0, ids of the first three pages, kv head | (tokens
+  // in the row - 1) << 28
+  const int32_t* segs;      // [n_segs + 2][8]: page-table offset, kv head | (tokens in the row - 1) << 28, first page, end page, visible
+                            //   tokens, q/out row * Hq + first query head, destination (-1 output, else partial slot), slot of the appended token or -1
   const int32_t* lmerge;    // [n_bins][32]: count, then (segment, LDS slot of its first piece, that piece's wavefront,
                             //   pieces) per segment the bin's cut divided, from word 4 on
   int32_t n_bins, bin_waves;
