@@ -475,7 +475,7 @@ def run_attention_workload(args, name, np, torch, binding, synth, HipSession, de
     mfma_ach = mfma_flops / (attn_ms * 1e-3) / 1e12
     note = {"decode": "attn_decode_batch_pmc.txt"}.get(name, f"attn_{name}_pmc.txt")
     # decode ranges run on the matrix cores for 8 query heads per kv head and for multi-token rows
-    kname = f"decode_mfma_kernel<G={G}>" if name in ("long", "draft") else (f"decode_only_kernel<bf16, G={G}>" if name in ("decode", "short") else f"attn_kernel<bf16, G={G}>")
+    kname = f"decode_mfma_bins_kernel<G={G}>" if name in ("long", "draft") else (f"decode_only_kernel<bf16, G={G}>" if name in ("decode", "short") else f"attn_kernel<bf16, G={G}>")
     roof_hbm = {"bound": "hbm", "achieved": round(hbm_ach, 1), "peak": HBM_PEAK_TBPS * 1e3, "unit": "GB/s",
                 "frac": round(hbm_ach / (HBM_PEAK_TBPS * 1e3), 4), "traffic": read_traffic_note(note),
                 "kernel": kname, "avg_launch_us": round(attn_ms * 1e3, 2), "launches": attn_n}
