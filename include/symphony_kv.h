@@ -67,7 +67,8 @@ typedef struct sym_tuning {
                               or on the vector ALUs (0); bf16 only.  Default: 1 when
                               Hq/Hkv = 8, else 0                                          */
   int32_t min_units;       /* smallest piece, in pages, that a long range is cut into (the
-                              long ranges of a small decode batch: down to 1); >= 1, default 4 */
+                              long ranges of a small decode batch that runs through several
+                              layers: down to 1); >= 1, default 4                         */
   int32_t prefill_min;     /* a pred of at least this many new tokens is computed by tiles
                               (SYM_F32 with 8 query heads per kv head: unless the batch is small
                               and its files are long); >= 2, default 16 (fp32: 4)         */
@@ -388,6 +389,7 @@ int sym_plan_copies_first(sym_ctx* ctx);
  *                           tile holds all keys of its rows and writes the final output)
  *   tmerge    [n_tmerge][4]  first partial (chunk c, token t: first + c * tokens + t), chunks,
  *                           tokens, q row * Hq + first query head of the first token
+ * A host-only context plans as for a step of many layers (min_units).
  * Returns the number of words (or a negative status); writes at most cap words.             */
 int64_t sym_build_desc(sym_ctx* ctx, int32_t n_lips, const int32_t* n_tokens,
                        const int32_t* page_table_flat, const int64_t* pt_offsets,

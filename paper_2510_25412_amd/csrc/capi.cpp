@@ -189,6 +189,7 @@ DescParams desc_params(const sym_ctx* c, int64_t partials, int64_t max_words, bo
   p.bin_waves = (c->G < 8 && !c->decode_mode) ? c->bin_waves : 0;
   p.fuse_append = (fuse_append && p.bin_waves && c->fuse_append) ? 1 : 0;
   p.spread_small = p.mfma_bins = c->cfg.decode_waves <= 0 ? 1 : 0;
+  p.layers = c->cfg.device < 0 ? 1024 : c->n_layers;      // a host-only context shows the plan of a step of many layers
   p.decode_mfma = c->decode_mode;
   p.bin_tolerance = c->bin_tolerance;
   p.mix_lead = c->mix_lead;

@@ -132,6 +132,7 @@ struct DescParams {
   int32_t decode_mfma = 0;    // 1: every decode row goes to the matrix-core kernel (rows of several tokens always do)
   int32_t mfma_bins = 0;      // 1: bins for that kernel too, in a batch without tiles (not when the caller set the wavefront slots)
   int32_t spread_small = 0;   // 1: a small decode batch is spread over more, smaller workgroups (not when the caller set the wavefront slots)
+  int32_t layers = 1;         // layers that run by this plan
   int32_t bin_tolerance = 3;  // percent by which the fullest bin may exceed the mean before ranges are split finer
   int32_t fuse_append = 0;    // 1: single-token LIPs are appended by the attention kernel (bins only)
   // order of a launch with tiles and decode bins, in percent of the tile groups: `mix_lead` tile groups first, then

@@ -1007,6 +1007,38 @@ def test_every_planner_setting_with_the_chips_own_wavefront_slots(Hq, Hkv, files
         sess.close()
 
 
+@pytest.mark.parametrize("Hq,Hkv,layers,lengths,new,units", [
+    (4, 1, 3, [1000], 1, 4), (4, 1, 4, [1000], 1, 1), (8, 4, 7, [900, 40], 1, 4), (8, 4, 8, [900, 40], 1, 1), (1, 1, 15, [600], 1, 4), (1, 1, 16, [600], 1, 1),
+    (8, 1, 1, [2000], 1, 2), (64, 8, 1, [1023], 1, 2), (64, 8, 1, [1024], 1, 4), (64, 8, 2, [1024], 1, 2), (32, 8, 1, [2044], 4, 2), (32, 8, 1, [2045], 4, 4), (32, 8, 2, [2045], 4, 3),
+    (8, 8, 3, [1500], 3, 4), (8, 8, 4, [1500], 3, 2)])
+def test_finer_cut_of_long_ranges_by_the_layers_that_share_a_plan(Hq, Hkv, layers, lengths, new, units):
+    """A small batch of long files: min_units pages per wavefront where few layers run by the plan, fewer from layers x heads per kv
+    head = 16 on (matrix cores: from a 64th of the pages by layers x query columns); every layer's outputs against the oracle, on either side of the line."""
+    drv = _hip()
+    wl = synth.custom(f"finer_{Hq}_{Hkv}_{layers}", synth.Shape(Hq, Hkv, 128, 16, synth.BF16), [("new", n) for n in lengths], [(f, new) for f in range(len(lengths))], 256, seed=layers)
+    ref, osess = run_oracle(wl, dtype=np.float64)
+    sess = drv.HipSession(wl.shape, wl.n_pages, wl.free_order, max_lips=8, max_tokens=max(lengths) + 64, max_entries=1024, poison=True, n_layers=layers)
+    sess.setup(wl.setup_ops())
+    db = sess.upload_batch(wl.batch())
+    if layers == 1:
+        got = [sess.pred(db)]
+    else:
+        got = [torch.empty_like(db["out"]) for _ in range(layers)]
+        sess.ctx.pred_begin(db["kv"], db["n_tokens"], sess.stream)
+        for l in range(layers):
+            sess.ctx.pred_layer(l, db["q"], db["k_new"], db["v_new"], got[l], sess.stream)
+    torch.cuda.synchronize()
+    for l in range(layers):
+        check_outputs(got[l].cpu().numpy(), ref)
+    check_state(wl, sess, osess)
+    tables = [sess.pages(f) for f in range(len(lengths))]
+    total = sum(len(t) for t in tables)
+    w = sess.ctx.build_desc([new] * len(lengths), np.concatenate(tables).astype(np.int32), np.concatenate([[0], np.cumsum([len(t) for t in tables])]).astype(np.int64),
+                            [n + new for n in lengths])
+    assert (int(w[34]), int(w[35])) == (-(-total * Hkv // (4 * units)), 4)
+    sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,dtype,multi", [(32, 8, 128, synth.BF16, 1), (32, 8, 128, synth.BF16, 3), (8, 8, 64, synth.F32, 3),
                                                   (64, 8, 128, synth.BF16, 1), (16, 8, 128, synth.BF16, 1)])
 def test_layered_pred_layer_by_layer_against_the_oracle(Hq, Hkv, D, dtype, multi):
