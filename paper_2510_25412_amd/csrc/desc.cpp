@@ -84,6 +84,8 @@ constexpr int64_t kTileStart = 10, kTileMerge = 11, kUnitsPerStep = 4;
 // A segment record, and what is added to get from a kv head's to the next one's (plus G in S_QROW).
 typedef int32_t SegRecord __attribute__((vector_size(SEG_WORDS * sizeof(int32_t))));
 constexpr SegRecord kNextHead = {0, 1, 0, 0, 0, 0, 0, 0};
+// A row tile's record.
+typedef int32_t RtileRecord __attribute__((vector_size(RTILE_WORDS * sizeof(int32_t))));
 // Most key chunks of a row tile: a token's chunks are merged one group of four after the other.  Kernel time over 525 shapes (4..200
 // new tokens on 0..8000) against 64: 0.985 (16: 0.986); one file of 8000 tokens, 8 new ones, 8 heads: 24.7 -> 18.5 us.
 constexpr int64_t kRowTileChunks = 32;
@@ -300,13 +302,18 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
   int64_t chunk_budget = (int64_t)prm.max_partials - 2 * (int64_t)RT * prm.max_waves - 2 * n_shared_partials;
   int64_t n_rtiles = 0, n_rtile_split = 0, n_chunk_partials = 0, rsteps = 0;
   constexpr int32_t kRowTileWaves = 8;
-  auto rpages = [&](int32_t b, int32_t t0) { return (int32_t)((len_after[b] - n_tokens[b] + std::min(t0 + RQ, n_tokens[b]) + P - 1) / P); };   // pages the tile reads
+  auto& rpages = out->rtile_pages;                          // pages every tile reads, file by file in the order of rorder, first tokens first
   auto rchunks = [&](int32_t pages) { return rsteps > 0 ? (pages + (int32_t)rsteps * kRowTileWaves - 1) / ((int32_t)rsteps * kRowTileWaves) : 1; };
   auto count_rtiles = [&]() {
     n_rtiles = n_rtile_split = n_chunk_partials = 0;
+    if (rsteps == 0) {                                      // whole tiles
+      n_rtiles = (int64_t)rpages.size() * H;
+      return;
+    }
+    const int32_t* pages = rpages.data();
     for (int32_t b : rorder)
       for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += RQ) {
-        const int32_t nc = rchunks(rpages(b, t0));
+        const int32_t nc = rchunks(*pages++);
         n_rtiles += (int64_t)nc * H;
         if (nc > 1) {
           n_rtile_split += H;
@@ -318,8 +325,16 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     std::stable_sort(rorder.begin(), rorder.end(), [&](int32_t x, int32_t y) { return len_after[x] > len_after[y]; });
     auto& lens = out->tile_lens;
     lens.clear();
-    for (int32_t b : rorder)
-      for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += RQ) lens.emplace_back((rpages(b, t0) + kRowTileWaves - 1) / kRowTileWaves, H);
+    rpages.clear();
+    for (int32_t b : rorder) {
+      const int64_t len0 = len_after[b] - n_tokens[b];
+      int64_t pages = (len0 + P - 1) / P;
+      for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += RQ) {
+        while (pages * P < len0 + std::min(t0 + RQ, n_tokens[b])) ++pages;
+        rpages.push_back((int32_t)pages);
+        lens.emplace_back((int32_t)((pages + kRowTileWaves - 1) / kRowTileWaves), H);
+      }
+    }
     rsteps = chunk_steps(lens, 2 * (int64_t)prm.cus, 4, 4, kRowTileChunks, 1, 0, RQ, chunk_budget);
     count_rtiles();
     chunk_budget -= n_chunk_partials;
@@ -1007,14 +1022,17 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     const bool by_length = n_rtiles > prm.cus, paired = n_rtiles <= 2 * (int64_t)prm.cus;
     auto& place = out->tile_order;                         // per piece length, longest first: place of the next such piece
     if (by_length) {
-      int32_t longest = rpages(rorder[0], n_tokens[rorder[0]] - 1);
+      int32_t longest = *std::max_element(rpages.begin(), rpages.end());
       if (rsteps > 0) longest = (int32_t)std::min<int64_t>(longest, rsteps * kRowTileWaves);
       place.assign((size_t)longest + 2, 0);
-      for (int32_t b : rorder)
-        for (int32_t t0 = 0; t0 < n_tokens[b]; t0 += RQ) {
-          const int32_t pages = rpages(b, t0), nc = rchunks(pages), per = (pages + nc - 1) / nc;
-          for (int32_t c = 0; c < nc; ++c) ++place[(size_t)(longest - (std::min((c + 1) * per, pages) - std::min(c * per, pages))) + 1];
+      for (int32_t pages : rpages) {
+        if (rsteps == 0) {
+          ++place[(size_t)(longest - pages) + 1];
+          continue;
         }
+        const int32_t nc = rchunks(pages), per = (pages + nc - 1) / nc;
+        for (int32_t c = 0; c < nc; ++c) ++place[(size_t)(longest - (std::min((c + 1) * per, pages) - std::min(c * per, pages))) + 1];
+      }
       for (int32_t i = 0; i <= longest; ++i) place[i + 1] += place[i];
     }
     const int32_t longest = (int32_t)place.size() - 2;
@@ -1022,34 +1040,31 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     int32_t* tm = tm_next;
     int64_t chunk_base = shared_base + n_shared_partials + n_btile_partials;
     int32_t* rr = rows + n_rows * ROW_WORDS;
+    const int32_t* file_pages = rpages.data();             // of the file's first tile
     for (int32_t b : rorder) {
-      const int32_t len0 = (int32_t)(len_after[b] - n_tokens[b]), tok0 = tok_of[b];
+      const int32_t len0 = (int32_t)(len_after[b] - n_tokens[b]), tok0 = tok_of[b], file_tiles = (n_tokens[b] + RQ - 1) / RQ;
+      const int32_t* tile_pages = file_pages + file_tiles;
+      file_pages += file_tiles;
       for (int32_t t = 0; t < n_tokens[b]; ++t, rr += ROW_WORDS) {
         rr[0] = ptoff[b];
         rr[1] = len0 + t + 1;
         rr[2] = tok0 + t;
         rr[3] = 0;
       }
-      for (int32_t t0 = (n_tokens[b] - 1) / RQ * RQ; t0 >= 0; t0 -= RQ) {
-        const int32_t count = std::min(RQ, n_tokens[b] - t0), pages = rpages(b, t0), nc = rchunks(pages);
-        const int32_t per = (pages + nc - 1) / nc;
+      for (int32_t t0 = (file_tiles - 1) * RQ; t0 >= 0; t0 -= RQ) {
+        const int32_t count = std::min(RQ, n_tokens[b] - t0), pages = *--tile_pages, nc = rchunks(pages);
+        const int32_t per = nc == 1 ? pages : (pages + nc - 1) / nc;
         for (int32_t c = 0; c < nc; ++c) {
           int64_t at = next++;
           if (by_length) {
             at = place[longest - (std::min((c + 1) * per, pages) - std::min(c * per, pages))]++;
             if (paired && at >= alone) at = alone + pieces - 1 - at;
           }
+          const int32_t p0 = c * per, p1 = std::min(p0 + per, pages);
+          RtileRecord rec = {ptoff[b], len0 + t0 + 1, tok0 + t0, count, 0, std::min(p0, pages), p1, nc > 1 ? (int32_t)(chunk_base + (int64_t)c * count) : -1};
+          RtileRecord next_head = {0, 0, 0, 0, 1, 0, 0, nc > 1 ? nc * count : 0};
           int32_t* rt = w + off_rtiles + at * H * RTILE_WORDS;
-          for (int32_t g = 0; g < H; ++g, rt += RTILE_WORDS) {
-            rt[RT_TBL] = ptoff[b];
-            rt[RT_VIS] = len0 + t0 + 1;
-            rt[RT_QROW] = tok0 + t0;
-            rt[RT_COUNT] = count;
-            rt[RT_HEAD] = g;
-            rt[RT_PAGE0] = std::min(c * per, pages);
-            rt[RT_PAGE1] = std::min((c + 1) * per, pages);
-            rt[RT_DEST] = nc > 1 ? (int32_t)(chunk_base + ((int64_t)g * nc + c) * count) : -1;
-          }
+          for (int32_t g = 0; g < H; ++g, rec += next_head) std::memcpy(rt + g * RTILE_WORDS, &rec, sizeof rec);
         }
         if (nc > 1) {
           for (int32_t g = 0; g < H; ++g, tm += TMERGE_WORDS, ++n_tmerge) {

@@ -107,6 +107,7 @@ struct BatchDesc {
   std::vector<std::pair<int64_t, int32_t>> tile_groups;
   std::vector<int32_t> share_start, share_base, share_k, share_ml, share_nc, member_rows, shared_tiles, qrow_of, groups, grp_members;
   std::vector<int32_t> rtile_order;                          // LIPs whose tokens go to row tiles, longest file first
+  std::vector<int32_t> rtile_pages;                          // pages that every tile of them reads
   std::vector<std::pair<int32_t, int32_t>> tile_lens;        // (steps over the keys, how many such tiles)
   std::vector<int32_t> rows_tmp, row_lip, row_pages, seg_tmp, item_order, item_bin, bin_first, wave_pos;
   std::vector<uint64_t> bin_bits;                            // per load, the bins that carry it (see build_desc)
