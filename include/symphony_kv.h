@@ -289,7 +289,7 @@ int64_t sym_static_scratch_bytes(void);
  *     by the merge of partial results when ranges were divided.
  * Between sym_pred_begin and the last of the n_layers sym_pred_layer calls (or sym_pred_end,
  * which abandons the layers not yet run: their new rows stay unwritten) every call that changes
- * file-system state or reads files is refused with SYM_EBUSY; kv_open, kv_len, kv_pages and
+ * file-system state or reads files, and sym_pred_batch_raw, is refused with SYM_EBUSY; kv_open, kv_len, kv_pages and
  * the other introspection calls work.  A single-layer context may use either these calls or
  * sym_pred_batch; a context with several layers only these.                               */
 int sym_pred_begin(sym_ctx* ctx, int32_t n_lips, const sym_kv* kv, const int32_t* n_tokens,

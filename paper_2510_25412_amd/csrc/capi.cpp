@@ -97,6 +97,7 @@ struct sym_ctx {
   std::vector<uint8_t*> host_chunks;   // pinned memory of the host slots, kHostChunk pages each
   int64_t pages_offloaded = 0, pages_restored = 0;
   BatchDesc desc;
+  BatchDesc shown;                             // what sym_build_desc builds
   int32_t desc_hdr[DESC_HEADER_WORDS] = {};   // header of the last descriptor built for a launch (its words lie in pinned memory)
   std::vector<const int32_t*> tables;
   std::vector<int64_t> len_after;
@@ -450,8 +451,8 @@ int run_moves(sym_ctx* c, hipStream_t st) {
   return SYM_OK;
 }
 
-// Builds c->desc from caller-supplied page tables (lock held).  Returns words or a negative status.
-int64_t desc_from_flat(sym_ctx* c, int32_t n_lips, const int32_t* n_tokens, const int32_t* page_table_flat,
+// Builds a descriptor from caller-supplied page tables (lock held).  Returns words or a negative status.
+int64_t desc_from_flat(sym_ctx* c, BatchDesc* d, int32_t n_lips, const int32_t* n_tokens, const int32_t* page_table_flat,
                        const int64_t* pt_offsets, const int64_t* lengths, const std::function<int32_t*(int64_t)>& alloc) {
   c->tables.resize(n_lips);
   for (int32_t b = 0; b < n_lips; ++b) {
@@ -463,12 +464,10 @@ int64_t desc_from_flat(sym_ctx* c, int32_t n_lips, const int32_t* n_tokens, cons
       if (c->tables[b][i] < 0 || c->tables[b][i] >= c->cfg.n_pages) return fail(c, SYM_EINVAL, "page id out of range");
   }
   const DescParams prm = desc_params(c, partial_slots(c), c->cfg.device < 0 ? 0x7fffffff : (c->cfg.workspace_bytes - partial_bytes(c)) / 4 - 64);
-  c->desc.alloc = alloc;
-  const int rc = build_desc(prm, n_lips, n_tokens, lengths, c->tables.data(), &c->desc);
-  c->desc.alloc = nullptr;
-  if (rc) return fail(c, rc, "build_desc: bad batch or no room for the descriptor");
-  std::memcpy(c->desc_hdr, c->desc.words, sizeof(c->desc_hdr));
-  return c->desc.n_words;
+  d->alloc = alloc;
+  const int rc = build_desc(prm, n_lips, n_tokens, lengths, c->tables.data(), d);
+  d->alloc = nullptr;
+  return rc ? fail(c, rc, "build_desc: bad batch or no room for the descriptor") : d->n_words;
 }
 
 // The host half of a batch (lock held, arguments checked): validates, reserves staging, commits the append, builds the
@@ -831,12 +830,13 @@ int64_t sym_build_desc(sym_ctx* c, int32_t n_lips, const int32_t* n_tokens, cons
                        const int64_t* pt_offsets, const int64_t* lengths, int32_t* words_out, int64_t cap) {
   if (!c || n_lips < 0 || (n_lips > 0 && (!n_tokens || !page_table_flat || !pt_offsets || !lengths))) return SYM_EINVAL;
   std::lock_guard<std::mutex> lk(c->mu);
-  const int64_t n = desc_from_flat(c, n_lips, n_tokens, page_table_flat, pt_offsets, lengths, [c](int64_t words) {
+  BatchDesc* d = &c->shown;                 // not c->desc: the layers of an open batch still run by that
+  const int64_t n = desc_from_flat(c, d, n_lips, n_tokens, page_table_flat, pt_offsets, lengths, [c](int64_t words) {
     c->scratch_words.resize((size_t)words);
     return c->scratch_words.data();
   });
   if (n < 0) return n;
-  if (words_out) copy_bytes(words_out, c->desc.words, (size_t)std::min(n, std::max<int64_t>(cap, 0)) * 4);
+  if (words_out) copy_bytes(words_out, d->words, (size_t)std::min(n, std::max<int64_t>(cap, 0)) * 4);
   return n;
 }
 
@@ -1000,12 +1000,14 @@ int sym_pred_batch_raw(sym_ctx* c, int32_t n_lips, const int32_t* n_tokens, cons
   if (!q || !out || !n_tokens || !page_table_flat || !pt_offsets || !lengths) return SYM_EINVAL;
   std::lock_guard<std::mutex> lk(c->mu);
   if (c->cfg.device < 0) return fail(c, SYM_EINVAL, "host-only context");
+  if (int busy = refuse_if_open(c, "pred_batch_raw")) return busy;      // it would take the workspace from under the open batch
   int si = -1;
-  const int64_t dwords = desc_from_flat(c, n_lips, n_tokens, page_table_flat, pt_offsets, lengths, [&](int64_t words) -> int32_t* {
+  const int64_t dwords = desc_from_flat(c, &c->desc, n_lips, n_tokens, page_table_flat, pt_offsets, lengths, [&](int64_t words) -> int32_t* {
     if (align_up(words * 4, 256) + partial_bytes(c) > c->cfg.workspace_bytes) return nullptr;
     return (stage_reserve(c, words + 4) || stage_acquire(c, words + 4, &si)) ? nullptr : c->stage[si];
   });
   if (dwords < 0) return (int)dwords;
+  std::memcpy(c->desc_hdr, c->desc.words, sizeof(c->desc_hdr));
   hipStream_t st = (hipStream_t)stream;
   int rc;
   if ((rc = launch_prologue(c, si, dwords, nullptr, 0, nullptr, 0, nullptr, nullptr, st)) || (rc = stage_release(c, si, st))) return rc;

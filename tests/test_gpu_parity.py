@@ -1039,6 +1039,41 @@ def test_finer_cut_of_long_ranges_by_the_layers_that_share_a_plan(Hq, Hkv, layer
     sess.close()
 
 
+@pytest.mark.parametrize("batch", [[(0, 1), (1, 1)], [(0, 40), (1, 1)], [(0, 3), (1, 1)]])
+def test_other_descriptors_leave_an_open_batch_alone(batch):
+    """Between sym_pred_begin and the last layer: sym_build_desc may be called and changes nothing for the layers to come;
+    sym_pred_batch_raw, which needs the workspace that the open batch lies in, is refused."""
+    drv = _hip()
+    from paper_2510_25412_amd import binding
+    wl = synth.custom(f"open_{batch[0][1]}", synth.Shape(32, 8, 128, 16, synth.BF16), [("new", 300), ("new", 1500)], batch, 256, seed=31)
+    ref, osess = run_oracle(wl, dtype=np.float64)
+    sess = drv.HipSession(wl.shape, wl.n_pages, wl.free_order, max_lips=8, max_tokens=2048, max_entries=1024, poison=True, n_layers=3)
+    sess.setup(wl.setup_ops())
+    db = sess.upload_batch(wl.batch())
+    got = [torch.empty_like(db["out"]) for _ in range(3)]
+    tables = [sess.pages(0)[:1]] * 5
+    other = ([1] * 5, np.concatenate(tables).astype(np.int32), np.arange(6, dtype=np.int64), [9] * 5)
+    q5 = torch.zeros((5, 32, 128), dtype=torch.bfloat16, device="cuda")
+    o5 = torch.empty((5, 32, 128), dtype=torch.float32, device="cuda")
+    raw = lambda: sess.ctx.pred_batch_raw(*other, q5, o5, sess.stream)  # noqa: E731
+    sess.ctx.pred_begin(db["kv"], db["n_tokens"], sess.stream)
+    for l in (0, 2, 1):
+        sess.ctx.pred_layer(l, db["q"], db["k_new"], db["v_new"], got[l], sess.stream)
+        assert len(sess.ctx.build_desc(*other)) > 0
+        if l != 1:
+            with pytest.raises(binding.SymError) as e:
+                raw()
+            assert e.value.code == binding.SYM_EBUSY
+    torch.cuda.synchronize()
+    for l in range(3):
+        check_outputs(got[l].cpu().numpy(), ref)
+    check_state(wl, sess, osess)
+    raw()                                                              # the batch is complete
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(o5).all())
+    sess.close()
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,dtype,multi", [(32, 8, 128, synth.BF16, 1), (32, 8, 128, synth.BF16, 3), (8, 8, 64, synth.F32, 3),
                                                   (64, 8, 128, synth.BF16, 1), (16, 8, 128, synth.BF16, 1)])
 def test_layered_pred_layer_by_layer_against_the_oracle(Hq, Hkv, D, dtype, multi):
