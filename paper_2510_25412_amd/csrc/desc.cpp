@@ -67,13 +67,13 @@ int64_t chunk_steps(const std::vector<std::pair<int32_t, int32_t>>& lens, int64_
 // the lines are where they were for the coarser cut, and have not been weighed against the finer one over numbers of files and heads.
 constexpr int64_t kWholePages = 24, kWholePagesWide = 32;
 // A small batch of long ranges is cut finer than min_units only where that saves more in the layers of the step than the longer plan
-// costs once (1 to 4 us of planning and upload).  Vector units: layers x query heads per kv head, the work per page, reach kSpreadLayers.
-// Matrix cores: layers x query columns (heads x tokens of a row) x kSpreadUnits reach the pages of the batch.  Whole steps, four pages
-// per wavefront / the finer cut: 1 head per kv head, 10 files of 600 tokens on 2 kv heads, 1 layer 18.9 / 21.7 us, 4 layers 46.8 / 50.5,
-// 16 layers 133.7 / 130.8; 4 heads, a file of 1000 tokens on 8 kv heads 17.9 / 20.0, 2 layers 29.4 / 31.3, 4 layers 53.2 / 47.3; 8 heads, 600
-// tokens on 8 kv heads 19.1 / 18.3, 2000 tokens 19.5 / 20.1, four of 900 20.3 / 22.5; 4 tokens of 4 heads on 700 19.9 / 18.7, on four of
-// 900 21.0 / 22.7, 4 layers 73.2 / 71.6.
-constexpr int64_t kSpreadLayers = 16, kSpreadUnits = 64;
+// costs once (1 to 4 us of planning and upload).  Matrix cores: layers x query columns (heads x tokens of a row) x kSpreadUnits reach the
+// pages of the batch.  Vector units: layers x query heads per kv head, the work per page, reach kSpreadLayers or a 16th of the pages.
+// Whole steps, four pages per wavefront / the finer cut: 1 head per kv head, 10 files of 600 tokens on 2 kv heads, 1 layer 18.9 / 21.7
+// us, 4 layers 46.8 / 50.5, 16 layers 133.7 / 130.8; 4 heads, a file of 1000 tokens on 8 kv heads 17.9 / 20.0, 2 layers 29.4 / 31.3, 3 layers
+// 41.0 / 39.0, 4 layers 53.2 / 47.3, on 1 kv head 2 layers, alone, 43.3 / 39.8; 8 heads, 600 tokens on 8 kv heads 19.1 / 18.3, 2000 tokens
+// 19.5 / 20.1, four of 900 20.3 / 22.5; 4 tokens of 4 heads on 700 19.9 / 18.7, on four of 900 21.0 / 22.7, 4 layers 73.2 / 71.6.
+constexpr int64_t kSpreadLayers = 12, kSpreadUnits = 64;
 // bf16 tiles, in steps of a 32-key block: what the start and the end of a tile cost, and the merge launch.  196 random prompt batches
 // whose plan some setting changes, attention and merge together, against whole tiles: 0.82 of the time, one more than 4 % slower (6 %).  A
 // start of 6: 0.81, five slower, by up to 12 %; a merge of 8: 0.79, ten slower.
@@ -421,7 +421,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
     // serves few layers (kSpreadLayers).
     int64_t upw = prm.min_units_per_wave;
     const int64_t gain = (int64_t)prm.layers * G * (mfma_bins ? max_nt : 1);
-    if (small_decode && longest_range > kWholePagesWide && (mfma_bins ? gain * kSpreadUnits >= total_units : gain >= kSpreadLayers)) {
+    if (small_decode && longest_range > kWholePagesWide && (gain * (mfma_bins ? kSpreadUnits : kSpreadUnits / 4) >= total_units || (!mfma_bins && gain >= kSpreadLayers))) {
       const int64_t trip = 16 * W, most = mfma_bins ? trip : 2 * trip;
       int64_t fewest = (longest_range + most - 1) / most;
       if (mfma_bins || longest_range > trip) fewest = std::max<int64_t>(fewest, 2);
