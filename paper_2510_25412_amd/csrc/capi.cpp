@@ -399,8 +399,12 @@ uint8_t* host_slot(const sym_ctx* c, int32_t s) { return c->host_chunks[s / kHos
 
 constexpr int64_t kSwapChunk = 1 << 18;                               // pages per swap launch
 int64_t swap_stage_words(int64_t pages) { return 4 * std::min(pages, kSwapChunk); }
-int64_t move_chunk(const sym_ctx* c) { return std::min<int64_t>((c->cfg.workspace_bytes / 4 - 64) / 2, 1 << 20); }   // tokens per move launch
-int64_t move_stage_words(const sym_ctx* c, int64_t tokens) { return 2 * std::min(tokens, std::max<int64_t>(move_chunk(c), 0)) + 4; }
+constexpr int kPageTokens = 16;                                       // page_tokens of every configuration that sym_init accepts
+constexpr int64_t kMoveChunk = 1 << 16;                               // destination pages per move launch
+// words that the moves of `tokens` tokens into `files` new files may stage: P source slots and the destination per page
+int64_t move_stage_words(const sym_ctx* c, int64_t tokens, int64_t files) {
+  return std::min(tokens / c->cfg.page_tokens + files, kMoveChunk) * (c->cfg.page_tokens + 1);
+}
 
 // Carries out the page copies of c->splan ((page, slot) pairs when to_host, (slot, page) otherwise).
 int run_swaps(sym_ctx* c, bool to_host, hipStream_t st) {
@@ -429,24 +433,32 @@ int run_swaps(sym_ctx* c, bool to_host, hipStream_t st) {
   return SYM_OK;
 }
 
-// Carries out the copies of c->gplan on the device: the move list goes through pinned staging
-// into the workspace (bulk copy by the prologue kernel), chunk by chunk, then the move kernel.
+// Carries out the copies of c->gplan on the device, chunk by chunk: the move kernel reads its list from pinned staging.
 int run_moves(sym_ctx* c, hipStream_t st) {
-  const std::vector<int32_t>& mv = c->gplan.moves;
-  const int64_t n = (int64_t)mv.size() / 2;
-  const int64_t cap = move_chunk(c);
-  for (int64_t off = 0; off < n; off += cap) {
-    const int64_t cnt = std::min(cap, n - off);
+  const std::vector<GatherPlan::Fill>& fills = c->gplan.fills;
+  const int64_t n = (int64_t)fills.size();
+  const int P = c->cfg.page_tokens;
+  for (int64_t off = 0; off < n; off += kMoveChunk) {
+    const int64_t cnt = std::min(kMoveChunk, n - off);
     int si, rc;
-    if ((rc = stage_acquire(c, 2 * cnt + 4, &si))) return rc;
-    copy_bytes(c->stage[si], mv.data() + 2 * off, (size_t)cnt * 8);
-    if ((rc = launch_prologue(c, si, 2 * cnt, nullptr, 0, nullptr, 0, nullptr, nullptr, st)) || (rc = stage_release(c, si, st))) return rc;
-    for (int32_t l = 0; l < c->n_layers; ++l) {
-      MoveArgs ma{pool_of(c, l), c->page_bytes, (const int32_t*)c->cfg.workspace, cnt, c->cfg.n_kv_heads};
+    if ((rc = stage_acquire(c, cnt * (P + 1), &si))) return rc;
+    int32_t* src = c->stage[si];
+    int32_t* dst = src + cnt * P;
+    for (int64_t i = 0; i < cnt; ++i) {
+      const GatherPlan::Fill& f = fills[(size_t)(off + i)];
+      const int32_t tokens = f.dst % P + 1;
+      const int32_t* from = c->gplan.src.data() + f.src;
+      dst[i] = f.dst;
+      if (tokens == kPageTokens) std::memcpy(src + i * kPageTokens, from, kPageTokens * 4);      // (a known length: four moves)
+      else std::memcpy(src + i * P, from, (size_t)tokens * 4);
+    }
+    MoveArgs ma{(uint8_t*)c->cfg.pool, c->page_bytes, c->layer_bytes, src, dst, (int32_t)cnt, c->n_layers, c->cfg.n_kv_heads};
+    {
       Timed t(c, SYM_K_MOVE, st);
       hipError_t e = launch_move(ma, st);
       if (e != hipSuccess) return fail_hip(c, e, "move launch");
     }
+    if ((rc = stage_release(c, si, st))) return rc;
   }
   return SYM_OK;
 }
@@ -881,7 +893,7 @@ int sym_kv_extract(sym_ctx* c, int32_t n_files, const sym_kv* src, const int64_t
     need += k;
   }
   if (need > c->fs->free_pages()) return fail(c, SYM_ENOSPC, "page pool exhausted");
-  if (int rc = stage_reserve(c, move_stage_words(c, idx_off[n_files] - idx_off[0]))) return rc;      // before any state change
+  if (int rc = stage_reserve(c, move_stage_words(c, idx_off[n_files] - idx_off[0], n_files))) return rc;      // before any state change
   for (int32_t i = 0; i < n_files; ++i) out[i] = c->fs->gather_commit(&c->gplan, i);
   return c->cfg.device < 0 ? SYM_OK : run_moves(c, (hipStream_t)stream);
 }
@@ -892,7 +904,7 @@ sym_kv sym_kv_merge(sym_ctx* c, int32_t m, const sym_kv* files, void* stream) {
   if (int busy = refuse_if_open(c, "kv_merge")) return busy;
   int64_t tokens = 0;
   for (int32_t i = 0; i < m; ++i) tokens += std::max<int64_t>(c->fs->len(files[i]), 0);
-  if (int rc = stage_reserve(c, move_stage_words(c, tokens))) return rc;      // before any state change
+  if (int rc = stage_reserve(c, move_stage_words(c, tokens, 1))) return rc;      // before any state change
   const sym_kv h = c->fs->gather(m, files, nullptr, nullptr, &c->gplan, &c->err);
   if (h < 0 || c->cfg.device < 0) return h;
   const int rc = run_moves(c, (hipStream_t)stream);
@@ -956,8 +968,14 @@ int64_t sym_last_swaps(sym_ctx* c, int32_t* out, int64_t cap) {
 int64_t sym_last_moves(sym_ctx* c, int32_t* out, int64_t cap) {
   if (!c || cap < 0) return SYM_EINVAL;
   std::lock_guard<std::mutex> lk(c->mu);
-  const int64_t n = (int64_t)c->gplan.moves.size() / 2;
-  if (out) copy_bytes(out, c->gplan.moves.data(), (size_t)std::min(n, cap) * 8);
+  const int32_t P = c->cfg.page_tokens;
+  int64_t n = 0;
+  for (const GatherPlan::Fill& f : c->gplan.fills)
+    for (int32_t t = 0; t <= f.dst % P; ++t, ++n)
+      if (out && n < cap) {
+        out[2 * n] = c->gplan.src[(size_t)f.src + t];
+        out[2 * n + 1] = f.dst / P * P + t;
+      }
   return n;
 }
 

@@ -2589,20 +2589,29 @@ __global__ void gather_kernel(GatherArgs a, uint8_t* k_out, uint8_t* v_out) {
   *(uint4*)dst = *(const uint4*)src;
 }
 
-// extract / merge (paper section 4.2): K and V rows of whole tokens copied from one slot of the
-// pool to another, bit for bit.  A token is Hkv * 4 pieces of 128 bytes (kv head, K/V, row half);
-// a thread moves 16 bytes, eight neighbouring threads one piece, so every access is a full
-// 128-byte line.  Sources are pages of existing files, destinations fresh pages: disjoint.
+// extract / merge (paper section 4.2): K and V rows of whole tokens copied into fresh pages, bit for bit.  A workgroup fills one
+// page of one layer.  A thread owns one token and one of the eight 16-byte chunks of a 128-byte piece, and walks the pieces (kv
+// head, K/V, row half) with all its loads in flight: stores are a page from end to end, loads whole 128-byte lines.  Its source slot
+// and the page come straight from pinned host memory (a wavefront's are one line): copied to the device first, as pairs of slots, they took a
+// launch of 16 us.  Sources are pages of existing files, destinations fresh pages: disjoint.  Bound: HBM, read + write.
+// About half of the tokens of 64 files of 512..4096: 16 + 104 us of kernels -> 108 (5.6 TB/s read + written; eight loads in flight 115,
+// four 117, nontemporal stores 121; the list through LDS 110; several workgroups to a page 114 with two or four, 142 with eight).
+template <int U>
 __global__ __launch_bounds__(256) void move_kernel(MoveArgs a) {
-  const int per_tok = a.Hkv * 32;                                   // 16-byte chunks per token
-  const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (tid >= a.n_tokens * per_tok) return;
-  const int64_t t = tid / per_tok;
-  const int x = (int)(tid % per_tok);
-  const int s = a.moves[2 * t], d = a.moves[2 * t + 1];
-  const int64_t in_page = (int64_t)(x >> 3) * (kP * kHalfBytes) + (x & 7) * 16;
-  const u32x4_t v = __builtin_nontemporal_load((const u32x4_t*)(a.pool + (int64_t)(s / kP) * a.page_bytes + in_page + (s % kP) * kHalfBytes));
-  *(u32x4_t*)(a.pool + (int64_t)(d / kP) * a.page_bytes + in_page + (d % kP) * kHalfBytes) = v;
+  constexpr int kPiece = kP * kHalfBytes;
+  const int tid = threadIdx.x, t = (tid >> 3) & (kP - 1), first = tid >> 7, chunk = (tid & 7) * 16;
+  const int slot = a.src[(int64_t)blockIdx.x * kP + t], dst = a.dst[blockIdx.x];
+  if (t > dst % kP) return;                                         // the page's last tokens do not exist
+  uint8_t* pool = a.pool + (int64_t)blockIdx.y * a.layer_bytes;
+  const uint8_t* s = pool + (int64_t)(slot / kP) * a.page_bytes + first * kPiece + (slot % kP) * kHalfBytes + chunk;
+  uint8_t* d = pool + (int64_t)(dst / kP) * a.page_bytes + first * kPiece + t * kHalfBytes + chunk;
+  for (int p = 0; p < a.Hkv * 2; p += U) {                          // two pieces per pass of the workgroup, U passes at a time
+    u32x4_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load((const u32x4_t*)(s + (int64_t)(p + u) * (2 * kPiece)));
+#pragma unroll
+    for (int u = 0; u < U; ++u) *(u32x4_t*)(d + (int64_t)(p + u) * (2 * kPiece)) = v[u];
+  }
 }
 
 // offload / restore (paper section 4.3): whole pages between the pool and pinned host memory, over
@@ -2884,10 +2893,12 @@ hipError_t launch_gather(const GatherArgs& a, void* k_out, void* v_out, hipStrea
 }
 
 hipError_t launch_move(const MoveArgs& a, hipStream_t st) {
-  if (a.n_tokens <= 0) return hipSuccess;
-  const int64_t blocks = (a.n_tokens * a.Hkv * 32 + 255) / 256;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(move_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
+  if (a.n_pages <= 0) return hipSuccess;
+  if (a.n_layers < 1 || a.n_layers > 65535) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)a.n_pages, (unsigned)a.n_layers), block(256);
+  if (a.Hkv % 8 == 0) hipLaunchKernelGGL(move_kernel<16>, grid, block, 0, st, a);      // all of a page of 8 kv heads at once
+  else if (a.Hkv % 4 == 0) hipLaunchKernelGGL(move_kernel<8>, grid, block, 0, st, a);
+  else hipLaunchKernelGGL(move_kernel<2>, grid, block, 0, st, a);
   return hipGetLastError();
 }
 

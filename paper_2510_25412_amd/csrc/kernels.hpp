@@ -97,9 +97,10 @@ struct GatherArgs {
 struct MoveArgs {
   uint8_t* pool;
   int64_t page_bytes;
-  const int32_t* moves;         // device [n_tokens][2]: source, destination token slot (page * P + slot)
-  int64_t n_tokens;
-  int32_t Hkv;
+  int64_t layer_bytes;
+  const int32_t* src;           // pinned host [n_pages][P]: source slots (page * P + slot) of the tokens of a destination page
+  const int32_t* dst;           // pinned host [n_pages]: destination page * P + tokens - 1
+  int32_t n_pages, n_layers, Hkv;
 };
 
 struct SwapArgs {

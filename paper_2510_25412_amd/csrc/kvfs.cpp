@@ -284,7 +284,7 @@ int Kvfs::append(int32_t n, const int32_t* handles, const int32_t* n_tokens, App
 
 int64_t Kvfs::gather_need(int32_t n_seg, const int32_t* seg_handle, const int64_t* seg_off, const int64_t* idx, GatherPlan* plan,
                           std::string* err) {
-  std::vector<int32_t>& src = plan->src;
+  auto& src = plan->src;
   std::vector<int32_t>& shared = plan->shared;
   const size_t s0 = src.size(), h0 = shared.size();
   plan->bounds.push_back((int64_t)s0);
@@ -348,18 +348,12 @@ int32_t Kvfs::gather_commit(GatherPlan* plan, int32_t k) {
   const int64_t s0 = plan->bounds[2 * k], h0 = plan->bounds[2 * k + 1];
   const int64_t n = (last ? (int64_t)plan->src.size() : plan->bounds[2 * k + 2]) - s0;
   const int64_t np = (last ? (int64_t)plan->shared.size() : plan->bounds[2 * k + 3]) - h0;
-  const int32_t* src = plan->src.data() + s0;
   const int32_t* shared = plan->shared.data() + h0;
   const int32_t id = new_file();
   std::vector<int32_t>& pages = files_[id].pages;
   pages.reserve((size_t)np);
   int64_t moved = 0;                                       // tokens of the pages that are copied
-  for (int64_t d = 0; d < np; ++d)
-    if (shared[d] < 0) moved += std::min<int64_t>(P_, n - d * P_);
-  const size_t at = plan->moves.size();
-  plan->moves.resize(at + (size_t)(2 * moved));
-  int32_t* mv = plan->moves.data() + at;
-  for (int64_t d = 0; d < np; ++d, src += P_) {
+  for (int64_t d = 0; d < np; ++d) {
     if (shared[d] >= 0) {
       ++refcount_[shared[d]];
       pages.push_back(shared[d]);
@@ -369,10 +363,8 @@ int32_t Kvfs::gather_commit(GatherPlan* plan, int32_t k) {
     }
     const int32_t dst = alloc_page(), c = (int32_t)std::min<int64_t>(P_, n - d * P_);
     pages.push_back(dst);
-    for (int32_t t = 0; t < c; ++t, mv += 2) {
-      mv[0] = src[t];
-      mv[1] = dst * P_ + t;
-    }
+    plan->fills.push_back({s0 + d * P_, dst * P_ + c - 1});
+    moved += c;
   }
   tokens_moved += moved;
   files_[id].len = n;

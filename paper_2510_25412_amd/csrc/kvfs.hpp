@@ -4,9 +4,12 @@
 #pragma once
 #include <cstdint>
 #include <functional>
+#include <memory>
+#include <new>
 #include <queue>
 #include <string>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 namespace symkv {
@@ -74,15 +77,32 @@ struct AppendPlan {
   void clear() { cow.clear(); slots.clear(); copies_first = false; }
 };
 
+// Grows without clearing: what a resize adds is written right after (an extract's 76 000 slots are 300 KB).
+template <typename T>
+struct Unset : std::allocator<T> {
+  template <typename U>
+  struct rebind {
+    typedef Unset<U> other;
+  };
+  template <typename U>
+  void construct(U* p) { ::new ((void*)p) U; }
+  template <typename U, typename... A>
+  void construct(U* p, A&&... a) { ::new ((void*)p) U(std::forward<A>(a)...); }
+};
+
 // Result of building a file out of tokens of existing files (extract / merge).
 struct GatherPlan {
-  std::vector<int32_t> moves;     // (source, destination) pairs of token slots (page * P + slot) to copy
+  struct Fill {
+    int64_t src;                  // where its tokens begin in src
+    int32_t dst;                  // page * P + tokens in it - 1
+  };
+  std::vector<Fill> fills;        // the fresh pages
   int64_t pages_shared = 0;       // destination pages that reference an existing page instead
   // scratch of the planning pass, one stretch per planned file
-  std::vector<int32_t> src;       // source slot of every destination token
+  std::vector<int32_t, Unset<int32_t>> src;   // source slot of every destination token
   std::vector<int32_t> shared;    // per destination page, the page it references or -1
   std::vector<int64_t> bounds;    // per planned file: where its stretch of src / of shared begins
-  void reset() { moves.clear(); src.clear(); shared.clear(); bounds.clear(); pages_shared = 0; }
+  void reset() { fills.clear(); src.clear(); shared.clear(); bounds.clear(); pages_shared = 0; }
 };
 
 // Page copies of an offload ((page, host slot) pairs, device to host) or of a restore ((host
@@ -115,10 +135,10 @@ class Kvfs {
   // after the other.  Segment s takes from file seg_handle[s]: with idx, the tokens
   // idx[seg_off[s]] .. idx[seg_off[s+1] - 1] (any order, repeats allowed); without, the whole
   // file in order.  A destination page that is slots 0, 1, 2, ... of one existing page
-  // references that page; every other one is a fresh page and its tokens go into plan->moves.
+  // references that page; every other one is a fresh page and goes into plan->fills.
   // gather_need validates one file and adds it to the plan's scratch; returns the fresh pages it
   // needs or a negative status.  gather_commit builds planned file k from that scratch (the
-  // caller has checked that the pages are free), appends its copies to plan->moves and returns
+  // caller has checked that the pages are free), appends its fresh pages to plan->fills and returns
   // the handle.  gather = one file, both steps, with the free-page check (on error nothing changed).
   int64_t gather_need(int32_t n_seg, const int32_t* seg_handle, const int64_t* seg_off, const int64_t* idx, GatherPlan* plan,
                       std::string* err);
