@@ -108,6 +108,7 @@ struct sym_ctx {
   hipEvent_t stage_ev[kStages];
   bool stage_pending[kStages] = {false, false, false, false};
   int stage_next = 0;
+  int64_t releases = 0;                // launches that were the last to read a staging buffer
   int fail_staging = 0;                // test hook: this many coming staging reservations fail (sym_test_fail_staging)
   uint8_t* static_scratch = nullptr;   // this device's copy of the library's file-scope scratch array (sym_pred_batch_static)
   // profiling
@@ -351,11 +352,36 @@ int launch_attention(sym_ctx* c, const Scratch& ws, int64_t blob_words, const vo
   return SYM_OK;
 }
 
+// Records the event that lets the staging buffer be reused: where it is not a launch's own completion.
+int stage_release(sym_ctx* c, int si, hipStream_t st) {
+  hipError_t e = hipEventRecord(c->stage_ev[si], st);
+  if (e != hipSuccess) return fail_hip(c, e, "hipEventRecord(stage)");
+  c->stage_pending[si] = true;
+  return SYM_OK;
+}
+// The same as the completion of a launch: done(si) is the event to hand to the launch, released(si) follows a launch that went well.
+// Of kRecordEvery such launches one records its event as a packet of its own: the runtime lets go of what it keeps about finished
+// launches only when it meets one (or a wait of the host's), and 60 000 launches kept took 4 ms of the next wait.
+constexpr int64_t kRecordEvery = 64;
+struct StageDone {
+  sym_ctx* c;
+  int si;                      // staging buffer that nothing reads behind the launch; -1: none
+  bool record;
+  StageDone(sym_ctx* ctx, int i) : c(ctx), si(i), record(i >= 0 && ++ctx->releases % kRecordEvery == 0) {}
+  hipEvent_t event() const { return si >= 0 && !record ? c->stage_ev[si] : nullptr; }
+  int launched(hipStream_t st) const {
+    if (record) return stage_release(c, si, st);
+    if (si >= 0) c->stage_pending[si] = true;
+    return SYM_OK;
+  }
+};
+
 // One prologue launch: the first copy_words words of the pinned buffer c->stage[si] (the descriptor, or the whole blob of
 // a batch) are copied to `dev_words` (default: the start of the workspace); `n_cow` page copies from the list `cow` and the
 // append of `n_tokens` rows k, v by the slot map `slots` (both lists in pinned or device memory) go to layer `layer`.
+// release: the staging buffer that nothing reads behind this launch (-1: none).
 int launch_prologue(sym_ctx* c, int si, int64_t copy_words, const int32_t* cow, int n_cow, const int32_t* slots, int32_t n_tokens,
-                    const void* k, const void* v, hipStream_t st, uint8_t* dev_words = nullptr, bool timed = true, int32_t layer = 0) {
+                    const void* k, const void* v, hipStream_t st, int release, uint8_t* dev_words = nullptr, bool timed = true, int32_t layer = 0) {
   PrologueArgs a;
   a.pool = pool_of(c, layer);
   a.page_bytes = c->page_bytes;
@@ -370,17 +396,12 @@ int launch_prologue(sym_ctx* c, int si, int64_t copy_words, const int32_t* cow, 
   a.Hkv = c->cfg.n_kv_heads;
   a.n_cow = n_cow;
   a.append_blocks = a.append_tokens = a.copy_blocks = 0;
+  const StageDone done(c, release);
+  a.done = done.event();
   Timed t(c, SYM_K_PROLOGUE, st, false, timed);
   hipError_t e = symkv::launch_prologue(a, st);
   if (e != hipSuccess) return fail_hip(c, e, "prologue launch");
-  return SYM_OK;
-}
-// Records the event that lets the staging buffer be reused.
-int stage_release(sym_ctx* c, int si, hipStream_t st) {
-  hipError_t e = hipEventRecord(c->stage_ev[si], st);
-  if (e != hipSuccess) return fail_hip(c, e, "hipEventRecord(stage)");
-  c->stage_pending[si] = true;
-  return SYM_OK;
+  return done.launched(st);
 }
 
 // Host slots live in pinned chunks of kHostChunk pages each, allocated when first needed.
@@ -452,13 +473,12 @@ int run_moves(sym_ctx* c, hipStream_t st) {
       if (tokens == kPageTokens) std::memcpy(src + i * kPageTokens, from, kPageTokens * 4);      // (a known length: four moves)
       else std::memcpy(src + i * P, from, (size_t)tokens * 4);
     }
-    MoveArgs ma{(uint8_t*)c->cfg.pool, c->page_bytes, c->layer_bytes, src, dst, (int32_t)cnt, c->n_layers, c->cfg.n_kv_heads};
-    {
-      Timed t(c, SYM_K_MOVE, st);
-      hipError_t e = launch_move(ma, st);
-      if (e != hipSuccess) return fail_hip(c, e, "move launch");
-    }
-    if ((rc = stage_release(c, si, st))) return rc;
+    const StageDone done(c, si);
+    MoveArgs ma{(uint8_t*)c->cfg.pool, c->page_bytes, c->layer_bytes, src, dst, (int32_t)cnt, c->n_layers, c->cfg.n_kv_heads, done.event()};
+    Timed t(c, SYM_K_MOVE, st);
+    hipError_t e = launch_move(ma, st);
+    if (e != hipSuccess) return fail_hip(c, e, "move launch");
+    if ((rc = done.launched(st))) return rc;
   }
   return SYM_OK;
 }
@@ -576,13 +596,11 @@ int pred_batch_locked(sym_ctx* c, int32_t n_lips, const sym_kv* kv, const int32_
   const int32_t* slots = c->stage[pb.si] + pb.slots_off;
   int n_cow = pb.n_cow;
   if (c->plan.copies_first) {       // an append of this batch overwrites slots that a copy of this batch reads: copies in a launch of their own
-    if ((rc = launch_prologue(c, pb.si, 0, cow, n_cow, nullptr, 0, nullptr, nullptr, st, ws.base, !no_alloc))) return rc;
+    if ((rc = launch_prologue(c, pb.si, 0, cow, n_cow, nullptr, 0, nullptr, nullptr, st, -1, ws.base, !no_alloc))) return rc;
     n_cow = 0;
   }
   // descriptor to the device; page copies and the appends the attention kernel does not do itself, read from the pinned buffer
-  if ((rc = launch_prologue(c, pb.si, pb.dwords, cow, n_cow, slots, pb.n_append, k_new, v_new, st, ws.base, !no_alloc)) ||
-      (rc = stage_release(c, pb.si, st)))
-    return rc;
+  if ((rc = launch_prologue(c, pb.si, pb.dwords, cow, n_cow, slots, pb.n_append, k_new, v_new, st, pb.si, ws.base, !no_alloc))) return rc;
   ++c->pred_batches;
   rc = launch_attention(c, used, pb.words, q, out, st, !no_alloc, k_new, v_new);
   const auto t_end = std::chrono::steady_clock::now();
@@ -649,7 +667,8 @@ int sym_init(const sym_config* cfg, sym_ctx** out) {
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device);
     int n_ev = 0;                                  // staging events created so far
     while (n_ev < kStages && e == hipSuccess)
-      if ((e = hipEventCreateWithFlags(&c->stage_ev[n_ev], hipEventDisableTiming)) == hipSuccess) ++n_ev;
+      // no system fence: the event says that a kernel has read the buffer; nothing the GPU wrote is read on the host behind it
+      if ((e = hipEventCreateWithFlags(&c->stage_ev[n_ev], hipEventDisableTiming | hipEventDisableSystemFence)) == hipSuccess) ++n_ev;
     // for the entry point that allocates nothing: this device's address of the library's static scratch
     // array (the device is current here), and staging buffers that hold its largest descriptor
     if (e == hipSuccess) e = static_scratch_address(cfg->device, &c->static_scratch);
@@ -871,9 +890,9 @@ int sym_kv_append(sym_ctx* c, sym_kv kv, int32_t n, const void* k, const void* v
   const int64_t layer_rows = (int64_t)n * c->cfg.n_kv_heads * 256;           // bytes of one layer's rows in k and in v
   for (int32_t l = 0; l < c->n_layers; ++l)
     if ((rc = launch_prologue(c, si, 0, c->stage[si], (int)(c->plan.cow.size() / 3), c->stage[si] + c->plan.cow.size(), n,
-                              (const uint8_t*)k + l * layer_rows, (const uint8_t*)v + l * layer_rows, st, nullptr, true, l)))
+                              (const uint8_t*)k + l * layer_rows, (const uint8_t*)v + l * layer_rows, st, l == c->n_layers - 1 ? si : -1, nullptr, true, l)))
       return rc;
-  return stage_release(c, si, st);
+  return SYM_OK;
 }
 
 int sym_kv_extract(sym_ctx* c, int32_t n_files, const sym_kv* src, const int64_t* idx_off, const int64_t* idx, sym_kv* out,
@@ -1028,7 +1047,7 @@ int sym_pred_batch_raw(sym_ctx* c, int32_t n_lips, const int32_t* n_tokens, cons
   std::memcpy(c->desc_hdr, c->desc.words, sizeof(c->desc_hdr));
   hipStream_t st = (hipStream_t)stream;
   int rc;
-  if ((rc = launch_prologue(c, si, dwords, nullptr, 0, nullptr, 0, nullptr, nullptr, st)) || (rc = stage_release(c, si, st))) return rc;
+  if ((rc = launch_prologue(c, si, dwords, nullptr, 0, nullptr, 0, nullptr, nullptr, st, si))) return rc;
   ++c->pred_batches;
   return launch_attention(c, workspace_of(c), dwords, q, out, st);
 }
@@ -1044,7 +1063,7 @@ int sym_pred_begin(sym_ctx* c, int32_t n_lips, const sym_kv* kv, const int32_t* 
   if ((rc = pred_plan_locked(c, n_lips, kv, n_tokens, workspace_of(c), false, &pb))) return rc;
   // the whole blob (descriptor, copy list, slot map) goes to the device once; the layers read it there
   hipStream_t st = (hipStream_t)stream;
-  if ((rc = launch_prologue(c, pb.si, pb.words, nullptr, 0, nullptr, 0, nullptr, nullptr, st)) || (rc = stage_release(c, pb.si, st))) return rc;
+  if ((rc = launch_prologue(c, pb.si, pb.words, nullptr, 0, nullptr, 0, nullptr, nullptr, st, pb.si))) return rc;
   OpenPred& o = c->pred;
   o.open = true;
   o.words = pb.words;
@@ -1077,11 +1096,11 @@ int sym_pred_layer(sym_ctx* c, int32_t layer, const void* q, const void* k_new, 
   const int32_t* slots = (const int32_t*)ws.base + o.slots_off;
   int rc, n_cow = o.n_cow;
   if (o.copies_first && n_cow > 0) {
-    if ((rc = launch_prologue(c, -1, 0, cow, n_cow, nullptr, 0, nullptr, nullptr, st, nullptr, true, layer))) return rc;
+    if ((rc = launch_prologue(c, -1, 0, cow, n_cow, nullptr, 0, nullptr, nullptr, st, -1, nullptr, true, layer))) return rc;
     n_cow = 0;
   }
   if (n_cow > 0 || o.n_append > 0)
-    if ((rc = launch_prologue(c, -1, 0, cow, n_cow, slots, o.n_append, k_new, v_new, st, nullptr, true, layer))) return rc;
+    if ((rc = launch_prologue(c, -1, 0, cow, n_cow, slots, o.n_append, k_new, v_new, st, -1, nullptr, true, layer))) return rc;
   rc = launch_attention(c, ws, o.words, q, out, st, true, k_new, v_new, layer);
   if (rc) return rc;
   o.done[layer] = 1;

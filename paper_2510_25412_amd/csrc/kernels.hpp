@@ -85,6 +85,7 @@ struct PrologueArgs {
   int64_t copy_words;
   int32_t n_tokens, Hkv, n_cow;
   int32_t append_blocks, append_tokens, copy_blocks;   // filled by launch_prologue
+  hipEvent_t done;              // completed by the launch, or null
 };
 
 struct GatherArgs {
@@ -101,6 +102,7 @@ struct MoveArgs {
   const int32_t* src;           // pinned host [n_pages][P]: source slots (page * P + slot) of the tokens of a destination page
   const int32_t* dst;           // pinned host [n_pages]: destination page * P + tokens - 1
   int32_t n_pages, n_layers, Hkv;
+  hipEvent_t done;              // completed by the launch, or null
 };
 
 struct SwapArgs {
