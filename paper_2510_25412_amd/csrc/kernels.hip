@@ -2515,37 +2515,48 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void merge_kernel(MergeArgs a)
 // follows.  The three parts touch disjoint bytes (a copy covers slots below r, appends write slots
 // from r on), so they need no ordering among themselves.  Slot map and copy list are read straight
 // from the pinned host buffer: an append workgroup reads its tokens' slots once, in one line, and
-// shares them through LDS (read by every thread for itself they bound the launch: requests over the
-// host link, four per token: a document of 7100 tokens 17.0 -> 15.6 us by events, whole call 17.3 -> 16.2 us = 3.6 TB/s
-// read + written; the mixed batch's 16 600 tokens 39.0 -> 36.5 us).
+// shares them through LDS (a request over the host link takes about 4.6 ns of all of them together: one for every workgroup, not for
+// every thread).  The rows themselves are requested meanwhile, and the next ones before the barrier of a loop would come round.
+// Bound: HBM, read + write.  By rocprofv3's trace, slots before the first row / now: a document of 7100 tokens 13.2 -> 11.8 us
+// (4.9 TB/s read + written), the mixed batch's 16 600 tokens 34.2 -> 26.7; descriptors and few tokens (256 of drafts, 900 of
+// prompts) the same.  The append workgroups come first in the grid (last: the mixed batch 31.9 us, a fork's descriptor 7.6 -> 7.5).
+// Workgroups of 512 threads where each has four tokens or more: 1024 threads 12.1 and 28.1 us, 256 threads 12.9 and 32.4.
 // ---------------------------------------------------------------------------------------
 constexpr int kAppendTokens = 16;        // most tokens per append workgroup
 
-__global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs a) {
+template <int NT>
+__global__ __launch_bounds__(NT) void prologue_kernel(PrologueArgs a) {
   __shared__ int32_t s_slot[kAppendTokens];
   int blk = blockIdx.x;
   if (blk < a.append_blocks) {
     const int t0 = blk * a.append_tokens, n = min(a.append_tokens, a.n_tokens - t0);
-    if ((int)threadIdx.x < n) s_slot[threadIdx.x] = a.slots[t0 + threadIdx.x];
-    __syncthreads();
     const int total = n * a.Hkv * 32;       // 16-byte chunks: token, kv head, K/V, chunk within the row
     const uint8_t* k0 = (const uint8_t*)a.k_new + (int64_t)t0 * a.Hkv * kRowBytes;
     const uint8_t* v0 = (const uint8_t*)a.v_new + (int64_t)t0 * a.Hkv * kRowBytes;
-    for (int x = threadIdx.x; x < total; x += 4 * 256) {
-      u32x4_t v[4];
+    const int my_slot = a.slots[t0 + min((int)threadIdx.x, n - 1)];
+    u32x4_t v[4];
+    auto request = [&](int x) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {         // past the end the last chunk is read again and not stored
-        const int i = min(x + u * 256, total - 1);
+        const int i = min(x + u * NT, total - 1);
         v[u] = *(const u32x4_t*)((((i >> 4) & 1) ? v0 : k0) + (i >> 5) * kRowBytes + (i & 15) * 16);
       }
+    };
+    request(threadIdx.x);                   // under way while the slots come over the host link
+    if ((int)threadIdx.x < n) s_slot[threadIdx.x] = my_slot;
+    __syncthreads();
+    for (int x = threadIdx.x;;) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int i = x + u * 256;
+        const int i = x + u * NT;
         const int th = min(i, total - 1) >> 5, tl = th / a.Hkv, g = th - tl * a.Hkv, slot = s_slot[tl];
         if (i < total && slot >= 0)         // negative: this token is appended by the attention kernel
           *(u32x4_t*)(a.pool + (int64_t)(slot / kP) * a.page_bytes + (int64_t)g * kSlab + ((i >> 4) & 1) * kBlk +
                       ((i & 15) >> 3) * (kP * kHalfBytes) + (slot % kP) * kHalfBytes + (i & 7) * 16) = v[u];
       }
+      x += 4 * NT;
+      if (x >= total) break;
+      request(x);
     }
     return;
   }
@@ -2556,7 +2567,7 @@ __global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs a) {
     uint8_t* d = a.pool + (int64_t)dst * a.page_bytes;
     const int per_seg = r * (kHalfBytes / 16);           // 16-byte chunks per (head, K/V, half)
     const int n_seg = a.Hkv * 4;
-    for (int x = threadIdx.x; x < n_seg * per_seg; x += 256) {
+    for (int x = threadIdx.x; x < n_seg * per_seg; x += NT) {
       const int seg = x / per_seg, w = x % per_seg;
       const int64_t off = (int64_t)seg * (kP * kHalfBytes) + w * 16;
       *(uint4*)(d + off) = *(const uint4*)(s + off);
@@ -2564,11 +2575,13 @@ __global__ __launch_bounds__(256) void prologue_kernel(PrologueArgs a) {
     return;
   }
   blk -= a.n_cow;
-  // 16 bytes per thread, enough blocks that the whole descriptor is one round trip to the host
-  const uint4* src = (const uint4*)a.host_words;
-  uint4* dst = (uint4*)a.dev_words;
-  const int64_t n16 = (a.copy_words + 3) / 4;          // the staging buffer is padded to 16 bytes
-  for (int64_t i = (int64_t)blk * 256 + threadIdx.x; i < n16; i += (int64_t)a.copy_blocks * 256) dst[i] = src[i];
+  if (blk < a.copy_blocks) {
+    // 16 bytes per thread, enough blocks that the whole descriptor is one round trip to the host
+    const uint4* src = (const uint4*)a.host_words;
+    uint4* dst = (uint4*)a.dev_words;
+    const int64_t n16 = (a.copy_words + 3) / 4;          // the staging buffer is padded to 16 bytes
+    for (int64_t i = (int64_t)blk * NT + threadIdx.x; i < n16; i += (int64_t)a.copy_blocks * NT) dst[i] = src[i];
+  }
 }
 
 // Inverse of append for a list of token slots: pool -> contiguous [n][Hkv][row].
@@ -2900,10 +2913,12 @@ hipError_t launch_prologue(PrologueArgs a, hipStream_t st) {
   // few tokens: one per workgroup (latency); many: up to 16, while there are 512 workgroups, two per compute unit
   a.append_tokens = std::min(std::max(a.n_tokens / 512, 1), kAppendTokens);
   a.append_blocks = (a.n_tokens + a.append_tokens - 1) / a.append_tokens;
-  a.copy_blocks = a.copy_words > 0 ? (int32_t)std::min<int64_t>(((a.copy_words + 3) / 4 + 255) / 256, 256) : 0;   // >= 1: also for one, two or three words
+  const int nt = a.append_tokens >= 4 ? 512 : 256;      // (512 for two and three tokens: 1559 rows of 64 floats 6.6 -> 7.4 us)
+  a.copy_blocks = a.copy_words > 0 ? (int32_t)std::min<int64_t>(((a.copy_words + 3) / 4 + nt - 1) / nt, 256) : 0;   // >= 1: also for one, two or three words
   const int64_t blocks = (int64_t)a.append_blocks + a.n_cow + a.copy_blocks;
   if (blocks <= 0) return a.done ? hipEventRecord(a.done, st) : hipSuccess;
-  return launch_done(prologue_kernel, dim3((unsigned)blocks), dim3(256), st, a.done, a);
+  if (nt == 512) return launch_done(prologue_kernel<512>, dim3((unsigned)blocks), dim3(512), st, a.done, a);
+  return launch_done(prologue_kernel<256>, dim3((unsigned)blocks), dim3(256), st, a.done, a);
 }
 
 hipError_t launch_gather(const GatherArgs& a, void* k_out, void* v_out, hipStream_t st) {
