@@ -48,8 +48,9 @@ class SymError(RuntimeError):
 
 
 _lib = None
-_I32P, _I64P = C.POINTER(C.c_int32), C.POINTER(C.c_int64)
+_I32P = C.POINTER(C.c_int32)
 
+# arrays go as addresses (c_void_p takes a number, a ctypes pointer or array)
 _SIGNATURES = {
     "sym_page_bytes": (C.c_int64, [C.POINTER(SymConfig)]),
     "sym_tuning_defaults": (C.c_int, [C.POINTER(SymConfig), C.POINTER(SymTuning)]),
@@ -62,31 +63,31 @@ _SIGNATURES = {
     "sym_kv_remove": (C.c_int, [C.c_void_p, C.c_int32]),
     "sym_kv_close": (C.c_int, [C.c_void_p, C.c_int32]),
     "sym_kv_len": (C.c_int64, [C.c_void_p, C.c_int32]),
-    "sym_kv_truncate": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I64P]),
+    "sym_kv_truncate": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
     "sym_kv_append": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_kv_extract": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I64P, _I64P, _I32P, C.c_void_p]),
-    "sym_kv_merge": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, C.c_void_p]),
-    "sym_last_moves": (C.c_int64, [C.c_void_p, _I32P, C.c_int64]),
-    "sym_kv_offload": (C.c_int, [C.c_void_p, C.c_int32, _I32P, C.c_void_p]),
-    "sym_kv_restore": (C.c_int, [C.c_void_p, C.c_int32, _I32P, C.c_void_p]),
+    "sym_kv_extract": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "sym_kv_merge": (C.c_int32, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
+    "sym_last_moves": (C.c_int64, [C.c_void_p, C.c_void_p, C.c_int64]),
+    "sym_kv_offload": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
+    "sym_kv_restore": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
     "sym_kv_waiting": (C.c_int, [C.c_void_p, C.c_int32]),
-    "sym_last_swaps": (C.c_int64, [C.c_void_p, _I32P, C.c_int64]),
-    "sym_pred_batch": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_pred_batch_static": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "sym_last_swaps": (C.c_int64, [C.c_void_p, C.c_void_p, C.c_int64]),
+    "sym_pred_batch": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "sym_pred_batch_static": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "sym_static_scratch_bytes": (C.c_int64, []),
     "sym_test_fail_staging": (C.c_int, [C.c_void_p, C.c_int32]),
-    "sym_pred_begin": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p]),
+    "sym_pred_begin": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
     "sym_pred_layer": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "sym_pred_end": (C.c_int, [C.c_void_p]),
     "sym_kv_read_layer": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_int64, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_pred_batch_raw": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, _I64P, _I64P, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_kv_pages": (C.c_int64, [C.c_void_p, C.c_int32, _I32P, C.c_int64]),
+    "sym_pred_batch_raw": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "sym_kv_pages": (C.c_int64, [C.c_void_p, C.c_int32, C.c_void_p, C.c_int64]),
     "sym_page_refcount": (C.c_int32, [C.c_void_p, C.c_int32]),
     "sym_free_pages": (C.c_int64, [C.c_void_p]),
     "sym_get_stats": (C.c_int, [C.c_void_p, C.POINTER(SymStats)]),
-    "sym_plan_append": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, _I32P, C.c_int64, _I32P, _I32P]),
+    "sym_plan_append": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]),
     "sym_plan_copies_first": (C.c_int, [C.c_void_p]),
-    "sym_build_desc": (C.c_int64, [C.c_void_p, C.c_int32, _I32P, _I32P, _I64P, _I64P, _I32P, C.c_int64]),
+    "sym_build_desc": (C.c_int64, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64]),
     "sym_kv_read": (C.c_int, [C.c_void_p, C.c_int32, C.c_int64, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
     "sym_sched_create": (C.c_void_p, [C.c_int32, C.c_double, C.c_double, C.c_double, C.c_double]),
     "sym_sched_destroy": (None, [C.c_void_p]),
@@ -96,9 +97,9 @@ _SIGNATURES = {
     "sym_sched_done": (None, [C.c_void_p, C.c_int32, C.c_double]),
     "sym_sched_next_deadline": (C.c_double, [C.c_void_p]),
     "sym_sched_state": (C.c_int, [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_double), C.POINTER(C.c_double),
-                                  C.POINTER(C.c_double), _I64P]),
+                                  C.POINTER(C.c_double), C.c_void_p]),
     "sym_profile_enable": (C.c_int, [C.c_void_p, C.c_int]),
-    "sym_profile_read": (C.c_int, [C.c_void_p, C.c_int, C.POINTER(C.c_double), _I64P]),
+    "sym_profile_read": (C.c_int, [C.c_void_p, C.c_int, C.POINTER(C.c_double), C.c_void_p]),
     "sym_calib_read": (C.c_int, [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]),
     "sym_calib_copy": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]),
     "sym_calib_mfma": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]),
@@ -120,8 +121,9 @@ def load():
 
 
 def _i32(a):
+    """A contiguous int32 array and its address (as a plain number: a ctypes pointer object takes ten times as long to make)."""
     a = np.ascontiguousarray(a, np.int32)
-    return a, a.ctypes.data_as(_I32P)
+    return a, a.__array_interface__["data"][0]
 
 
 def as_i32p(a):
@@ -132,7 +134,7 @@ def as_i32p(a):
 
 def _i64(a):
     a = np.ascontiguousarray(a, np.int64)
-    return a, a.ctypes.data_as(_I64P)
+    return a, a.__array_interface__["data"][0]
 
 
 def _ptr(t):
@@ -155,8 +157,8 @@ def make_config(n_q_heads, n_kv_heads, head_dim, page_tokens, dtype, n_pages, de
     cfg.pool, cfg.workspace, cfg.workspace_bytes = _ptr(pool), _ptr(workspace), workspace_bytes
     keep = None
     if free_order is not None:
-        keep, p = _i32(free_order)
-        cfg.free_order = p
+        keep, _ = _i32(free_order)
+        cfg.free_order = as_i32p(keep)
     cfg.softmax_scale, cfg.decode_waves, cfg.n_layers = softmax_scale, decode_waves, n_layers
     cfg._keep = keep
     if tuning:
@@ -289,7 +291,7 @@ class Context:
         ix_a, ix_p = _i64(flat)
         of_a, of_p = _i64(off)
         out = np.empty(len(s_a), np.int32)
-        self._chk(self.lib.sym_kv_extract(self.h, len(s_a), s_p, of_p, ix_p, out.ctypes.data_as(_I32P), stream))
+        self._chk(self.lib.sym_kv_extract(self.h, len(s_a), s_p, of_p, ix_p, out.ctypes.data, stream))
         return [int(h) for h in out]
 
     def kv_merge(self, files, stream=None):
@@ -310,13 +312,13 @@ class Context:
     def last_swaps(self):
         n = self._chk(self.lib.sym_last_swaps(self.h, None, 0))
         out = np.empty((n, 2), np.int32)
-        self._chk(self.lib.sym_last_swaps(self.h, out.ctypes.data_as(_I32P), n))
+        self._chk(self.lib.sym_last_swaps(self.h, out.ctypes.data, n))
         return out
 
     def last_moves(self):
         n = self._chk(self.lib.sym_last_moves(self.h, None, 0))
         out = np.empty((n, 2), np.int32)
-        self._chk(self.lib.sym_last_moves(self.h, out.ctypes.data_as(_I32P), n))
+        self._chk(self.lib.sym_last_moves(self.h, out.ctypes.data, n))
         return out
 
     # ---- pred ----
@@ -352,7 +354,7 @@ class Context:
         kept alive by the object."""
         kv_a, nt_a = np.ascontiguousarray(kv, np.int32), np.ascontiguousarray(n_tokens, np.int32)
         keep = (kv_a, nt_a, q, k_new, v_new, out)
-        args = (len(kv_a), C.cast(kv_a.ctypes.data, _I32P), C.cast(nt_a.ctypes.data, _I32P), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out))
+        args = (len(kv_a), kv_a.ctypes.data, nt_a.ctypes.data, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out))
         return keep, args
 
     def pred_prepared(self, prepared, stream=None):
@@ -371,7 +373,7 @@ class Context:
     def kv_pages(self, kv):
         n = self._chk(self.lib.sym_kv_pages(self.h, kv, None, 0))
         out = np.zeros(max(n, 1), np.int32)
-        self._chk(self.lib.sym_kv_pages(self.h, kv, out.ctypes.data_as(_I32P), n))
+        self._chk(self.lib.sym_kv_pages(self.h, kv, out.ctypes.data, n))
         return out[:n].tolist()
 
     def page_refcount(self, page):
@@ -391,8 +393,8 @@ class Context:
         cow = np.zeros(3 * max(len(kv_a), 1), np.int32)
         slots = np.zeros(max(int(nt_a.sum()) if len(nt_a) else 0, 1), np.int32)
         n_cow = C.c_int32(0)
-        self._chk(self.lib.sym_plan_append(self.h, len(kv_a), kv_p, nt_p, cow.ctypes.data_as(_I32P), len(kv_a),
-                                           C.byref(n_cow), slots.ctypes.data_as(_I32P)))
+        self._chk(self.lib.sym_plan_append(self.h, len(kv_a), kv_p, nt_p, cow.ctypes.data, len(kv_a),
+                                           C.byref(n_cow), slots.ctypes.data))
         T = int(nt_a.sum())
         return [tuple(int(x) for x in cow[3 * i:3 * i + 3]) for i in range(n_cow.value)], slots[:T].copy()
 
@@ -406,7 +408,7 @@ class Context:
         ln_a, ln_p = _i64(lengths)
         n = self._chk(self.lib.sym_build_desc(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, None, 0))
         out = np.zeros(n, np.int32)
-        self._chk(self.lib.sym_build_desc(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, out.ctypes.data_as(_I32P), n))
+        self._chk(self.lib.sym_build_desc(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, out.ctypes.data, n))
         return out
 
     def kv_read(self, kv, start, n, k_out, v_out, stream=None, layer=0):

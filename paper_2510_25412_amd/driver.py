@@ -39,7 +39,8 @@ class HipSession:
 
     @property
     def stream(self):
-        return torch.cuda.current_stream(self.device).cuda_stream
+        # the stream's handle alone: torch.cuda.current_stream makes an object of it, a microsecond of every call
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if self.device.index is None else self.device.index)
 
     def setup(self, ops):
         for op in ops:
