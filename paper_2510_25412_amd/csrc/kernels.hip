@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "desc.hpp"
 #include "kernels.hpp"
@@ -1270,7 +1271,8 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   constexpr bool split = SPLIT;
   const int pair = split ? (wv >> 1) : 0;
   const int wvr = split ? (wv & 1) : wv;                         // which 32 rows of the tile
-  const bool wave_live = wvr * 32 * CT < count * G;              // a wavefront whose rows are all padding only stages
+  const int wvu = __builtin_amdgcn_readfirstlane(wv);
+  const bool wave_live = (TW == 8 ? wvu : wvr) * 32 * CT < count * G;      // a wavefront whose rows are all padding only stages (eight wavefronts: a scalar)
 
   // ---- staging roles
   // K: thread copies chunk c = tid (and tid + 256 with four wavefronts) of the block: token c/16, dim chunk c%16
@@ -1283,7 +1285,6 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   // Which of the block's two pages a thread stages is the same for its whole wavefront, so the page
   // ids come through the scalar cache and the page base is scalar arithmetic; what differs per
   // thread is a fixed offset inside the page, computed once.
-  const int wvu = __builtin_amdgcn_readfirstlane(wv);
   const int k_page = TW == 4 ? 0 : (wvu >> 2);            // chunk tid: page of the block (chunk tid + 256: the other one)
   const int v_page = TW == 4 ? (wvu >> 1) : (wvu >> 2);
   const int kt = (tid >> 4) & 15, kdc = tid & 15;
@@ -1314,14 +1315,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
       v1.x = x1.x; v1.y = x1.y;
     }
   };
-  auto issue_loads = [&](int kb, uint4& k0, uint4& k1, uint4& v0, uint4& v1) {
-    if constexpr (TW == 4) {
-      issue_pages(page_id(2 * kb), page_id(2 * kb + 1), k0, k1, v0, v1);
-    } else {
-      const int id = page_id(2 * kb + k_page);
-      issue_pages(id, id, k0, k1, v0, v1);
-    }
-  };
+  auto issue_loads = [&](int kb, uint4& k0, uint4& k1, uint4& v0, uint4& v1) { issue_pages(page_id(2 * kb), page_id(2 * kb + 1), k0, k1, v0, v1); };
   int tl[CT], h[CT], qrow[CT], vis[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
@@ -1333,7 +1327,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
     vis[ct] = shared ? kv_end : min(L + t0 + tlc + 1, lim);   // tokens this row sees
   }
   // the first block by the record's ids; those of the blocks behind it are on their way meanwhile, all in one round trip
-  constexpr int kAhead = SPLIT ? 3 : 2;
+  constexpr int kAhead = SPLIT ? 3 : TW == 8 ? 5 : 2;
   int ids[kAhead][2];
 #pragma unroll
   for (int i = 0; i < kAhead; ++i) {
@@ -1356,13 +1350,15 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
     const int t = c >> 4, dc = c & 15;
     return base + (t * 16 + (dc ^ (t & 15))) * 16;
   };
-  auto store_lds = [&](int kb, uint8_t* base, const uint4& k0, const uint4& k1, const uint4& v0, const uint4& v1) {
+  auto store_k = [&](uint8_t* base, const uint4& k0, const uint4& k1) {
     *(uint4*)k_dst(base, tid) = k0;
     if constexpr (TW == 4) *(uint4*)k_dst(base, tid + 256) = k1;
+  };
+  auto store_v = [&](int kb, uint8_t* base, const uint4& v0, const uint4& v1, bool masked) {
     // tokens past the end of what the tile may see are cleared (their weight is 0, 0 * NaN is not);
     // only the last block can hold such tokens
     const int tok = kb * kKvBlock + pg * 16 + 4 * q4 + 2 * up;
-    const bool tail = kb * kKvBlock + kKvBlock > kv_end;
+    const bool tail = masked && kb * kKvBlock + kKvBlock > kv_end;
     const bool ok0 = !tail || tok < kv_end, ok1 = !tail || tok + 1 < kv_end;
     uint8_t* vb = base + kKLds + (2 * pg + (q4 & 1)) * 16 + (q4 >> 1) * 8 + up * 4 + vc * VD * kVRow;
     auto put = [&](int e, uint32_t lo_word0, uint32_t lo_word1, bool high) {
@@ -1378,6 +1374,10 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
       put(6, v0.w, v1.w, false); put(7, v0.w, v1.w, true);
     }
   };
+  auto store_lds = [&](int kb, uint8_t* base, const uint4& k0, const uint4& k1, const uint4& v0, const uint4& v1) {
+    store_k(base, k0, k1);
+    store_v(kb, base, v0, v1, true);
+  };
 
   f32x16_t O[CT][4];
   float m[CT], l[CT];
@@ -1391,7 +1391,7 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
       for (int v = 0; v < 16; ++v) O[ct][db][v] = 0.f;
   }
 
-  // The block loop is software-pipelined over three LDS buffers.  One step: block kb + 1 (loaded three
+  // Four wavefronts: the block loop is software-pipelined over three LDS buffers (eight: see below).  One step: block kb + 1 (loaded three
   // steps ago) goes from registers to LDS, the loads of block kb + 4 are issued into the same
   // registers, then the matrix cores start S^T = K Q^T of block kb + 1 while the vector units do the
   // softmax arithmetic of block kb, and O^T += V^T P^T of block kb follows.  So the MFMAs of one block
@@ -1592,6 +1592,124 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
         for (int v = 0; v < 16; ++v) O[0][db][v] = O[0][db][v] * a0 + xch[(2 + db * 16 + v) * 64] * a1;
       m[0] = mn;
     }
+  } else if constexpr (TW == 8) {
+    // Eight wavefronts, two on a SIMD: while wavefronts 0..3 are in a matrix phase (scores of the next block, weights x V of this
+    // one: sixteen MFMAs whose operands all lie in registers), wavefronts 4..7 are in a vector phase (operands of their next
+    // matrix phase from LDS, mask, maximum, exponentials), and at the next barrier they change over.  In step with each other the two
+    // want the same unit at the same time: a step took 2500 cycles for 1024 of MFMA.  Staging belongs to the matrix phase, whose issue slots are
+    // free between its MFMAs; in the vector phase it makes that the longer one (1914 us against 1520 in step and 1365 now).
+    // Four LDS buffers: in the matrix phase that follows block kb's weights a wavefront stores block kb + 3 over block kb - 1, which the
+    // other half read last two phases before; it is complete one phase before its first reader.
+    // What bounds it is the power limit: 32 chunks of 512 tokens on U{0..8192}: 3.17 M -> 2.50 M cycles, at 2.14 -> 1.91 GHz.  Whole calls:
+    // that batch 1520 -> 1365 us, three ragged prompts 68.5 -> 62.7, the mixed batch 1905 -> 1708.  Without the priority of the matrix
+    // phase 1387; MFMAs and vector instructions in a prescribed order 1363; page ids a phase earlier 1425 (the scheduler then puts the
+    // scores behind the products with V, and the other half waits for them).
+    issue_pages(ids[0][0], ids[0][0], kb0r, kb1r, vb0, vb1);
+    issue_pages(ids[1][0], ids[1][0], kc0, kc1, vc0, vc1);
+    store_lds(kb0, lds[0], ka0, ka1, va0, va1);
+    issue_pages(ids[2][0], ids[2][0], ka0, ka1, va0, va1);
+    store_lds(kb0 + 1, lds[1], kb0r, kb1r, vb0, vb1);
+    issue_pages(ids[3][0], ids[3][0], kb0r, kb1r, vb0, vb1);
+    store_lds(kb0 + 2, lds[2], kc0, kc1, vc0, vc1);
+    int next_id = ids[4][0];                           // page of the block to be requested next, fetched a step ahead
+    int k_at[8];                                       // this lane's operands in a K block: held, or each read adds its parts up again
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      k_at[ks] = (col * 16 + ((2 * ks + hf) ^ (col & 15))) * 16;
+      asm volatile("" : "+v"(k_at[ks]));
+    }
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(q[0][ks]));      // Q is here: no wait for it in the loop
+    __syncthreads();
+    // The walk over the blocks, for a wavefront with rows and for one that only stages.
+    auto walk = [&](auto live_) __attribute__((always_inline)) {
+      constexpr bool live = decltype(live_)::value;
+      bf16x8_t kk[8];                                  // operands of the next matrix phase
+      f16x8_t vv[4][2], P[2];
+      auto read_k = [&](const uint8_t* base) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) kk[ks] = *(const bf16x8_t*)(base + k_at[ks]);
+      };
+      if constexpr (live) {
+        read_k(lds[0]);
+        Sc = scores(kk);
+      }
+      // Block kb: its vector phase, then the matrix phase behind it.  K is of block kb + 1 in `nxt`, V^T of block kb in `cur`; block
+      // kb + 3 goes from its registers to `stage`.  Returns whether block kb was the last (the scores then computed are of no use).
+      auto turn = [&](const int kb, const uint8_t* cur, const uint8_t* nxt, uint8_t* stage, uint4& k0, uint4& k1, uint4& v0, uint4& v1) __attribute__((always_inline)) {
+        if constexpr (live) {
+          read_k(nxt);
+          const uint8_t* vbase = cur + kKLds + col * kVRow + hf * 16;
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < 4; ++db) vv[db][ks] = *(const f16x8_t*)(vbase + db * 32 * kVRow + ks * 32);
+          if (kb * kKvBlock + kKvBlock > mask_from) {    // the block reaches the causal edge of some row
+            const int tok0 = kb * kKvBlock + 4 * hf;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) Sc[v] = tok0 + 8 * (v >> 2) + (v & 3) < vis[0] ? Sc[v] : -__builtin_inff();
+          }
+          float mx = -__builtin_inff();
+#pragma unroll
+          for (int v = 0; v < 16; ++v) mx = fmaxf(mx, Sc[v]);
+          mx = pair32_max(mx) * a.scale_log2e;
+          if (__builtin_amdgcn_ballot_w64(mx > m[0] + kTau) != 0) {     // rare after the first block
+            const float mn = fmaxf(m[0], mx);
+            const float al = __builtin_amdgcn_exp2f(m[0] - mn);
+            l[0] *= al;
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+              for (int v = 0; v < 16; ++v) O[0][db][v] *= al;
+            m[0] = mn;
+          }
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) {
+            uint32_t pw[4];
+#pragma unroll
+            for (int u = 0; u < 8; u += 2) {
+              const int v = 8 * ks + u;
+              const f16x2_t pk = {(_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(Sc[v], a.scale_log2e, -m[0])),
+                                  (_Float16)__builtin_amdgcn_exp2f(__builtin_fmaf(Sc[v + 1], a.scale_log2e, -m[0]))};
+              l[0] = __builtin_amdgcn_fdot2(pk, f16x2_t{(_Float16)1.0f, (_Float16)1.0f}, l[0], false);
+              pw[u >> 1] = __builtin_bit_cast(uint32_t, pk);
+            }
+            P[ks] = __builtin_bit_cast(f16x8_t, make_uint4(pw[0], pw[1], pw[2], pw[3]));
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+        if constexpr (live) {
+          Sc = scores(kk);
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < 4; ++db) O[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vv[db][ks], P[ks], O[0][db], 0, 0, 0);
+        }
+        store_k(stage, k0, k1);
+        store_v(kb + 3, stage, v0, v1, false);
+        if ((kb + 4) * kKvBlock > kv_end) store_v(kb + 3, stage, v0, v1, true);      // again, without the tokens past the end
+        issue_pages(next_id, next_id, k0, k1, v0, v1);   // block kb + 5
+        next_id = page_id(2 * (kb + 6) + k_page);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        return kb + 1 >= nblk;
+      };
+      for (int kb = kb0;; kb += 4) {
+        if (turn(kb, lds[0], lds[1], lds[3], ka0, ka1, va0, va1)) break;
+        if (turn(kb + 1, lds[1], lds[2], lds[0], kb0r, kb1r, vb0, vb1)) break;
+        if (turn(kb + 2, lds[2], lds[3], lds[1], ka0, ka1, va0, va1)) break;
+        if (turn(kb + 3, lds[3], lds[0], lds[2], kb0r, kb1r, vb0, vb1)) break;
+      }
+    };
+    if (wvu >= 4) __syncthreads();                     // half a step behind; the other half waits for it at the end
+    if (wave_live) walk(std::true_type{});
+    else walk(std::false_type{});
+    if (wvu < 4) __syncthreads();
   } else {
   issue_pages(ids[0][0], ids[0][1], kb0r, kb1r, vb0, vb1);
   issue_pages(ids[1][0], ids[1][1], kc0, kc1, vc0, vc1);
@@ -2060,7 +2178,7 @@ __global__ __launch_bounds__(64 * TW, 8 / TW) void attn_kernel(DecodeArgs da, Pr
   const int32_t g = pa.group_map ? sload(pa.group_map + j) : (int32_t)j;   // no table: tiles only
   const bool is_decode = g < 0;
   // LDS: the K/V buffers of a tile workgroup, or the piece slots of a decode bin (a workgroup is one or the other)
-  constexpr int kTileLds = E::kDimsPerChunk == 8 ? (SPLIT ? 4 : 3) * (kKLds + kVLds) : 0;      // tiles exist for bf16 storage only
+  constexpr int kTileLds = E::kDimsPerChunk == 8 ? (SPLIT || TW == 8 ? 4 : 3) * (kKLds + kVLds) : 0;      // tiles exist for bf16 storage only
   constexpr int kBinLds = G < 8 ? 2 * TW * BinLds<E, G < 8 ? G : 1>::kSlot * 4 : 0;
   constexpr int kLds = kTileLds > kBinLds ? kTileLds : (kBinLds > 16 ? kBinLds : 16);
   __shared__ __align__(16) uint8_t lds[kLds];
