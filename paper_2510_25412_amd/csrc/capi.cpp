@@ -379,9 +379,10 @@ struct StageDone {
 // One prologue launch: the first copy_words words of the pinned buffer c->stage[si] (the descriptor, or the whole blob of
 // a batch) are copied to `dev_words` (default: the start of the workspace); `n_cow` page copies from the list `cow` and the
 // append of `n_tokens` rows k, v by the slot map `slots` (both lists in pinned or device memory) go to layer `layer`.
-// release: the staging buffer that nothing reads behind this launch (-1: none).
+// release: the staging buffer that nothing reads behind this launch (-1: none).  runs: the slot map as the plan's runs.
 int launch_prologue(sym_ctx* c, int si, int64_t copy_words, const int32_t* cow, int n_cow, const int32_t* slots, int32_t n_tokens,
-                    const void* k, const void* v, hipStream_t st, int release, uint8_t* dev_words = nullptr, bool timed = true, int32_t layer = 0) {
+                    const void* k, const void* v, hipStream_t st, int release, uint8_t* dev_words = nullptr, bool timed = true, int32_t layer = 0,
+                    const std::vector<int32_t>* runs = nullptr) {
   PrologueArgs a;
   a.pool = pool_of(c, layer);
   a.page_bytes = c->page_bytes;
@@ -396,6 +397,9 @@ int launch_prologue(sym_ctx* c, int si, int64_t copy_words, const int32_t* cow, 
   a.Hkv = c->cfg.n_kv_heads;
   a.n_cow = n_cow;
   a.append_blocks = a.append_tokens = a.copy_blocks = 0;
+  a.runs = runs ? runs->data() : nullptr;
+  static_assert(kPrologueRuns < AppendPlan::kRuns, "a cut-off list of runs is not taken for a whole one");
+  a.n_runs = runs ? (int32_t)(runs->size() / 2) : 0;
   const StageDone done(c, release);
   a.done = done.event();
   Timed t(c, SYM_K_PROLOGUE, st, false, timed);
@@ -576,6 +580,8 @@ int pred_plan_locked(sym_ctx* c, int32_t n_lips, const sym_kv* kv, const int32_t
     int64_t t = 0;
     for (int32_t b = 0; b < n_lips; t += n_tokens[b], ++b)
       if (c->desc.fused[b]) sl[t] = -1;
+    for (size_t r = 0; r < c->plan.runs.size(); r += 2)
+      if (sl[c->plan.runs[r]] < 0) c->plan.runs[r + 1] = -1;      // (a fused token is a run of its own)
   }
   pb->n_cow = (int)(c->plan.cow.size() / 3);
   // rows for the append kernel: none when the attention kernel appends every token of the batch itself
@@ -600,7 +606,7 @@ int pred_batch_locked(sym_ctx* c, int32_t n_lips, const sym_kv* kv, const int32_
     n_cow = 0;
   }
   // descriptor to the device; page copies and the appends the attention kernel does not do itself, read from the pinned buffer
-  if ((rc = launch_prologue(c, pb.si, pb.dwords, cow, n_cow, slots, pb.n_append, k_new, v_new, st, pb.si, ws.base, !no_alloc))) return rc;
+  if ((rc = launch_prologue(c, pb.si, pb.dwords, cow, n_cow, slots, pb.n_append, k_new, v_new, st, pb.si, ws.base, !no_alloc, 0, &c->plan.runs))) return rc;
   ++c->pred_batches;
   rc = launch_attention(c, used, pb.words, q, out, st, !no_alloc, k_new, v_new);
   const auto t_end = std::chrono::steady_clock::now();
@@ -890,7 +896,7 @@ int sym_kv_append(sym_ctx* c, sym_kv kv, int32_t n, const void* k, const void* v
   const int64_t layer_rows = (int64_t)n * c->cfg.n_kv_heads * 256;           // bytes of one layer's rows in k and in v
   for (int32_t l = 0; l < c->n_layers; ++l)
     if ((rc = launch_prologue(c, si, 0, c->stage[si], (int)(c->plan.cow.size() / 3), c->stage[si] + c->plan.cow.size(), n,
-                              (const uint8_t*)k + l * layer_rows, (const uint8_t*)v + l * layer_rows, st, l == c->n_layers - 1 ? si : -1, nullptr, true, l)))
+                              (const uint8_t*)k + l * layer_rows, (const uint8_t*)v + l * layer_rows, st, l == c->n_layers - 1 ? si : -1, nullptr, true, l, &c->plan.runs)))
       return rc;
   return SYM_OK;
 }

@@ -2635,6 +2635,9 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void merge_kernel(MergeArgs a)
 // from the pinned host buffer: an append workgroup reads its tokens' slots once, in one line, and
 // shares them through LDS (a request over the host link takes about 4.6 ns of all of them together: one for every workgroup, not for
 // every thread).  The rows themselves are requested meanwhile, and the next ones before the barrier of a loop would come round.
+// Few runs of consecutive slots (prompts, drafts, chunks of up to about 2000 tokens) come with the kernel's arguments instead: no request over the
+// host link stands before the first store (by rocprofv3's trace 900 tokens of three prompts 5.2 -> 4.5 us, 1559 rows of 64 floats 6.4
+// -> 5.3; whole calls 61.7 -> 60.0 and 23.2 -> 22.4).
 // Bound: HBM, read + write.  By rocprofv3's trace, slots before the first row / now: a document of 7100 tokens 13.2 -> 11.8 us
 // (4.9 TB/s read + written), the mixed batch's 16 600 tokens 34.2 -> 26.7; descriptors and few tokens (256 of drafts, 900 of
 // prompts) the same.  The append workgroups come first in the grid (last: the mixed batch 31.9 us, a fork's descriptor 7.6 -> 7.5).
@@ -2642,8 +2645,14 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void merge_kernel(MergeArgs a)
 // ---------------------------------------------------------------------------------------
 constexpr int kAppendTokens = 16;        // most tokens per append workgroup
 
-template <int NT>
-__global__ __launch_bounds__(NT) void prologue_kernel(PrologueArgs a) {
+// The slot map of a small batch, as part of the kernel's arguments: run r is tokens first[r] .. first[r + 1] - 1 in consecutive slots
+// from slot[r] (or appended elsewhere: -1).
+struct PrologueRuns {
+  int32_t first[kPrologueRuns + 1], slot[kPrologueRuns];
+};
+
+template <int NT, bool RUNS>
+__device__ __forceinline__ void prologue(const PrologueArgs& a, const __attribute__((address_space(4))) PrologueRuns* runs) {
   __shared__ int32_t s_slot[kAppendTokens];
   int blk = blockIdx.x;
   if (blk < a.append_blocks) {
@@ -2651,7 +2660,16 @@ __global__ __launch_bounds__(NT) void prologue_kernel(PrologueArgs a) {
     const int total = n * a.Hkv * 32;       // 16-byte chunks: token, kv head, K/V, chunk within the row
     const uint8_t* k0 = (const uint8_t*)a.k_new + (int64_t)t0 * a.Hkv * kRowBytes;
     const uint8_t* v0 = (const uint8_t*)a.v_new + (int64_t)t0 * a.Hkv * kRowBytes;
-    const int my_slot = a.slots[t0 + min((int)threadIdx.x, n - 1)];
+    int my_slot = 0, first = 0, end = 0;    // the slot of token t0 + thread, or the run that the thread writes out
+    if constexpr (RUNS) {
+      if ((int)threadIdx.x < a.n_runs) {
+        first = runs->first[threadIdx.x];
+        end = runs->first[threadIdx.x + 1];
+        my_slot = runs->slot[threadIdx.x];
+      }
+    } else {
+      my_slot = a.slots[t0 + min((int)threadIdx.x, n - 1)];
+    }
     u32x4_t v[4];
     auto request = [&](int x) __attribute__((always_inline)) {
 #pragma unroll
@@ -2661,7 +2679,11 @@ __global__ __launch_bounds__(NT) void prologue_kernel(PrologueArgs a) {
       }
     };
     request(threadIdx.x);                   // under way while the slots come over the host link
-    if ((int)threadIdx.x < n) s_slot[threadIdx.x] = my_slot;
+    if constexpr (RUNS) {
+      for (int t = max(first, t0); t < min(end, t0 + n); ++t) s_slot[t - t0] = my_slot < 0 ? -1 : my_slot + (t - first);
+    } else {
+      if ((int)threadIdx.x < n) s_slot[threadIdx.x] = my_slot;
+    }
     __syncthreads();
     for (int x = threadIdx.x;;) {
 #pragma unroll
@@ -2700,6 +2722,18 @@ __global__ __launch_bounds__(NT) void prologue_kernel(PrologueArgs a) {
     const int64_t n16 = (a.copy_words + 3) / 4;          // the staging buffer is padded to 16 bytes
     for (int64_t i = (int64_t)blk * NT + threadIdx.x; i < n16; i += (int64_t)a.copy_blocks * NT) dst[i] = src[i];
   }
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void prologue_kernel(PrologueArgs a) {
+  prologue<NT, false>(a, nullptr);
+}
+template <int NT>
+__global__ __launch_bounds__(NT) void prologue_runs_kernel(PrologueArgs a, PrologueRuns) {
+  // the runs where they lie, behind the arguments proper: named as a parameter and indexed by the thread they would be copied to scratch
+  auto args = (const __attribute__((address_space(4))) uint8_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(sizeof(PrologueArgs) % alignof(PrologueRuns) == 0, "the runs follow the arguments at once");
+  prologue<NT, true>(a, (const __attribute__((address_space(4))) PrologueRuns*)(args + sizeof(PrologueArgs)));
 }
 
 // Inverse of append for a list of token slots: pool -> contiguous [n][Hkv][row].
@@ -3009,8 +3043,8 @@ hipError_t launch_merge(const MergeArgs& a, int G, int D, hipStream_t st) {
 // packet of its own, which the next kernel waits for, 3.0 us in every call whatever its size (two kernels of 10 us with an event
 // recorded between them 25.4 us, with it attached and without a system fence 22.4, with no event at all 22.4; as a record without a
 // system fence 23.6).  A stream that is being captured takes it as a record: a graph's kernel nodes carry no events.
-template <typename K, typename A>
-hipError_t launch_done(K kernel, dim3 grid, dim3 block, hipStream_t st, hipEvent_t done, const A& a) {
+template <typename K, typename... A>
+hipError_t launch_done(K kernel, dim3 grid, dim3 block, hipStream_t st, hipEvent_t done, const A&... a) {
   if (done) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
@@ -3018,11 +3052,11 @@ hipError_t launch_done(K kernel, dim3 grid, dim3 block, hipStream_t st, hipEvent
       cs = hipStreamCaptureStatusActive;
     }
     if (cs == hipStreamCaptureStatusNone) {
-      hipExtLaunchKernelGGL(kernel, grid, block, 0, st, nullptr, done, 0, a);
+      hipExtLaunchKernelGGL(kernel, grid, block, 0, st, nullptr, done, 0, a...);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL(kernel, grid, block, 0, st, a);
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, a...);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess && done ? hipEventRecord(done, st) : e;
 }
@@ -3035,6 +3069,16 @@ hipError_t launch_prologue(PrologueArgs a, hipStream_t st) {
   a.copy_blocks = a.copy_words > 0 ? (int32_t)std::min<int64_t>(((a.copy_words + 3) / 4 + nt - 1) / nt, 256) : 0;   // >= 1: also for one, two or three words
   const int64_t blocks = (int64_t)a.append_blocks + a.n_cow + a.copy_blocks;
   if (blocks <= 0) return a.done ? hipEventRecord(a.done, st) : hipSuccess;
+  if (a.append_blocks > 0 && a.n_runs > 0 && a.n_runs <= kPrologueRuns) {
+    PrologueRuns r;
+    for (int i = 0; i < a.n_runs; ++i) {
+      r.first[i] = a.runs[2 * i];
+      r.slot[i] = a.runs[2 * i + 1];
+    }
+    r.first[a.n_runs] = a.n_tokens;
+    if (nt == 512) return launch_done(prologue_runs_kernel<512>, dim3((unsigned)blocks), dim3(512), st, a.done, a, r);
+    return launch_done(prologue_runs_kernel<256>, dim3((unsigned)blocks), dim3(256), st, a.done, a, r);
+  }
   if (nt == 512) return launch_done(prologue_kernel<512>, dim3((unsigned)blocks), dim3(512), st, a.done, a);
   return launch_done(prologue_kernel<256>, dim3((unsigned)blocks), dim3(256), st, a.done, a);
 }

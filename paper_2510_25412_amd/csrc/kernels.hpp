@@ -86,7 +86,10 @@ struct PrologueArgs {
   int32_t n_tokens, Hkv, n_cow;
   int32_t append_blocks, append_tokens, copy_blocks;   // filled by launch_prologue
   hipEvent_t done;              // completed by the launch, or null
+  const int32_t* runs;          // host: the slot map as (first token, slot or -1) pairs of consecutive slots, ...
+  int32_t n_runs;               // ... handed to the kernel with its arguments where they are at most kPrologueRuns; 0: none given
 };
+constexpr int kPrologueRuns = 128;
 
 struct GatherArgs {
   const uint8_t* pool;

@@ -273,7 +273,14 @@ int Kvfs::append(int32_t n, const int32_t* handles, const int32_t* n_tokens, App
     for (int32_t i = 0, s = (int32_t)(f.len % P_); i < n_tokens[b]; s = 0) {       // page by page
       if (s == 0) f.pages.push_back(alloc_page());
       const int32_t n_here = std::min(n_tokens[b] - i, P_ - s);
-      if (slot) std::iota(slot + i, slot + i + n_here, f.pages.back() * P_ + s);
+      if (slot) {
+        const int32_t at = f.pages.back() * P_ + s;
+        std::iota(slot + i, slot + i + n_here, at);
+        if (plan->runs.size() < 2 * AppendPlan::kRuns) {
+          plan->runs.push_back((int32_t)(slot - plan->slots.data()) + i);
+          plan->runs.push_back(at);
+        }
+      }
       i += n_here;
     }
     f.len += n_tokens[b];
