@@ -370,7 +370,7 @@ int build_desc(const DescParams& prm, int32_t n_lips, const int32_t* n_tokens, c
       int64_t units = 0;                                   // decode work in the same launch (plain decode rows)
       for (int32_t b = 0; b < n_lips; ++b)
         if (!is_prefill(b)) units += ((len_after[b] + P - 1) / P - share_start[b]) * H * ((n_tokens[b] + RT - 1) / RT);
-      bsteps = chunk_steps(lens, slots, kTileStart, kTileMerge, 64, 3, units / kUnitsPerStep, TQ, chunk_budget);      // the block loop is unrolled by three
+      bsteps = chunk_steps(lens, slots, kTileStart, kTileMerge, 64, 3, units / kUnitsPerStep, TQ, chunk_budget);      // tiles of 128 rows walk blocks by threes; for 256 rows pieces of any size measured the same
       count_btiles();
     }
   }
