@@ -425,10 +425,20 @@ uint8_t* host_slot(const sym_ctx* c, int32_t s) { return c->host_chunks[s / kHos
 constexpr int64_t kSwapChunk = 1 << 18;                               // pages per swap launch
 int64_t swap_stage_words(int64_t pages) { return 4 * std::min(pages, kSwapChunk); }
 constexpr int kPageTokens = 16;                                       // page_tokens of every configuration that sym_init accepts
-constexpr int64_t kMoveChunk = 1 << 16;                               // destination pages per move launch
+constexpr int64_t kMoveChunk = 65535;                                 // destination pages per move launch (a dimension of its grid)
 // words that the moves of `tokens` tokens into `files` new files may stage: P source slots and the destination per page
 int64_t move_stage_words(const sym_ctx* c, int64_t tokens, int64_t files) {
   return std::min(tokens / c->cfg.page_tokens + files, kMoveChunk) * (c->cfg.page_tokens + 1);
+}
+// Whether the list of `pages` destination pages goes to the device first, and the pages are then filled by many small workgroups that
+// read it there, or stays in pinned memory, read by one workgroup per page and layer.  The launch that brings it takes 4 us and 2.6 ns
+// a page; it pays from about 250 MB written on, with one layer (where it stands beside the host's planning only) from about 400 MB on.
+// Whole calls, pinned / brought first, about half of the tokens of 64 files of 512..4096: 8 kv heads x 32 layers 3050 / 2690 us (as pairs of
+// slots, a launch a layer 2860), x 8 layers 780 / 675 (735), one head x 8 layers 114 / 102 (145), 16 heads x 1 layer 203 / 180 (197); 8
+// heads x 1 layer 92 / 101 (122).  8 files of these: 8 heads x 32 layers 411 / 359, x 4 layers 43.7 / 43.0, one head x 8 layers 21.4 / 23.
+bool moves_near(const sym_ctx* c, int64_t pages) {
+  const int64_t least = (c->n_layers > 1 ? 240LL : 384LL) << 20;
+  return pages * c->n_layers * c->page_bytes >= least && pages * (kPageTokens + 1) * 4 + 16 <= c->cfg.workspace_bytes;
 }
 
 // Carries out the page copies of c->splan ((page, slot) pairs when to_host, (slot, page) otherwise).
@@ -458,7 +468,8 @@ int run_swaps(sym_ctx* c, bool to_host, hipStream_t st) {
   return SYM_OK;
 }
 
-// Carries out the copies of c->gplan on the device, chunk by chunk: the move kernel reads its list from pinned staging.
+// Carries out the copies of c->gplan on the device, chunk by chunk: the move kernel reads its list from pinned staging, or from the
+// workspace, where a launch brings it first when many layers read it.
 int run_moves(sym_ctx* c, hipStream_t st) {
   const std::vector<GatherPlan::Fill>& fills = c->gplan.fills;
   const int64_t n = (int64_t)fills.size();
@@ -477,8 +488,14 @@ int run_moves(sym_ctx* c, hipStream_t st) {
       if (tokens == kPageTokens) std::memcpy(src + i * kPageTokens, from, kPageTokens * 4);      // (a known length: four moves)
       else std::memcpy(src + i * P, from, (size_t)tokens * 4);
     }
-    const StageDone done(c, si);
-    MoveArgs ma{(uint8_t*)c->cfg.pool, c->page_bytes, c->layer_bytes, src, dst, (int32_t)cnt, c->n_layers, c->cfg.n_kv_heads, done.event()};
+    const bool near = moves_near(c, cnt);
+    if (near) {
+      if ((rc = launch_prologue(c, si, cnt * (P + 1), nullptr, 0, nullptr, 0, nullptr, nullptr, st, si))) return rc;
+      src = (int32_t*)c->cfg.workspace;
+      dst = src + cnt * P;
+    }
+    const StageDone done(c, near ? -1 : si);
+    MoveArgs ma{(uint8_t*)c->cfg.pool, c->page_bytes, c->layer_bytes, src, dst, near, (int32_t)cnt, c->n_layers, c->cfg.n_kv_heads, done.event()};
     Timed t(c, SYM_K_MOVE, st);
     hipError_t e = launch_move(ma, st);
     if (e != hipSuccess) return fail_hip(c, e, "move launch");

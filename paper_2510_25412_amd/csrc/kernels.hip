@@ -2754,23 +2754,27 @@ __global__ void gather_kernel(GatherArgs a, uint8_t* k_out, uint8_t* v_out) {
   *(uint4*)dst = *(const uint4*)src;
 }
 
-// extract / merge (paper section 4.2): K and V rows of whole tokens copied into fresh pages, bit for bit.  A workgroup fills one
-// page of one layer.  A thread owns one token and one of the eight 16-byte chunks of a 128-byte piece, and walks the pieces (kv
-// head, K/V, row half) with all its loads in flight: stores are a page from end to end, loads whole 128-byte lines.  Its source slot
-// and the page come straight from pinned host memory (a wavefront's are one line): copied to the device first, as pairs of slots, they took a
-// launch of 16 us.  Sources are pages of existing files, destinations fresh pages: disjoint.  Bound: HBM, read + write.
-// About half of the tokens of 64 files of 512..4096: 16 + 104 us of kernels -> 108 (5.6 TB/s read + written; eight loads in flight 115,
-// four 117, nontemporal stores 121; the list through LDS 110; several workgroups to a page 114 with two or four, 142 with eight).
+// extract / merge (paper section 4.2): K and V rows of whole tokens copied into fresh pages, bit for bit.  A workgroup works on one
+// page of one layer.  A thread owns one token and one of the eight 16-byte chunks of a 128-byte piece, and takes pieces (kv
+// head, K/V, row half), two to a pass of the workgroup: stores are a page from end to end, loads whole 128-byte lines.  Sources are
+// pages of existing files, destinations fresh pages: disjoint.  Bound: HBM, read + write.
+// A list in pinned host memory: one workgroup per page and layer, since each sends requests over the host link (a wavefront's source
+// slots are one line), and all its loads in flight.  About half of the tokens of 64 files of 512..4096, one layer of 8 heads: 108 us
+// by rocprofv3's trace (5.6 TB/s read + written), and no launch for the list before it (as pairs of slots 16 us + 104; eight loads in
+// flight 115, four 117, nontemporal stores 121; the list through LDS 110; several workgroups to a page 114 with two or four, 142 with eight).
+// A list in device memory (brought there for what is large: many layers above all): a workgroup per pass, so that the loads
+// and stores under way at one time lie close together.  The same files, 8 heads x 32 layers, 2.68 ms of kernel (6.2 TB/s) against 3.05
+// ms with the pinned list and 3.1 ms with one workgroup per page and the list in device memory; one head x 32 layers 350 us against 402.
 template <int U>
 __global__ __launch_bounds__(256) void move_kernel(MoveArgs a) {
   constexpr int kPiece = kP * kHalfBytes;
   const int tid = threadIdx.x, t = (tid >> 3) & (kP - 1), first = tid >> 7, chunk = (tid & 7) * 16;
-  const int slot = a.src[(int64_t)blockIdx.x * kP + t], dst = a.dst[blockIdx.x];
+  const int slot = a.src[(int64_t)blockIdx.y * kP + t], dst = a.dst[blockIdx.y];
   if (t > dst % kP) return;                                         // the page's last tokens do not exist
-  uint8_t* pool = a.pool + (int64_t)blockIdx.y * a.layer_bytes;
+  uint8_t* pool = a.pool + (int64_t)blockIdx.z * a.layer_bytes;
   const uint8_t* s = pool + (int64_t)(slot / kP) * a.page_bytes + first * kPiece + (slot % kP) * kHalfBytes + chunk;
   uint8_t* d = pool + (int64_t)(dst / kP) * a.page_bytes + first * kPiece + t * kHalfBytes + chunk;
-  for (int p = 0; p < a.Hkv * 2; p += U) {                          // two pieces per pass of the workgroup, U passes at a time
+  for (int p = blockIdx.x * U; p < a.Hkv * 2; p += gridDim.x * U) { // two pieces per pass of the workgroup, U passes at a time
     u32x4_t v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load((const u32x4_t*)(s + (int64_t)(p + u) * (2 * kPiece)));
@@ -3092,8 +3096,10 @@ hipError_t launch_gather(const GatherArgs& a, void* k_out, void* v_out, hipStrea
 
 hipError_t launch_move(const MoveArgs& a, hipStream_t st) {
   if (a.n_pages <= 0) return hipSuccess;
-  if (a.n_layers < 1 || a.n_layers > 65535) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)a.n_pages, (unsigned)a.n_layers), block(256);
+  if (a.n_pages > 65535 || a.n_layers < 1 || a.n_layers > 65535) return hipErrorInvalidValue;
+  const dim3 block(256);
+  if (a.near) return launch_done(move_kernel<1>, dim3((unsigned)a.Hkv * 2, (unsigned)a.n_pages, (unsigned)a.n_layers), block, st, a.done, a);
+  const dim3 grid(1, (unsigned)a.n_pages, (unsigned)a.n_layers);
   if (a.Hkv % 8 == 0) return launch_done(move_kernel<16>, grid, block, st, a.done, a);      // all of a page of 8 kv heads at once
   if (a.Hkv % 4 == 0) return launch_done(move_kernel<8>, grid, block, st, a.done, a);
   return launch_done(move_kernel<2>, grid, block, st, a.done, a);

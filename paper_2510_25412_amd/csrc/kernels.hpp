@@ -102,8 +102,9 @@ struct MoveArgs {
   uint8_t* pool;
   int64_t page_bytes;
   int64_t layer_bytes;
-  const int32_t* src;           // pinned host [n_pages][P]: source slots (page * P + slot) of the tokens of a destination page
-  const int32_t* dst;           // pinned host [n_pages]: destination page * P + tokens - 1
+  const int32_t* src;           // [n_pages][P]: source slots (page * P + slot) of the tokens of a destination page
+  const int32_t* dst;           // [n_pages]: destination page * P + tokens - 1
+  bool near;                    // src and dst are in device memory (otherwise pinned host memory)
   int32_t n_pages, n_layers, Hkv;
   hipEvent_t done;              // completed by the launch, or null
 };

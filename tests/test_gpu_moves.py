@@ -5,7 +5,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2510_25412_amd import driver, synth
+from paper_2510_25412_amd import binding, driver, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +37,34 @@ def test_moved_rows_are_the_source_rows(Hkv, layers, dtype):
             torch.cuda.synchronize()
             assert torch.equal(got_k, k[layer]) and torch.equal(got_v, v[layer]), (h, layer)
     sess.close()
+
+
+# 240 MiB written is the line with several layers, 384 MiB with one; the list of 960 pages is 65 KB
+@pytest.mark.parametrize("Hkv,layers,tokens,ws,launches", [(16, 2, 960 * 16 - 7, 1 << 20, 2), (16, 2, 959 * 16, 1 << 20, 1), (1, 32, 960 * 16 - 15, 1 << 20, 2),
+                                                           (3, 16, 640 * 16, 1 << 20, 2), (16, 1, 3072 * 16 - 1, 1 << 20, 2), (16, 1, 3071 * 16, 1 << 20, 1),
+                                                           (16, 2, 960 * 16, 65296, 2), (16, 2, 960 * 16, 65292, 1)])
+def test_list_of_a_large_move_is_brought_to_the_device_once(Hkv, layers, tokens, ws, launches):
+    # its layers and heads would otherwise fetch it again and again over the host link
+    print(f"[case] large move Hkv={Hkv} layers={layers} tokens={tokens} ws={ws}", flush=True)
+    pages = 2 * (tokens // 16 + 2)
+    cfg = binding.make_config(Hkv, Hkv, 128, 16, synth.BF16, pages, device=0, decode_waves=1, n_layers=layers)
+    pool = torch.full((layers * pages * binding.page_bytes(cfg),), 0xFF, dtype=torch.uint8, device="cuda")
+    workspace = torch.empty(ws, dtype=torch.uint8, device="cuda")
+    cfg.pool, cfg.workspace, cfg.workspace_bytes = pool.data_ptr(), workspace.data_ptr(), ws
+    ctx, st = binding.Context(cfg), torch.cuda.current_stream().cuda_stream
+    k, v = (torch.randint(-32768, 32767, (layers, tokens + 1, Hkv, 128), dtype=torch.int16, device="cuda").view(torch.bfloat16) for _ in range(2))
+    src = ctx.kv_open(None)
+    ctx.kv_append(src, tokens + 1, k, v, st)
+    before = ctx.get_stats()["kernel_launches"]
+    idx = np.arange(1, tokens + 1)
+    idx[::7] = idx[::7][::-1].copy()                      # every page has slots of other pages
+    new = ctx.kv_extract_batch([src], [idx], st)[0]
+    assert ctx.get_stats()["kernel_launches"] - before == launches
+    at = torch.from_numpy(idx).cuda()
+    for layer in range(layers):
+        got_k, got_v = (torch.empty((tokens, Hkv, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        ctx.kv_read(new, 0, tokens, got_k, got_v, st, layer=layer)
+        torch.cuda.synchronize()
+        for got, want in ((got_k, k), (got_v, v)):
+            assert torch.equal(got.view(torch.int16), want[layer, at].view(torch.int16)), layer
+    ctx.close()
