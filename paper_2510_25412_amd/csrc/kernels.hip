@@ -2762,6 +2762,8 @@ __global__ void gather_kernel(GatherArgs a, uint8_t* k_out, uint8_t* v_out) {
 // slots are one line), and all its loads in flight.  About half of the tokens of 64 files of 512..4096, one layer of 8 heads: 108 us
 // by rocprofv3's trace (5.6 TB/s read + written), and no launch for the list before it (as pairs of slots 16 us + 104; eight loads in
 // flight 115, four 117, nontemporal stores 121; the list through LDS 110; several workgroups to a page 114 with two or four, 142 with eight).
+// Slots and destination are one round trip: one after the other, 200 tokens of 8 heads 9.9 us instead of 8.4, 8 files of 512..4096
+// with 6 heads x 4 layers 42.1 instead of 41.1 (64 files, one layer of 8 heads: 76.8 against 78, under 92 us of the host's planning).
 // A list in device memory (brought there for what is large: many layers above all): a workgroup per pass, so that the loads
 // and stores under way at one time lie close together.  The same files, 8 heads x 32 layers, 2.68 ms of kernel (6.2 TB/s) against 3.05
 // ms with the pinned list and 3.1 ms with one workgroup per page and the list in device memory; one head x 32 layers 350 us against 402.
@@ -2770,6 +2772,7 @@ __global__ __launch_bounds__(256) void move_kernel(MoveArgs a) {
   constexpr int kPiece = kP * kHalfBytes;
   const int tid = threadIdx.x, t = (tid >> 3) & (kP - 1), first = tid >> 7, chunk = (tid & 7) * 16;
   const int slot = a.src[(int64_t)blockIdx.y * kP + t], dst = a.dst[blockIdx.y];
+  if constexpr (U > 1) asm volatile("" ::"v"(slot));                // both requests under way before the branch waits for one
   if (t > dst % kP) return;                                         // the page's last tokens do not exist
   uint8_t* pool = a.pool + (int64_t)blockIdx.z * a.layer_bytes;
   const uint8_t* s = pool + (int64_t)(slot / kP) * a.page_bytes + first * kPiece + (slot % kP) * kHalfBytes + chunk;
