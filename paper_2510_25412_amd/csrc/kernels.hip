@@ -3105,6 +3105,8 @@ hipError_t launch_move(const MoveArgs& a, hipStream_t st) {
   const dim3 grid(1, (unsigned)a.n_pages, (unsigned)a.n_layers);
   if (a.Hkv % 8 == 0) return launch_done(move_kernel<16>, grid, block, st, a.done, a);      // all of a page of 8 kv heads at once
   if (a.Hkv % 4 == 0) return launch_done(move_kernel<8>, grid, block, st, a.done, a);
+  // (two instead of four for 6 heads: 8 files of 512..4096 x 2 layers 27.0 instead of 26.2 us, 64 files x 1 layer 65.8 instead of 64.3)
+  if (a.Hkv % 2 == 0) return launch_done(move_kernel<4>, grid, block, st, a.done, a);
   return launch_done(move_kernel<2>, grid, block, st, a.done, a);
 }
 

@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("Hkv,layers,dtype", [(1, 1, synth.BF16), (2, 3, synth.BF16), (3, 1, synth.F32), (4, 1, synth.BF16),
-                                              (5, 2, synth.BF16), (8, 3, synth.F32), (12, 1, synth.BF16), (16, 1, synth.BF16)])
+                                              (5, 2, synth.BF16), (8, 3, synth.F32), (12, 1, synth.BF16), (16, 1, synth.BF16),
+                                              (6, 2, synth.BF16), (10, 1, synth.F32)])
 def test_moved_rows_are_the_source_rows(Hkv, layers, dtype):
     print(f"[case] moves Hkv={Hkv} layers={layers} {dtype}", flush=True)
     D, tdt = (128, torch.bfloat16) if dtype == synth.BF16 else (64, torch.float32)
