@@ -108,7 +108,7 @@ struct sym_ctx {
   hipEvent_t stage_ev[kStages];
   bool stage_pending[kStages] = {false, false, false, false};
   int stage_next = 0;
-  int64_t releases = 0;                // launches that were the last to read a staging buffer
+  int64_t recorded_at = 0;             // kernel_launches when an event of the ring was last recorded as a packet of its own
   int fail_staging = 0;                // test hook: this many coming staging reservations fail (sym_test_fail_staging)
   uint8_t* static_scratch = nullptr;   // this device's copy of the library's file-scope scratch array (sym_pred_batch_static)
   // profiling
@@ -357,17 +357,20 @@ int stage_release(sym_ctx* c, int si, hipStream_t st) {
   hipError_t e = hipEventRecord(c->stage_ev[si], st);
   if (e != hipSuccess) return fail_hip(c, e, "hipEventRecord(stage)");
   c->stage_pending[si] = true;
+  c->recorded_at = c->kernel_launches;
   return SYM_OK;
 }
 // The same as the completion of a launch: done(si) is the event to hand to the launch, released(si) follows a launch that went well.
-// Of kRecordEvery such launches one records its event as a packet of its own: the runtime lets go of what it keeps about finished
-// launches only when it meets one (or a wait of the host's), and 60 000 launches kept took 4 ms of the next wait.
-constexpr int64_t kRecordEvery = 64;
+// The first release with kRecordEvery launches (of any kind: a step through many layers has one release) since the last record records its
+// event as a packet of its own: the runtime lets go of what it keeps about finished launches only when it meets one (or a wait of
+// the host's), and 60 000 launches kept took 4 ms of the next wait.  Steps of 80 layers on one short file: 456 us with a record
+// at every 64, 256 or 1024 launches (520 with one at every step); the longest of 640 steps the same.
+constexpr int64_t kRecordEvery = 256;
 struct StageDone {
   sym_ctx* c;
   int si;                      // staging buffer that nothing reads behind the launch; -1: none
   bool record;
-  StageDone(sym_ctx* ctx, int i) : c(ctx), si(i), record(i >= 0 && ++ctx->releases % kRecordEvery == 0) {}
+  StageDone(sym_ctx* ctx, int i) : c(ctx), si(i), record(i >= 0 && ctx->kernel_launches - ctx->recorded_at >= kRecordEvery) {}
   hipEvent_t event() const { return si >= 0 && !record ? c->stage_ev[si] : nullptr; }
   int launched(hipStream_t st) const {
     if (record) return stage_release(c, si, st);
