@@ -47,10 +47,9 @@ class SymError(RuntimeError):
         self.code = code
 
 
-_lib = None
-_I32P = C.POINTER(C.c_int32)
+_lib = _by_address = None
+_I32P, _I64P = C.POINTER(C.c_int32), C.POINTER(C.c_int64)
 
-# arrays go as addresses (c_void_p takes a number, a ctypes pointer or array)
 _SIGNATURES = {
     "sym_page_bytes": (C.c_int64, [C.POINTER(SymConfig)]),
     "sym_tuning_defaults": (C.c_int, [C.POINTER(SymConfig), C.POINTER(SymTuning)]),
@@ -63,31 +62,31 @@ _SIGNATURES = {
     "sym_kv_remove": (C.c_int, [C.c_void_p, C.c_int32]),
     "sym_kv_close": (C.c_int, [C.c_void_p, C.c_int32]),
     "sym_kv_len": (C.c_int64, [C.c_void_p, C.c_int32]),
-    "sym_kv_truncate": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
+    "sym_kv_truncate": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I64P]),
     "sym_kv_append": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_kv_extract": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_kv_merge": (C.c_int32, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
-    "sym_last_moves": (C.c_int64, [C.c_void_p, C.c_void_p, C.c_int64]),
-    "sym_kv_offload": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
-    "sym_kv_restore": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
+    "sym_kv_extract": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I64P, _I64P, _I32P, C.c_void_p]),
+    "sym_kv_merge": (C.c_int32, [C.c_void_p, C.c_int32, _I32P, C.c_void_p]),
+    "sym_last_moves": (C.c_int64, [C.c_void_p, _I32P, C.c_int64]),
+    "sym_kv_offload": (C.c_int, [C.c_void_p, C.c_int32, _I32P, C.c_void_p]),
+    "sym_kv_restore": (C.c_int, [C.c_void_p, C.c_int32, _I32P, C.c_void_p]),
     "sym_kv_waiting": (C.c_int, [C.c_void_p, C.c_int32]),
-    "sym_last_swaps": (C.c_int64, [C.c_void_p, C.c_void_p, C.c_int64]),
-    "sym_pred_batch": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_pred_batch_static": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "sym_last_swaps": (C.c_int64, [C.c_void_p, _I32P, C.c_int64]),
+    "sym_pred_batch": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "sym_pred_batch_static": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "sym_static_scratch_bytes": (C.c_int64, []),
     "sym_test_fail_staging": (C.c_int, [C.c_void_p, C.c_int32]),
-    "sym_pred_begin": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "sym_pred_begin": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, C.c_void_p]),
     "sym_pred_layer": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "sym_pred_end": (C.c_int, [C.c_void_p]),
     "sym_kv_read_layer": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_int64, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_pred_batch_raw": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
-    "sym_kv_pages": (C.c_int64, [C.c_void_p, C.c_int32, C.c_void_p, C.c_int64]),
+    "sym_pred_batch_raw": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, _I64P, _I64P, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "sym_kv_pages": (C.c_int64, [C.c_void_p, C.c_int32, _I32P, C.c_int64]),
     "sym_page_refcount": (C.c_int32, [C.c_void_p, C.c_int32]),
     "sym_free_pages": (C.c_int64, [C.c_void_p]),
     "sym_get_stats": (C.c_int, [C.c_void_p, C.POINTER(SymStats)]),
-    "sym_plan_append": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]),
+    "sym_plan_append": (C.c_int, [C.c_void_p, C.c_int32, _I32P, _I32P, _I32P, C.c_int64, _I32P, _I32P]),
     "sym_plan_copies_first": (C.c_int, [C.c_void_p]),
-    "sym_build_desc": (C.c_int64, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64]),
+    "sym_build_desc": (C.c_int64, [C.c_void_p, C.c_int32, _I32P, _I32P, _I64P, _I64P, _I32P, C.c_int64]),
     "sym_kv_read": (C.c_int, [C.c_void_p, C.c_int32, C.c_int64, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
     "sym_sched_create": (C.c_void_p, [C.c_int32, C.c_double, C.c_double, C.c_double, C.c_double]),
     "sym_sched_destroy": (None, [C.c_void_p]),
@@ -97,9 +96,9 @@ _SIGNATURES = {
     "sym_sched_done": (None, [C.c_void_p, C.c_int32, C.c_double]),
     "sym_sched_next_deadline": (C.c_double, [C.c_void_p]),
     "sym_sched_state": (C.c_int, [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_double), C.POINTER(C.c_double),
-                                  C.POINTER(C.c_double), C.c_void_p]),
+                                  C.POINTER(C.c_double), _I64P]),
     "sym_profile_enable": (C.c_int, [C.c_void_p, C.c_int]),
-    "sym_profile_read": (C.c_int, [C.c_void_p, C.c_int, C.POINTER(C.c_double), C.c_void_p]),
+    "sym_profile_read": (C.c_int, [C.c_void_p, C.c_int, C.POINTER(C.c_double), _I64P]),
     "sym_calib_read": (C.c_int, [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]),
     "sym_calib_copy": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p]),
     "sym_calib_mfma": (C.c_int, [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]),
@@ -120,8 +119,22 @@ def load():
     return _lib
 
 
+def _load_by_address():
+    """The same library with integer arrays passed as addresses (plain numbers: a ctypes pointer object takes ten times as long to make).
+    For this module's own calls, which convert their arrays first; load()'s functions refuse arrays of another type."""
+    global _by_address
+    if _by_address is None:
+        load()
+        lib = C.CDLL(LIB_PATH)               # function objects of its own
+        for name, (res, args) in _SIGNATURES.items():
+            fn = getattr(lib, name)
+            fn.restype, fn.argtypes = res, [C.c_void_p if a in (_I32P, _I64P) else a for a in args]
+        _by_address = lib
+    return _by_address
+
+
 def _i32(a):
-    """A contiguous int32 array and its address (as a plain number: a ctypes pointer object takes ten times as long to make)."""
+    """A contiguous int32 array and its address."""
     a = np.ascontiguousarray(a, np.int32)
     return a, a.__array_interface__["data"][0]
 
@@ -228,7 +241,7 @@ class Context:
     """One sym_ctx.  Methods mirror the C entry points one to one."""
 
     def __init__(self, cfg):
-        self.lib = load()
+        self.lib, self._fn = load(), _load_by_address()
         self.cfg = cfg
         h = C.c_void_p()
         rc = self.lib.sym_init(C.byref(cfg), C.byref(h))
@@ -271,7 +284,7 @@ class Context:
     def kv_truncate(self, kv, new_len):
         kv_a, kv_p = _i32(kv)
         ln_a, ln_p = _i64(new_len)
-        self._chk(self.lib.sym_kv_truncate(self.h, len(kv_a), kv_p, ln_p))
+        self._chk(self._fn.sym_kv_truncate(self.h, len(kv_a), kv_p, ln_p))
 
     def kv_append(self, kv, n, k, v, stream=None):
         self._chk(self.lib.sym_kv_append(self.h, kv, n, _ptr(k), _ptr(v), stream))
@@ -291,46 +304,46 @@ class Context:
         ix_a, ix_p = _i64(flat)
         of_a, of_p = _i64(off)
         out = np.empty(len(s_a), np.int32)
-        self._chk(self.lib.sym_kv_extract(self.h, len(s_a), s_p, of_p, ix_p, out.ctypes.data, stream))
+        self._chk(self._fn.sym_kv_extract(self.h, len(s_a), s_p, of_p, ix_p, out.ctypes.data, stream))
         return [int(h) for h in out]
 
     def kv_merge(self, files, stream=None):
         f_a, f_p = _i32(files)
-        return self._chk(self.lib.sym_kv_merge(self.h, len(f_a), f_p, stream))
+        return self._chk(self._fn.sym_kv_merge(self.h, len(f_a), f_p, stream))
 
     def kv_offload(self, kv, stream=None):
         kv_a, kv_p = _i32(kv)
-        self._chk(self.lib.sym_kv_offload(self.h, len(kv_a), kv_p, stream))
+        self._chk(self._fn.sym_kv_offload(self.h, len(kv_a), kv_p, stream))
 
     def kv_restore(self, kv, stream=None):
         kv_a, kv_p = _i32(kv)
-        self._chk(self.lib.sym_kv_restore(self.h, len(kv_a), kv_p, stream))
+        self._chk(self._fn.sym_kv_restore(self.h, len(kv_a), kv_p, stream))
 
     def kv_waiting(self, kv):
         return bool(self._chk(self.lib.sym_kv_waiting(self.h, kv)))
 
     def last_swaps(self):
-        n = self._chk(self.lib.sym_last_swaps(self.h, None, 0))
+        n = self._chk(self._fn.sym_last_swaps(self.h, None, 0))
         out = np.empty((n, 2), np.int32)
-        self._chk(self.lib.sym_last_swaps(self.h, out.ctypes.data, n))
+        self._chk(self._fn.sym_last_swaps(self.h, out.ctypes.data, n))
         return out
 
     def last_moves(self):
-        n = self._chk(self.lib.sym_last_moves(self.h, None, 0))
+        n = self._chk(self._fn.sym_last_moves(self.h, None, 0))
         out = np.empty((n, 2), np.int32)
-        self._chk(self.lib.sym_last_moves(self.h, out.ctypes.data, n))
+        self._chk(self._fn.sym_last_moves(self.h, out.ctypes.data, n))
         return out
 
     # ---- pred ----
     def pred_batch(self, kv, n_tokens, q, k_new, v_new, out, stream=None):
         kv_a, kv_p = _i32(kv)
         nt_a, nt_p = _i32(n_tokens)
-        self._chk(self.lib.sym_pred_batch(self.h, len(kv_a), kv_p, nt_p, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out), stream))
+        self._chk(self._fn.sym_pred_batch(self.h, len(kv_a), kv_p, nt_p, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out), stream))
 
     def pred_begin(self, kv, n_tokens, stream=None):
         kv_a, kv_p = _i32(kv)
         nt_a, nt_p = _i32(n_tokens)
-        self._chk(self.lib.sym_pred_begin(self.h, len(kv_a), kv_p, nt_p, stream))
+        self._chk(self._fn.sym_pred_begin(self.h, len(kv_a), kv_p, nt_p, stream))
 
     def pred_layer(self, layer, q, k_new, v_new, out, stream=None):
         rc = self.lib.sym_pred_layer(self.h, layer, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out), stream)
@@ -343,7 +356,7 @@ class Context:
     def pred_batch_static(self, kv, n_tokens, q, k_new, v_new, out, stream=None):
         kv_a, kv_p = _i32(kv)
         nt_a, nt_p = _i32(n_tokens)
-        self._chk(self.lib.sym_pred_batch_static(self.h, len(kv_a), kv_p, nt_p, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out), stream))
+        self._chk(self._fn.sym_pred_batch_static(self.h, len(kv_a), kv_p, nt_p, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out), stream))
 
     def test_fail_staging(self, count):
         self._chk(self.lib.sym_test_fail_staging(self.h, count))
@@ -358,7 +371,7 @@ class Context:
         return keep, args
 
     def pred_prepared(self, prepared, stream=None):
-        rc = self.lib.sym_pred_batch(self.h, *prepared[1], stream)
+        rc = self._fn.sym_pred_batch(self.h, *prepared[1], stream)
         if rc < 0:
             self._chk(rc)
 
@@ -367,13 +380,13 @@ class Context:
         pt_a, pt_p = _i32(page_table_flat)
         po_a, po_p = _i64(pt_offsets)
         ln_a, ln_p = _i64(lengths)
-        self._chk(self.lib.sym_pred_batch_raw(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, _ptr(q), _ptr(out), stream))
+        self._chk(self._fn.sym_pred_batch_raw(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, _ptr(q), _ptr(out), stream))
 
     # ---- introspection ----
     def kv_pages(self, kv):
-        n = self._chk(self.lib.sym_kv_pages(self.h, kv, None, 0))
+        n = self._chk(self._fn.sym_kv_pages(self.h, kv, None, 0))
         out = np.zeros(max(n, 1), np.int32)
-        self._chk(self.lib.sym_kv_pages(self.h, kv, out.ctypes.data, n))
+        self._chk(self._fn.sym_kv_pages(self.h, kv, out.ctypes.data, n))
         return out[:n].tolist()
 
     def page_refcount(self, page):
@@ -393,7 +406,7 @@ class Context:
         cow = np.zeros(3 * max(len(kv_a), 1), np.int32)
         slots = np.zeros(max(int(nt_a.sum()) if len(nt_a) else 0, 1), np.int32)
         n_cow = C.c_int32(0)
-        self._chk(self.lib.sym_plan_append(self.h, len(kv_a), kv_p, nt_p, cow.ctypes.data, len(kv_a),
+        self._chk(self._fn.sym_plan_append(self.h, len(kv_a), kv_p, nt_p, cow.ctypes.data, len(kv_a),
                                            C.byref(n_cow), slots.ctypes.data))
         T = int(nt_a.sum())
         return [tuple(int(x) for x in cow[3 * i:3 * i + 3]) for i in range(n_cow.value)], slots[:T].copy()
@@ -406,9 +419,9 @@ class Context:
         pt_a, pt_p = _i32(page_table_flat)
         po_a, po_p = _i64(pt_offsets)
         ln_a, ln_p = _i64(lengths)
-        n = self._chk(self.lib.sym_build_desc(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, None, 0))
+        n = self._chk(self._fn.sym_build_desc(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, None, 0))
         out = np.zeros(n, np.int32)
-        self._chk(self.lib.sym_build_desc(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, out.ctypes.data, n))
+        self._chk(self._fn.sym_build_desc(self.h, len(nt_a), nt_p, pt_p, po_p, ln_p, out.ctypes.data, n))
         return out
 
     def kv_read(self, kv, start, n, k_out, v_out, stream=None, layer=0):
