@@ -5,6 +5,8 @@ import torch
 
 from . import binding, synth
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # not a public name: a torch may lack it
+
 
 def to_device(a, device):
     """Stored patterns (uint16 bf16 bits or float32) -> device tensor of the storage dtype."""
@@ -40,7 +42,9 @@ class HipSession:
     @property
     def stream(self):
         # the stream's handle alone: torch.cuda.current_stream makes an object of it, a microsecond of every call
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if self.device.index is None else self.device.index)
+        if _raw_stream is None:
+            return torch.cuda.current_stream(self.device).cuda_stream
+        return _raw_stream(torch.cuda.current_device() if self.device.index is None else self.device.index)
 
     def setup(self, ops):
         for op in ops:
