@@ -2641,7 +2641,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64) void merge_kernel(MergeArgs a)
 // Bound: HBM, read + write.  By rocprofv3's trace, slots before the first row / now: a document of 7100 tokens 13.2 -> 11.8 us
 // (4.9 TB/s read + written), the mixed batch's 16 600 tokens 34.2 -> 26.7; descriptors and few tokens (256 of drafts, 900 of
 // prompts) the same.  The append workgroups come first in the grid (last: the mixed batch 31.9 us, a fork's descriptor 7.6 -> 7.5).
-// Workgroups of 512 threads where each has four tokens or more: 1024 threads 12.1 and 28.1 us, 256 threads 12.9 and 32.4.
+// Workgroups of 512 threads for both (the line: launch_prologue): 1024 threads 12.1 and 28.1 us, 256 threads 12.9 and 32.4.
 // ---------------------------------------------------------------------------------------
 constexpr int kAppendTokens = 16;        // most tokens per append workgroup
 
@@ -2728,12 +2728,11 @@ template <int NT>
 __global__ __launch_bounds__(NT) void prologue_kernel(PrologueArgs a) {
   prologue<NT, false>(a, nullptr);
 }
-template <int NT>
-__global__ __launch_bounds__(NT) void prologue_runs_kernel(PrologueArgs a, PrologueRuns) {
+__global__ __launch_bounds__(256) void prologue_runs_kernel(PrologueArgs a, PrologueRuns) {
   // the runs where they lie, behind the arguments proper: named as a parameter and indexed by the thread they would be copied to scratch
   auto args = (const __attribute__((address_space(4))) uint8_t*)__builtin_amdgcn_kernarg_segment_ptr();
   static_assert(sizeof(PrologueArgs) % alignof(PrologueRuns) == 0, "the runs follow the arguments at once");
-  prologue<NT, true>(a, (const __attribute__((address_space(4))) PrologueRuns*)(args + sizeof(PrologueArgs)));
+  prologue<256, true>(a, (const __attribute__((address_space(4))) PrologueRuns*)(args + sizeof(PrologueArgs)));
 }
 
 // Inverse of append for a list of token slots: pool -> contiguous [n][Hkv][row].
@@ -3072,19 +3071,22 @@ hipError_t launch_prologue(PrologueArgs a, hipStream_t st) {
   // few tokens: one per workgroup (latency); many: up to 16, while there are 512 workgroups, two per compute unit
   a.append_tokens = std::min(std::max(a.n_tokens / 512, 1), kAppendTokens);
   a.append_blocks = (a.n_tokens + a.append_tokens - 1) / a.append_tokens;
-  const int nt = a.append_tokens >= 4 ? 512 : 256;      // (512 for two and three tokens: 1559 rows of 64 floats 6.6 -> 7.4 us)
+  // 512 threads where each has more than two 16-byte chunks; below, most of the four it requests at a time would be none (by events
+  // around the launch, 512 / 256 threads: 8 kv heads 2500 tokens 10.6 / 10.0 us, 3000 10.8 / 11.3, 7100 13.6 / 14.3; 4 heads 2600 tokens
+  // 9.8 / 9.3, 6000 10.9 / 11.5; one head 2600 tokens 9.2 / 8.8; 16 heads 2600 tokens 13.2 / 12.6, 8190 20.6 / 20.9)
+  const int nt = a.append_tokens > 4 && a.append_tokens * a.Hkv > 32 ? 512 : 256;
   a.copy_blocks = a.copy_words > 0 ? (int32_t)std::min<int64_t>(((a.copy_words + 3) / 4 + nt - 1) / nt, 256) : 0;   // >= 1: also for one, two or three words
   const int64_t blocks = (int64_t)a.append_blocks + a.n_cow + a.copy_blocks;
   if (blocks <= 0) return a.done ? hipEventRecord(a.done, st) : hipSuccess;
   if (a.append_blocks > 0 && a.n_runs > 0 && a.n_runs <= kPrologueRuns) {
+    static_assert(kPrologueRuns * kP / 512 <= 4 && kPrologueRuns <= 256, "workgroups of 256 threads, a run for each thread at most");
     PrologueRuns r;
     for (int i = 0; i < a.n_runs; ++i) {
       r.first[i] = a.runs[2 * i];
       r.slot[i] = a.runs[2 * i + 1];
     }
     r.first[a.n_runs] = a.n_tokens;
-    if (nt == 512) return launch_done(prologue_runs_kernel<512>, dim3((unsigned)blocks), dim3(512), st, a.done, a, r);
-    return launch_done(prologue_runs_kernel<256>, dim3((unsigned)blocks), dim3(256), st, a.done, a, r);
+    return launch_done(prologue_runs_kernel, dim3((unsigned)blocks), dim3(256), st, a.done, a, r);
   }
   if (nt == 512) return launch_done(prologue_kernel<512>, dim3((unsigned)blocks), dim3(512), st, a.done, a);
   return launch_done(prologue_kernel<256>, dim3((unsigned)blocks), dim3(256), st, a.done, a);

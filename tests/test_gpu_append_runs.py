@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 
 # 128 runs are the most that travel with the arguments: 2041 tokens from slot 7 on are 128 runs, 2057 are 129
 @pytest.mark.parametrize("before,new", [([0], [1]), ([7], [9]), ([7], [10]), ([7], [2041]), ([7], [2057]), ([0, 15, 16, 31], [1, 2, 16, 33]),
-                                        ([3] * 64, [13] * 64), ([3] * 64, [14] * 64), ([3] * 64 + [9], [14] * 64 + [1]), ([40] * 70, [1, 5] * 35)])
+                                        ([3] * 64, [13] * 64), ([3] * 64, [14] * 64), ([3] * 64 + [9], [14] * 64 + [1]), ([40] * 70, [1, 5] * 35),
+                                        # 128 whole pages, the most tokens that 128 runs hold; the workgroups' lines at five tokens each
+                                        ([0], [2048]), ([0] * 32, [64] * 32), ([7], [2559]), ([7], [2560]), ([7], [3584])])
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
 def test_appended_rows_read_back(before, new, dtype):
     print(f"[case] runs {before[:4]} {new[:4]} x{len(new)} {dtype}", flush=True)
