@@ -19,7 +19,7 @@
  *    data_ptr()).  The library allocates no device memory, never synchronises `stream`
  *    and enqueues all device work on the `stream` argument (a hipStream_t passed as
  *    void*; NULL = the default stream).  All calls on one context must be issued on one
- *    stream, or be ordered by the caller: the descriptor area of the workspace is reused
+ *    stream, or be ordered by the caller: the start of the workspace (descriptors, lists of large moves) is reused
  *    from call to call in stream order.
  *  - "host" pointers are ordinary host memory, read (or written) before the call returns.
  *  - One mutex per context makes calls thread-safe; a context created with device = -1
@@ -190,7 +190,7 @@ int     sym_kv_append(sym_ctx* ctx, sym_kv kv, int32_t n, const void* k, const v
 /* kv_extract, kv_merge (section 4.2: a new file from chosen token indices of an existing one, and
  * a new file that is several existing files joined, e.g. to prune a context).
  * Both make NEW anonymous files; the source files are not modified.
- *   sym_kv_extract: for n_files files at once (one launch): token j of new file i is token
+ *   sym_kv_extract: for n_files files at once: token j of new file i is token
  *     idx[idx_off[i] + j] of src[i], j < idx_off[i+1] - idx_off[i].  src, idx_off [n_files + 1],
  *     idx: host; indices in any order, repeats allowed, each inside its source file (else
  *     SYM_EINVAL); an empty range gives an empty file.  out [n_files]: host, receives the new

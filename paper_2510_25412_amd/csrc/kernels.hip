@@ -1279,7 +1279,8 @@ __device__ __forceinline__ void tile_block(const PrefillArgs& a, const int block
   // V: thread takes tokens (4*q4 + 2*up, +1) of page pg, dim chunk vc: VD dims x 2 tokens
   constexpr int VD = TW == 4 ? 8 : 4;                       // dims per thread
   const int up = tid & 1, q4 = (tid >> 1) & 3, vc = (tid >> 3) & (128 / VD - 1), pg = tid >> (TW == 4 ? 7 : 8);
-  // K/V of the blocks in flight (loaded three blocks ahead of their use): three register sets
+  // K/V of the blocks in flight.  Four wavefronts: loaded three blocks ahead of their use, three register sets.  Eight: two blocks
+  // ahead of their way into LDS, which is three ahead of their use; the third set serves the start alone.
   uint4 ka0, ka1, va0, va1, kb0r, kb1r, vb0, vb1, kc0, kc1, vc0, vc1;
   const uint8_t* slab = a.pool + (int64_t)g * kSlab;
   // Which of the block's two pages a thread stages is the same for its whole wavefront, so the page
@@ -2715,13 +2716,11 @@ __device__ __forceinline__ void prologue(const PrologueArgs& a, const __attribut
     return;
   }
   blk -= a.n_cow;
-  if (blk < a.copy_blocks) {
-    // 16 bytes per thread, enough blocks that the whole descriptor is one round trip to the host
-    const uint4* src = (const uint4*)a.host_words;
-    uint4* dst = (uint4*)a.dev_words;
-    const int64_t n16 = (a.copy_words + 3) / 4;          // the staging buffer is padded to 16 bytes
-    for (int64_t i = (int64_t)blk * NT + threadIdx.x; i < n16; i += (int64_t)a.copy_blocks * NT) dst[i] = src[i];
-  }
+  // 16 bytes per thread, enough blocks that the whole descriptor is one round trip to the host
+  const uint4* src = (const uint4*)a.host_words;
+  uint4* dst = (uint4*)a.dev_words;
+  const int64_t n16 = (a.copy_words + 3) / 4;            // the staging buffer is padded to 16 bytes
+  for (int64_t i = (int64_t)blk * NT + threadIdx.x; i < n16; i += (int64_t)a.copy_blocks * NT) dst[i] = src[i];
 }
 
 template <int NT>

@@ -89,6 +89,9 @@ struct PrologueArgs {
   const int32_t* runs;          // host: the slot map as (first token, slot or -1) pairs of consecutive slots, ...
   int32_t n_runs;               // ... handed to the kernel with its arguments where they are at most kPrologueRuns; 0: none given
 };
+// Each run saves the launch a part of a round trip over the host link and costs the call host time, used or not.  Calls with room for 64 / 128 /
+// 255 runs, one after the other: 200 tokens of 8 kv heads 9.0 / 9.7 / 9.8 us, 2033 tokens 9.3 / 10.1 / 10.2; a call alone: 2033 tokens 20.4 / 18.9 /
+// 19.0 us, 3000 tokens 21.5 / 21.5 / 21.1, 4064 22.1 / 22.2 / 21.8.
 constexpr int kPrologueRuns = 128;
 
 struct GatherArgs {
