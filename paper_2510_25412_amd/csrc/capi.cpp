@@ -434,7 +434,7 @@ int64_t move_stage_words(const sym_ctx* c, int64_t tokens, int64_t files) {
   return std::min(tokens / c->cfg.page_tokens + files, kMoveChunk) * (c->cfg.page_tokens + 1);
 }
 // Whether the list of `pages` destination pages goes to the device first, and the pages are then filled by many small workgroups that
-// read it there, or stays in pinned memory, read by one workgroup per page and layer.  The launch that brings it takes 4 us and 2.6 ns
+// read it there, or stays in pinned memory, read by one workgroup per page and layer.  The launch that brings it takes 5 us and 1.2 ns
 // a page; it pays from about 250 MB written on, with one layer (where it stands beside the host's planning only) from about 400 MB on.
 // Whole calls, pinned / brought first, about half of the tokens of 64 files of 512..4096: 8 kv heads x 32 layers 3050 / 2690 us (as pairs of
 // slots, a launch a layer 2860), x 8 layers 780 / 675 (735), one head x 8 layers 114 / 102 (145), 16 heads x 1 layer 203 / 180 (197); 8
