@@ -40,10 +40,11 @@ def test_moved_rows_are_the_source_rows(Hkv, layers, dtype):
     sess.close()
 
 
-# 240 MiB written is the line with several layers, 384 MiB with one; the list of 960 pages is 65 KB
+# 240 MiB written is the line with several layers, 384 MiB with one; the list of 960 pages is 65 KB; a launch moves 65535 pages at most
 @pytest.mark.parametrize("Hkv,layers,tokens,ws,launches", [(16, 2, 960 * 16 - 7, 1 << 20, 2), (16, 2, 959 * 16, 1 << 20, 1), (1, 32, 960 * 16 - 15, 1 << 20, 2),
                                                            (3, 16, 640 * 16, 1 << 20, 2), (16, 1, 3072 * 16 - 1, 1 << 20, 2), (16, 1, 3071 * 16, 1 << 20, 1),
-                                                           (16, 2, 960 * 16, 65296, 2), (16, 2, 960 * 16, 65292, 1)])
+                                                           (16, 2, 960 * 16, 65296, 2), (16, 2, 960 * 16, 65292, 1),
+                                                           (1, 1, 65535 * 16 + 40, 8 << 20, 3)])
 def test_list_of_a_large_move_is_brought_to_the_device_once(Hkv, layers, tokens, ws, launches):
     # its layers and heads would otherwise fetch it again and again over the host link
     print(f"[case] large move Hkv={Hkv} layers={layers} tokens={tokens} ws={ws}", flush=True)
