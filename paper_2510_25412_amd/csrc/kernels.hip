@@ -2760,17 +2760,17 @@ __global__ void gather_kernel(GatherArgs a, uint8_t* k_out, uint8_t* v_out) {
 // slots are one line), and all its loads in flight.  About half of the tokens of 64 files of 512..4096, one layer of 8 heads: 108 us
 // by rocprofv3's trace (5.6 TB/s read + written), and no launch for the list before it (as pairs of slots 16 us + 104; eight loads in
 // flight 115, four 117, nontemporal stores 121; the list through LDS 110; several workgroups to a page 114 with two or four, 142 with eight).
-// Slots and destination are one round trip: one after the other, 200 tokens of 8 heads 9.9 us instead of 8.4, 8 files of 512..4096
-// with 6 heads x 4 layers 42.1 instead of 41.1 (64 files, one layer of 8 heads: 76.8 against 78, under 92 us of the host's planning).
+// Slots and destination are one round trip (TOGETHER) where all workgroups start at once (the line: launch_move); behind other workgroups' copies
+// the second round trip costs nothing.
 // A list in device memory (brought there for what is large: many layers above all): a workgroup per pass, so that the loads
 // and stores under way at one time lie close together.  The same files, 8 heads x 32 layers, 2.68 ms of kernel (6.2 TB/s) against 3.05
 // ms with the pinned list and 3.1 ms with one workgroup per page and the list in device memory; one head x 32 layers 350 us against 402.
-template <int U>
+template <int U, bool TOGETHER>
 __global__ __launch_bounds__(256) void move_kernel(MoveArgs a) {
   constexpr int kPiece = kP * kHalfBytes;
   const int tid = threadIdx.x, t = (tid >> 3) & (kP - 1), first = tid >> 7, chunk = (tid & 7) * 16;
   const int slot = a.src[(int64_t)blockIdx.y * kP + t], dst = a.dst[blockIdx.y];
-  if constexpr (U > 1) asm volatile("" ::"v"(slot));                // both requests under way before the branch waits for one
+  if constexpr (TOGETHER) asm volatile("" ::"v"(slot));             // both requests under way before the branch waits for one
   if (t > dst % kP) return;                                         // the page's last tokens do not exist
   uint8_t* pool = a.pool + (int64_t)blockIdx.z * a.layer_bytes;
   const uint8_t* s = pool + (int64_t)(slot / kP) * a.page_bytes + first * kPiece + (slot % kP) * kHalfBytes + chunk;
@@ -3098,17 +3098,27 @@ hipError_t launch_gather(const GatherArgs& a, void* k_out, void* v_out, hipStrea
   return hipGetLastError();
 }
 
+// One workgroup per page and layer.
+template <bool TOGETHER>
+hipError_t launch_move_pages(const MoveArgs& a, hipStream_t st) {
+  const dim3 grid(1, (unsigned)a.n_pages, (unsigned)a.n_layers), block(256);
+  if (a.Hkv % 8 == 0) return launch_done(move_kernel<16, TOGETHER>, grid, block, st, a.done, a);      // all of a page of 8 kv heads at once
+  if (a.Hkv % 4 == 0) return launch_done(move_kernel<8, TOGETHER>, grid, block, st, a.done, a);
+  // (two instead of four for 6 heads: 8 files of 512..4096 x 2 layers 27.0 instead of 26.2 us, 64 files x 1 layer 65.8 instead of 64.3)
+  if (a.Hkv % 2 == 0) return launch_done(move_kernel<4, TOGETHER>, grid, block, st, a.done, a);
+  return launch_done(move_kernel<2, TOGETHER>, grid, block, st, a.done, a);
+}
+
 hipError_t launch_move(const MoveArgs& a, hipStream_t st) {
   if (a.n_pages <= 0) return hipSuccess;
   if (a.n_pages > 65535 || a.n_layers < 1 || a.n_layers > 65535) return hipErrorInvalidValue;
   const dim3 block(256);
-  if (a.near) return launch_done(move_kernel<1>, dim3((unsigned)a.Hkv * 2, (unsigned)a.n_pages, (unsigned)a.n_layers), block, st, a.done, a);
-  const dim3 grid(1, (unsigned)a.n_pages, (unsigned)a.n_layers);
-  if (a.Hkv % 8 == 0) return launch_done(move_kernel<16>, grid, block, st, a.done, a);      // all of a page of 8 kv heads at once
-  if (a.Hkv % 4 == 0) return launch_done(move_kernel<8>, grid, block, st, a.done, a);
-  // (two instead of four for 6 heads: 8 files of 512..4096 x 2 layers 27.0 instead of 26.2 us, 64 files x 1 layer 65.8 instead of 64.3)
-  if (a.Hkv % 2 == 0) return launch_done(move_kernel<4>, grid, block, st, a.done, a);
-  return launch_done(move_kernel<2>, grid, block, st, a.done, a);
+  if (a.near) return launch_done(move_kernel<1, false>, dim3((unsigned)a.Hkv * 2, (unsigned)a.n_pages, (unsigned)a.n_layers), block, st, a.done, a);
+  // 2048 workgroups of 256 threads are all that 256 compute units hold.  By events around the launch, slots and destination in one round trip /
+  // one after the other: 8 kv heads 16 pages 9.3 / 10.5 us, 128 10.3 / 11.5, 512 21.0 / 22.0, 2048 60.7 / 61.1, 512 x 4 layers 57.2 / 58.1; one head
+  // 512 pages 10.3 / 10.9; but 4096 pages of 8 heads 81.9 / 81.1, of 2 heads 33.4 / 32.2, 8192 of 4 heads 82.6 / 81.4; 1024 x 4 layers 83.7 / 83.4
+  if ((int64_t)a.n_pages * a.n_layers <= 2048) return launch_move_pages<true>(a, st);
+  return launch_move_pages<false>(a, st);
 }
 
 hipError_t launch_swap(const SwapArgs& a, hipStream_t st) {

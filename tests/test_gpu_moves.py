@@ -44,7 +44,10 @@ def test_moved_rows_are_the_source_rows(Hkv, layers, dtype):
 @pytest.mark.parametrize("Hkv,layers,tokens,ws,launches", [(16, 2, 960 * 16 - 7, 1 << 20, 2), (16, 2, 959 * 16, 1 << 20, 1), (1, 32, 960 * 16 - 15, 1 << 20, 2),
                                                            (3, 16, 640 * 16, 1 << 20, 2), (16, 1, 3072 * 16 - 1, 1 << 20, 2), (16, 1, 3071 * 16, 1 << 20, 1),
                                                            (16, 2, 960 * 16, 65296, 2), (16, 2, 960 * 16, 65292, 1),
-                                                           (1, 1, 65535 * 16 + 40, 8 << 20, 3)])
+                                                           (1, 1, 65535 * 16 + 40, 8 << 20, 3),
+                                                           # the list pinned, 2048 workgroups and more: every number of loads in flight
+                                                           (2, 1, 2048 * 16 - 3, 1 << 20, 1), (2, 1, 2048 * 16 + 1, 1 << 20, 1), (4, 3, 683 * 16, 1 << 20, 1),
+                                                           (3, 1, 2050 * 16 - 15, 1 << 20, 1), (8, 1, 2049 * 16, 1 << 20, 1)])
 def test_list_of_a_large_move_is_brought_to_the_device_once(Hkv, layers, tokens, ws, launches):
     # its layers and heads would otherwise fetch it again and again over the host link
     print(f"[case] large move Hkv={Hkv} layers={layers} tokens={tokens} ws={ws}", flush=True)
